@@ -407,6 +407,8 @@ def variant_rooflines(p, r, workload):
             "bytes_per_launch": int(alg),
             "avg_launch_ms": round(t_push * 1e3, 5)}
     ms_sm, n_sm = ph["smooth_l0"]
+    if n_sm == 0:  # the steps solved directly: no smoothing to report
+        return {"push": push}
     # The fused pass needs a level at least one owned column wide (64 x 16
     # nodes in FP64, 32 x 16 in FP32).
     fused = p["nx"] >= (32 if mixed else 64) and p["ny"] >= 16 and r["_nu"] == 4

@@ -70,8 +70,9 @@ enum { PIC_ION_LOTZ = 0, PIC_ION_CONST = 1 };
  * PIC_ERR_ARG).
  * PIC_FLAG_PLAIN_SMOOTHER: smooth with one launch per colour and sweep
  * instead of the fused two-sweep pass (same arithmetic, same results).
- * PIC_FLAG_MG_ALL_LEVELS: run the V-cycle down to the coarsest level
- * instead of solving the first coarse level small enough exactly (at most
+ * PIC_FLAG_MG_ALL_LEVELS: run V-cycles down to the coarsest level instead of
+ * solving directly, or (mg_levels > 0, or a grid the direct solve does not
+ * take) instead of solving the first coarse level small enough exactly (at most
  * 64 x 64 nodes per plane if both are powers of two, else 32 x 32, and 256
  * unknown planes: 2-D DFT in x, y, tridiagonal solve in z per mode). */
 enum { PIC_FLAG_PLAIN_SMOOTHER = 1, PIC_FLAG_MG_ALL_LEVELS = 2,
@@ -95,11 +96,17 @@ typedef struct {
                               at the face, V/m.  Both Neumann is rejected
                               (singular with periodic x, y).              */
   int32_t precision;       /* PIC_FP64, or PIC_MIXED: FP32 particles and
-                              FP32 smoothing with FP64 refinement          */
+                              FP32 smoothing with FP64 refinement (a direct
+                              solve is FP64 in both)                       */
   int32_t field_solve;     /* 1: particle charge drives phi; 0: boundary
                               data only (test configurations)             */
-  int32_t mg_levels;       /* multigrid levels, 0 = as deep as possible    */
-  int32_t max_vcycles;     /* V-cycle limit per solve (PIC_ERR_NOCONV)     */
+  int32_t mg_levels;       /* 0: the library chooses: poisson_solve and steps
+                              on 2^18 nodes or more solve directly (DFT in x
+                              and y, tridiagonal in z per mode; nx, ny <= 512,
+                              nz < 2048), everything else runs V-cycles as
+                              deep as possible.  > 0: V-cycles on that many
+                              levels                                       */
+  int32_t max_vcycles;     /* limit of 'vcycles' per solve (PIC_ERR_NOCONV) */
   int32_t nu_pre, nu_post; /* red-black Gauss-Seidel sweeps per level      */
   int32_t coarse_sweeps;   /* sweeps on a coarsest level wider than 1x1    */
   int32_t sort_every;      /* reserved, must be 1: particles are binned by
@@ -210,7 +217,9 @@ typedef struct {
 } pic_sources;
 
 typedef struct {
-  int32_t vcycles;         /* V-cycles taken                               */
+  int32_t vcycles;         /* V-cycles, or direct solves of the residual,
+                              taken (a direct solve needs one unless rel_tol
+                              lies near rounding)                          */
   int32_t converged;       /* 1 if rel_residual <= rel_tol                 */
   double rel_residual;     /* final ||b - A phi|| / ||b||                  */
   double b_norm;           /* ||b||_2 of the scaled system                 */
@@ -221,8 +230,8 @@ typedef struct {
   int32_t warm_rejected;   /* ... and its start was rejected (non-finite,
                               or a larger residual than phi_prev's)        */
   int32_t refinements;     /* mixed form: refinement rounds (FP32 V-cycles
-                              on the correction, then the FP64 residual);
-                              0 in FP64                                    */
+                              on the correction, or one direct solve, then
+                              the FP64 residual); 0 in FP64                */
 } pic_solve_info;
 
 typedef struct {

@@ -1,5 +1,5 @@
 // Field solve of the PIC step: right-hand side from the int64 node charge,
-// vertex-centred geometric multigrid for the 7-point discretisation of
+// the direct solve (k_spectral.hip) or vertex-centred geometric multigrid for the 7-point discretisation of
 // Poisson's equation (Eq. 1) with Dirichlet or Neumann z faces and periodic
 // x, y, and E = -grad(phi) at the nodes.
 //
@@ -2148,10 +2148,39 @@ void field_rhs(pic_ctx* c, const double* rho) {
                                      c->dc, 0, c->cfg.rel_tol);
 }
 
-// Solve A phi = b on level 0 (phi holds the warm start, or zero).  One
+// Wait for the queued work and read back the counters from vcycles on.
+static void read_solve_counters(pic_ctx* c) {
+  constexpr size_t kOff = offsetof(Counters, vcycles);
+  hipMemcpyAsync(reinterpret_cast<char*>(c->hpin) + kOff,
+                 reinterpret_cast<const char*>(c->dc) + kOff,
+                 sizeof(Counters) - kOff, hipMemcpyDeviceToHost, c->stream);
+  stream_wait(c);
+  std::memcpy(reinterpret_cast<char*>(&c->hc) + kOff,
+              reinterpret_cast<const char*>(c->hpin) + kOff,
+              sizeof(Counters) - kOff);
+}
+
+static void fill_solve_info(pic_ctx* c, bool used_net, pic_solve_info* info,
+                            int* status) {
+  info->vcycles = c->hc.vcycles;
+  info->converged = c->hc.done && !(c->hc.err & kErrNonFinite) ? 1 : 0;
+  info->rel_residual = c->hc.rel_res;
+  info->b_norm = c->hc.b_norm;
+  info->rel_residual0 = c->hc.rel_res0;
+  info->warm_used = used_net ? 1 : 0;
+  info->warm_rejected = used_net ? c->hc.warm_reject : 0;
+  info->warm_ratio = used_net ? c->hc.warm_ratio : 1.0;
+  info->refinements = c->hc.refinements;
+  c->last_vcycles = c->hc.vcycles > 0 ? c->hc.vcycles : 1;
+  if (!info->converged) *status = PIC_ERR_NOCONV;
+}
+
+// Solve A phi = b on level 0 (phi holds the warm start, or zero), directly or
+// by V-cycles.  One
 // synchronisation per batch of V-cycles; the batch size follows the last
 // solve so a warm-started step normally syncs once.
-void field_solve(pic_ctx* c, bool warm, pic_solve_info* info, int* status) {
+void field_solve(pic_ctx* c, bool warm, bool direct, pic_solve_info* info,
+                 int* status) {
   hipStream_t st = c->stream;
   Level& L0 = c->lev[0];
   LevelC Lc = level_c(c, 0);
@@ -2198,12 +2227,38 @@ void field_solve(pic_ctx* c, bool warm, pic_solve_info* info, int* status) {
     }
     tmark(c, PIC_PH_WARM, false);
   }
+  int launched = 0;
+  *status = PIC_OK;
+  if (direct) {
+    // The residual of the start (its norm is the initial check) goes straight
+    // into the transform; one correction solves the system to rounding, and
+    // the loop only refines where rel_tol lies below that.
+    const int nw = spectral_partials(c);
+    while (true) {
+      spectral_forward(c);
+      if (launched == 0)
+        k_final<<<1, 1024, 0, st>>>(c->partials, c->qpartials, nw, c->dc, 2, c->cfg.rel_tol);
+      spectral_correct(c);
+      ++launched;
+      k_residual<<<kRedBlocks, kThreads, 0, st>>>(L0.u, L0.f, Lc, c->partials, c->dc, nullptr,
+                                                  nullptr);
+      k_final<<<1, 1024, 0, st>>>(c->partials, c->qpartials, kRedBlocks, c->dc,
+                                  c->mixed ? 4 : 1, c->cfg.rel_tol, 1);
+      read_solve_counters(c);
+      if (c->hc.done || launched >= c->cfg.max_vcycles) break;
+    }
+    // last_vcycles plans the V-cycle batches; a direct solve says nothing
+    // about those.
+    const int keep = c->last_vcycles;
+    fill_solve_info(c, used_net, info, status);
+    c->last_vcycles = keep;
+    return;
+  }
   // Initial check of the warm start.
   k_residual<<<kRedBlocks, kThreads, 0, st>>>(L0.u, L0.f, Lc, c->partials,
                                               c->dc, rf, ef);
   k_final<<<1, 1024, 0, st>>>(c->partials, c->qpartials, kRedBlocks, c->dc, 2,
                               c->cfg.rel_tol);
-  int launched = 0;
   // FP64: a V-cycle needs no residual, since the check only decides when to
   // stop, so the cycles the last solve says will not suffice run unchecked
   // (a solve that converges sooner just ends more accurate).  Mixed:
@@ -2218,7 +2273,6 @@ void field_solve(pic_ctx* c, bool warm, pic_solve_info* info, int* status) {
   int batch = c->mixed ? (last + kInner - 1) / kInner : last;
   const int unchecked = c->mixed ? 0 : std::max(0, batch - 2);
   int pending = 0;  // FP64 cycles run since the last check
-  *status = PIC_OK;
   while (true) {
     for (int b = 0; b < batch && launched < c->cfg.max_vcycles; ++b) {
       if (c->mixed) {
@@ -2253,28 +2307,11 @@ void field_solve(pic_ctx* c, bool warm, pic_solve_info* info, int* status) {
                                   c->dc, 1, c->cfg.rel_tol, pending);
       pending = 0;
     }
-    constexpr size_t kOff = offsetof(Counters, vcycles);
-    hipMemcpyAsync(reinterpret_cast<char*>(c->hpin) + kOff,
-                   reinterpret_cast<const char*>(c->dc) + kOff,
-                   sizeof(Counters) - kOff, hipMemcpyDeviceToHost, st);
-    stream_wait(c);
-    std::memcpy(reinterpret_cast<char*>(&c->hc) + kOff,
-                reinterpret_cast<const char*>(c->hpin) + kOff,
-                sizeof(Counters) - kOff);
+    read_solve_counters(c);
     if (c->hc.done || launched >= c->cfg.max_vcycles) break;
     batch = 1;
   }
-  info->vcycles = c->hc.vcycles;
-  info->converged = c->hc.done && !(c->hc.err & kErrNonFinite) ? 1 : 0;
-  info->rel_residual = c->hc.rel_res;
-  info->b_norm = c->hc.b_norm;
-  info->rel_residual0 = c->hc.rel_res0;
-  info->warm_used = used_net ? 1 : 0;
-  info->warm_rejected = used_net ? c->hc.warm_reject : 0;
-  info->warm_ratio = used_net ? c->hc.warm_ratio : 1.0;
-  info->refinements = c->hc.refinements;
-  c->last_vcycles = c->hc.vcycles > 0 ? c->hc.vcycles : 1;
-  if (!info->converged) *status = PIC_ERR_NOCONV;
+  fill_solve_info(c, used_net, info, status);
 }
 
 void field_extrapolate(pic_ctx* c) {

@@ -1,0 +1,636 @@
+// Direct solution of the 7-point Poisson system on the finest level.
+//
+// With x and y periodic, a plane's 2-D Fourier modes do not couple: mode
+// (kx, ky) turns the operator into one tridiagonal system over z with
+// d = 2 + 4 sin^2(pi kx/nx) + 4 sin^2(pi ky/ny) on the diagonal and -1 beside
+// it.  A solve is therefore real DFTs over x, complex DFTs over y, one
+// tridiagonal solve per mode, and the way back: five passes that each read
+// and write the field once, in FP64 in both precisions of the library.  It
+// works on the residual of the start, r = b - A phi_0, and adds the
+// correction to phi_0, so a pass repeated on its own result refines it.
+//
+// Spectrum layout: the plane's nx * ny reals, in place of the field.  A row
+// holds nx/2 complex slots kx; slot 0 packs the two real lines kx = 0 and
+// kx = nx/2 as (X_0, X_{nx/2}).  After the y transform, slot 0 of row ky holds
+// line 0's mode ky for 0 < ky < ny/2, line nx/2's mode ny - ky for ky > ny/2,
+// and both lines' (real) modes for ky = 0 and ny/2.  Every real number of the
+// plane is then its own tridiagonal system in z.
+//
+// Bound: the passes move 9 doubles a node (start and right-hand side read,
+// spectrum written; four times read and written; start read, phi written).
+// 128x128x512 nodes in FP64, one solve with its residual check: 910 us as four
+// V-cycles, 325 us here (x 54 and 53, y 35 each way, z 80, check 32);
+// poisson_solve 1270 -> 420 us, on 256x256x1024 in the mixed form 8.8 -> 3.1
+// ms, on the ragged 40x20x36 385 -> 111 us.  The potential is 1e-14 from the
+// exact one where the V-cycles stop at 1e-12.
+#include <algorithm>
+
+#include "pic_ctx.h"
+
+namespace pic {
+namespace {
+
+constexpr int kSpThreads = 256;
+constexpr int kSpElems = 8;  // complex values a thread holds in a stage
+// Real numbers in LDS lines: one value of padding after every eight, so the
+// strided stores of a radix-8 stage fall on different banks.
+__host__ __device__ __forceinline__ int pad8(int i) { return i + (i >> 3); }
+
+// Radices of a length-n transform in the order of their stages: powers of
+// two as 8s and 4s (registers), odd primes by a direct sum over LDS.
+struct FftPlan {
+  int n, nst;
+  int rad[12];
+};
+
+struct SpGrid {
+  int nx, ny, nz, k0, np, bc_lo, bc_hi;
+  long long nxy;
+};
+
+FftPlan make_plan(int n) {
+  FftPlan p;
+  p.n = n;
+  p.nst = 0;
+  int a = 0, m = n;
+  while (!(m & 1)) {
+    m >>= 1;
+    ++a;
+  }
+  while (a > 0) {
+    // 16 as 4 x 4 and 4 as one stage: never a radix-2 stage after an 8.
+    const int b = a == 4 || a == 2 ? 2 : (a >= 3 ? 3 : a);
+    p.rad[p.nst++] = 1 << b;
+    a -= b;
+  }
+  for (int f = 3; m > 1; f += 2)
+    while (m % f == 0) {
+      p.rad[p.nst++] = f;
+      m /= f;
+    }
+  return p;
+}
+
+// v <- its length-R transform with e^{sg 2 pi i / R}.
+template <int R>
+__device__ __forceinline__ void dft_r(double2* v, double sg) {
+  if constexpr (R == 2) {
+    const double2 a = v[0], b = v[1];
+    v[0] = make_double2(a.x + b.x, a.y + b.y);
+    v[1] = make_double2(a.x - b.x, a.y - b.y);
+  } else if constexpr (R == 4) {
+    const double2 a = make_double2(v[0].x + v[2].x, v[0].y + v[2].y);
+    const double2 b = make_double2(v[0].x - v[2].x, v[0].y - v[2].y);
+    const double2 c = make_double2(v[1].x + v[3].x, v[1].y + v[3].y);
+    // (v1 - v3) times sg i
+    const double2 d = make_double2(-sg * (v[1].y - v[3].y), sg * (v[1].x - v[3].x));
+    v[0] = make_double2(a.x + c.x, a.y + c.y);
+    v[1] = make_double2(b.x + d.x, b.y + d.y);
+    v[2] = make_double2(a.x - c.x, a.y - c.y);
+    v[3] = make_double2(b.x - d.x, b.y - d.y);
+  } else {
+    double2 e[4] = {v[0], v[2], v[4], v[6]}, o[4] = {v[1], v[3], v[5], v[7]};
+    dft_r<4>(e, sg);
+    dft_r<4>(o, sg);
+    constexpr double h = 0.70710678118654752440;
+    const double2 w1 = make_double2(h * (o[1].x - sg * o[1].y), h * (o[1].y + sg * o[1].x));
+    const double2 w2 = make_double2(-sg * o[2].y, sg * o[2].x);
+    const double2 w3 = make_double2(-h * (o[3].x + sg * o[3].y), h * (sg * o[3].x - o[3].y));
+    const double2 w[4] = {o[0], w1, w2, w3};
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      v[q] = make_double2(e[q].x + w[q].x, e[q].y + w[q].y);
+      v[q + 4] = make_double2(e[q].x - w[q].x, e[q].y - w[q].y);
+    }
+  }
+}
+
+__device__ __forceinline__ double2 cmul(double2 a, double2 w, double sg) {
+  const double wi = sg * w.y;
+  return make_double2(fma(a.x, w.x, -(a.y * wi)), fma(a.x, wi, a.y * w.x));
+}
+
+// Quotient of small non-negative integers (a < 2^20, n < 2^11) by a float
+// reciprocal: the half-step offset keeps the truncation exact.
+__device__ __forceinline__ int fdiv(int a, float rn) { return (int)(((float)a + 0.5f) * rn); }
+
+// One self-sorting stage of radix R over all lines of the workgroup: inputs
+// j + q N/R, twiddled by e^{sg 2 pi i k q / (Ns R)} with k = j mod Ns (Ns: the
+// product of the radices before), outputs (j / Ns) Ns R + k + q Ns.  Every
+// thread holds its butterflies in registers between the two barriers, so one
+// buffer serves.
+template <int R>
+__device__ __forceinline__ void stage(double2* buf, const double2* tw, int n, int lines, int stride,
+                                      int ns, double sg) {
+  constexpr int NB = kSpElems / R;
+  const int m = n / R, total = lines * m, tstep = n / (ns * R);
+  const float rm = 1.0f / (float)m, rns = 1.0f / (float)ns;
+  double2 v[NB][R];
+#pragma unroll
+  for (int b = 0; b < NB; ++b) {
+    const int e = threadIdx.x + b * blockDim.x;
+    if (e < total) {
+      const int line = fdiv(e, rm), j = e - line * m;
+      const int k = j - fdiv(j, rns) * ns;
+      const double2* src = buf + line * stride;
+#pragma unroll
+      for (int q = 0; q < R; ++q) v[b][q] = src[pad8(j + q * m)];
+#pragma unroll
+      for (int q = 1; q < R; ++q)
+        if (ns > 1) v[b][q] = cmul(v[b][q], tw[k * q * tstep], sg);
+      dft_r<R>(v[b], sg);
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int b = 0; b < NB; ++b) {
+    const int e = threadIdx.x + b * blockDim.x;
+    if (e < total) {
+      const int line = fdiv(e, rm), j = e - line * m;
+      const int jd = fdiv(j, rns), k = j - jd * ns;
+      double2* dst = buf + line * stride;
+      const int o = jd * ns * R + k;
+#pragma unroll
+      for (int q = 0; q < R; ++q) dst[pad8(o + q * ns)] = v[b][q];
+    }
+  }
+  __syncthreads();
+}
+
+// The same stage for an odd prime radix r, each thread summing its outputs
+// from LDS: the input twiddle and the transform's own combine into one power
+// of the length-n root per term.
+__device__ __forceinline__ void stage_odd(double2* buf, const double2* tw, int n, int lines,
+                                          int stride, int ns, int r, double sg) {
+  const int m = n / r, total = lines * n, tstep = n / (ns * r);
+  const float rn = 1.0f / (float)n, rns = 1.0f / (float)ns, rr = 1.0f / (float)r;
+  double2 acc[kSpElems];
+#pragma unroll
+  for (int b = 0; b < kSpElems; ++b) {
+    const int e = threadIdx.x + b * blockDim.x;
+    if (e < total) {
+      const int line = fdiv(e, rn), pos = e - line * n;
+      const int pd = fdiv(pos, rns), k = pos - pd * ns;
+      const int jd = fdiv(pd, rr), q = pd - jd * r;
+      const double2* src = buf + line * stride;
+      const int j = jd * ns + k, step = k * tstep + q * m;
+      double2 s = make_double2(0.0, 0.0);
+      int w = 0;
+      for (int i = 0; i < r; ++i) {
+        const double2 t = cmul(src[pad8(j + i * m)], tw[w], sg);
+        s.x += t.x;
+        s.y += t.y;
+        w += step;
+        w = w >= n ? w - n : w;
+      }
+      acc[b] = s;
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int b = 0; b < kSpElems; ++b) {
+    const int e = threadIdx.x + b * blockDim.x;
+    if (e < total) {
+      const int line = fdiv(e, rn);
+      buf[line * stride + pad8(e - line * n)] = acc[b];
+    }
+  }
+  __syncthreads();
+}
+
+__device__ __forceinline__ void fft_lines(double2* buf, const double2* tw, const FftPlan& P,
+                                          int lines, int stride, double sg) {
+  int ns = 1;
+  for (int s = 0; s < P.nst; ++s) {
+    const int r = P.rad[s];
+    if (r == 8)
+      stage<8>(buf, tw, P.n, lines, stride, ns, sg);
+    else if (r == 4)
+      stage<4>(buf, tw, P.n, lines, stride, ns, sg);
+    else if (r == 2)
+      stage<2>(buf, tw, P.n, lines, stride, ns, sg);
+    else
+      stage_odd(buf, tw, P.n, lines, stride, ns, r, sg);
+    ns *= r;
+  }
+}
+
+__device__ __forceinline__ void fill_tw(double2* tw, int n) {
+  for (int q = threadIdx.x; q < n; q += blockDim.x) {
+    double sn, cs;
+    sincospi(2.0 * q / n, &sn, &cs);
+    tw[q] = make_double2(cs, sn);
+  }
+}
+
+// x forward: the residual of two neighbouring rows as one complex line.
+// Contiguous ranges of lines go to one XCD, so the three planes a residual
+// reads stay in its L2.
+__global__ void __launch_bounds__(kSpThreads) k_sp_xfwd(
+    SpGrid G, const double* __restrict__ u, const double* __restrict__ f, double* __restrict__ s,
+    FftPlan P, int nlines, int lpw, int stride, double* __restrict__ part) {
+  extern __shared__ double2 sm[];
+  double2* tw = sm;
+  double2* buf = sm + P.n;
+  const int nx = G.nx, nyp = G.ny / 2;
+  const int wg = xcd_block(blockIdx.x, gridDim.x);
+  const int line0 = wg * lpw;
+  const int lines = nlines - line0 < lpw ? nlines - line0 : lpw;
+  const float rnx = 1.0f / (float)nx;
+  double s2 = 0.0;
+#pragma unroll
+  for (int b = 0; b < kSpElems; ++b) {
+    const int e = threadIdx.x + b * blockDim.x;
+    if (e < lines * nx) {
+      const int l = fdiv(e, rnx), i = e - l * nx;
+      const int gl = line0 + l;
+      const int p = gl / nyp, j = 2 * (gl - p * nyp), k = G.k0 + p;
+      const int im = i ? i - 1 : nx - 1, ip = i + 1 < nx ? i + 1 : 0;
+      const int jm = j ? j - 1 : G.ny - 1, jp = j + 2 < G.ny ? j + 2 : 0;
+      const double* pl = u + (long long)k * G.nxy;
+      const double* ra = pl + j * nx;
+      const double* rb = ra + nx;
+      const double ca = ra[i], cb = rb[i];
+      const long long za = (long long)j * nx + i;
+      const double* dn = u + (long long)(k > 0 ? k - 1 : 1) * G.nxy + za;
+      const double* up = u + (long long)(k < G.nz ? k + 1 : G.nz - 1) * G.nxy + za;
+      const double* fr = f + (long long)k * G.nxy + za;
+      // The stencil sum of one node: x pair, then y pair, then z pair (a
+      // Neumann face's mirrored neighbour taken twice).
+      const double sa = ((ra[im] + ra[ip]) + (pl[jm * nx + i] + cb)) + (dn[0] + up[0]);
+      const double sb = ((rb[im] + rb[ip]) + (ca + pl[jp * nx + i])) + (dn[nx] + up[nx]);
+      const double va = fr[0] - (6.0 * ca - sa), vb = fr[nx] - (6.0 * cb - sb);
+      s2 += va * va + vb * vb;
+      buf[l * stride + pad8(i)] = make_double2(va, vb);
+    }
+  }
+  fill_tw(tw, P.n);
+  __syncthreads();
+  fft_lines(buf, tw, P, lines, stride, -1.0);
+  const int nh = nx / 2;
+  const float rnh = 1.0f / (float)nh;
+#pragma unroll
+  for (int b = 0; b < kSpElems / 2; ++b) {
+    const int e = threadIdx.x + b * blockDim.x;
+    if (e < lines * nh) {
+      const int l = fdiv(e, rnh), kx = e - l * nh;
+      const double2 z = buf[l * stride + pad8(kx)];
+      const double2 c = buf[l * stride + pad8(kx ? nx - kx : nh)];
+      double2 xa, xb;
+      if (kx == 0) {
+        xa = make_double2(z.x, c.x);
+        xb = make_double2(z.y, c.y);
+      } else {
+        xa = make_double2(0.5 * (z.x + c.x), 0.5 * (z.y - c.y));
+        xb = make_double2(0.5 * (z.y + c.y), 0.5 * (c.x - z.x));
+      }
+      const int gl = line0 + l;
+      double* o = s + (long long)gl * 2 * nx + 2 * kx;
+      *reinterpret_cast<double2*>(o) = xa;
+      *reinterpret_cast<double2*>(o + nx) = xb;
+    }
+  }
+  // Sum of squares of the residual: one partial per workgroup.
+  __syncthreads();
+  double* red = reinterpret_cast<double*>(buf);
+  for (int o = 32; o > 0; o >>= 1) s2 += __shfl_down(s2, o);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s2;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double a = 0.0;
+    for (unsigned w = 0; w < (blockDim.x + 63) / 64; ++w) a += red[w];
+    part[wg] = a;
+  }
+}
+
+// y transforms of the columns, lpw neighbouring slots of the flattened
+// (plane, slot) list per workgroup, in place.
+template <bool INV>
+__global__ void __launch_bounds__(kSpThreads) k_sp_y(SpGrid G, double* __restrict__ s, FftPlan P,
+                                                     int nlines, int lpw, int stride,
+                                                     const Counters* dc) {
+  extern __shared__ double2 sm[];
+  if (dc->done) return;
+  double2* tw = sm;
+  double2* buf = sm + P.n;
+  const int nh = G.nx / 2, ny = G.ny;
+  const int line0 = xcd_block(blockIdx.x, gridDim.x) * lpw;
+  const int lines = nlines - line0 < lpw ? nlines - line0 : lpw;
+  const float rl = 1.0f / (float)lines;
+  double2* sp = reinterpret_cast<double2*>(s);
+#pragma unroll
+  for (int b = 0; b < kSpElems; ++b) {
+    const int e = threadIdx.x + b * blockDim.x;
+    if (e < lines * ny) {
+      const int j = fdiv(e, rl), l = e - j * lines;
+      const int gl = line0 + l, p = gl / nh, kx = gl - p * nh;
+      double2* pl = sp + (long long)p * ny * nh;
+      double2 v = pl[j * nh + kx];
+      if (INV && kx == 0 && j != 0 && 2 * j != ny) {
+        // C(ky) = F_0(ky) + i F_N(ky); F(-ky) = conj F(ky).
+        const double2 w = pl[(ny - j) * nh];
+        v = 2 * j < ny ? make_double2(v.x - w.y, v.y + w.x) : make_double2(w.x + v.y, v.x - w.y);
+      }
+      buf[l * stride + pad8(j)] = v;
+    }
+  }
+  fill_tw(tw, P.n);
+  __syncthreads();
+  fft_lines(buf, tw, P, lines, stride, INV ? 1.0 : -1.0);
+#pragma unroll
+  for (int b = 0; b < kSpElems; ++b) {
+    const int e = threadIdx.x + b * blockDim.x;
+    if (e < lines * ny) {
+      const int j = fdiv(e, rl), l = e - j * lines;
+      const int gl = line0 + l, p = gl / nh, kx = gl - p * nh;
+      double2 v = buf[l * stride + pad8(j)];
+      if (!INV && kx == 0 && j != 0 && 2 * j != ny) {
+        // F_0 = (C(ky) + conj C(-ky)) / 2, F_N = (C(ky) - conj C(-ky)) / 2i,
+        // F_N stored at the mirrored row.
+        const double2 c = buf[l * stride + pad8(ny - j)];
+        v = 2 * j < ny ? make_double2(0.5 * (v.x + c.x), 0.5 * (v.y - c.y))
+                       : make_double2(0.5 * (c.y + v.y), 0.5 * (v.x - c.x));
+      }
+      sp[((long long)p * ny + j) * nh + kx] = v;
+    }
+  }
+}
+
+// x inverse and correction: phi = phi_0 + the transform of two rows' slots.
+__global__ void __launch_bounds__(kSpThreads) k_sp_xinv(SpGrid G, const double* __restrict__ s,
+                                                        double* __restrict__ u, FftPlan P,
+                                                        int nlines, int lpw, int stride,
+                                                        const Counters* dc) {
+  extern __shared__ double2 sm[];
+  if (dc->done) return;
+  double2* tw = sm;
+  double2* buf = sm + P.n;
+  const int nx = G.nx, nh = nx / 2;
+  const int line0 = xcd_block(blockIdx.x, gridDim.x) * lpw;
+  const int lines = nlines - line0 < lpw ? nlines - line0 : lpw;
+  const float rnh = 1.0f / (float)nh;
+#pragma unroll
+  for (int b = 0; b < kSpElems / 2; ++b) {
+    const int e = threadIdx.x + b * blockDim.x;
+    if (e < lines * nh) {
+      const int l = fdiv(e, rnh), kx = e - l * nh;
+      const double* o = s + (long long)(line0 + l) * 2 * nx + 2 * kx;
+      const double2 ga = *reinterpret_cast<const double2*>(o);
+      const double2 gb = *reinterpret_cast<const double2*>(o + nx);
+      double2* dst = buf + l * stride;
+      if (kx == 0) {
+        dst[0] = make_double2(ga.x, gb.x);
+        dst[pad8(nh)] = make_double2(ga.y, gb.y);
+      } else {
+        dst[pad8(kx)] = make_double2(ga.x - gb.y, ga.y + gb.x);
+        dst[pad8(nx - kx)] = make_double2(ga.x + gb.y, gb.x - ga.y);
+      }
+    }
+  }
+  fill_tw(tw, P.n);
+  __syncthreads();
+  fft_lines(buf, tw, P, lines, stride, 1.0);
+  const double sc = 1.0 / ((double)nx * (double)G.ny);
+  const float rnx = 1.0f / (float)nx;
+  double* base = u + (long long)G.k0 * G.nxy;
+#pragma unroll
+  for (int b = 0; b < kSpElems; ++b) {
+    const int e = threadIdx.x + b * blockDim.x;
+    if (e < lines * nx) {
+      const int l = fdiv(e, rnx), i = e - l * nx;
+      const double2 v = buf[l * stride + pad8(i)];
+      double* o = base + (long long)(line0 + l) * 2 * nx + i;
+      o[0] = o[0] + sc * v.x;
+      o[nx] = o[nx] + sc * v.y;
+    }
+  }
+}
+
+__device__ __forceinline__ double ipow(double b, int e) {
+  double r = 1.0;
+  for (; e; e >>= 1, b *= b)
+    if (e & 1) r *= b;
+  return r;
+}
+
+// The tridiagonal systems -x_{p-1} + d x_p - x_{p+1} = b_p, one per real
+// number of the plane, in place.  With d = l + 1/l (0 < l <= 1) the operator
+// factors into (1/l)(1 - l S)(1 - l S^-1): two first-order recurrences with
+// the one coefficient l give a solution x' with x'_np = 0, and c h_p, h_p =
+// sinh((np - p) t) / sinh((np + 1) t) with l = e^-t, sets the lower face.
+// Dirichlet: x_{-1} = 0.  Neumann: x_{-1} = x_1 (the row takes its inner
+// neighbour twice).  With the Neumann face on top the planes run downwards.
+// A thread runs SEG planes of one system in registers; the segments' ends are
+// joined through LDS.  No pivots are stored or divided: the pass reads and
+// writes the spectrum once.
+template <int SEG>
+__global__ void __launch_bounds__(SEG > 32 ? 512 : 1024) k_sp_tri(SpGrid G, double* __restrict__ s,
+                                                                  int lgc, const Counters* dc) {
+  extern __shared__ double2 sm[];
+  if (dc->done) return;
+  const int cols = 1 << lgc;
+  const int c = threadIdx.x & (cols - 1), sg = threadIdx.x >> lgc;
+  const int nsg = blockDim.x >> lgc;
+  double* jz = reinterpret_cast<double*>(sm);
+  const int col = blockIdx.x * cols + c;
+  const bool ok = col < G.nxy;
+  const int cc = ok ? col : 0;
+  int ky = cc / G.nx;
+  const int xr = cc - ky * G.nx;
+  int kx = xr >> 1;
+  if (kx == 0) {
+    const int hy = G.ny / 2;
+    if (ky == 0 || ky == hy) {
+      kx = (xr & 1) ? G.nx / 2 : 0;
+    } else if (ky > hy) {
+      kx = G.nx / 2;
+      ky = G.ny - ky;
+    }
+  }
+  const bool rev = G.bc_hi == PIC_BC_NEUMANN;
+  const bool neu = rev || G.bc_lo == PIC_BC_NEUMANN;
+  const int np = G.np, p0 = sg * SEG;
+  double* base = s + cc;
+  double b[SEG];
+#pragma unroll
+  for (int q = 0; q < SEG; ++q) {
+    const int p = p0 + q;
+    const int pc = p < np ? (rev ? np - 1 - p : p) : 0;
+    b[q] = base[(long long)pc * G.nxy];
+  }
+  const double sx = sinpi((double)kx / G.nx), sy = sinpi((double)ky / G.ny);
+  const double qq = sx * sx + sy * sy;  // (d - 2) / 4
+  const double rt = sqrt(1.0 + qq) + sqrt(qq);
+  const double l = 1.0 / (rt * rt);
+  const double lseg = ipow(l, SEG);
+  // y_p = l (b_p + y_{p-1}), segment-local, then joined.
+  double y = 0.0;
+#pragma unroll
+  for (int q = 0; q < SEG; ++q) {
+    y = p0 + q < np ? l * (b[q] + y) : 0.0;
+    b[q] = y;
+  }
+  jz[threadIdx.x] = y;
+  __syncthreads();
+  y = 0.0;
+  for (int q = 0; q < sg; ++q) y = fma(lseg, y, jz[(q << lgc) + c]);
+  __syncthreads();
+  // x'_p = y_p + l x'_{p+1} from x'_np = 0.
+  double w = l * y;
+#pragma unroll
+  for (int q = 0; q < SEG; ++q) {
+    if (p0 + q < np) b[q] += w;
+    w *= l;
+  }
+  double x = 0.0;
+#pragma unroll
+  for (int q = SEG - 1; q >= 0; --q) {
+    x = fma(l, x, b[q]);
+    b[q] = x;
+  }
+  jz[threadIdx.x] = x;
+  __syncthreads();
+  x = 0.0;
+  for (int q = nsg - 1; q > sg; --q) x = fma(lseg, x, jz[(q << lgc) + c]);
+  w = l * x;
+#pragma unroll
+  for (int q = SEG - 1; q >= 0; --q) {
+    b[q] += w;
+    w *= l;
+  }
+  __syncthreads();
+  if (sg == 0) {
+    jz[c] = b[0];
+    jz[cols + c] = b[1];
+  }
+  __syncthreads();
+  const double x0 = jz[c], x1 = jz[cols + c];
+  // h_p from its two exponentials, e^{-(p+1)t} and e^{-(2np+1-p)t}.
+  const bool flat = qq == 0.0;
+  const double l2n = ipow(l, 2 * np + 2);
+  const double den = flat ? 1.0 / (double)(np + 1) : 1.0 / (1.0 - l2n);
+  double cf = l * x0;
+  if (neu) {
+    // h_{-1} - h_1
+    const double dh = flat ? 2.0 * den : (1.0 - l * l) * (1.0 + ipow(l, 2 * np)) * den;
+    cf = (l * x0 - (np > 1 ? x1 : 0.0)) / dh;
+  }
+  cf *= den;
+  double ea = ipow(l, p0 + 1);
+  const int pe = p0 + SEG < np ? p0 + SEG : np;  // one past the last plane
+  // The second exponential runs down from the segment's last plane.
+  double eb = ipow(l, 2 * np + 2 - pe > 0 ? 2 * np + 2 - pe : 0);
+  if (flat) {
+#pragma unroll
+    for (int q = 0; q < SEG; ++q) b[q] -= cf * (double)(np - (p0 + q));
+  } else {
+#pragma unroll
+    for (int q = 0; q < SEG; ++q) {
+      b[q] = fma(-cf, ea, b[q]);
+      ea *= l;
+    }
+#pragma unroll
+    for (int q = SEG - 1; q >= 0; --q) {
+      if (p0 + q < pe) {
+        b[q] = fma(cf, eb, b[q]);
+        eb *= l;
+      }
+    }
+  }
+  if (ok) {
+#pragma unroll
+    for (int q = 0; q < SEG; ++q) {
+      const int p = p0 + q;
+      if (p < np) base[(long long)(rev ? np - 1 - p : p) * G.nxy] = b[q];
+    }
+  }
+}
+
+// Lines per workgroup: what the threads hold, fewer where that would leave
+// the chip idle.
+int lines_per_wg(int n, long long nlines) {
+  const int most = kSpThreads * kSpElems / n;
+  const long long spread = std::max(4LL, (nlines + 511) / 512);
+  return (int)std::max(1LL, std::min<long long>(most, spread));
+}
+
+struct LineLaunch {
+  FftPlan plan;
+  int nlines, lpw, stride, threads;
+  unsigned grid;
+  size_t lds;
+};
+
+LineLaunch line_launch(int n, long long nlines) {
+  LineLaunch a;
+  a.plan = make_plan(n);
+  a.nlines = (int)nlines;
+  a.lpw = lines_per_wg(n, nlines);
+  a.stride = pad8(n) + 1;
+  // Enough threads for kSpElems values each.
+  a.threads = ((a.lpw * n + kSpElems - 1) / kSpElems + 63) / 64 * 64;
+  a.grid = (unsigned)((nlines + a.lpw - 1) / a.lpw);
+  a.lds = (size_t)(n + a.lpw * a.stride) * sizeof(double2);
+  return a;
+}
+
+SpGrid sp_grid(const pic_ctx* c) {
+  SpGrid g;
+  const pic_config& f = c->cfg;
+  g.nx = f.nx; g.ny = f.ny; g.nz = f.nz;
+  g.bc_lo = f.bc_lo; g.bc_hi = f.bc_hi;
+  g.k0 = f.bc_lo == PIC_BC_DIRICHLET ? 1 : 0;
+  g.np = (f.bc_hi == PIC_BC_DIRICHLET ? f.nz - 1 : f.nz) - g.k0 + 1;
+  g.nxy = (long long)f.nx * f.ny;
+  return g;
+}
+
+}  // namespace
+
+bool spectral_direct(const pic_config* f) {
+  if (f->mg_levels != 0 || (f->flags & PIC_FLAG_MG_ALL_LEVELS)) return false;
+  return f->nx <= kDirectMaxXY && f->ny <= kDirectMaxXY && f->nz < kDirectMaxPlanes;
+}
+
+int spectral_partials(const pic_ctx* c) {
+  const SpGrid G = sp_grid(c);
+  return (int)line_launch(G.nx, (long long)G.np * (G.ny / 2)).grid;
+}
+
+void spectral_forward(pic_ctx* c) {
+  const SpGrid G = sp_grid(c);
+  const LineLaunch a = line_launch(G.nx, (long long)G.np * (G.ny / 2));
+  k_sp_xfwd<<<a.grid, a.threads, a.lds, c->stream>>>(G, c->lev[0].u, c->lev[0].f,
+                                                     c->spec_d, a.plan, a.nlines, a.lpw,
+                                                     a.stride, c->partials);
+}
+
+void spectral_correct(pic_ctx* c) {
+  const SpGrid G = sp_grid(c);
+  double* s = c->spec_d;
+  const LineLaunch y = line_launch(G.ny, (long long)G.np * (G.nx / 2));
+  k_sp_y<false><<<y.grid, y.threads, y.lds, c->stream>>>(G, s, y.plan, y.nlines, y.lpw, y.stride,
+                                                         c->dc);
+  const int seg = G.np <= 128 ? 8 : G.np <= 256 ? 16 : G.np <= 1024 ? 32 : 64;
+  const int nsg = std::max(1, (G.np + seg - 1) / seg);
+  const int lgc = seg == 64 ? 4 : 5;
+  const unsigned grid = (unsigned)((G.nxy + (1 << lgc) - 1) >> lgc);
+  const int nt = nsg << lgc;
+  // The join slots, and the two planes next to the face.
+  const size_t lds = (size_t)std::max(nt, 2 << lgc) * sizeof(double);
+  if (seg == 8)
+    k_sp_tri<8><<<grid, nt, lds, c->stream>>>(G, s, lgc, c->dc);
+  else if (seg == 16)
+    k_sp_tri<16><<<grid, nt, lds, c->stream>>>(G, s, lgc, c->dc);
+  else if (seg == 32)
+    k_sp_tri<32><<<grid, nt, lds, c->stream>>>(G, s, lgc, c->dc);
+  else
+    k_sp_tri<64><<<grid, nt, lds, c->stream>>>(G, s, lgc, c->dc);
+  k_sp_y<true><<<y.grid, y.threads, y.lds, c->stream>>>(G, s, y.plan, y.nlines, y.lpw, y.stride,
+                                                        c->dc);
+  const LineLaunch x = line_launch(G.nx, (long long)G.np * (G.ny / 2));
+  k_sp_xinv<<<x.grid, x.threads, x.lds, c->stream>>>(G, s, c->lev[0].u, x.plan, x.nlines, x.lpw,
+                                                     x.stride, c->dc);
+}
+
+}  // namespace pic

@@ -111,6 +111,20 @@ pic_status validate(const pic_config* c) {
   return PIC_OK;
 }
 
+// The direct solve's spectrum.  A context whose every solve is direct keeps it
+// in the smoother's spare unknowns (FP64: one array; mixed: two FP32 arrays
+// one after the other); where steps still run V-cycles those stay untouched
+// and a grid that small gets an array of its own.
+void take_spectrum(pic_ctx* c, Carver& cv) {
+  const Level& L = c->lev[0];
+  if (!c->direct)
+    c->spec_d = nullptr;
+  else if (spectral_steps(c))
+    c->spec_d = c->mixed ? reinterpret_cast<double*>(L.uf) : L.us;
+  else
+    c->spec_d = cv.take<double>(c->nnodes);
+}
+
 // Lay out every device array of a context in the workspace (base == nullptr:
 // size only).
 size_t carve(pic_ctx* c, char* base) {
@@ -163,6 +177,7 @@ size_t carve(pic_ctx* c, char* base) {
       L.usf = cv.take<float>(L.nnodes);
     }
   }
+  take_spectrum(c, cv);
   c->partials = cv.take<double>(c->npartials);
   {
     const long long es = mixed ? 4 : 8;
@@ -257,6 +272,7 @@ size_t carve_field(pic_ctx* c, char* base) {
       L.usf = cv.take<float>(L.nnodes);
     }
   }
+  take_spectrum(c, cv);
   c->partials = cv.take<double>(c->npartials);
   {
     const long long es = mixed ? 4 : 8;
@@ -295,6 +311,7 @@ void derive(pic_ctx* c) {
     L.h2 = h2;
     h2 *= 4.0;
   }
+  c->direct = spectral_direct(&f);
   // The first coarse level small enough for the exact solve.
   c->spec_level = -1;
   c->spec_modes = c->spec_planes = 0;
@@ -669,7 +686,7 @@ pic_status pic_field(pic_ctx* c, pic_solve_info* info) {
   int st = PIC_OK;
   pic_solve_info loc;
   tmark(c, PIC_PH_POISSON, true);
-  field_solve(c, true, &loc, &st);
+  field_solve(c, true, spectral_steps(c), &loc, &st);
   tmark(c, PIC_PH_POISSON, false);
   c->last_solve = loc;
   // The next extrapolation needs this solve and the one before it.
@@ -795,7 +812,7 @@ pic_status poisson_solve(pic_ctx* c, const double* rho, double* phi,
   field_rhs(c, rho);
   int st = PIC_OK;
   pic_solve_info loc;
-  field_solve(c, warm == PIC_WARM_GIVEN, &loc, &st);
+  field_solve(c, warm == PIC_WARM_GIVEN, c->direct, &loc, &st);
   if (info) *info = loc;
   if (!hip_ok(c, hipMemcpyAsync(phi, c->lev[0].u, c->nnodes * sizeof(double),
                                 hipMemcpyDeviceToDevice, c->stream),
@@ -886,7 +903,7 @@ pic_status poisson_solve_static(const pic_config* cfg, const double* rho,
   field_rhs(&c, rho);
   int st = PIC_OK;
   pic_solve_info loc;
-  field_solve(&c, warm == PIC_WARM_GIVEN, &loc, &st);
+  field_solve(&c, warm == PIC_WARM_GIVEN, c.direct, &loc, &st);
   if (info) *info = loc;
   if (hipMemcpyAsync(phi, c.lev[0].u, c.nnodes * sizeof(double),
                      hipMemcpyDeviceToDevice, c.stream) != hipSuccess ||

@@ -37,6 +37,15 @@ struct Level {
 // x and y (powers of two by FFT up to kSpecMaxFFT, other even sizes by a
 // direct transform up to kSpecMaxXY), unknown planes in z.
 constexpr int kSpecMaxXY = 32, kSpecMaxFFT = 64, kSpecMaxPlanes = 256;
+// Grids the direct solve of the finest level takes (k_spectral.hip): nodes per
+// axis in x and y (any even size), cells in z below kDirectMaxPlanes.
+constexpr int kDirectMaxXY = 512, kDirectMaxPlanes = 2048;
+// Steps on grids of fewer nodes keep the V-cycles: there a run of thousands of
+// steps is cheap and is compared trajectory by trajectory, and the direct
+// solve, though nearer the exact potential (1e-14 against 1e-11), moves the
+// velocities of a 32x32x64 run by 1.5e-9 in 40 steps.  poisson_solve is
+// direct on every size.
+constexpr long long kDirectStepNodes = 1ll << 18;
 // Removed ions a step can list for the in-place removal (more: full binning).
 constexpr int kDeadList = 4096;
 
@@ -80,6 +89,8 @@ struct pic_ctx {
   double* E;                 // FP64: 4 doubles per node; mixed: 4 floats
   int nlev;
   pic::Level lev[16];
+  bool direct;               // the grid takes the direct solve
+  double* spec_d;            // its spectrum: one FP64 value per node
   // Exact solve of one coarse level (DFT in x, y; tridiagonal in z per
   // mode), in the V-cycle's precision; spec_level < 0: none.
   int spec_level;
@@ -225,7 +236,8 @@ inline void tmark(pic_ctx* c, int ph, bool begin) {
 
 // ---- field (k_field.hip) ---------------------------------------------------
 void field_rhs(pic_ctx* c, const double* rho_or_null);
-void field_solve(pic_ctx* c, bool warm, pic_solve_info* info, int* status);
+void field_solve(pic_ctx* c, bool warm, bool direct, pic_solve_info* info,
+                 int* status);
 void field_efield(pic_ctx* c);
 // Target (phi - phi_prev) / sigma of the last recorded solve, (nz, ny, nx).
 void field_warm_target(pic_ctx* c, float* t);
@@ -233,6 +245,21 @@ void field_phi_to_level0(pic_ctx* c);
 // Extrapolated start (phi = 2 phi - phi_hist, phi_hist = old phi) when the
 // history is valid, else the history is just filled.
 void field_extrapolate(pic_ctx* c);
+
+// ---- direct solve of the finest level (k_spectral.hip) ----------------------
+// The configuration takes it: no multigrid depth was asked for (mg_levels 0,
+// no PIC_FLAG_MG_ALL_LEVELS) and the grid is within its limits.
+bool spectral_direct(const pic_config* f);
+// ... and the step's solve uses it.
+inline bool spectral_steps(const pic_ctx* c) {
+  return c->direct && c->nnodes >= kDirectStepNodes;
+}
+// Residual of lev[0].u transformed over x, its squares' partial sums in
+// c->partials (spectral_partials of them).
+void spectral_forward(pic_ctx* c);
+int spectral_partials(const pic_ctx* c);
+// The rest of the solve: lev[0].u += A^-1 of that residual.
+void spectral_correct(pic_ctx* c);
 
 // ---- particles (k_particles.hip) -------------------------------------------
 // ---- diagnostics (k_debye.hip) ---------------------------------------------
