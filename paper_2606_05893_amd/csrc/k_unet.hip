@@ -15,6 +15,7 @@
 // reduction runs over voxels, staged through LDS.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <new>
@@ -688,71 +689,166 @@ __global__ void __launch_bounds__(256) k_conv3p(
   }
 }
 
-// Weight gradient dW[co][k] += sum_v g[v][co] x[v + tap(k)][ci(k)] over a
-// chunk of voxels (dW unpadded: row stride 27 CIN); a workgroup owns 64 columns of k, each wave 16 of them
-// for all COUT rows.  32-voxel slices of g and x are staged in LDS.
+// Four rows of 16 bf16 read from LDS transposed (ds_read_b64_tr_b16): within
+// 16 lanes, lane 4r + c supplies the address of row r's elements 4c .. 4c + 3
+// and lane i receives element i of the four rows.
+typedef short s4v __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) s4v* lds_s4;
+__device__ __forceinline__ bf16x8 lds_tr8(const char* r0, const char* r4) {
+  s4v v[2];
+  v[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)r0);
+  v[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)r4);
+  bf16x8 r;
+  __builtin_memcpy(&r, v, 16);
+  return r;
+}
+
+// Weight gradient dW[co][tap][ci] += sum_v g[v][co] x[v + tap][ci] as a GEMM
+// whose K runs over voxels: an MFMA takes 32 voxels (two rows of 16, P planes
+// apart) of 16 output channels of g against the same rows of x shifted by the
+// tap, and a wave keeps the 27 taps' 16 x 16 sums of one (co tile, ci slice)
+// pair in registers over every tile its workgroup visits.  The voxel-major
+// operands come straight from the channels-last halo by transposing LDS reads,
+// so a tap's shift is an address offset.  A wave holds the g rows of a YB x P
+// block of row pairs and reads each x row pair of the surrounding halo once
+// per x shift for every (dy, dz) that reaches it: 3 (YB + 2)(P + 2) + YB P
+// fragment reads for 27 YB P products.  A workgroup's waves take WM tiles of
+// output channels and split the tile's y rows WK ways; their sums meet in LDS
+// and go to dW as one atomic add per element and workgroup.
+//
+// Bound: the latency between two barriers (staging stores, fragment reads,
+// products) at two wavefronts a SIMD, which the 27 accumulators cost; the LDS
+// reads alone take 0.95 of the matrix time with YB = 2 and 0.7 with YB = 4.
+// YB = 4 for 32 output channels spilled beside the prefetched tile (96 -> 32
+// at 64x64x256: 358 us against 203), three wavefronts a SIMD spilled
+// everywhere (16 -> 16: 414 against 158), and without the prefetch 48 -> 16
+// took 806 us against 491.  At 128x128x512, against one 32-voxel chunk at a
+// time gathered through LDS by 2-byte reads: 16 -> 16 1944 -> 158 us, 48 -> 16
+// 4979 -> 491, 96 -> 32 1298 -> 203, 64 -> 64 194 -> 77; the whole gradient
+// 22.2 -> 11.2 ms.
+template <int COUT>
+struct WgTile {
+  static constexpr int M = COUT / 16;
+  static constexpr int WM = M < 4 ? M : 4, WK = 4 / WM;
+  static constexpr int YB = M <= 2 ? 2 : 4, P = 2;
+  static constexpr int TY = YB * WK, TZ = 2 * P;
+  static constexpr int HY = TY + 2, HZ = TZ + 2, HV = 18 * HY * HZ;
+  static constexpr int GV = 16 * TY * TZ;
+};
+
 template <int CIN, int COUT>
-__global__ void __launch_bounds__(256) k_wgrad3(const bf16* __restrict__ x,
+__global__ void __launch_bounds__(256, 2) k_wgrad3(const bf16* __restrict__ x,
                                                 const bf16* __restrict__ g,
-                                                float* __restrict__ dW, Dims d,
-                                                long long chunk) {
-  constexpr int MT = COUT / 16;
-  __shared__ __attribute__((aligned(16))) bf16 gs[32][COUT];
-  __shared__ __attribute__((aligned(16))) bf16 xs[32][64];
+                                                float* __restrict__ dW, Dims d, int nsp) {
+  using T = WgTile<COUT>;
+  constexpr int WM = T::WM, WK = T::WK, YB = T::YB, P = T::P;
+  constexpr int TY = T::TY, TZ = T::TZ, HY = T::HY, HZ = T::HZ, HV = T::HV, GV = T::GV;
+  constexpr int kRed = WK > 1 ? WM * 27 * 256 * 4 / 16 : 0;  // sums' exchange, uint4
+  constexpr int kStage = 2 * HV + 2 * GV * WM;
+  // Halo of x (two planes of 16-byte halves), then g per co tile alike.
+  __shared__ uint4 lds[kStage > kRed ? kStage : kRed];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int kbase = blockIdx.x * 64;
-  const long long v0 = (long long)blockIdx.y * chunk;
-  long long v1 = v0 + chunk;
-  if (v1 > d.V) v1 = d.V;
-  f4 acc[MT];
-  for (int m = 0; m < MT; ++m) acc[m] = f4{0.f, 0.f, 0.f, 0.f};
-  for (long long vs = v0; vs < v1; vs += 32) {
-    // Stage g (32 x COUT) and x (32 x 64 columns).
-    for (int q = threadIdx.x; q < 32 * COUT / 8; q += 256) {
-      const int vr = q / (COUT / 8), c8 = (q % (COUT / 8)) * 8;
-      const long long v = vs + vr;
-      uint4 val = make_uint4(0, 0, 0, 0);
-      if (v < v1) val = *reinterpret_cast<const uint4*>(g + v * COUT + c8);
-      *reinterpret_cast<uint4*>(&gs[vr][c8]) = val;
+  const int wm = wave % WM, wk = wave / WM;
+  // The pairs of one run of tiles are neighbours, so they share its lines in
+  // one XCD's L2.
+  constexpr int kPairs = (CIN / 16) * (COUT / 16 / WM);
+  const int bi = (int)xcd_block(blockIdx.x, gridDim.x);
+  const int pair = bi % kPairs, wg = bi / kPairs;
+  const int sl = pair % (CIN / 16), mg = pair / (CIN / 16) * WM;
+  const int ntx = (d.W + 15) / 16, nty = (d.H + TY - 1) / TY, ntz = (d.D + TZ - 1) / TZ;
+  const int ntiles = ntx * nty * ntz;
+  const char* lx = reinterpret_cast<const char*>(lds);
+  const char* lg = lx + (size_t)(2 * HV + 2 * GV * wm) * 16;
+  // This lane's part of a transposed read: row (q >> 2) of four voxels, 8-byte
+  // part q & 3; lane group kg takes voxels 8 (kg & 1) of the pair's row kg >> 1.
+  const int q = lane & 15, kg = lane >> 4;
+  const int vx = 8 * (kg & 1) + (q >> 2);
+  const int offx = ((q >> 1) & 1) * HV * 16 + (q & 1) * 8 +
+                   (((kg >> 1) * P * HY + wk * YB) * 18 + vx) * 16;
+  const int offg = ((q >> 1) & 1) * GV * 16 + (q & 1) * 8 +
+                   (((kg >> 1) * P * TY + wk * YB) * 16 + vx) * 16;
+  f4 acc[27];
+#pragma unroll
+  for (int t = 0; t < 27; ++t) acc[t] = f4{0.f, 0.f, 0.f, 0.f};
+  // Neighbouring tiles share halo voxels: a contiguous run per workgroup.
+  const int t0 = (int)((long long)ntiles * wg / nsp);
+  const int t1 = (int)((long long)ntiles * (wg + 1) / nsp);
+  // The next tile's loads are in flight while the current one is multiplied.
+  constexpr int PER = 2 * GV * WM / 256;
+  HaloRegs<18, HY, HZ, 256> hr;
+  uint4 gr[PER];
+  auto load = [&](int t) {
+    const int tx = t % ntx, r = t / ntx;
+    const int x0 = tx * 16, y0 = (r % nty) * TY, z0 = (r / nty) * TZ;
+    halo_load_c<18, HY, HZ, 256, false>(hr, x, CIN, sl * 16, d, x0, y0, z0);
+#pragma unroll
+    for (int m = 0; m < PER; ++m) {
+      const int e = (int)threadIdx.x + m * 256;
+      const int c8 = e % (2 * WM), v = e / (2 * WM);
+      const int gx = x0 + (v & 15), gy = y0 + (v >> 4) % TY, gz = z0 + (v >> 4) / TY;
+      gr[m] = make_uint4(0, 0, 0, 0);
+      if (gx < d.W && gy < d.H && gz < d.D)
+        gr[m] = ld16(g + (((size_t)gz * d.H + gy) * d.W + gx) * COUT + mg * 16 + c8 * 8);
     }
-    {
-      const int q = threadIdx.x;            // 32 voxels x 8 groups of 8
-      const int vr = q >> 3, kg = (q & 7) * 8;
-      const long long v = vs + vr;
-      const int k = kbase + kg;
-      const int tap = k / CIN, c = k - tap * CIN;
-      uint4 val = make_uint4(0, 0, 0, 0);
-      if (v < v1 && tap < 27) {
-        const int xq = (int)(v % d.W), yq = (int)((v / d.W) % d.H),
-                  zq = (int)(v / ((long long)d.W * d.H));
-        const long long nv = nb_voxel(d, zq, yq, xq, tap);
-        if (nv >= 0) val = *reinterpret_cast<const uint4*>(x + nv * CIN + c);
-      }
-      *reinterpret_cast<uint4*>(&xs[vr][kg]) = val;
+  };
+  if (t0 < t1) load(t0);
+  for (int t = t0; t < t1; ++t) {
+    halo_store(lds, hr);
+#pragma unroll
+    for (int m = 0; m < PER; ++m) {
+      const int e = (int)threadIdx.x + m * 256;
+      lds[2 * HV + (e % (2 * WM)) * GV + e / (2 * WM)] = gr[m];
     }
     __syncthreads();
-    bf16x8 b;
-    {
-      bf16 tmp[8];
-      for (int j = 0; j < 8; ++j) tmp[j] = xs[8 * (lane >> 4) + j][wave * 16 + (lane & 15)];
-      __builtin_memcpy(&b, tmp, 16);
-    }
-    for (int m = 0; m < MT; ++m) {
-      bf16 tmp[8];
-      for (int j = 0; j < 8; ++j) tmp[j] = gs[8 * (lane >> 4) + j][m * 16 + (lane & 15)];
-      bf16x8 a;
-      __builtin_memcpy(&a, tmp, 16);
-      acc[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc[m], 0, 0, 0);
-    }
+    if (t + 1 < t1) load(t + 1);
+    bf16x8 a[YB][P];
+#pragma unroll
+    for (int y = 0; y < YB; ++y)
+#pragma unroll
+      for (int z = 0; z < P; ++z) {
+        const char* p = lg + offg + (z * TY + y) * 16 * 16;
+        a[y][z] = lds_tr8(p, p + 64);
+      }
+#pragma unroll
+    for (int hz = 0; hz < P + 2; ++hz)
+#pragma unroll
+      for (int hy = 0; hy < YB + 2; ++hy)
+#pragma unroll
+        for (int ox = 0; ox < 3; ++ox) {
+          const char* p = lx + offx + ((hz * HY + hy) * 18 + ox) * 16;
+          const bf16x8 b = lds_tr8(p, p + 64);
+#pragma unroll
+          for (int oz = 0; oz < 3; ++oz)
+#pragma unroll
+            for (int oy = 0; oy < 3; ++oy) {
+              const int y = hy - oy, z = hz - oz;
+              if (y >= 0 && y < YB && z >= 0 && z < P)
+                acc[(oz * 3 + oy) * 3 + ox] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                    a[y][z], b, acc[(oz * 3 + oy) * 3 + ox], 0, 0, 0);
+            }
+        }
     __syncthreads();
   }
-  const int k = kbase + wave * 16 + (lane & 15);
-  if (k >= 27 * CIN) return;
-  for (int m = 0; m < MT; ++m)
-    for (int j = 0; j < 4; ++j) {
-      const int co = m * 16 + 4 * (lane >> 4) + j;
-      atomicAdd(&dW[(long long)co * (27 * CIN) + k], acc[m][j]);
+  if constexpr (WK > 1) {
+    f4* red = reinterpret_cast<f4*>(lds) + wm * 27 * 64 + lane;
+    for (int k = 1; k < WK; ++k) {
+      if (wk == k)
+#pragma unroll
+        for (int t = 0; t < 27; ++t) red[t * 64] = acc[t];
+      __syncthreads();
+      if (wk == 0)
+#pragma unroll
+        for (int t = 0; t < 27; ++t) acc[t] = acc[t] + red[t * 64];
+      __syncthreads();
     }
+  }
+  if (wk) return;
+  const int co0 = (mg + wm) * 16 + 4 * kg, ci = sl * 16 + q;
+#pragma unroll
+  for (int t = 0; t < 27; ++t)
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      atomicAdd(&dW[(long long)(co0 + j) * (27 * CIN) + t * CIN + ci], acc[t][j]);
 }
 
 // First layer (2 input channels): FP32 arithmetic, 16 outputs per voxel.
@@ -1408,11 +1504,15 @@ void conv_upcat_launch(hipStream_t st, const bf16* coarse, const bf16* skip,
 template <int CIN, int COUT>
 void wgrad_launch(hipStream_t st, const bf16* x, const bf16* g, float* dW,
                   Dims d) {
-  long long chunk = d.V / 256;
-  if (chunk < 2048) chunk = 2048;
-  chunk = (chunk + 31) / 32 * 32;
-  dim3 grid(kpad(CIN) / 64, (unsigned)((d.V + chunk - 1) / chunk));
-  pic::k_wgrad3<CIN, COUT><<<grid, 256, 0, st>>>(x, g, dW, d, chunk);
+  using T = pic::WgTile<COUT>;
+  const long long ntiles = (long long)((d.W + 15) / 16) * ((d.H + T::TY - 1) / T::TY) *
+                           ((d.D + T::TZ - 1) / T::TZ);
+  // One round of resident workgroups over all (co, ci) pairs, at least two
+  // tiles each: every workgroup ends with 27 x 256 atomic adds per pair.
+  const int pairs = (CIN / 16) * ((COUT / 16) / T::WM);
+  const int round = 512;
+  const long long want = std::max(1LL, std::min<long long>(round / pairs, (ntiles + 1) / 2));
+  pic::k_wgrad3<CIN, COUT><<<(unsigned)(pairs * want), 256, 0, st>>>(x, g, dW, d, (int)want);
 }
 
 bool wgrad(hipStream_t st, int cin, int cout, const bf16* x, const bf16* g,
