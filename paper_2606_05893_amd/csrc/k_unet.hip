@@ -39,6 +39,12 @@ __device__ __forceinline__ float bf2f(bf16 h) {
 }
 typedef __bf16 bf16x2v __attribute__((ext_vector_type(2)));
 typedef float f2v __attribute__((ext_vector_type(2)));
+// The gradient word g (two BF16 values) where the activations y are positive.
+__device__ __forceinline__ unsigned relu_mask2(unsigned g, unsigned y) {
+  const unsigned lo = __uint_as_float(y << 16) > 0.f ? g & 0xffffu : 0u;
+  const unsigned hi = __uint_as_float(y & 0xffff0000u) > 0.f ? g & 0xffff0000u : 0u;
+  return lo | hi;
+}
 // Round to nearest even (the CDNA4 conversion instruction, two at a time).
 __device__ __forceinline__ unsigned f2bf2(float lo, float hi) {
   const bf16x2v h = __builtin_convertvector((f2v){lo, hi}, bf16x2v);
@@ -253,105 +259,128 @@ __device__ __forceinline__ void stage_halo(uint4* lds, const bf16* __restrict__ 
 }
 
 
-// out = act(conv(in) + bias), LDS-tiled.  A workgroup owns an output tile
-// of 16 (x) x TY x TZ voxels; per slice of 16 input channels it stages the
-// tile's halo (18 x (TY+2) x (TZ+2) voxels, 32 B each, x and y periodic, z
-// zero-padded) in LDS, so an input voxel is read from memory about twice
-// per layer instead of once per tap; the two 8-channel halves of a voxel sit
-// in separate LDS planes so that 16 lanes reading consecutive voxels touch
-// 256 contiguous bytes.  A K-chunk of 32 is two taps x 16
-// channels (lane group g = lane / 16: tap 2c + g / 2, channels 8 (g % 2) ..
-// +7); the A operand comes from LDS, the B operand (weights) from the
-// cache.  Each wave owns MT rows of 16 voxels and all COUT / 16 column
-// tiles, with MT * COUT / 16 <= 16 accumulator tiles.
-template <int CIN, int COUT, int TY, int TZ>
-__global__ void __launch_bounds__(256) k_conv3t(const bf16* __restrict__ in,
-                                                const bf16* __restrict__ Wk,
-                                                const float* __restrict__ bias,
-                                                bf16* __restrict__ out, Dims d,
-                                                int relu) {
-  constexpr int NT = COUT / 16;
-  constexpr int TX = 16;
-  constexpr int HX = TX + 2, HY = TY + 2, HZ = TZ + 2;
+// out = conv(in) for the backward-data shapes of the decoders' concatenations
+// (48, 96 and 192 output channels).  A workgroup owns 48 output channels of a
+// tile of 16 (x) x 8 x 4 voxels; per slice of 16 input channels it stages the
+// tile's halo (x and y periodic, z zero-padded) in LDS, the two 8-channel
+// halves of a voxel in separate planes, and the slice's weights in operand
+// order.  A K-chunk of 32 is two taps x 16 channels (lane group g = lane / 16:
+// tap 2c + g / 2, channels 8 (g % 2) .. +7).  Each wave owns eight rows of 16
+// voxels and the three column tiles (the product taken as W X, so a lane ends
+// with four consecutive channels of one voxel): 8 + 3 LDS reads for 24
+// products, below the LDS rate.  The coarse part (the first 2 CIN channels) and
+// the skip part of the gradient go to tensors of their own.  With one slice the weights are staged once and the workgroup
+// runs over many tiles.
+//
+// Bound: matrix products and the staging they wait for.  With the weights read
+// from the cache for every four rows the kernel waited on those loads: 16 -> 48
+// at 128x128x512 832 us, 32 -> 96 at half of that 651, 64 -> 192 at a quarter
+// 590; 356, 207 and 106 now.
+template <int CIN>
+__global__ void __launch_bounds__(256, 2) k_conv3w(const bf16* __restrict__ in,
+                                                   const bf16* __restrict__ Wk,
+                                                   bf16* __restrict__ gup,
+                                                   bf16* __restrict__ gskip, Dims d, int nsp) {
+  constexpr int NT = 3, MT = 8, TY = 8, TZ = 4;
+  constexpr int HX = 18, HY = TY + 2, HZ = TZ + 2;
   constexpr int HV = HX * HY * HZ;
-  constexpr int MT = TY * TZ / 4;
   constexpr int KPAD = KP(CIN);
   constexpr int NS = CIN / 16;
-  static_assert(CIN % 16 == 0 && COUT % 16 == 0, "channel multiples of 16");
-  static_assert(MT >= 1 && MT * NT <= 16, "accumulator budget");
   __shared__ uint4 lds[HV * 2];
+  __shared__ uint4 lw[14 * NT * 64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int ntx = (d.W + TX - 1) / TX, nty = (d.H + TY - 1) / TY;
-  // Neighbouring tiles share halo voxels: keep them on one XCD's L2.
-  int bi = (int)xcd_block(blockIdx.x, gridDim.x);
-  const int tx = bi % ntx;
-  bi /= ntx;
-  const int ty = bi % nty, tz = bi / nty;
-  const int x0 = tx * TX, y0 = ty * TY, z0 = tz * TZ;
+  const int ntx = (d.W + 15) / 16, nty = (d.H + TY - 1) / TY, ntz = (d.D + TZ - 1) / TZ;
+  const int ntiles = ntx * nty * ntz;
+  // 2 CIN channels of the coarse part, CIN of the skip part.
+  constexpr int groups = CIN / 16, CU = 2 * CIN;
+  // The channel groups of one run of tiles are neighbours on one XCD.
+  const int bi = (int)xcd_block(blockIdx.x, gridDim.x);
+  const int cg = bi % groups, wg = bi / groups;
+  const int t0 = (int)((long long)ntiles * wg / nsp);
+  const int t1 = (int)((long long)ntiles * (wg + 1) / nsp);
   const int kg = lane >> 4, rl = lane & 15;
-  const int half = kg & 1;
-  f4 acc[MT][NT];
+  auto stage_w = [&](int sl) {
+    for (int e = threadIdx.x; e < 14 * NT * 64; e += 256) {
+      const int l = e & 63, cn = e >> 6, nt = cn % NT, ch = cn / NT;
+      const int tap = 2 * ch + (l >> 5);
+      uint4 v = make_uint4(0, 0, 0, 0);
+      if (tap < 27)
+        v = ld16(Wk + (size_t)(cg * 48 + nt * 16 + (l & 15)) * KPAD + tap * CIN + sl * 16 +
+                 ((l >> 4) & 1) * 8);
+      lw[e] = v;
+    }
+  };
+  if (NS == 1) stage_w(0);
+  const uint4* la = lds + (kg & 1) * HV + rl;
+  HaloRegs<HX, HY, HZ, 256> hr;
+  auto load = [&](int t, int sl) {
+    const int tx = t % ntx, r = t / ntx;
+    halo_load(hr, in, CIN, d, tx * 16, (r % nty) * TY, (r / nty) * TZ, sl);
+  };
+  // The next tile's halo is in flight during the products where the weights
+  // stay; restaging them beside it would spill.
+  if (NS == 1 && t0 < t1) load(t0, 0);
+  for (int t = t0; t < t1; ++t) {
+    f4 acc[MT][NT];
 #pragma unroll
-  for (int mt = 0; mt < MT; ++mt)
+    for (int m = 0; m < MT; ++m)
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = f4{0.f, 0.f, 0.f, 0.f};
-  for (int sl = 0; sl < NS; ++sl) {
-    stage_halo<CIN, 0, HX, HY, HZ, 256>(lds, in, nullptr, d, x0, y0, z0, sl);
-    __syncthreads();
-    // Chunks 0..12 hold two taps; chunk 13 holds tap 26 and padding.
-    auto chunk = [&](int ch, bool last) {
-      const int tap = 2 * ch + (kg >> 1);
-      const bool tv = !last || tap < 27;
-      const int oz = tap / 9, oy = (tap / 3) % 3, ox = tap % 3;
-      bf16x8 b[NT];
+      for (int n = 0; n < NT; ++n) acc[m][n] = f4{0.f, 0.f, 0.f, 0.f};
+    for (int sl = 0; sl < NS; ++sl) {
+      if (NS > 1) load(t, sl);
+      halo_store(lds, hr);
+      if (NS > 1) stage_w(sl);
+      __syncthreads();
+      if (NS == 1 && t + 1 < t1) load(t + 1, 0);
+#pragma unroll 2
+      for (int ch = 0; ch < 14; ++ch) {
+        // Chunk 13 holds tap 26 and a slot of zero weights.
+        const int tap = min(2 * ch + (kg >> 1), 26);
+        const int oz = tap / 9, oy = (tap / 3) % 3, ox = tap % 3;
+        bf16x8 b[NT];
 #pragma unroll
-      for (int nt = 0; nt < NT; ++nt)
-        b[nt] = tv ? load8(Wk + (size_t)(nt * 16 + rl) * KPAD + tap * CIN + sl * 16 + half * 8)
-                   : zero8();
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt) {
-        const int r = wave * MT + mt;
-        const int ly = r % TY, lz = r / TY;
-        const int hv = ((lz + oz) * HY + (ly + oy)) * HX + rl + ox;
-        bf16x8 a = zero8();
-        if (tv) {
-          const uint4 w = lds[half * HV + hv];
-          __builtin_memcpy(&a, &w, 16);
+        for (int n = 0; n < NT; ++n) {
+          const uint4 w = lw[(ch * NT + n) * 64 + lane];
+          __builtin_memcpy(&b[n], &w, 16);
         }
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
-          acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b[nt], acc[mt][nt], 0, 0, 0);
+        for (int m = 0; m < MT; ++m) {
+          // Rows wave * 8 + m: y = m, z = wave.
+          const uint4 w = la[((wave + oz) * HY + m + oy) * HX + ox];
+          bf16x8 a;
+          __builtin_memcpy(&a, &w, 16);
+#pragma unroll
+          for (int n = 0; n < NT; ++n)
+            acc[m][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[n], a, acc[m][n], 0, 0, 0);
+        }
       }
-    };
-#pragma unroll 1
-    for (int ch = 0; ch < 13; ++ch) chunk(ch, false);
-    chunk(13, true);
-    __syncthreads();
-  }
-#pragma unroll
-  for (int mt = 0; mt < MT; ++mt) {
-    const int r = wave * MT + mt;
-    const int gy = y0 + r % TY, gz = z0 + r / TY;
-    if (gy >= d.H || gz >= d.D) continue;
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
-      const int co = nt * 16 + rl;
-      const float bv = bias ? bias[co] : 0.0f;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int x = x0 + 4 * kg + j;
-        if (x >= d.W) continue;
-        float v = acc[mt][nt][j] + bv;
-        if (relu) v = v > 0.0f ? v : 0.0f;
-        out[(((size_t)gz * d.H + gy) * d.W + x) * COUT + co] = f2bf(v);
-      }
+      __syncthreads();
     }
+    const int tx = t % ntx, r = t / ntx;
+    const int gx = tx * 16 + rl, y0 = (r % nty) * TY, gz = (r / nty) * TZ + wave;
+    if (gz < d.D && gx < d.W)
+#pragma unroll
+      for (int m = 0; m < MT; ++m) {
+        if (y0 + m >= d.H) continue;
+        const size_t v = ((size_t)gz * d.H + y0 + m) * d.W + gx;
+#pragma unroll
+        for (int n = 0; n < NT; ++n) {
+          // Four consecutive channels of one voxel, of one part.
+          const int c = cg * 48 + n * 16, c4 = c + 4 * kg;
+          uint2 w;
+          w.x = f2bf2(acc[m][n][0], acc[m][n][1]);
+          w.y = f2bf2(acc[m][n][2], acc[m][n][3]);
+          *reinterpret_cast<uint2*>(c < CU ? gup + v * CU + c4 : gskip + v * CIN + (c4 - CU)) = w;
+        }
+      }
   }
 }
 
-// out = act(conv(in) + bias), register-blocked over output rows.  A
+// out = act(conv(in) + bias), register-blocked over output rows; with a mask
+// (backward data: the activations the gradient goes to) the stored values are
+// zeroed where it is not positive.  A
 // workgroup owns an output tile of 16 (x) x 4WY x 4WZ voxels and stages its
-// halo per slice of 16 input channels in LDS as k_conv3t does.  Each wave
+// halo per slice of 16 input channels in LDS (two 8-channel planes).  Each wave
 // owns one 16-channel tile of C_out and a block of 4 x 4 output rows (y, z)
 // of 16 voxels.  An input row of the halo is one MFMA operand whose K of 32
 // is two x-offsets of the row (x offsets 0 and 1, or 2 and a slot whose
@@ -368,11 +397,11 @@ __global__ void __launch_bounds__(256) k_conv3t(const bf16* __restrict__ in,
 // With CU > 0 the input is the decoder's concatenation [up(in), skip]
 // formed in the staging (in: CU channels at half the dims; skip: CIN - CU
 // channels), so the concatenated tensor is never written.
-template <int CIN, int COUT, int WY, int WZ, int CU = 0>
+template <int CIN, int COUT, int WY, int WZ, int CU = 0, bool MASK = false>
 __global__ void __launch_bounds__(64 * (COUT / 16) * WY * WZ) k_conv3r(
     const bf16* __restrict__ in, const bf16* __restrict__ skip,
     const bf16* __restrict__ Wk, const float* __restrict__ bias,
-    bf16* __restrict__ out, Dims d, int relu) {
+    bf16* __restrict__ out, Dims d, int relu, const bf16* __restrict__ mask) {
   static_assert(CU % 16 == 0 && CU < CIN, "concatenation split on slices");
   constexpr int NTC = COUT / 16, RY = 4, RZ = 4;
   constexpr int TX = 16, TY = WY * RY, TZ = WZ * RZ;
@@ -523,6 +552,17 @@ __global__ void __launch_bounds__(64 * (COUT / 16) * WY * WZ) k_conv3r(
 #pragma unroll
   for (int j = 0; j < 4; ++j) bv[j] = bias ? bias[c0 + j] : 0.0f;
   if (x < d.W) {
+    // The mask words of all rows in flight before the first is needed.
+    uint2 mw[RZ][RY];
+    if constexpr (MASK)
+#pragma unroll
+      for (int zo = 0; zo < RZ; ++zo)
+#pragma unroll
+        for (int yo = 0; yo < RY; ++yo) {
+          const int gy = min(y0 + wy * RY + yo, d.H - 1), gz = min(z0 + wz * RZ + zo, d.D - 1);
+          mw[zo][yo] = *reinterpret_cast<const uint2*>(
+              mask + (((size_t)gz * d.H + gy) * d.W + x) * COUT + c0);
+        }
 #pragma unroll
     for (int zo = 0; zo < RZ; ++zo)
 #pragma unroll
@@ -538,7 +578,12 @@ __global__ void __launch_bounds__(64 * (COUT / 16) * WY * WZ) k_conv3r(
         uint2 w;
         w.x = f2bf2(v[0], v[1]);
         w.y = f2bf2(v[2], v[3]);
-        *reinterpret_cast<uint2*>(out + (((size_t)gz * d.H + gy) * d.W + x) * COUT + c0) = w;
+        const size_t o = (((size_t)gz * d.H + gy) * d.W + x) * COUT + c0;
+        if constexpr (MASK) {
+          w.x = relu_mask2(w.x, mw[zo][yo].x);
+          w.y = relu_mask2(w.y, mw[zo][yo].y);
+        }
+        *reinterpret_cast<uint2*>(out + o) = w;
       }
   }
 }
@@ -706,7 +751,8 @@ __device__ __forceinline__ bf16x8 lds_tr8(const char* r0, const char* r4) {
 // Weight gradient dW[co][tap][ci] += sum_v g[v][co] x[v + tap][ci] as a GEMM
 // whose K runs over voxels: an MFMA takes 32 voxels (two rows of 16, P planes
 // apart) of 16 output channels of g against the same rows of x shifted by the
-// tap, and a wave keeps the 27 taps' 16 x 16 sums of one (co tile, ci slice)
+// tap (with CU > 0 x is the decoder's concatenation formed in the staging, as in
+// the forward pass), and a wave keeps the 27 taps' 16 x 16 sums of one (co tile, ci slice)
 // pair in registers over every tile its workgroup visits.  The voxel-major
 // operands come straight from the channels-last halo by transposing LDS reads,
 // so a tap's shift is an address offset.  A wave holds the g rows of a YB x P
@@ -724,8 +770,7 @@ __device__ __forceinline__ bf16x8 lds_tr8(const char* r0, const char* r4) {
 // everywhere (16 -> 16: 414 against 158), and without the prefetch 48 -> 16
 // took 806 us against 491.  At 128x128x512, against one 32-voxel chunk at a
 // time gathered through LDS by 2-byte reads: 16 -> 16 1944 -> 158 us, 48 -> 16
-// 4979 -> 491, 96 -> 32 1298 -> 203, 64 -> 64 194 -> 77; the whole gradient
-// 22.2 -> 11.2 ms.
+// 4979 -> 491, 96 -> 32 1298 -> 203, 64 -> 64 194 -> 79.
 template <int COUT>
 struct WgTile {
   static constexpr int M = COUT / 16;
@@ -736,10 +781,30 @@ struct WgTile {
   static constexpr int GV = 16 * TY * TZ;
 };
 
-template <int CIN, int COUT>
+// The bias sums of the workgroup's four waves (wave w: output channel tile
+// w % wm) joined in LDS and added by one request: the 16 floats of a tile are
+// one line, and an add per wave and row from every workgroup queued on it for
+// 100 us.
+__device__ __forceinline__ void bias_out(float* lds, f4 accb, float* db, int wm, bool on) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  if ((lane & 15) == 0)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) lds[wave * 16 + 4 * (lane >> 4) + j] = accb[j];
+  __syncthreads();
+  if (on && (int)threadIdx.x < 16 * wm) {
+    float v = 0.f;
+    for (int w = threadIdx.x >> 4; w < 4; w += wm) v += lds[w * 16 + (threadIdx.x & 15)];
+    atomicAdd(&db[threadIdx.x], v);
+  }
+  __syncthreads();
+}
+
+template <int CIN, int COUT, int CU>
 __global__ void __launch_bounds__(256, 2) k_wgrad3(const bf16* __restrict__ x,
-                                                const bf16* __restrict__ g,
-                                                float* __restrict__ dW, Dims d, int nsp) {
+                                                   const bf16* __restrict__ skip,
+                                                   const bf16* __restrict__ g,
+                                                   float* __restrict__ dW,
+                                                   float* __restrict__ db, Dims d, int nsp) {
   using T = WgTile<COUT>;
   constexpr int WM = T::WM, WK = T::WK, YB = T::YB, P = T::P;
   constexpr int TY = T::TY, TZ = T::TZ, HY = T::HY, HZ = T::HZ, HV = T::HV, GV = T::GV;
@@ -770,6 +835,10 @@ __global__ void __launch_bounds__(256, 2) k_wgrad3(const bf16* __restrict__ x,
   f4 acc[27];
 #pragma unroll
   for (int t = 0; t < 27; ++t) acc[t] = f4{0.f, 0.f, 0.f, 0.f};
+  f4 accb = f4{0.f, 0.f, 0.f, 0.f};
+  bf16x8 ones;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) ones[e] = (__bf16)1.0f;
   // Neighbouring tiles share halo voxels: a contiguous run per workgroup.
   const int t0 = (int)((long long)ntiles * wg / nsp);
   const int t1 = (int)((long long)ntiles * (wg + 1) / nsp);
@@ -780,7 +849,7 @@ __global__ void __launch_bounds__(256, 2) k_wgrad3(const bf16* __restrict__ x,
   auto load = [&](int t) {
     const int tx = t % ntx, r = t / ntx;
     const int x0 = tx * 16, y0 = (r % nty) * TY, z0 = (r / nty) * TZ;
-    halo_load_c<18, HY, HZ, 256, false>(hr, x, CIN, sl * 16, d, x0, y0, z0);
+    halo_load_cat<CIN, CU>(hr, x, skip, d, x0, y0, z0, sl);
 #pragma unroll
     for (int m = 0; m < PER; ++m) {
       const int e = (int)threadIdx.x + m * 256;
@@ -827,8 +896,16 @@ __global__ void __launch_bounds__(256, 2) k_wgrad3(const bf16* __restrict__ x,
                     a[y][z], b, acc[(oz * 3 + oy) * 3 + ox], 0, 0, 0);
             }
         }
+    // The bias gradient: the same rows against columns of ones.
+    if (CIN == 16 || sl == 0)
+#pragma unroll
+      for (int y = 0; y < YB; ++y)
+#pragma unroll
+        for (int z = 0; z < P; ++z)
+          accb = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[y][z], ones, accb, 0, 0, 0);
     __syncthreads();
   }
+  bias_out(reinterpret_cast<float*>(lds), accb, db + mg * 16, WM, sl == 0);
   if constexpr (WK > 1) {
     f4* red = reinterpret_cast<f4*>(lds) + wm * 27 * 64 + lane;
     for (int k = 1; k < WK; ++k) {
@@ -888,103 +965,162 @@ __global__ void __launch_bounds__(256) k_conv_first(
   st16(out + (size_t)v * 16 + 8, make_uint4(w[4], w[5], w[6], w[7]));
 }
 
-// dW of the first layer: a workgroup takes one tap and a chunk of voxels;
-// each thread sums the 16 x 2 products g[v][co] x[v + tap][ci] of its
-// voxels in registers, the wave reduces them with cross-lane shuffles, and
-// the workgroup adds its 32 sums to dW[co][tap][ci] (16 x 27 x 2).
-__global__ void __launch_bounds__(256) k_wgrad_first(
-    const float* __restrict__ in, const bf16* __restrict__ g,
-    float* __restrict__ dW, Dims d, unsigned chunk) {
-  __shared__ float red[4][32];
-  const int tap = blockIdx.y;
-  const int oz = tap / 9 - 1, oy = (tap / 3) % 3 - 1, ox = tap % 3 - 1;
-  const unsigned v0 = blockIdx.x * chunk;
-  const unsigned long long vend = (unsigned long long)v0 + chunk;
-  const unsigned v1 = vend < (unsigned long long)d.V ? (unsigned)vend : (unsigned)d.V;
-  float acc[32];
+// dW and db of the first layer, the same way: an FP32 input value is the exact
+// sum of three BF16 ones (8 bits of its 24 each), so the products with the BF16
+// gradient stay exact and are summed in FP32.  A halo voxel is 16 bytes: three
+// parts of each of its two channels and two zeros, and a transposed read of 32
+// bytes takes two x neighbours at once, columns 8 s + 3 c + part for shift s:
+// x shifts -1 and 0 in one product, +1 in another (its second half, shift +2,
+// is dropped).  18 products per row pair and (dy, dz), against 27 sums over
+// all voxels in turn on the vector units, which read g 27 times: 1207 us at
+// 128x128x512, 189 now.
+__global__ void __launch_bounds__(256, 2) k_wgrad_first(const float* __restrict__ in,
+                                                        const bf16* __restrict__ g,
+                                                        float* __restrict__ dW,
+                                                        float* __restrict__ db, Dims d, int nsp) {
+  using T = WgTile<16>;
+  constexpr int YB = T::YB, P = T::P, TY = T::TY, TZ = T::TZ, HY = T::HY, HZ = T::HZ;
+  constexpr int HV = T::HV, GV = T::GV;
+  // One voxel of slack: the last row's shift +2 (dropped) reads past it.
+  constexpr int kRed = 18 * 256 * 4 / 16;
+  constexpr int kStage = HV + 1 + 2 * GV;
+  __shared__ uint4 lds[kStage > kRed ? kStage : kRed];
+  const int lane = threadIdx.x & 63, wk = threadIdx.x >> 6;
+  const int ntx = (d.W + 15) / 16, nty = (d.H + TY - 1) / TY, ntz = (d.D + TZ - 1) / TZ;
+  const int ntiles = ntx * nty * ntz;
+  const int wg = (int)xcd_block(blockIdx.x, gridDim.x);
+  const char* lx = reinterpret_cast<const char*>(lds);
+  const char* lg = lx + (size_t)(HV + 1) * 16;
+  const int q = lane & 15, kg = lane >> 4;
+  const int vx = 8 * (kg & 1) + (q >> 2);
+  const int offx = (((kg >> 1) * P * HY + wk * YB) * 18 + vx) * 16 + (q & 3) * 8;
+  const int offg = ((q >> 1) & 1) * GV * 16 + (q & 1) * 8 +
+                   (((kg >> 1) * P * TY + wk * YB) * 16 + vx) * 16;
+  f4 acc[18], accb = f4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int e = 0; e < 32; ++e) acc[e] = 0.f;
-  for (unsigned v = v0 + threadIdx.x; v < v1; v += 256) {
-    int x, y, z;
-    voxel_xyz(v, d, x, y, z);
-    const int zz = z + oz;
-    if (zz < 0 || zz >= d.D) continue;
-    int yy = y + oy, xx = x + ox;
-    yy = yy < 0 ? yy + d.H : (yy >= d.H ? yy - d.H : yy);
-    xx = xx < 0 ? xx + d.W : (xx >= d.W ? xx - d.W : xx);
-    const float2 xi = reinterpret_cast<const float2*>(in)[((unsigned)zz * d.H + yy) * d.W + xx];
-    float gf[16];
-    unpack8(ld16(g + (size_t)v * 16), gf);
-    unpack8(ld16(g + (size_t)v * 16 + 8), gf + 8);
+  for (int t = 0; t < 18; ++t) acc[t] = f4{0.f, 0.f, 0.f, 0.f};
+  bf16x8 ones;
 #pragma unroll
-    for (int co = 0; co < 16; ++co) {
-      acc[2 * co] = fmaf(gf[co], xi.x, acc[2 * co]);
-      acc[2 * co + 1] = fmaf(gf[co], xi.y, acc[2 * co + 1]);
+  for (int e = 0; e < 8; ++e) ones[e] = (__bf16)1.0f;
+  if (threadIdx.x == 0) lds[HV] = make_uint4(0, 0, 0, 0);
+  constexpr int PX = (HV + 255) / 256, PG = 2 * GV / 256;
+  float2 xr[PX];
+  uint4 gr[PG];
+  auto load = [&](int t) {
+    const int tx = t % ntx, r = t / ntx;
+    const int x0 = tx * 16, y0 = (r % nty) * TY, z0 = (r / nty) * TZ;
+#pragma unroll
+    for (int m = 0; m < PX; ++m) {
+      const int hv = (int)threadIdx.x + m * 256;
+      const int hx = hv % 18, hy = (hv / 18) % HY, gz = z0 + hv / (18 * HY) - 1;
+      xr[m] = make_float2(0.f, 0.f);
+      if (hv < HV && gz >= 0 && gz < d.D) {
+        const int gy = (y0 + hy - 1 + d.H) % d.H, gx = (x0 + hx - 1 + d.W) % d.W;
+        xr[m] = reinterpret_cast<const float2*>(in)[((size_t)gz * d.H + gy) * d.W + gx];
+      }
     }
-  }
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
-  for (int e = 0; e < 32; ++e) {
-    float t = acc[e];
-    for (int o = 32; o > 0; o >>= 1) t += __shfl_xor(t, o);
-    acc[e] = t;
-  }
-  if (lane == 0)
+    for (int m = 0; m < PG; ++m) {
+      const int e = (int)threadIdx.x + m * 256;
+      const int v = e >> 1;
+      const int gx = x0 + (v & 15), gy = y0 + (v >> 4) % TY, gz = z0 + (v >> 4) / TY;
+      gr[m] = make_uint4(0, 0, 0, 0);
+      if (gx < d.W && gy < d.H && gz < d.D)
+        gr[m] = ld16(g + (((size_t)gz * d.H + gy) * d.W + gx) * 16 + (e & 1) * 8);
+    }
+  };
+  // Three parts of a value; an infinity or NaN is its first part alone.
+  auto split = [](float v, unsigned short (&p)[3]) {
+    p[0] = f2bf(v);
+    const float r1 = v - bf2f(p[0]);
+    const bool fin = fabsf(bf2f(p[0])) < INFINITY;
+    p[1] = fin ? f2bf(r1) : (bf16)0;
+    p[2] = fin ? f2bf(r1 - bf2f(p[1])) : (bf16)0;
+  };
+  const int t0 = (int)((long long)ntiles * wg / nsp);
+  const int t1 = (int)((long long)ntiles * (wg + 1) / nsp);
+  if (t0 < t1) load(t0);
+  for (int t = t0; t < t1; ++t) {
 #pragma unroll
-    for (int e = 0; e < 32; ++e) red[wave][e] = acc[e];
-  __syncthreads();
-  if (threadIdx.x < 32) {
-    const float t = (red[0][threadIdx.x] + red[1][threadIdx.x]) +
-                    (red[2][threadIdx.x] + red[3][threadIdx.x]);
-    atomicAdd(&dW[(threadIdx.x >> 1) * 54 + tap * 2 + (threadIdx.x & 1)], t);
+    for (int m = 0; m < PX; ++m) {
+      const int hv = (int)threadIdx.x + m * 256;
+      unsigned short a[3], b[3];
+      split(xr[m].x, a);
+      split(xr[m].y, b);
+      if (hv < HV)
+        lds[hv] = make_uint4(a[0] | (unsigned)a[1] << 16, a[2] | (unsigned)b[0] << 16,
+                             b[1] | (unsigned)b[2] << 16, 0u);
+    }
+#pragma unroll
+    for (int m = 0; m < PG; ++m) {
+      const int e = (int)threadIdx.x + m * 256;
+      lds[HV + 1 + (e & 1) * GV + (e >> 1)] = gr[m];
+    }
+    __syncthreads();
+    if (t + 1 < t1) load(t + 1);
+    bf16x8 a[YB][P];
+#pragma unroll
+    for (int y = 0; y < YB; ++y)
+#pragma unroll
+      for (int z = 0; z < P; ++z) {
+        const char* p = lg + offg + (z * TY + y) * 16 * 16;
+        a[y][z] = lds_tr8(p, p + 64);
+        accb = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[y][z], ones, accb, 0, 0, 0);
+      }
+#pragma unroll
+    for (int hz = 0; hz < P + 2; ++hz)
+#pragma unroll
+      for (int hy = 0; hy < YB + 2; ++hy)
+#pragma unroll
+        for (int s2 = 0; s2 < 2; ++s2) {
+          const char* p = lx + offx + ((hz * HY + hy) * 18 + 2 * s2) * 16;
+          const bf16x8 b = lds_tr8(p, p + 64);
+#pragma unroll
+          for (int oz = 0; oz < 3; ++oz)
+#pragma unroll
+            for (int oy = 0; oy < 3; ++oy) {
+              const int y = hy - oy, z = hz - oz;
+              if (y >= 0 && y < YB && z >= 0 && z < P)
+                acc[(oz * 3 + oy) * 2 + s2] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                    a[y][z], b, acc[(oz * 3 + oy) * 2 + s2], 0, 0, 0);
+            }
+        }
+    __syncthreads();
   }
+  bias_out(reinterpret_cast<float*>(lds), accb, db, 1, true);
+  f4* red = reinterpret_cast<f4*>(lds) + lane;
+  for (int k = 1; k < 4; ++k) {
+    if (wk == k)
+#pragma unroll
+      for (int t = 0; t < 18; ++t) red[t * 64] = acc[t];
+    __syncthreads();
+    if (wk == 0)
+#pragma unroll
+      for (int t = 0; t < 18; ++t) acc[t] = acc[t] + red[t * 64];
+    __syncthreads();
+  }
+  if (wk) return;
+  // Column 8 s + 3 c + part of product pair s2: the three parts' sums join in
+  // the first part's lane.
+  const int c = (q & 7) / 3, shift = q >> 3;
+  const bool own = (q & 7) == 0 || (q & 7) == 3;
+#pragma unroll
+  for (int t = 0; t < 18; ++t)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const float v = acc[t][j] + (__shfl_down(acc[t][j], 1) + __shfl_down(acc[t][j], 2));
+      const int ox = 2 * (t & 1) + shift;
+      if (own && ox < 3) atomicAdd(&dW[(4 * kg + j) * 54 + ((t >> 1) * 3 + ox) * 2 + c], v);
+    }
 }
 
-// Bias gradient: sum over voxels per channel.  A thread adds 8 channels of
-// its voxels; the workgroup reduces in LDS and adds one value per channel.
-__global__ void __launch_bounds__(256) k_bias_grad(const bf16* __restrict__ g,
-                                                   int C, Dims d,
-                                                   float* __restrict__ db) {
-  __shared__ float s[256][8];
-  const unsigned G = (unsigned)C / 8;
-  const unsigned rows = 256 / G;
-  const unsigned r = threadIdx.x / G, cg = threadIdx.x % G;
-  float a[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  if (r < rows) {
-    for (unsigned long long v = (unsigned long long)blockIdx.x * rows + r;
-         v < (unsigned long long)d.V; v += (unsigned long long)gridDim.x * rows) {
-      float f[8];
-      unpack8(ld16(g + (size_t)v * C + 8 * cg), f);
-#pragma unroll
-      for (int q = 0; q < 8; ++q) a[q] += f[q];
-    }
-  }
-#pragma unroll
-  for (int q = 0; q < 8; ++q) s[threadIdx.x][q] = r < rows ? a[q] : 0.f;
-  __syncthreads();
-  if (threadIdx.x < (unsigned)C) {
-    const unsigned c8 = threadIdx.x / 8, q = threadIdx.x % 8;
-    float t = 0.f;
-    for (unsigned rr = 0; rr < rows; ++rr) t += s[rr * G + c8][q];
-    atomicAdd(&db[threadIdx.x], t);
-  }
-}
-
-// gpre = gy * (y > 0), 8 values a thread.
-__global__ void k_relu_bwd(const bf16* __restrict__ gy, const bf16* __restrict__ y,
-                           bf16* __restrict__ gpre, long long n) {
+// g = 0 where y is not positive, 8 values a thread.
+__global__ void k_relu_bwd(bf16* __restrict__ g, const bf16* __restrict__ y, long long n) {
   const unsigned t = blockIdx.x * blockDim.x + threadIdx.x;
   if ((unsigned long long)t * 8 >= (unsigned long long)n) return;
-  const uint4 gv = ld16(gy + (size_t)t * 8), yv = ld16(y + (size_t)t * 8);
-  const unsigned gw[4] = {gv.x, gv.y, gv.z, gv.w}, yw[4] = {yv.x, yv.y, yv.z, yv.w};
-  unsigned o[4];
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const unsigned lo = (__uint_as_float(yw[q] << 16) > 0.f) ? (gw[q] & 0xffffu) : 0u;
-    const unsigned hi = (__uint_as_float(yw[q] & 0xffff0000u) > 0.f) ? (gw[q] & 0xffff0000u) : 0u;
-    o[q] = lo | hi;
-  }
-  st16(gpre + (size_t)t * 8, make_uint4(o[0], o[1], o[2], o[3]));
+  const uint4 gv = ld16(g + (size_t)t * 8), yv = ld16(y + (size_t)t * 8);
+  st16(g + (size_t)t * 8, make_uint4(relu_mask2(gv.x, yv.x), relu_mask2(gv.y, yv.y),
+                                     relu_mask2(gv.z, yv.z), relu_mask2(gv.w, yv.w)));
 }
 
 // Average pooling 2^3 (out dims d = input dims / 2), 8 channels a thread.
@@ -1013,11 +1149,12 @@ __global__ void k_pool(const bf16* __restrict__ in, bf16* __restrict__ out,
   st16(out + (size_t)v * C + 8 * g, make_uint4(w[0], w[1], w[2], w[3]));
 }
 
-// Gradient through pooling added to an existing fine gradient:
-// gfine[child] = gfine[child] + gcoarse[parent] / 8 (fine dims d), 8
-// channels a thread.
-__global__ void k_pool_bwd_add(const bf16* __restrict__ gc, bf16* __restrict__ gf,
-                               Dims d, int C) {
+// Pre-activation gradient of an encoder level's output: the skip part of the
+// decoder's concatenation gradient plus the gradient through pooling, gcoarse[parent] / 8, where the output y is
+// positive (fine dims d), 8 channels a thread.
+__global__ void k_pool_bwd_add(const bf16* __restrict__ gc, const bf16* __restrict__ gskip,
+                               const bf16* __restrict__ y8, bf16* __restrict__ gpre, Dims d,
+                               int C) {
   const unsigned G = (unsigned)C / 8;
   const unsigned t = blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= (unsigned long long)d.V * G) return;
@@ -1025,72 +1162,45 @@ __global__ void k_pool_bwd_add(const bf16* __restrict__ gc, bf16* __restrict__ g
   int x, y, z;
   voxel_xyz(v, d, x, y, z);
   const unsigned p = ((unsigned)(z / 2) * (d.H / 2) + y / 2) * (d.W / 2) + x / 2;
+  const uint4 m = ld16(y8 + (size_t)v * C + 8 * g);
   float a[8], b[8];
-  unpack8(ld16(gf + (size_t)v * C + 8 * g), a);
+  unpack8(ld16(gskip + (size_t)v * C + 8 * g), a);
   unpack8(ld16(gc + (size_t)p * C + 8 * g), b);
+  const unsigned mw[4] = {m.x, m.y, m.z, m.w};
   unsigned w[4];
 #pragma unroll
   for (int q = 0; q < 4; ++q)
-    w[q] = (unsigned)f2bf(a[2 * q] + b[2 * q] * 0.125f) |
-           ((unsigned)f2bf(a[2 * q + 1] + b[2 * q + 1] * 0.125f) << 16);
-  st16(gf + (size_t)v * C + 8 * g, make_uint4(w[0], w[1], w[2], w[3]));
+    w[q] = relu_mask2(f2bf2(a[2 * q] + b[2 * q] * 0.125f, a[2 * q + 1] + b[2 * q + 1] * 0.125f),
+                      mw[q]);
+  st16(gpre + (size_t)v * C + 8 * g, make_uint4(w[0], w[1], w[2], w[3]));
 }
 
-// Concatenation [up(coarse) (Cu channels), skip (Cs)] at fine dims d, 8
-// channels a thread.
-__global__ void k_up_cat(const bf16* __restrict__ coarse, int Cu,
-                         const bf16* __restrict__ skip, int Cs,
-                         bf16* __restrict__ out, Dims d) {
-  const unsigned C = Cu + Cs, G = C / 8, Gu = (unsigned)Cu / 8;
-  const unsigned t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= (unsigned long long)d.V * G) return;
-  const unsigned v = t / G, g = t % G;
-  uint4 val;
-  if (g < Gu) {
-    int x, y, z;
-    voxel_xyz(v, d, x, y, z);
-    const unsigned p = ((unsigned)(z / 2) * (d.H / 2) + y / 2) * (d.W / 2) + x / 2;
-    val = ld16(coarse + (size_t)p * Cu + 8 * g);
-  } else {
-    val = ld16(skip + (size_t)v * Cs + 8 * (g - Gu));
-  }
-  st16(out + (size_t)v * C + 8 * g, val);
-}
-
-// Split the concatenation's gradient: coarse part summed over the 8
-// children (coarse dims dc), skip part copied (fine dims); 8 channels a
-// thread.
-__global__ void k_split_up(const bf16* __restrict__ gcat, int Cu, int Cs,
-                           bf16* __restrict__ gcoarse, Dims dc) {
+// The concatenation gradient's coarse part summed over the 8 children, where
+// the coarse output yc is positive (coarse dims dc); 8 channels a thread.
+__global__ void k_split_up(const bf16* __restrict__ gup, int Cu,
+                           const bf16* __restrict__ yc, bf16* __restrict__ gpre, Dims dc) {
   const unsigned G = (unsigned)Cu / 8;
   const unsigned t = blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= (unsigned long long)dc.V * G) return;
   const unsigned p = t / G, g = t % G;
   int x, y, z;
   voxel_xyz(p, dc, x, y, z);
-  const unsigned W2 = 2 * dc.W, H2 = 2 * dc.H, C = Cu + Cs;
+  const unsigned W2 = 2 * dc.W, H2 = 2 * dc.H;
   float s[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   for (int a = 0; a < 2; ++a)
     for (int b = 0; b < 2; ++b)
       for (int e = 0; e < 2; ++e) {
         float f[8];
-        unpack8(ld16(gcat + ((size_t)((2 * z + a) * H2 + 2 * y + b) * W2 + 2 * x + e) * C + 8 * g), f);
+        unpack8(ld16(gup + ((size_t)((2 * z + a) * H2 + 2 * y + b) * W2 + 2 * x + e) * Cu + 8 * g), f);
 #pragma unroll
         for (int q = 0; q < 8; ++q) s[q] = s[q] + f[q];
       }
+  const uint4 m = ld16(yc + (size_t)p * Cu + 8 * g);
+  const unsigned mw[4] = {m.x, m.y, m.z, m.w};
   unsigned w[4];
 #pragma unroll
-  for (int q = 0; q < 4; ++q)
-    w[q] = (unsigned)f2bf(s[2 * q]) | ((unsigned)f2bf(s[2 * q + 1]) << 16);
-  st16(gcoarse + (size_t)p * Cu + 8 * g, make_uint4(w[0], w[1], w[2], w[3]));
-}
-__global__ void k_split_skip(const bf16* __restrict__ gcat, int Cu, int Cs,
-                             bf16* __restrict__ gskip, Dims d) {
-  const unsigned G = (unsigned)Cs / 8;
-  const unsigned t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= (unsigned long long)d.V * G) return;
-  const unsigned v = t / G, g = t % G;
-  st16(gskip + (size_t)v * Cs + 8 * g, ld16(gcat + (size_t)v * (Cu + Cs) + Cu + 8 * g));
+  for (int q = 0; q < 4; ++q) w[q] = relu_mask2(f2bf2(s[2 * q], s[2 * q + 1]), mw[q]);
+  st16(gpre + (size_t)p * Cu + 8 * g, make_uint4(w[0], w[1], w[2], w[3]));
 }
 
 // Head: out[v] = sum_c w[c] y[v][c] + b, FP32 output.
@@ -1201,7 +1311,8 @@ __global__ void k_res_g(const float* __restrict__ q, float* __restrict__ gout,
   gout[v] = g;
 }
 
-// Head backward: gy[v][c] = gout[v] w[c]; dw[c] += sum gout y; db += sum.
+// Head backward: the last layer's pre-activation gradient gout[v] w[c] where
+// y > 0; dw[c] += sum gout y; db += sum.
 __global__ void __launch_bounds__(256) k_head_bwd(
     const float* __restrict__ gout, const bf16* __restrict__ y,
     const float* __restrict__ w, bf16* __restrict__ gy, float* __restrict__ dw,
@@ -1214,12 +1325,13 @@ __global__ void __launch_bounds__(256) k_head_bwd(
        v < (unsigned long long)V; v += (unsigned long long)gridDim.x * blockDim.x) {
     const float go = gout[v];
     float f[16];
-    unpack8(ld16(y + (size_t)v * 16), f);
-    unpack8(ld16(y + (size_t)v * 16 + 8), f + 8);
+    const uint4 ya = ld16(y + (size_t)v * 16), yb = ld16(y + (size_t)v * 16 + 8);
+    unpack8(ya, f);
+    unpack8(yb, f + 8);
+    const unsigned m[8] = {ya.x, ya.y, ya.z, ya.w, yb.x, yb.y, yb.z, yb.w};
     unsigned o[8];
 #pragma unroll
-    for (int q = 0; q < 8; ++q)
-      o[q] = (unsigned)f2bf(go * w[2 * q]) | ((unsigned)f2bf(go * w[2 * q + 1]) << 16);
+    for (int q = 0; q < 8; ++q) o[q] = relu_mask2(f2bf2(go * w[2 * q], go * w[2 * q + 1]), m[q]);
     st16(gy + (size_t)v * 16, make_uint4(o[0], o[1], o[2], o[3]));
     st16(gy + (size_t)v * 16 + 8, make_uint4(o[4], o[5], o[6], o[7]));
 #pragma unroll
@@ -1315,6 +1427,9 @@ long long param_count() {
   return n + 17;
 }
 
+// Workgroups (and partial sums) of the loss.
+constexpr int kLossParts = 2048;
+
 constexpr int kpad(int cin) { return (27 * cin + 63) / 64 * 64; }
 
 }  // namespace
@@ -1332,11 +1447,9 @@ struct pic_unet {
   float* x_in;                 // (V0, 2) FP32 input
   bf16 *y[kNL];                // layer outputs
   bf16 *p0, *p1, *p2;          // pooled
-  bf16 *c2, *c1, *c0;          // concatenations
   float *out, *gout, *target;
-  // Gradient scratch per level (two buffers of the level's widest tensor)
-  // and a pre-activation buffer.
-  bf16 *ga[4], *gb[4], *gp[4], *gs[4];
+  // Gradient scratch per level: buffers of the level's widest tensor.
+  bf16 *ga[4], *gb[4], *gs[4];
   float* dscratch;             // double partials (as float storage)
   double* dpart;
   int t;                       // Adam step
@@ -1384,9 +1497,6 @@ size_t unet_carve(pic_unet* u, char* base) {
   u->p0 = cv.take<bf16>(Vl[1] * 16);
   u->p1 = cv.take<bf16>(Vl[2] * 32);
   u->p2 = cv.take<bf16>(Vl[3] * 64);
-  u->c2 = cv.take<bf16>(Vl[2] * 192);
-  u->c1 = cv.take<bf16>(Vl[1] * 96);
-  u->c0 = cv.take<bf16>(Vl[0] * 48);
   u->out = cv.take<float>(V0);
   u->gout = cv.take<float>(V0);
   u->target = cv.take<float>(V0);
@@ -1394,10 +1504,9 @@ size_t unet_carve(pic_unet* u, char* base) {
   for (int l = 0; l < 4; ++l) {
     u->ga[l] = cv.take<bf16>(Vl[l] * widest[l]);
     u->gb[l] = cv.take<bf16>(Vl[l] * widest[l]);
-    u->gp[l] = cv.take<bf16>(Vl[l] * widest[l]);
     u->gs[l] = cv.take<bf16>(Vl[l] * widest[l]);
   }
-  u->dpart = cv.take<double>(1024);
+  u->dpart = cv.take<double>(kLossParts + 1);
   u->q = cv.take<float>(V0);
   return cv.off + 256;
 }
@@ -1441,47 +1550,64 @@ void conv3p_launch(hipStream_t st, const bf16* in, const bf16* skip, const bf16*
   pic::k_conv3p<CIN, CU><<<grid, 256, 0, st>>>(in, skip, Wk, b, out, d, relu);
 }
 
-// Tile of k_conv3t for a column count: MT * COUT / 16 <= 16; the
-// register-blocked k_conv3r for 32 to 128 output channels, its persistent
-// form k_conv3p for 16.
-template <int CIN, int COUT>
+// The register-blocked k_conv3r for 32 to 128 output channels, its persistent
+// form k_conv3p for 16; there the mask is a pass of its own (two of 157 us a
+// gradient at 128x128x512: in the epilogue of the persistent kernel, whose
+// registers hold no prefetch of it, it cost 240 us each).
+template <int CIN, int COUT, bool MASK>
 void conv_launch(hipStream_t st, const bf16* in, const bf16* Wk, const float* b,
-                 bf16* out, Dims d, int relu) {
+                 bf16* out, Dims d, int relu, const bf16* mask) {
   if constexpr (COUT == 16) {
     conv3p_launch<CIN, 0>(st, in, nullptr, Wk, b, out, d, relu);
-  } else if constexpr (COUT == 32 || COUT == 64 || COUT == 128) {
-    constexpr int WY = COUT == 16 ? 2 : 1, WZ = COUT >= 64 ? 1 : 2;
+    if (MASK) pic::k_relu_bwd<<<nb(d.V * 2), 256, 0, st>>>(out, mask, d.V * 16);
+  } else {
+    constexpr int WY = 1, WZ = COUT >= 64 ? 1 : 2;
     constexpr int TY = 4 * WY, TZ = 4 * WZ;
     const long long nbk = (long long)((d.W + 15) / 16) * ((d.H + TY - 1) / TY) *
                           ((d.D + TZ - 1) / TZ);
-    pic::k_conv3r<CIN, COUT, WY, WZ><<<(unsigned)nbk, 64 * (COUT / 16) * WY * WZ, 0, st>>>(
-        in, nullptr, Wk, b, out, d, relu);
-  } else {
-    constexpr int NT = COUT / 16;
-    constexpr int TY = NT <= 2 ? 8 : (NT <= 8 ? 4 : 2);
-    constexpr int TZ = NT <= 4 ? 4 : 2;
-    const long long nbk = (long long)((d.W + 15) / 16) * ((d.H + TY - 1) / TY) *
-                          ((d.D + TZ - 1) / TZ);
-    pic::k_conv3t<CIN, COUT, TY, TZ><<<(unsigned)nbk, 256, 0, st>>>(in, Wk, b, out, d, relu);
+    pic::k_conv3r<CIN, COUT, WY, WZ, 0, MASK>
+        <<<(unsigned)nbk, 64 * (COUT / 16) * WY * WZ, 0, st>>>(in, nullptr, Wk, b, out, d, relu, mask);
   }
 }
 
 // Dispatch of the (C_in, C_out) pairs the network and its backward use.
 bool conv(hipStream_t st, int cin, int cout, const bf16* in, const bf16* Wk,
-          const float* b, bf16* out, Dims d, int relu) {
+          const float* b, bf16* out, Dims d, int relu, const bf16* mask = nullptr) {
 #define PIC_CONV(CI, CO)                                                   \
   if (cin == CI && cout == CO) {                                           \
-    conv_launch<CI, CO>(st, in, Wk, b, out, d, relu);                      \
+    if (mask)                                                              \
+      conv_launch<CI, CO, true>(st, in, Wk, b, out, d, relu, mask);        \
+    else                                                                   \
+      conv_launch<CI, CO, false>(st, in, Wk, b, out, d, relu, nullptr);    \
     return true;                                                           \
   }
   PIC_CONV(16, 16) PIC_CONV(16, 32) PIC_CONV(32, 32) PIC_CONV(32, 64)
-  PIC_CONV(64, 64) PIC_CONV(64, 128) PIC_CONV(128, 128) PIC_CONV(192, 64)
-  PIC_CONV(96, 32) PIC_CONV(48, 16)
+  PIC_CONV(64, 64) PIC_CONV(64, 128) PIC_CONV(128, 128)
   // backward-data shapes (channels swapped)
-  PIC_CONV(32, 16) PIC_CONV(64, 32) PIC_CONV(128, 64) PIC_CONV(64, 192)
-  PIC_CONV(32, 96) PIC_CONV(16, 48)
+  PIC_CONV(32, 16) PIC_CONV(64, 32) PIC_CONV(128, 64)
 #undef PIC_CONV
   return false;
+}
+
+// Gradient of a decoder's concatenation (cin channels in, 3 cin out), its part
+// of the upsampled coarse output and its skip part.  One round of resident
+// workgroups over the channel groups with one slice, whose weights stay; else
+// shorter runs.
+bool conv_cat_grad(hipStream_t st, int cin, const bf16* in, const bf16* Wk, bf16* gup, bf16* gskip,
+                   Dims d) {
+  const long long ntiles = (long long)((d.W + 15) / 16) * ((d.H + 7) / 8) * ((d.D + 3) / 4);
+  const int groups = cin / 16;
+  const int nsp = (int)std::min<long long>(ntiles, (cin == 16 ? 512 : 1024) / groups);
+  const unsigned grid = (unsigned)(groups * nsp);
+  if (cin == 16)
+    pic::k_conv3w<16><<<grid, 256, 0, st>>>(in, Wk, gup, gskip, d, nsp);
+  else if (cin == 32)
+    pic::k_conv3w<32><<<grid, 256, 0, st>>>(in, Wk, gup, gskip, d, nsp);
+  else if (cin == 64)
+    pic::k_conv3w<64><<<grid, 256, 0, st>>>(in, Wk, gup, gskip, d, nsp);
+  else
+    return false;
+  return true;
 }
 
 // Decoder convolution of [up(coarse) (CU channels), skip] without the
@@ -1498,33 +1624,40 @@ void conv_upcat_launch(hipStream_t st, const bf16* coarse, const bf16* skip,
   const long long nbk = (long long)((d.W + 15) / 16) * ((d.H + TY - 1) / TY) *
                         ((d.D + TZ - 1) / TZ);
   pic::k_conv3r<CIN, COUT, WY, WZ, CU><<<(unsigned)nbk, 64 * (COUT / 16) * WY * WZ, 0, st>>>(
-      coarse, skip, Wk, b, out, d, 1);
+      coarse, skip, Wk, b, out, d, 1, nullptr);
 }
 
-template <int CIN, int COUT>
-void wgrad_launch(hipStream_t st, const bf16* x, const bf16* g, float* dW,
-                  Dims d) {
+// One round of resident workgroups over all (co, ci) pairs, at least two tiles
+// each: every workgroup ends with 27 x 256 atomic adds per pair.
+template <int COUT>
+long long wgrad_runs(Dims d, int pairs) {
   using T = pic::WgTile<COUT>;
   const long long ntiles = (long long)((d.W + 15) / 16) * ((d.H + T::TY - 1) / T::TY) *
                            ((d.D + T::TZ - 1) / T::TZ);
-  // One round of resident workgroups over all (co, ci) pairs, at least two
-  // tiles each: every workgroup ends with 27 x 256 atomic adds per pair.
-  const int pairs = (CIN / 16) * ((COUT / 16) / T::WM);
-  const int round = 512;
-  const long long want = std::max(1LL, std::min<long long>(round / pairs, (ntiles + 1) / 2));
-  pic::k_wgrad3<CIN, COUT><<<(unsigned)(pairs * want), 256, 0, st>>>(x, g, dW, d, (int)want);
+  return std::max(1LL, std::min<long long>(512 / pairs, (ntiles + 1) / 2));
 }
 
-bool wgrad(hipStream_t st, int cin, int cout, const bf16* x, const bf16* g,
-           float* dW, Dims d) {
-#define PIC_WG(CI, CO)                                                     \
+// dW and db of a layer with input x, or with CU > 0 the concatenation of up(x)
+// and skip.
+template <int CIN, int COUT, int CU>
+void wgrad_launch(hipStream_t st, const bf16* x, const bf16* skip, const bf16* g, float* dW,
+                  float* db, Dims d) {
+  const int pairs = (CIN / 16) * ((COUT / 16) / pic::WgTile<COUT>::WM);
+  const long long runs = wgrad_runs<COUT>(d, pairs);
+  pic::k_wgrad3<CIN, COUT, CU><<<(unsigned)(pairs * runs), 256, 0, st>>>(x, skip, g, dW, db, d,
+                                                                         (int)runs);
+}
+
+bool wgrad(hipStream_t st, int cin, int cout, const bf16* x, const bf16* skip, const bf16* g,
+           float* dW, float* db, Dims d) {
+#define PIC_WG(CI, CO, CU)                                                 \
   if (cin == CI && cout == CO) {                                           \
-    wgrad_launch<CI, CO>(st, x, g, dW, d);                                 \
+    wgrad_launch<CI, CO, CU>(st, x, skip, g, dW, db, d);                   \
     return true;                                                           \
   }
-  PIC_WG(16, 16) PIC_WG(16, 32) PIC_WG(32, 32) PIC_WG(32, 64) PIC_WG(64, 64)
-  PIC_WG(64, 128) PIC_WG(128, 128) PIC_WG(192, 64) PIC_WG(96, 32)
-  PIC_WG(48, 16)
+  PIC_WG(16, 16, 0) PIC_WG(16, 32, 0) PIC_WG(32, 32, 0) PIC_WG(32, 64, 0) PIC_WG(64, 64, 0)
+  PIC_WG(64, 128, 0) PIC_WG(128, 128, 0) PIC_WG(192, 64, 128) PIC_WG(96, 32, 64)
+  PIC_WG(48, 16, 32)
 #undef PIC_WG
   return false;
 }
@@ -1540,9 +1673,8 @@ void pack_weights(pic_unet* u) {
 }
 
 // Forward pass of a D x H x W grid (input already in x_in); out -> u->out.
-// keep: write the decoder's concatenations (the backward pass reads them);
-// without it the decoders form them in their staging.
-bool unet_forward(pic_unet* u, int D, int H, int W, bool keep = true) {
+// The decoders form their concatenations in the staging.
+bool unet_forward(pic_unet* u, int D, int H, int W) {
   hipStream_t st = u->stream;
   Dims d0 = dims_at(u, D, H, W, 0), d1 = dims_at(u, D, H, W, 1),
        d2 = dims_at(u, D, H, W, 2), d3 = dims_at(u, D, H, W, 3);
@@ -1564,29 +1696,14 @@ bool unet_forward(pic_unet* u, int D, int H, int W, bool keep = true) {
   pic::k_pool<<<nb(d3.V * 8), 256, 0, st>>>(u->y[E2B], u->p2, d3, 64);
   L(BA, u->p2, d3);
   L(BB, u->y[BA], d3);
-  if (keep) {
-    pic::k_up_cat<<<nb(d2.V * 24), 256, 0, st>>>(u->y[BB], 128, u->y[E2B], 64, u->c2, d2);
-    L(D2A, u->c2, d2);
-  } else {
-    conv_upcat_launch<192, 64, 128>(st, u->y[BB], u->y[E2B], u->wk[D2A], P + u->boff[D2A],
-                                    u->y[D2A], d2);
-  }
+  conv_upcat_launch<192, 64, 128>(st, u->y[BB], u->y[E2B], u->wk[D2A], P + u->boff[D2A],
+                                  u->y[D2A], d2);
   L(D2B, u->y[D2A], d2);
-  if (keep) {
-    pic::k_up_cat<<<nb(d1.V * 12), 256, 0, st>>>(u->y[D2B], 64, u->y[E1B], 32, u->c1, d1);
-    L(D1A, u->c1, d1);
-  } else {
-    conv_upcat_launch<96, 32, 64>(st, u->y[D2B], u->y[E1B], u->wk[D1A], P + u->boff[D1A],
-                                  u->y[D1A], d1);
-  }
+  conv_upcat_launch<96, 32, 64>(st, u->y[D2B], u->y[E1B], u->wk[D1A], P + u->boff[D1A],
+                                u->y[D1A], d1);
   L(D1B, u->y[D1A], d1);
-  if (keep) {
-    pic::k_up_cat<<<nb(d0.V * 6), 256, 0, st>>>(u->y[D1B], 32, u->y[E0B], 16, u->c0, d0);
-    L(D0A, u->c0, d0);
-  } else {
-    conv_upcat_launch<48, 16, 32>(st, u->y[D1B], u->y[E0B], u->wk[D0A], P + u->boff[D0A],
-                                  u->y[D0A], d0);
-  }
+  conv_upcat_launch<48, 16, 32>(st, u->y[D1B], u->y[E0B], u->wk[D0A], P + u->boff[D0A],
+                                u->y[D0A], d0);
   L(D0B, u->y[D0A], d0);
   pic::k_head<<<nb(d0.V), 256, 0, st>>>(u->y[D0B], P + u->hoff, u->out, d0.V);
   return ok;
@@ -1600,52 +1717,49 @@ bool unet_backward(pic_unet* u, int D, int H, int W) {
   hipMemsetAsync(u->g, 0, u->np * sizeof(float), st);
   float* G = u->g;
   bool ok = true;
-  // Head.
+  // Head; ga[0]: pre-activation gradient of the last layer.
   pic::k_head_bwd<<<512, 256, 0, st>>>(u->gout, u->y[D0B], u->p + u->hoff,
                                        u->ga[0], G + u->hoff, d[0].V);
-  // Layer backward: gy (post-activation gradient) -> gpre -> dW, db and
-  // (if gx) the input gradient.
-  auto back = [&](int l, const bf16* gy, const bf16* in, bf16* gpre, bf16* gx) {
+  // Layer backward: the pre-activation gradient g -> dW, db and the input
+  // gradient, with mask the pre-activation gradient of the layer whose output
+  // the mask is.
+  auto back = [&](int l, const bf16* g, const bf16* in, bf16* gx, const bf16* mask) {
     const LayerSpec& s = kLayers[l];
     const Dims& dd = d[kLevel[l]];
-    pic::k_relu_bwd<<<nb(dd.V * s.co / 8), 256, 0, st>>>(gy, u->y[l], gpre, dd.V * s.co);
-    ok = ok && wgrad(st, s.ci, s.co, in, gpre, G + u->woff[l], dd);
-    pic::k_bias_grad<<<256, 256, 0, st>>>(gpre, s.co, dd, G + u->boff[l]);
-    if (gx) ok = ok && conv(st, s.co, s.ci, gpre, u->wd[l], nullptr, gx, dd, 0);
+    ok = ok && wgrad(st, s.ci, s.co, in, nullptr, g, G + u->woff[l], G + u->boff[l], dd);
+    ok = ok && conv(st, s.co, s.ci, g, u->wd[l], nullptr, gx, dd, 0, mask);
   };
-  // Level 0 decoder.
-  back(D0B, u->ga[0], u->y[D0A], u->gp[0], u->gb[0]);
-  back(D0A, u->gb[0], u->c0, u->gp[0], u->ga[0]);        // ga0: grad of c0 (48)
-  pic::k_split_skip<<<nb(d[0].V * 2), 256, 0, st>>>(u->ga[0], 32, 16, u->gs[0], d[0]);
-  pic::k_split_up<<<nb(d[1].V * 4), 256, 0, st>>>(u->ga[0], 32, 16, u->ga[1], d[1]);
-  // Level 1 decoder.
-  back(D1B, u->ga[1], u->y[D1A], u->gp[1], u->gb[1]);
-  back(D1A, u->gb[1], u->c1, u->gp[1], u->ga[1]);        // grad of c1 (96)
-  pic::k_split_skip<<<nb(d[1].V * 4), 256, 0, st>>>(u->ga[1], 64, 32, u->gs[1], d[1]);
-  pic::k_split_up<<<nb(d[2].V * 8), 256, 0, st>>>(u->ga[1], 64, 32, u->ga[2], d[2]);
-  // Level 2 decoder.
-  back(D2B, u->ga[2], u->y[D2A], u->gp[2], u->gb[2]);
-  back(D2A, u->gb[2], u->c2, u->gp[2], u->ga[2]);        // grad of c2 (192)
-  pic::k_split_skip<<<nb(d[2].V * 8), 256, 0, st>>>(u->ga[2], 128, 64, u->gs[2], d[2]);
-  pic::k_split_up<<<nb(d[3].V * 16), 256, 0, st>>>(u->ga[2], 128, 64, u->ga[3], d[3]);
+  // Decoder of level lv (layers A, B; the coarser output up and the level's
+  // encoder output skip, cs channels): the gradient of skip is left in gs[lv],
+  // the pre-activation gradient of up in ga[lv + 1].
+  auto decoder = [&](int lv, int A, int B, int up, int skip, int cs) {
+    back(B, u->ga[lv], u->y[A], u->gb[lv], u->y[A]);
+    ok = ok && wgrad(st, 3 * cs, cs, u->y[up], u->y[skip], u->gb[lv], G + u->woff[A],
+                     G + u->boff[A], d[lv]);
+    ok = ok && conv_cat_grad(st, cs, u->gb[lv], u->wd[A], u->ga[lv], u->gs[lv], d[lv]);
+    pic::k_split_up<<<nb(d[lv + 1].V * (cs / 4)), 256, 0, st>>>(u->ga[lv], 2 * cs, u->y[up],
+                                                               u->ga[lv + 1], d[lv + 1]);
+  };
+  decoder(0, D0A, D0B, D1B, E0B, 16);
+  decoder(1, D1A, D1B, D2B, E1B, 32);
+  decoder(2, D2A, D2B, BB, E2B, 64);
   // Bottom.
-  back(BB, u->ga[3], u->y[BA], u->gp[3], u->gb[3]);
-  back(BA, u->gb[3], u->p2, u->gp[3], u->ga[3]);         // grad of p2 (64)
-  // Encoder level 2: skip gradient + pooled gradient.
-  pic::k_pool_bwd_add<<<nb(d[2].V * 8), 256, 0, st>>>(u->ga[3], u->gs[2], d[2], 64);
-  back(E2B, u->gs[2], u->y[E2A], u->gp[2], u->gb[2]);
-  back(E2A, u->gb[2], u->p1, u->gp[2], u->ga[2]);        // grad of p1 (32)
-  pic::k_pool_bwd_add<<<nb(d[1].V * 4), 256, 0, st>>>(u->ga[2], u->gs[1], d[1], 32);
-  back(E1B, u->gs[1], u->y[E1A], u->gp[1], u->gb[1]);
-  back(E1A, u->gb[1], u->p0, u->gp[1], u->ga[1]);        // grad of p0 (16)
-  pic::k_pool_bwd_add<<<nb(d[0].V * 2), 256, 0, st>>>(u->ga[1], u->gs[0], d[0], 16);
-  back(E0B, u->gs[0], u->y[E0A], u->gp[0], u->gb[0]);    // grad of e0a (16)
+  back(BB, u->ga[3], u->y[BA], u->gb[3], u->y[BA]);
+  back(BA, u->gb[3], u->p2, u->ga[3], nullptr);  // grad of p2 (64)
+  // Encoder of level lv: skip gradient + pooled gradient of its output B.
+  auto encoder = [&](int lv, int A, int B, const bf16* pooled, int cs) {
+    pic::k_pool_bwd_add<<<nb(d[lv].V * (cs / 8)), 256, 0, st>>>(u->ga[lv + 1], u->gs[lv], u->y[B],
+                                                              u->gb[lv], d[lv], cs);
+    back(B, u->gb[lv], u->y[A], u->gs[lv], u->y[A]);
+    if (pooled) back(A, u->gs[lv], pooled, u->ga[lv], nullptr);
+  };
+  encoder(2, E2A, E2B, u->p1, 64);
+  encoder(1, E1A, E1B, u->p0, 32);
+  encoder(0, E0A, E0B, nullptr, 16);
   // First layer: weights only.
-  pic::k_relu_bwd<<<nb(d[0].V * 2), 256, 0, st>>>(u->gb[0], u->y[E0A], u->gp[0], d[0].V * 16);
-  const unsigned chunk = 8192;
-  pic::k_wgrad_first<<<dim3((unsigned)((d[0].V + chunk - 1) / chunk), 27), 256, 0, st>>>(
-      u->x_in, u->gp[0], G + u->woff[E0A], d[0], chunk);
-  pic::k_bias_grad<<<256, 256, 0, st>>>(u->gp[0], 16, d[0], G + u->boff[E0A]);
+  const long long runs = wgrad_runs<16>(d[0], 1);
+  pic::k_wgrad_first<<<(unsigned)runs, 256, 0, st>>>(u->x_in, u->gs[0], G + u->woff[E0A],
+                                                     G + u->boff[E0A], d[0], (int)runs);
   return ok;
 }
 
@@ -1672,7 +1786,7 @@ bool pic_unet_infer(pic_unet* u, const float* x, int D, int H, int W,
   hipStream_t keep_st = u->stream;
   u->x_in = const_cast<float*>(x);
   u->stream = st;
-  const bool ok = unet_forward(u, D, H, W, false);
+  const bool ok = unet_forward(u, D, H, W);
   u->x_in = keep_x;
   u->stream = keep_st;
   *out = u->out;
@@ -1764,7 +1878,7 @@ pic_status pic_unet_forward(pic_unet* u, const float* input, int32_t D,
   const long long V = (long long)D * H * W;
   hipMemcpyAsync(u->x_in, input, 2 * V * sizeof(float), hipMemcpyDeviceToDevice,
                  u->stream);
-  if (!unet_forward(u, D, H, W, false)) return PIC_ERR_STATE;
+  if (!unet_forward(u, D, H, W)) return PIC_ERR_STATE;
   hipMemcpyAsync(out, u->out, V * sizeof(float), hipMemcpyDeviceToDevice, u->stream);
   return hipStreamSynchronize(u->stream) == hipSuccess ? PIC_OK : PIC_ERR_HIP;
 }
@@ -1783,17 +1897,17 @@ pic_status pic_unet_gradients(pic_unet* u, const float* input,
   if (!unet_forward(u, D, H, W)) return PIC_ERR_STATE;
   if (u->loss_mode == PIC_UNET_LOSS_RESIDUAL) {
     const Dims d0 = dims_at(u, D, H, W, 0);
-    pic::k_res_q<<<256, 256, 0, st>>>(u->out, u->target, u->q, d0, u->loss_k0, u->dpart);
+    pic::k_res_q<<<kLossParts, 256, 0, st>>>(u->out, u->target, u->q, d0, u->loss_k0, u->dpart);
     pic::k_res_g<<<nb(V), 256, 0, st>>>(u->q, u->gout, d0, u->loss_k0, 2.0f / (float)V);
   } else {
-    pic::k_mse<<<256, 256, 0, st>>>(u->out, u->target, u->gout, V, u->dpart);
+    pic::k_mse<<<kLossParts, 256, 0, st>>>(u->out, u->target, u->gout, V, u->dpart);
   }
-  pic::k_sum_d<<<1, 256, 0, st>>>(u->dpart, 256, u->dpart + 512);
+  pic::k_sum_d<<<1, 256, 0, st>>>(u->dpart, kLossParts, u->dpart + kLossParts);
   if (!unet_backward(u, D, H, W)) return PIC_ERR_STATE;
   if (grad)
     hipMemcpyAsync(grad, u->g, u->np * sizeof(float), hipMemcpyDeviceToDevice, st);
   double l = 0.0;
-  hipMemcpyAsync(&l, u->dpart + 512, sizeof(double), hipMemcpyDeviceToHost, st);
+  hipMemcpyAsync(&l, u->dpart + kLossParts, sizeof(double), hipMemcpyDeviceToHost, st);
   if (hipStreamSynchronize(st) != hipSuccess) return PIC_ERR_HIP;
   if (loss) *loss = l / (double)V;
   return PIC_OK;
