@@ -1022,12 +1022,19 @@ template <>
 struct SmoothTile<float> {
   static constexpr int SX = 32, SY = 16;
 };
+// Levels below that in x or y (small grids, and the coarse levels of larger
+// ones) take 16 x 16 columns: they are bound by the march's latency and the
+// launches, not by the recomputed halo.  A 32x32x64 step's 32 one-colour
+// launches of 3.3 us became 8 of 8.6.
+struct SmoothSmall {
+  static constexpr int SX = 16, SY = 16;
+};
 constexpr int kSH = 4;
 constexpr int kSR = 6;
 // One x-pair of the widened column per thread.
-template <typename T>
+template <class Tile>
 __host__ __device__ constexpr int smooth_threads() {
-  return (SmoothTile<T>::SX + 2 * kSH) / 2 * (SmoothTile<T>::SY + 2 * kSH);
+  return (Tile::SX + 2 * kSH) / 2 * (Tile::SY + 2 * kSH);
 }
 static_assert((kSH & 1) == 0, "x-pairs need even x");
 
@@ -1054,18 +1061,18 @@ enum : int { kSmPlain = 0, kSmZeroIn = 1, kSmAcc64 = 2 };
 
 // NEU: a z face of the level holds unknowns (Neumann condition), so face
 // planes are updated; with Dirichlet faces they never are.
-template <typename T, bool NEU, int MODE>
-__global__ void __launch_bounds__(smooth_threads<T>()) k_smooth2(
+template <typename T, class Tile, bool NEU, int MODE>
+__global__ void __launch_bounds__(smooth_threads<Tile>()) k_smooth2(
     const T* __restrict__ uin, T* __restrict__ uout, const T* __restrict__ f,
     LevelC L, int seg, const Counters* dc, double* __restrict__ u64) {
   static_assert(MODE == kSmPlain || std::is_same<T, float>::value,
                 "pass modes of the FP32 correction solve");
   using P2 = typename Pair2<T>::type;
-  constexpr int kSX = SmoothTile<T>::SX, kSY = SmoothTile<T>::SY;
+  constexpr int kSX = Tile::SX, kSY = Tile::SY;
   constexpr int kSPX = kSX + 2 * kSH, kSPY = kSY + 2 * kSH;
   constexpr int kSP = kSPX * kSPY;  // nodes per plane slot
   constexpr int kHX = kSPX / 2, kHP = kHX * kSPY;
-  static_assert((kSX & 1) == 0 && kHX * kSPY == smooth_threads<T>(), "tile");
+  static_assert((kSX & 1) == 0 && kHX * kSPY == smooth_threads<Tile>(), "tile");
   __shared__ T ring[kSR][kSP];
   if (dc->done) return;
   const int tiles_x = (L.nx + kSX - 1) / kSX;
@@ -1958,7 +1965,7 @@ void spectral_solve(pic_ctx* c, int l) {
     k_spec_inv<T><<<(unsigned)np, kSpecThreads, 0, st>>>(Lc, s, lev_u<T>(L), nm, c->dc);
 }
 
-// Workgroups of k_smooth2<T, *> the current device runs at once.
+// Workgroups of k_smooth2<T, SmoothTile<T>, *> the current device runs at once.
 template <typename T>
 long long smooth_slots() {
   static long long cached[64] = {0};
@@ -1967,8 +1974,9 @@ long long smooth_slots() {
   if (dev < 0 || dev >= 64) dev = 0;
   if (!cached[dev]) {
     int per_cu = 0, cus = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_smooth2<T, false, kSmPlain>,
-                                                     smooth_threads<T>(), 0) != hipSuccess ||
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
+            &per_cu, k_smooth2<T, SmoothTile<T>, false, kSmPlain>,
+            smooth_threads<SmoothTile<T>>(), 0) != hipSuccess ||
         per_cu < 1)
       per_cu = 1;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
@@ -1989,31 +1997,37 @@ bool level_fused(pic_ctx* c, int l) {
   if (l == c->spec_level || l >= c->nlev - 1 || l >= tail_first<T>(c)) return false;
   const Level& L = c->lev[l];
   return lev_s<T>(c->lev[l]) && !(c->cfg.flags & PIC_FLAG_PLAIN_SMOOTHER) &&
-         c->cfg.nu_pre == 2 && c->cfg.nu_post == 2 && L.nx >= SmoothTile<T>::SX &&
-         L.ny >= SmoothTile<T>::SY;
+         c->cfg.nu_pre == 2 && c->cfg.nu_post == 2 && L.nx >= SmoothSmall::SX &&
+         L.ny >= SmoothSmall::SY;
 }
 
-template <typename T, bool NEU>
+// ... with the small column.
+template <typename T>
+bool small_columns(const Level& L) {
+  return L.nx < SmoothTile<T>::SX || L.ny < SmoothTile<T>::SY;
+}
+
+template <typename T, class Tile, bool NEU>
 void launch_smooth(unsigned grid, hipStream_t st, const T* in, T* out,
                    const T* f, LevelC L, int seg, const Counters* dc, int mode,
                    double* u64) {
-  constexpr int nt = smooth_threads<T>();
+  constexpr int nt = smooth_threads<Tile>();
   if constexpr (std::is_same<T, float>::value) {
     switch (mode) {
       case kSmZeroIn:
-        k_smooth2<T, NEU, kSmZeroIn><<<grid, nt, 0, st>>>(in, out, f, L, seg, dc, u64);
+        k_smooth2<T, Tile, NEU, kSmZeroIn><<<grid, nt, 0, st>>>(in, out, f, L, seg, dc, u64);
         return;
       case kSmAcc64:
-        k_smooth2<T, NEU, kSmAcc64><<<grid, nt, 0, st>>>(in, out, f, L, seg, dc, u64);
+        k_smooth2<T, Tile, NEU, kSmAcc64><<<grid, nt, 0, st>>>(in, out, f, L, seg, dc, u64);
         return;
       case kSmZeroIn | kSmAcc64:
-        k_smooth2<T, NEU, kSmZeroIn | kSmAcc64><<<grid, nt, 0, st>>>(in, out, f, L, seg, dc, u64);
+        k_smooth2<T, Tile, NEU, kSmZeroIn | kSmAcc64><<<grid, nt, 0, st>>>(in, out, f, L, seg, dc, u64);
         return;
       default:
         break;
     }
   }
-  k_smooth2<T, NEU, kSmPlain><<<grid, nt, 0, st>>>(in, out, f, L, seg, dc, u64);
+  k_smooth2<T, Tile, NEU, kSmPlain><<<grid, nt, 0, st>>>(in, out, f, L, seg, dc, u64);
 }
 
 // One V(nu_pre, nu_post) cycle from level l down.  Level 0 of an FP32
@@ -2070,7 +2084,9 @@ void vcycle(pic_ctx* c, int l, int l0_mode = kSmPlain) {
   if (fused) {
     // One round of workgroups: as many z segments as the device keeps
     // resident, since each segment's march is a latency-bound chain.
-    constexpr int kSX = SmoothTile<T>::SX, kSY = SmoothTile<T>::SY;
+    const bool small = small_columns<T>(L);
+    const int kSX = small ? SmoothSmall::SX : SmoothTile<T>::SX;
+    const int kSY = small ? SmoothSmall::SY : SmoothTile<T>::SY;
     const long long nxy_t = (long long)((L.nx + kSX - 1) / kSX) * ((L.ny + kSY - 1) / kSY);
     const long long slots = smooth_slots<T>();
     seg = (int)(((long long)(L.nz + 1) * nxy_t + slots - 1) / slots);
@@ -2089,10 +2105,16 @@ void vcycle(pic_ctx* c, int l, int l0_mode = kSmPlain) {
   };
   auto smooth_fused = [&](const T* in, T* out, int mode) {
     if (l == 0) tmark(c, PIC_PH_SMOOTH0, true);
-    if (Lc.k0 == 0 || Lc.k1 == Lc.nz)
-      launch_smooth<T, true>(fgrid, st, in, out, f, Lc, seg, c->dc, mode, c->lev[0].u);
-    else
-      launch_smooth<T, false>(fgrid, st, in, out, f, Lc, seg, c->dc, mode, c->lev[0].u);
+    const bool neu = Lc.k0 == 0 || Lc.k1 == Lc.nz;
+    auto go = [&](auto tile, auto n) {
+      launch_smooth<T, decltype(tile), decltype(n)::value>(fgrid, st, in, out, f, Lc, seg, c->dc,
+                                                           mode, c->lev[0].u);
+    };
+    if (small_columns<T>(L)) {
+      if (neu) go(SmoothSmall(), std::true_type()); else go(SmoothSmall(), std::false_type());
+    } else {
+      if (neu) go(SmoothTile<T>(), std::true_type()); else go(SmoothTile<T>(), std::false_type());
+    }
     if (l == 0) tmark(c, PIC_PH_SMOOTH0, false);
   };
   const int pre_mode = l == 0 ? (l0_mode & kSmZeroIn) : kSmPlain;
