@@ -1733,15 +1733,68 @@ __global__ void __launch_bounds__(kT) k_mcc(
   }
 }
 
-// Sort of a record list by (hi, lo) (keys are unique): every kSortChunk
-// chunk is sorted in LDS by its own workgroup (bitonic), then rounds of
-// pairwise merges place each record at its rank in its own run plus the
-// number of smaller keys in the partner run (binary search).  The rounds
-// up to kMergeSeg run in LDS, one workgroup per segment, in one launch
-// (the short lists end there); the host launches the wider rounds for the
-// list's capacity, those whose run width reaches the list's length do
-// nothing, and a last pass brings the result back into the first buffer
-// when an odd number of them ran.
+// Sort of a record list by (hi, lo) (keys are unique).  A short list takes one
+// launch (k_rank_sort).  A long one is sorted per kSortChunk chunk in LDS
+// (bitonic, a workgroup each), then merged: each record goes to its rank in
+// its own run plus the number of smaller keys in the partner runs (binary
+// searches).  The rounds up to kMergeSeg run in LDS, one workgroup per segment,
+// in one launch; the host launches the wider ones, four runs into one, for the
+// list's capacity, those whose run width reaches the list's length do nothing,
+// and a last pass brings the result back into the first buffer when an odd
+// number of them ran.
+
+// Every record to the number of smaller ones, from the list itself to another
+// buffer: 64 records per workgroup, each of its 16 waves comparing them with a
+// sixteenth of the list, whose records it reads by scalar loads.  n^2 / 16
+// comparisons a lane and one launch; correct for any n, and the faster way to
+// about 10^4 records.  The four lists of a 128x128x512 step (690 to some
+// thousand records in a capacity of 4 M) take 59 us; the chunk sorts and LDS
+// merges took 94, and the ten merge rounds of two runs and the copy that
+// followed each, which found nothing to do, another 134.  Empty lists cost 2 us
+// each against 13 (32x32x64, capacity 65536).
+__global__ void __launch_bounds__(1024) k_rank_sort(const Rec* __restrict__ a,
+                                                    Rec* __restrict__ out,
+                                                    const unsigned long long* __restrict__ count,
+                                                    long long cap) {
+  __shared__ unsigned rank[64];
+  const long long nl = (long long)*count;
+  const unsigned n = (unsigned)(nl < cap ? nl : cap);
+  const unsigned lane = threadIdx.x & 63;
+  const unsigned wave = (unsigned)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const unsigned per = (n + 15) / 16;
+  const unsigned j0 = min(wave * per, n), j1 = min(j0 + per, n);
+  for (unsigned long long g = blockIdx.x; g * 64 < n; g += gridDim.x) {
+    if (threadIdx.x < 64) rank[threadIdx.x] = 0u;
+    __syncthreads();
+    const unsigned i = (unsigned)(g * 64) + lane;
+    const Rec x = a[i < n ? i : n - 1];
+    unsigned r = 0;
+    // Batches of scalar loads in flight together (16 bytes a record: lo, hi,
+    // val).
+    const uint4* list = reinterpret_cast<const uint4*>(a);
+    constexpr int kB = 8;
+    auto below = [&](uint4 y, unsigned j) {
+      const unsigned long long lo = y.x | (unsigned long long)y.y << 32;
+      // Equal keys (a caller's duplicate ids) keep their order.
+      return y.z < x.hi || (y.z == x.hi && (lo < x.lo || (lo == x.lo && j < i))) ? 1u : 0u;
+    };
+    unsigned j = j0;
+    for (; j + kB <= j1; j += kB) {
+      const uint4* p = list + j;
+      uint4 y[kB];
+#pragma unroll
+      for (int u = 0; u < kB; ++u) y[u] = p[u];
+#pragma unroll
+      for (int u = 0; u < kB; ++u) r += below(y[u], j + u);
+    }
+    for (; j < j1; ++j) r += below(list[j], j);
+    atomicAdd(&rank[lane], r);
+    __syncthreads();
+    if (threadIdx.x < 64 && i < n) out[rank[lane]] = x;
+    __syncthreads();
+  }
+}
+
 __global__ void __launch_bounds__(kSortT) k_sort_chunks(
     Rec* __restrict__ a, Rec* __restrict__ tmp,
     const unsigned long long* __restrict__ count, long long cap) {
@@ -1783,39 +1836,46 @@ __global__ void __launch_bounds__(kSortT) k_sort_chunks(
   }
 }
 
-// Record i of a merge round: runs of width w (sorted) pairwise into runs
-// of 2w; its position is its rank in its own run plus the number of smaller
-// keys in the partner run (binary search).
+// Record i of a merge round: sorted runs of width w, four at a time into runs of
+// 4w; its position is its rank in its own run plus the numbers of smaller keys
+// in the three others, whose binary searches step together (their loads are in
+// flight at once: a round costs little more than one of two runs and there are
+// half as many).
 __device__ __forceinline__ void merge_one(const Rec* __restrict__ src,
                                           Rec* __restrict__ dst, long long n,
                                           long long w, long long i) {
-  const long long pair = i / (2 * w);
-  const long long a0 = pair * 2 * w;
-  const long long a1 = a0 + w < n ? a0 + w : n;      // run A = [a0, a1)
-  const long long b1 = a1 + w < n ? a1 + w : n;      // run B = [a1, b1)
+  const long long run = i / w, first = run & ~3ll;
   const Rec x = src[i];
-  long long pos;
-  if (i < a1) {
-    long long lo = a1, hi = b1;                        // count of B < x
-    while (lo < hi) {
-      const long long mid = (lo + hi) >> 1;
-      if (rec_less(src[mid], x)) lo = mid + 1; else hi = mid;
-    }
-    pos = a0 + (i - a0) + (lo - a1);
-  } else {
-    long long lo = a0, hi = a1;                        // count of A < x
-    while (lo < hi) {
-      const long long mid = (lo + hi) >> 1;
-      if (rec_less(src[mid], x)) lo = mid + 1; else hi = mid;
-    }
-    pos = a0 + (i - a1) + (lo - a0);
+  long long lo[3], hi[3], base[3];
+#pragma unroll
+  for (int q = 0; q < 3; ++q) {
+    const long long o = first + q + (first + q >= run ? 1 : 0);
+    base[q] = lo[q] = o * w < n ? o * w : n;
+    hi[q] = (o + 1) * w < n ? (o + 1) * w : n;
   }
+  while (lo[0] < hi[0] || lo[1] < hi[1] || lo[2] < hi[2]) {
+    Rec y[3];
+    long long mid[3];
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      mid[q] = (lo[q] + hi[q]) >> 1;
+      y[q] = src[mid[q] < n ? mid[q] : n - 1];
+    }
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
+      if (lo[q] < hi[q]) {
+        if (rec_less(y[q], x)) lo[q] = mid[q] + 1; else hi[q] = mid[q];
+      }
+  }
+  long long pos = i - run * w + first * w;
+#pragma unroll
+  for (int q = 0; q < 3; ++q) pos += lo[q] - base[q];
   dst[pos] = x;
 }
 
 // The merge rounds of widths kSortChunk .. kMergeSeg / 2 of one segment,
-// in LDS: each round reads every record and its new place (merge_one's
-// rule), then, after a barrier, writes them back.
+// in LDS, two runs at a time: each round reads every record and its new
+// place (its rank in both runs), then, after a barrier, writes them back.
 __global__ void __launch_bounds__(kMergeT) k_merge_lds(
     Rec* __restrict__ a, const unsigned long long* __restrict__ count,
     long long cap) {
@@ -1896,7 +1956,7 @@ __global__ void k_copy_recs(const Rec* __restrict__ src, Rec* __restrict__ dst,
   long long n = (long long)*count;
   if (n > cap) n = cap;
   int rounds = 0;
-  for (long long w = kMergeSeg; w < n; w *= 2) ++rounds;
+  for (long long w = kMergeSeg; w < n; w *= 4) ++rounds;
   if ((rounds & 1) == 0) return;
   for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n;
        i += (long long)gridDim.x * blockDim.x)
@@ -1973,7 +2033,9 @@ __global__ void k_match(const Rec* __restrict__ ev, const Rec* __restrict__ nc,
   if (ne > cap) ne = cap;
   long long nn = (long long)dc->n_ncand;
   if (nn > cap) nn = cap;
-  const long long e = blockIdx.x * (long long)blockDim.x + threadIdx.x;
+  const long long stride = (long long)gridDim.x * blockDim.x;
+  for (long long b0 = blockIdx.x * (long long)blockDim.x; b0 < ne; b0 += stride) {
+  const long long e = b0 + threadIdx.x;
   bool hit = false;
   unsigned nidx = 0;
   if (e < ne) {
@@ -1996,6 +2058,7 @@ __global__ void k_match(const Rec* __restrict__ ev, const Rec* __restrict__ nc,
     o.hi = 0; o.lo = ev[e].lo; o.val = (unsigned)s;
     ok[s] = o;
     okp[s] = make_uint2(ev[e].val, nidx);
+  }
   }
 }
 
@@ -2520,26 +2583,38 @@ long long bound(const pic_ctx* c, int s) {
 
 uint32_t* ts_cur(pic_ctx* c, int s) { return c->tsb[s][c->tcur[s]]; }
 
-// Sort a record list of at most cap entries (device count); tmp holds as
-// many.  The result ends in a.
-void sort_records(pic_ctx* c, Rec* a, Rec* tmp,
-                  const unsigned long long* count, long long cap) {
+// Sort a record list of at most cap entries (device count).  The result is in
+// a: the short way sorts into the spare buffer (as large) and swaps the two.
+// The way is chosen by the list's length in the last step (SortList slot;
+// unknown after a load or a failed step): lengths change little from step to
+// step, and either way is right for any length.
+constexpr long long kRankList = 8192;
+
+void sort_records(pic_ctx* c, Rec*& a, const unsigned long long* count, long long cap,
+                  SortList slot) {
   hipStream_t st = c->stream;
+  const long long hint = c->sort_len[slot];
+  if (hint >= 0 && hint <= kRankList) {
+    const unsigned grid = (unsigned)std::min<long long>((cap + 63) / 64, 256);
+    k_rank_sort<<<grid, 1024, 0, st>>>(a, c->rec_tmp, count, cap);
+    std::swap(a, c->rec_tmp);
+    return;
+  }
   // Grids bounded so that a short list in a large capacity costs little:
   // the kernels stride over the device count.
   const long long nchunk = std::min<long long>((cap + kSortChunk - 1) / kSortChunk, 4096);
-  k_sort_chunks<<<(unsigned)nchunk, kSortT, 0, st>>>(a, tmp, count, cap);
+  k_sort_chunks<<<(unsigned)nchunk, kSortT, 0, st>>>(a, c->rec_tmp, count, cap);
   if (cap > kSortChunk)
     k_merge_lds<<<(unsigned)std::min<long long>((cap + kMergeSeg - 1) / kMergeSeg, 1024),
                   kMergeT, 0, st>>>(a, count, cap);
   Rec* src = a;
-  Rec* dst = tmp;
+  Rec* dst = c->rec_tmp;
   const unsigned nround = std::min<unsigned>(nblk(cap), kFixedBlocks);
-  for (long long w = kMergeSeg; w < cap; w *= 2) {
+  for (long long w = kMergeSeg; w < cap; w *= 4) {
     k_merge_round<<<nround, kT, 0, st>>>(src, dst, count, cap, w);
-    Rec* t = src; src = dst; dst = t;
+    std::swap(src, dst);
   }
-  if (cap > kMergeSeg) k_copy_recs<<<256, kT, 0, st>>>(tmp, a, count, cap);
+  if (cap > kMergeSeg) k_copy_recs<<<256, kT, 0, st>>>(c->rec_tmp, a, count, cap);
 }
 
 double qm_dt(int s, double dt) {
@@ -2873,12 +2948,12 @@ void push_collide_t(pic_ctx* c, double dt) {
         cur<PT>(c, 0), c->key[0], c->cand, ts_cur(c, 0), c->cand_cnt,
         c->chunks, c->cstart + nt, c->n_binned[0], m, step, seed, c->ev,
         c->flag, cap, c->el_cnt, c->dc);
-    sort_records(c, c->ev, c->rec_tmp, &c->dc->n_events, cap);
+    sort_records(c, c->ev, &c->dc->n_events, cap, kSortEvents);
     k_neutral_cands<PT><<<(unsigned)((bound(c, 1) + kNCChunk - 1) / kNCChunk), kT, 0, st>>>(
         cur<PT>(c, 1), c->key[1], c->flag, c->nc, cap, c->dc);
-    sort_records(c, c->nc, c->rec_tmp, &c->dc->n_ncand, cap);
-    k_match<<<nblk(cap), kT, 0, st>>>(c->ev, c->nc, c->ok, c->okp, cap, c->dc);
-    sort_records(c, c->ok, c->rec_tmp, &c->dc->n_ok, cap);
+    sort_records(c, c->nc, &c->dc->n_ncand, cap, kSortNeutrals);
+    k_match<<<std::min<unsigned>(nblk(cap), kFixedBlocks), kT, 0, st>>>(c->ev, c->nc, c->ok, c->okp, cap, c->dc);
+    sort_records(c, c->ok, &c->dc->n_ok, cap, kSortMatched);
     k_ionise<PT><<<64, kT, 0, st>>>(cur<PT>(c, 0), cur<PT>(c, 1), cur<PT>(c, 2),
                                     c->key[0], c->key[1], c->key[2], c->ok,
                                     c->okp, m, step, seed, c->cfg.capacity[0],
@@ -2909,7 +2984,7 @@ void push_collide_t(pic_ctx* c, double dt) {
   tmark(c, PIC_PH_COLLIDE, false);
   // Cathode list sorted by (species, id).
   tmark(c, PIC_PH_ABSORBED, true);
-  sort_records(c, c->ab_rec, c->rec_tmp, &c->dc->n_ab, cap);
+  sort_records(c, c->ab_rec, &c->dc->n_ab, cap, kSortAbsorbed);
   k_ab_gather<<<64, kT, 0, st>>>(c->ab_rec, c->ab_raw_pos, c->ab_raw_vel,
                                  c->ab_species, c->ab_id, c->ab_pos, c->ab_vel,
                                  cap, c->dc);
@@ -3082,8 +3157,8 @@ void compact_neutrals_t(pic_ctx* c) {
 
 }  // namespace
 
-void sort_event_records(pic_ctx* c, Rec* a, unsigned long long* count) {
-  sort_records(c, a, c->rec_tmp, count, c->cfg.max_events);
+void sort_event_records(pic_ctx* c, Rec*& a, unsigned long long* count) {
+  sort_records(c, a, count, c->cfg.max_events, kSortIon2);
 }
 
 void parts_md_return(pic_ctx* c, double lattice_a, unsigned mask,

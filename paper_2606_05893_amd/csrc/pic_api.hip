@@ -343,6 +343,13 @@ void derive(pic_ctx* c) {
   c->ev_cap_p2 = pow2_at_least(std::max<long long>(f.max_events, 2));
 }
 
+// Lengths of the record lists, for the next step's sorts.
+void note_list_lengths(pic_ctx* c, bool known) {
+  const Counters& h = c->hc;
+  const unsigned long long n[kSortLists] = {h.n_events, h.n_ncand, h.n_ok, h.n_ab, h.f3_ion2};
+  for (int k = 0; k < kSortLists; ++k) c->sort_len[k] = known ? (long long)n[k] : -1;
+}
+
 pic_status sync_counters(pic_ctx* c) {
   if (!hip_ok(c, hipMemcpyAsync(c->hpin, c->dc, sizeof(Counters),
                                 hipMemcpyDeviceToHost, c->stream),
@@ -507,6 +514,7 @@ pic_status pic_init(const pic_config* cfg, void* ws, size_t bytes,
   std::memset(&c->src, 0, sizeof(c->src));
   std::memset(&c->last_solve, 0, sizeof(c->last_solve));
   std::memset(&c->hc, 0, sizeof(c->hc));
+  note_list_lengths(c, false);
   c->timing = false;
   c->ev_made = false;
   if (!hip_ok(c, hipMemsetAsync(ws, 0, bytes, c->stream), "workspace clear") ||
@@ -783,6 +791,7 @@ pic_status pic_advance(pic_ctx* c, double dt, pic_absorbed* out,
   parts_sources_host(c);
   parts_push_neutral(c, dt);
   const pic_status st = advance_finish(c, dt, add, out, diag);
+  note_list_lengths(c, st == PIC_OK);
   // After a failed step the neutrals are counted and the charge deposited
   // afresh.
   c->acc_next_valid = st == PIC_OK;
@@ -956,6 +965,7 @@ pic_status pic_load_particles(pic_ctx* c, int32_t s, int64_t n,
     return set_err(c, PIC_ERR_CAPACITY, "load exceeds capacity");
   if (n > 0 && (!pos || !vel || !ids)) return PIC_ERR_ARG;
   parts_load(c, s, n, pos, vel, ids);
+  note_list_lengths(c, false);
   if (s == 1) c->ncount_valid = false;
   if (s == 2) c->ion_moved_accum = 0;
   c->acc_next_valid = false;
@@ -1093,6 +1103,7 @@ pic_status pic_checkpoint_load(pic_ctx* c, const void* host, size_t bytes) {
   if (st == PIC_OK) st = pic_set_sources(c, &h.src);
   if (st != PIC_OK) return st;
   c->ncount_valid = false;  // the neutrals are replaced
+  note_list_lengths(c, false);
   c->ion_moved_accum = 0;
   c->acc_next_valid = false;
   for (int s = 0; s < PIC_NSPECIES; ++s) c->n[s] = h.n[s];

@@ -49,6 +49,9 @@ constexpr long long kDirectStepNodes = 1ll << 18;
 // Removed ions a step can list for the in-place removal (more: full binning).
 constexpr int kDeadList = 4096;
 
+// The sorted record lists of a step.
+enum SortList { kSortEvents, kSortNeutrals, kSortMatched, kSortAbsorbed, kSortIon2, kSortLists };
+
 struct QueueCall {
   int species;
   long long n, offset;
@@ -128,7 +131,8 @@ struct pic_ctx {
   uint32_t* el_cnt;          // elastic collisions per tile (+ tail)
   pic::Rec *ev, *nc, *ok;    // events, neutral candidates, matched events
   uint2* okp;                // (electron, neutral) index of a matched event
-  pic::Rec* rec_tmp;         // merge buffer of the record sorts
+  pic::Rec* rec_tmp;         // spare buffer of the record sorts
+  long long sort_len[pic::kSortLists];  // lists' lengths last step (-1: unknown)
   long long ev_cap_p2;       // power-of-two capacity of the record lists
 
   // Cathode-absorbed list: raw (unsorted) and sorted outputs.
@@ -277,7 +281,7 @@ void parts_coulomb(pic_ctx* c, double dt);
 // ---- ion processes (k_ionproc.hip) ----------------------------------------
 void parts_ion_processes(pic_ctx* c, double dt);
 // Sort an event record list of at most max_events entries by (hi, lo).
-void sort_event_records(pic_ctx* c, Rec* a, unsigned long long* count);
+void sort_event_records(pic_ctx* c, Rec*& a, unsigned long long* count);
 
 void parts_deposit(pic_ctx* c);
 // The last step's cathode records of the species in mask, offset back along
