@@ -110,15 +110,12 @@ __device__ __forceinline__ unsigned tile_of_cell(unsigned cell, const GridC& g) 
   return ((k / kTile) * (unsigned)g.tny + j / kTile) * (unsigned)g.tnx + i / kTile;
 }
 
-// Tile (u) of a cell and its slot among the 27 tiles around the source tile
-// (tx, ty, tz), x and y periodic, or -1 when it lies further away.  One
-// decode of the cell (two divisions); tile coordinates are shifts.
-__device__ __forceinline__ int dest_slot(unsigned cell, int tx, int ty, int tz,
+// Tile (u) of cell (i, j, k) and its slot among the 27 tiles around the
+// source tile (tx, ty, tz), x and y periodic, or -1 when it lies further
+// away.  Tile coordinates are shifts.
+__device__ __forceinline__ int dest_slot(unsigned i, unsigned j, unsigned k,
+                                         int tx, int ty, int tz,
                                          const GridC& g, unsigned& u) {
-  const unsigned i = cell % (unsigned)g.nx;
-  const unsigned r = cell / (unsigned)g.nx;
-  const unsigned j = r % (unsigned)g.ny;
-  const unsigned k = r / (unsigned)g.ny;
   const int ux = (int)(i / kTile), uy = (int)(j / kTile), uz = (int)(k / kTile);
   u = ((unsigned)uz * (unsigned)g.tny + (unsigned)uy) * (unsigned)g.tnx + (unsigned)ux;
   int ox = ux - tx, oy = uy - ty;
@@ -131,17 +128,21 @@ __device__ __forceinline__ int dest_slot(unsigned cell, int tx, int ty, int tz,
   return ((oz + 1) * 3 + (oy + 1)) * 3 + (ox + 1);
 }
 
+// The same of a cell index (two divisions).
+__device__ __forceinline__ int dest_slot(unsigned cell, int tx, int ty, int tz,
+                                         const GridC& g, unsigned& u) {
+  const unsigned r = cell / (unsigned)g.nx;
+  return dest_slot(cell % (unsigned)g.nx, r % (unsigned)g.ny,
+                   r / (unsigned)g.ny, tx, ty, tz, g, u);
+}
+
 // Count a pushed particle's destination tile for the binning pass: per
 // neighbouring tile in LDS (sc, sd), else straight into the global counts.
 // Returns the slot (13: its own tile; -1: farther; -2: removed).
 constexpr int kSlotSelf = 13;
-__device__ __forceinline__ int count_dest(unsigned cell, int tx, int ty,
-                                          int tz, const GridC& g,
-                                          unsigned* sc, unsigned* sd,
+__device__ __forceinline__ int count_slot(int d, unsigned u, unsigned* sc,
+                                          unsigned* sd,
                                           unsigned* __restrict__ cnt) {
-  if (cell == kDead) return -2;
-  unsigned u;
-  const int d = dest_slot(cell, tx, ty, tz, g, u);
   if (d >= 0) {
     atomicAdd(&sc[d], 1u);
     sd[d] = u;
@@ -151,17 +152,61 @@ __device__ __forceinline__ int count_dest(unsigned cell, int tx, int ty,
   return d;
 }
 
+__device__ __forceinline__ int count_dest(unsigned cell, int tx, int ty,
+                                          int tz, const GridC& g,
+                                          unsigned* sc, unsigned* sd,
+                                          unsigned* __restrict__ cnt) {
+  if (cell == kDead) return -2;
+  unsigned u;
+  const int d = dest_slot(cell, tx, ty, tz, g, u);
+  return count_slot(d, u, sc, sd, cnt);
+}
+
 // Cell of an in-domain position (0 <= z/dx < nz): the one the MCC uses for
 // the target density and the binning uses for tiles.
 __device__ __forceinline__ unsigned cell_of(double x, double y, double z,
-                                            const GridC& g) {
-  int i = (int)floor(x * g.inv_dx);
-  int j = (int)floor(y * g.inv_dx);
-  const int k = (int)floor(z * g.inv_dx);
+                                            const GridC& g, int& i, int& j,
+                                            int& k) {
+  i = (int)floor(x * g.inv_dx);
+  j = (int)floor(y * g.inv_dx);
+  k = (int)floor(z * g.inv_dx);
   if (i >= g.nx) i -= g.nx;
   if (j >= g.ny) j -= g.ny;
   return ((unsigned)k * (unsigned)g.ny + (unsigned)j) * (unsigned)g.nx + (unsigned)i;
 }
+
+__device__ __forceinline__ unsigned cell_of(double x, double y, double z,
+                                            const GridC& g) {
+  int i, j, k;
+  return cell_of(x, y, z, g, i, j, k);
+}
+
+// The quantised CIC weights of one particle.  The integers (8192 - f or f
+// per axis, f in [0, 8192]) and their products, at most 2^39, are exact in
+// FP64, so they are multiplied there: an FP64 product is one full-rate
+// instruction, an int64 one three at a quarter of the rate, and the gather
+// and the deposit of a push form twelve each (the mixed push of 10 M
+// electrons and 5 M ions: 578 us with int64 products, 569 us with these).
+struct CicW {
+  double x[2], y[2], z[2];   // multiples of 2^-13 in [0, 1]
+  __device__ __forceinline__ CicW(int fx, int fy, int fz) {
+    x[1] = (double)fx * 0x1p-13; x[0] = 1.0 - x[1];
+    y[1] = (double)fy * 0x1p-13; y[0] = 1.0 - y[1];
+    z[1] = (double)fz * 0x1p-13; z[0] = 1.0 - z[1];
+  }
+  // Weight of corner (a, b, c), a multiple of 2^-39.
+  __device__ __forceinline__ double w(int a, int b, int c) const {
+    return (x[a] * y[b]) * z[c];
+  }
+  // sign * weight * 2^39 as an integer: the sum with 1.5 * 2^52 holds it in
+  // its low mantissa bits.
+  __device__ __forceinline__ unsigned long long q(int a, int b, int c,
+                                                  double sign_q) const {
+    const double m = ((x[a] * sign_q) * y[b]) * z[c] + 0x1.8p52;
+    return (unsigned long long)__double_as_longlong(m) - 0x4338000000000000ull;
+  }
+};
+constexpr double kQUnits = 0x1p39;   // charge units of a whole weight
 
 // ---- chunk work lists ----------------------------------------------------------
 // A tile's binned particles of a species are split into pieces of at most
@@ -463,30 +508,27 @@ __global__ void __launch_bounds__(kT) k_deposit(
   for (int sp = 0; sp < 2; ++sp) {
     const PT& p = sp ? pi : pe;
     const uint32_t* ts = sp ? tsi : tse;
-    const long long sign = sp ? 1 : -1;
+    const double sign = sp ? kQUnits : -kQUnits;
     unsigned b, e;
     piece(ts, t, kp, b, e);
     for (unsigned q = b + threadIdx.x; q < e; q += blockDim.x) {
       int ix, fx, iy, fy, iz, fz;
       Acc<PT>::cic(p, q, g, ix, fx, iy, fy, iz, fz);
-      const long long wx[2] = {kQ - fx, fx}, wy[2] = {kQ - fy, fy},
-                      wz[2] = {kQ - fz, fz};
+      const CicW w(fx, fy, fz);
       const int lx = ix - x0, ly = iy - y0, lz = iz - z0;
       const bool inside = lx >= 0 && lx < kTile && ly >= 0 && ly < kTile &&
                           lz >= 0 && lz < kTile;
       for (int c = 0; c < 2; ++c)
         for (int bb = 0; bb < 2; ++bb)
           for (int a = 0; a < 2; ++a) {
-            const long long v = sign * (wx[a] * wy[bb] * wz[c]);
+            const unsigned long long v = w.q(a, bb, c, sign);
             if (inside) {
-              atomicAdd(&s[((lz + c) * 9 + (ly + bb)) * 9 + (lx + a)],
-                        (unsigned long long)v);
+              atomicAdd(&s[((lz + c) * 9 + (ly + bb)) * 9 + (lx + a)], v);
             } else {
               const long long node =
                   ((long long)(iz + c) * g.ny + wrap_index(iy + bb, g.ny)) * g.nx +
                   wrap_index(ix + a, g.nx);
-              atomicAdd(reinterpret_cast<unsigned long long*>(&acc[node]),
-                        (unsigned long long)v);
+              atomicAdd(reinterpret_cast<unsigned long long*>(&acc[node]), v);
             }
           }
     }
@@ -519,8 +561,8 @@ __device__ __forceinline__ void dep_global(long long* __restrict__ acc,
                                            const GridC& g, int ix, int fx,
                                            int iy, int fy, int iz, int fz,
                                            long long sign) {
-  const long long wx[2] = {kQ - fx, fx}, wy[2] = {kQ - fy, fy},
-                  wz[2] = {kQ - fz, fz};
+  const CicW w(fx, fy, fz);
+  const double units = (double)sign * kQUnits;
   for (int c = 0; c < 2; ++c)
     for (int bb = 0; bb < 2; ++bb)
       for (int a = 0; a < 2; ++a) {
@@ -528,7 +570,7 @@ __device__ __forceinline__ void dep_global(long long* __restrict__ acc,
             ((long long)(iz + c) * g.ny + wrap_index(iy + bb, g.ny)) * g.nx +
             wrap_index(ix + a, g.nx);
         atomicAdd(reinterpret_cast<unsigned long long*>(&acc[node]),
-                  (unsigned long long)(sign * (wx[a] * wy[bb] * wz[c])));
+                  w.q(a, bb, c, units));
       }
 }
 
@@ -542,15 +584,18 @@ __device__ __forceinline__ void dep_tile(unsigned long long* sq,
   if (lx < 0 || lx > kDepW - 2 || ly < 0 || ly > kDepW - 2 || lz < 0 ||
       lz > kDepW - 2) {
     dep_global(acc, g, ix, fx, iy, fy, iz, fz, sign);
+    // Keeps the two paths' last adds apart: merged, they are one flat
+    // atomic, which every particle then issues in place of an LDS one.
+    asm volatile("");
     return;
   }
-  const long long wx[2] = {kQ - fx, fx}, wy[2] = {kQ - fy, fy},
-                  wz[2] = {kQ - fz, fz};
+  const CicW w(fx, fy, fz);
+  const double units = (double)sign * kQUnits;
   for (int c = 0; c < 2; ++c)
     for (int bb = 0; bb < 2; ++bb)
       for (int a = 0; a < 2; ++a)
         atomicAdd(&sq[((lz + c) * kDepW + (ly + bb)) * kDepW + (lx + a)],
-                  (unsigned long long)(sign * (wx[a] * wy[bb] * wz[c])));
+                  w.q(a, bb, c, units));
 }
 
 __device__ __forceinline__ void dep_flush(const unsigned long long* sq,
@@ -637,8 +682,7 @@ __device__ __forceinline__ void gather_global(const double* __restrict__ E,
   cic_axis(x, g.inv_dx, ix, fx);
   cic_axis(y, g.inv_dx, iy, fy);
   cic_axis(z, g.inv_dx, iz, fz);
-  const long long wx[2] = {kQ - fx, fx}, wy[2] = {kQ - fy, fy},
-                  wz[2] = {kQ - fz, fz};
+  const CicW cw(fx, fy, fz);
   ex = 0.0; ey = 0.0; ez = 0.0;
 #pragma unroll
   for (int c = 0; c < 2; ++c) {
@@ -648,7 +692,7 @@ __device__ __forceinline__ void gather_global(const double* __restrict__ E,
           ((long long)(iz + c) * g.ny + wrap_index(iy + b, g.ny)) * g.nx;
 #pragma unroll
       for (int a = 0; a < 2; ++a) {
-        const double w = (double)(wx[a] * wy[b] * wz[c]) * kQScale;
+        const double w = cw.w(a, b, c);
         const long long node = row + wrap_index(ix + a, g.nx);
         ex = ex + w * E[node];
         ey = ey + w * E[nn + node];
@@ -664,8 +708,7 @@ __device__ __forceinline__ void gather_lds(const double* sx, const double* sy,
                                            const double* sz, int lx, int ly,
                                            int lz, int fx, int fy, int fz,
                                            double& ex, double& ey, double& ez) {
-  const long long wx[2] = {kQ - fx, fx}, wy[2] = {kQ - fy, fy},
-                  wz[2] = {kQ - fz, fz};
+  const CicW cw(fx, fy, fz);
   ex = 0.0; ey = 0.0; ez = 0.0;
 #pragma unroll
   for (int c = 0; c < 2; ++c) {
@@ -674,7 +717,7 @@ __device__ __forceinline__ void gather_lds(const double* sx, const double* sy,
       const int row = ((lz + c) * 9 + (ly + b)) * 9 + lx;
 #pragma unroll
       for (int a = 0; a < 2; ++a) {
-        const double w = (double)(wx[a] * wy[b] * wz[c]) * kQScale;
+        const double w = cw.w(a, b, c);
         ex = ex + w * sx[row + a];
         ey = ey + w * sy[row + a];
         ez = ez + w * sz[row + a];
@@ -687,11 +730,25 @@ __device__ __forceinline__ void gather_lds(const double* sx, const double* sy,
 struct PushOut {
   bool cathode, anode, cand;
   unsigned cell;
+  int ci, cj, ck;      // the cell's coordinates (cell != kDead)
+  int nc;              // electrons: neutrals in the cell
   double ke;           // |v|^2 after the kick
   double x, y, z, vx, vy, vz;
   float oxf, oyf, ozf; // mixed layout: the stored in-cell offsets
   unsigned long long id;  // electron candidates: the id of the draw
 };
+
+// Its destination tile, counted from the coordinates the push already has.
+__device__ __forceinline__ int count_dest(const PushOut& o, int tx, int ty,
+                                          int tz, const GridC& g,
+                                          unsigned* sc, unsigned* sd,
+                                          unsigned* __restrict__ cnt) {
+  if (o.cell == kDead) return -2;
+  unsigned u;
+  const int d = dest_slot((unsigned)o.ci, (unsigned)o.cj, (unsigned)o.ck, tx,
+                          ty, tz, g, u);
+  return count_slot(d, u, sc, sd, cnt);
+}
 
 // CIC cell and quantised weights of a pushed particle's stored position
 // (FP64: wrapped coordinates; mixed: cell and FP32 offsets), as the
@@ -709,24 +766,46 @@ __device__ __forceinline__ void cic_stored(const Parts&, const PushOut& o,
 __device__ __forceinline__ void cic_stored(const PartsM&, const PushOut& o,
                                            const GridC& g, int& ix, int& fx,
                                            int& iy, int& fy, int& iz, int& fz) {
-  Acc<PartsM>::decode(o.cell, g, ix, iy, iz);
+  ix = o.ci; iy = o.cj; iz = o.ck;
   fx = (int)floorf(o.oxf * 8192.0f + 0.5f);
   fy = (int)floorf(o.oyf * 8192.0f + 0.5f);
   fz = (int)floorf(o.ozf * 8192.0f + 0.5f);
 }
 
-// Drift, boundaries, write-back and (electrons) the null-collision
-// candidate draw U1 < 1 - exp(-N_c c_coll); velocities already kicked.
-template <int SP>
+// Null-collision probability with nc neutrals in the cell.
+__device__ __forceinline__ double mcc_p(double c_coll, int nc) {
+  return 1.0 - exp(-((double)nc * c_coll));
+}
+
+// Null-collision candidate draw of a pushed electron, U1 < 1 - exp(-N_c
+// c_coll), with the neutral count its push read (0: no draw).  ptab: the
+// probabilities of the counts below kPTab, or null.
+constexpr int kPTab = 64;
+__device__ __forceinline__ void mcc_draw(const MccC& m, uint32_t step,
+                                         uint64_t seed, Counters* dc,
+                                         PushOut& o, uint64_t idv,
+                                         const double* ptab) {
+  if (o.nc > 0) {
+    const double pstar =
+        ptab && o.nc < kPTab ? ptab[o.nc] : mcc_p(m.c_coll, o.nc);
+    double u1, u2;
+    uniform2(idv, step, kTagMcc0, seed, u1, u2);
+    if (fabs(u1 - pstar) < 1e-6) atomicAdd(&dc->n_near, 1ull);
+    o.cand = u1 < pstar;
+    o.id = idv;
+  }
+}
+
+// Drift, boundaries and write-back of a particle of species sp (0 electron,
+// 1 neutral, 2 ion, 3 Cu2+), its velocity already kicked; an electron's
+// neutral count is read for mcc_draw.
 __device__ __forceinline__ void finish_push(Parts& p, long long i, double x,
                                             double y, double z, double vx,
                                             double vy, double vz, double dt,
                                             const GridC& g, uint32_t* key,
-                                            int* ncount, const MccC& m,
-                                            uint32_t step, uint64_t seed,
-                                            Counters* dc, PushOut& o,
-                                            uint64_t idv) {
-  const bool np = SP == 0 && m.sph_on && sphere_hit(m, g, x, y, z, vx, vy, vz);
+                                            const int* ncount, const MccC& m,
+                                            Counters* dc, PushOut& o, int sp) {
+  const bool np = sp == 0 && m.sph_on && sphere_hit(m, g, x, y, z, vx, vy, vz);
   x = x + vx * dt;
   y = y + vy * dt;
   z = z + vz * dt;
@@ -734,6 +813,7 @@ __device__ __forceinline__ void finish_push(Parts& p, long long i, double x,
   o.cathode = false;
   o.anode = false;
   o.cand = false;
+  o.nc = 0;
   o.cell = kDead;
   const double gz = z * g.inv_dx;
   const double xw = wrap_coord(x, g.lx), yw = wrap_coord(y, g.ly);
@@ -753,26 +833,16 @@ __device__ __forceinline__ void finish_push(Parts& p, long long i, double x,
   } else {
     x = xw;
     y = yw;
-    o.cell = cell_of(x, y, z, g);
+    o.cell = cell_of(x, y, z, g, o.ci, o.cj, o.ck);
+    if (sp == 0 && m.enabled) o.nc = ncount[o.cell];
     p.x[i] = x; p.y[i] = y; p.z[i] = z;
     // A neutral's velocity does not change; its cell count is added by the
     // caller (aggregated in LDS).
-    if (SP != 1) {
+    if (sp != 1) {
       p.vx[i] = vx; p.vy[i] = vy; p.vz[i] = vz;
     }
   }
   key[i] = o.cell;
-  if (SP == 0 && o.cell != kDead && m.enabled) {
-    const int nc = ncount[o.cell];
-    if (nc > 0) {
-      const double pstar = 1.0 - exp(-((double)nc * m.c_coll));
-      double u1, u2;
-      uniform2(idv, step, kTagMcc0, seed, u1, u2);
-      if (fabs(u1 - pstar) < 1e-6) atomicAdd(&dc->n_near, 1ull);
-      o.cand = u1 < pstar;
-      o.id = idv;
-    }
-  }
   o.x = x; o.y = y; o.z = z; o.vx = vx; o.vy = vy; o.vz = vz;
 }
 
@@ -796,14 +866,13 @@ __device__ __forceinline__ void list_dead(bool dead, long long i,
 }
 
 // Cathode sink record (wave-aggregated slot).  All lanes must call it.
-template <int SP>
 __device__ __forceinline__ void sink(const Parts& p, long long i,
                                      const PushOut& o, const GridC& g,
                                      Rec* ab_rec, double* ab_pos,
                                      double* ab_vel, long long ab_cap,
-                                     Counters* dc) {
-  wave_count(o.anode, &dc->anode[SP]);
-  wave_count(o.cathode, &dc->cathode[SP]);
+                                     Counters* dc, int sp) {
+  wave_count(o.anode, &dc->anode[sp]);
+  wave_count(o.cathode, &dc->cathode[sp]);
   const unsigned long long slot = wave_append(o.cathode, &dc->n_ab);
   if (!o.cathode) return;
   if ((long long)slot < ab_cap) {
@@ -811,7 +880,7 @@ __device__ __forceinline__ void sink(const Parts& p, long long i,
     const double xc = wrap_coord(o.x + o.vx * tc, g.lx);
     const double yc = wrap_coord(o.y + o.vy * tc, g.ly);
     Rec r;
-    r.hi = SP; r.lo = p.id[i]; r.val = (unsigned)slot;
+    r.hi = sp; r.lo = p.id[i]; r.val = (unsigned)slot;
     ab_rec[slot] = r;
     ab_pos[3 * slot] = xc; ab_pos[3 * slot + 1] = yc; ab_pos[3 * slot + 2] = 0.0;
     ab_vel[3 * slot] = o.vx; ab_vel[3 * slot + 1] = o.vy;
@@ -819,6 +888,13 @@ __device__ __forceinline__ void sink(const Parts& p, long long i,
   } else {
     atomicOr(&dc->err, kErrEvents);
   }
+}
+
+// Sum over a wave, in every lane (butterfly order).
+__device__ __forceinline__ double wave_sum(double v) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v = v + __shfl_xor(v, o, 64);
+  return v;
 }
 
 __device__ __forceinline__ double block_sum(double v, double* sk) {
@@ -837,162 +913,6 @@ __device__ __forceinline__ double block_sum(double v, double* sk) {
 // nodes are staged in LDS once and serve both the ions and the electrons
 // binned in the tile.  Electron candidates are written to the tile's own
 // segment of the candidate list (no global counter).
-struct TileArgs {
-  Parts pe, pi;
-  const uint32_t *tse, *tsi;
-  const uint2* chunks;
-  const unsigned* nchunks;
-  uint32_t *keye, *keyi;
-  double qm_e, qm_i, dt;
-  int* ncount;
-  CandRec* cand;
-  uint32_t* cand_cnt;
-  Rec* ab_rec;
-  double *ab_pos, *ab_vel;
-  long long ab_cap;
-  double *part_e, *part_i;
-  unsigned *cnt_e, *cnt_i;   // destination-tile counts for the binning
-  long long* dep;            // charge of the pushed state (int64 units)
-  uint32_t* dead2;           // removed ions' indices
-};
-
-__global__ void __launch_bounds__(kT) k_push_tile(
-    TileArgs A, const double* __restrict__ E, long long nn, GridC g, MccC m,
-    uint32_t step, uint64_t seed, Counters* dc) {
-  __shared__ double sx[729], sy[729], sz[729];
-  __shared__ unsigned long long sq[kDepN];
-  __shared__ double sk[kT];
-  __shared__ unsigned s_cand;
-  __shared__ unsigned s_nc[2][27], s_nd[2][27];  // destinations: e, ions
-  const unsigned nchk = *A.nchunks;
-  if (blockIdx.x >= nchk) return;
-  const unsigned cb = xcd_block(blockIdx.x, nchk);
-  const unsigned t = A.chunks[cb].x, kp = A.chunks[cb].y;
-  unsigned be, ee, bi, ei;
-  piece(A.tse, t, kp, be, ee);
-  piece(A.tsi, t, kp, bi, ei);
-  if (be == ee && bi == ei) {
-    if (threadIdx.x == 0) {
-      A.part_e[cb] = 0.0;
-      A.part_i[cb] = 0.0;
-      A.cand_cnt[cb] = 0;
-    }
-    return;
-  }
-  const int tx = (int)(t % g.tnx);
-  const int ty = (int)((t / g.tnx) % g.tny);
-  const int tz = (int)(t / ((unsigned)g.tnx * g.tny));
-  const int x0 = tx * kTile, y0 = ty * kTile, z0 = tz * kTile;
-  for (int q = threadIdx.x; q < 729; q += blockDim.x) {
-    const int a = q % 9, b = (q / 9) % 9, c = q / 81;
-    const int gk = z0 + c;
-    double vx = 0.0, vy = 0.0, vz = 0.0;
-    if (gk <= g.nz) {
-      const long long node = ((long long)gk * g.ny + wrap_index(y0 + b, g.ny)) *
-                                 g.nx + wrap_index(x0 + a, g.nx);
-      vx = E[node]; vy = E[nn + node]; vz = E[2 * nn + node];
-    }
-    sx[q] = vx; sy[q] = vy; sz[q] = vz;
-  }
-  for (int q = threadIdx.x; q < kDepN; q += blockDim.x) sq[q] = 0ull;
-  if (threadIdx.x == 0) s_cand = 0;
-  if (threadIdx.x < 54) (&s_nc[0][0])[threadIdx.x] = 0u;
-  __syncthreads();
-  double ke_i = 0.0, ke_e = 0.0;
-  // Ions.
-  for (unsigned base = bi; base < ei; base += blockDim.x) {
-    const long long i = base + threadIdx.x;
-    const bool live = i < ei;
-    PushOut o;
-    o.cathode = false;
-    o.anode = false;
-    bool moved = false;
-    if (live) {
-      const double x = A.pi.x[i], y = A.pi.y[i], z = A.pi.z[i];
-      int ix, fx, iy, fy, iz, fz;
-      cic_axis(x, g.inv_dx, ix, fx);
-      cic_axis(y, g.inv_dx, iy, fy);
-      cic_axis(z, g.inv_dx, iz, fz);
-      if (ix >= g.nx) ix -= g.nx;
-      if (iy >= g.ny) iy -= g.ny;
-      const int lx = ix - x0, ly = iy - y0, lz = iz - z0;
-      double ex, ey, ez;
-      if (lx >= 0 && lx < kTile && ly >= 0 && ly < kTile && lz >= 0 && lz < kTile)
-        gather_lds(sx, sy, sz, lx, ly, lz, fx, fy, fz, ex, ey, ez);
-      else
-        gather_global(E, nn, g, x, y, z, ex, ey, ez);
-      const double vx = A.pi.vx[i] + A.qm_i * ex;
-      const double vy = A.pi.vy[i] + A.qm_i * ey;
-      const double vz = A.pi.vz[i] + A.qm_i * ez;
-      finish_push<2>(A.pi, i, x, y, z, vx, vy, vz, A.dt, g, A.keyi, A.ncount, m,
-                     step, seed, dc, o, 0ull);
-      ke_i = ke_i + o.ke;
-      moved = count_dest(o.cell, tx, ty, tz, g, s_nc[1], s_nd[1], A.cnt_i) != kSlotSelf &&
-              o.cell != kDead;
-      if (o.cell != kDead) {
-        int dx_, fx_, dy_, fy_, dz_, fz_;
-        cic_stored(Parts(), o, g, dx_, fx_, dy_, fy_, dz_, fz_);
-        dep_tile(sq, A.dep, g, x0, y0, z0, dx_, fx_, dy_, fy_, dz_, fz_, 1);
-      }
-    }
-    sink<2>(A.pi, i, o, g, A.ab_rec, A.ab_pos, A.ab_vel, A.ab_cap, dc);
-    wave_count(moved, &dc->ion_moved);
-    list_dead(live && o.cell == kDead, i, A.dead2, &dc->n_dead2);
-  }
-  // Electrons.
-  for (unsigned base = be; base < ee; base += blockDim.x) {
-    const long long i = base + threadIdx.x;
-    const bool live = i < ee;
-    PushOut o;
-    o.cathode = false;
-    o.anode = false;
-    o.cand = false;
-    if (live) {
-      const double x = A.pe.x[i], y = A.pe.y[i], z = A.pe.z[i];
-      int ix, fx, iy, fy, iz, fz;
-      cic_axis(x, g.inv_dx, ix, fx);
-      cic_axis(y, g.inv_dx, iy, fy);
-      cic_axis(z, g.inv_dx, iz, fz);
-      if (ix >= g.nx) ix -= g.nx;
-      if (iy >= g.ny) iy -= g.ny;
-      const int lx = ix - x0, ly = iy - y0, lz = iz - z0;
-      double ex, ey, ez;
-      if (lx >= 0 && lx < kTile && ly >= 0 && ly < kTile && lz >= 0 && lz < kTile)
-        gather_lds(sx, sy, sz, lx, ly, lz, fx, fy, fz, ex, ey, ez);
-      else
-        gather_global(E, nn, g, x, y, z, ex, ey, ez);
-      const double vx = A.pe.vx[i] + A.qm_e * ex;
-      const double vy = A.pe.vy[i] + A.qm_e * ey;
-      const double vz = A.pe.vz[i] + A.qm_e * ez;
-      finish_push<0>(A.pe, i, x, y, z, vx, vy, vz, A.dt, g, A.keye, A.ncount, m,
-                     step, seed, dc, o, A.pe.id[i]);
-      ke_e = ke_e + o.ke;
-      count_dest(o.cell, tx, ty, tz, g, s_nc[0], s_nd[0], A.cnt_e);
-      if (o.cell != kDead) {
-        int dx_, fx_, dy_, fy_, dz_, fz_;
-        cic_stored(Parts(), o, g, dx_, fx_, dy_, fy_, dz_, fz_);
-        dep_tile(sq, A.dep, g, x0, y0, z0, dx_, fx_, dy_, fy_, dz_, fz_, -1);
-      }
-      if (o.cand) A.cand[be + atomicAdd(&s_cand, 1u)] = cand_rec(o, i);
-    }
-    sink<0>(A.pe, i, o, g, A.ab_rec, A.ab_pos, A.ab_vel, A.ab_cap, dc);
-  }
-  const double si = block_sum(ke_i, sk);
-  const double se = block_sum(ke_e, sk);
-  if (threadIdx.x == 0) {
-    A.part_i[cb] = si;
-    A.part_e[cb] = se;
-    A.cand_cnt[cb] = s_cand;
-  }
-  // The destination counts are complete (block_sum synchronised).
-  if (threadIdx.x < 54) {
-    const int sp = threadIdx.x / 27, d = threadIdx.x % 27;
-    const unsigned n = s_nc[sp][d];
-    if (n) atomicAdd(&(sp ? A.cnt_i : A.cnt_e)[s_nd[sp][d]], n);
-  }
-  dep_flush(sq, A.dep, g, x0, y0, z0);
-}
-
 // Particles not covered by tile ranges (sources and queue appended this
 // step; all neutrals): one thread per particle, field from global memory.
 template <int SP>
@@ -1023,8 +943,8 @@ __global__ void __launch_bounds__(kT) k_push_list(
       vy = vy + qm_dt * ey;
       vz = vz + qm_dt * ez;
     }
-    finish_push<SP>(p, i, x, y, z, vx, vy, vz, dt, g, key, ncount, m, step,
-                    seed, dc, o, SP == 0 ? p.id[i] : 0ull);
+    finish_push(p, i, x, y, z, vx, vy, vz, dt, g, key, ncount, m, dc, o, SP);
+    if (SP == 0) mcc_draw(m, step, seed, dc, o, p.id[i], nullptr);
     if (SP != 1 && o.cell != kDead) {
       int dx_, fx_, dy_, fy_, dz_, fz_;
       cic_stored(Parts(), o, g, dx_, fx_, dy_, fy_, dz_, fz_);
@@ -1032,7 +952,7 @@ __global__ void __launch_bounds__(kT) k_push_list(
                  SP == 0 ? -1 : (SP == 3 ? 2 : 1));
     }
   }
-  sink<SP>(p, i, o, g, ab_rec, ab_pos, ab_vel, ab_cap, dc);
+  sink(p, i, o, g, ab_rec, ab_pos, ab_vel, ab_cap, dc, SP);
   if (SP == 2) list_dead(live && o.cell == kDead, i, dead2, &dc->n_dead2);
   if (SP == 0) {
     const unsigned long long cs = wave_append(o.cand, &dc->n_tail_cand);
@@ -1056,15 +976,13 @@ struct PushM {
 // Drift in cell units and carry into the cell index; returns the cell key
 // or kDead, and fills the FP64 PushOut (absolute position before the x, y
 // wrap for the cathode crossing point).
-template <int SP>
 __device__ __forceinline__ void finish_push_m(PartsM& p, long long i, PushM q,
                                               float dtdx, const GridC& g,
-                                              uint32_t* key, int* ncount,
-                                              const MccC& m, uint32_t step,
-                                              uint64_t seed, Counters* dc,
-                                              PushOut& o) {
+                                              uint32_t* key, const int* ncount,
+                                              const MccC& m, Counters* dc,
+                                              PushOut& o, int sp) {
   bool np = false;
-  if (SP == 0 && m.sph_on)
+  if (sp == 0 && m.sph_on)
     np = sphere_hit(m, g, ((double)q.ix + (double)q.ox) * g.dx,
                     ((double)q.iy + (double)q.oy) * g.dx,
                     ((double)q.iz + (double)q.oz) * g.dx, (double)q.vx,
@@ -1086,6 +1004,7 @@ __device__ __forceinline__ void finish_push_m(PartsM& p, long long i, PushM q,
   o.cathode = false;
   o.anode = false;
   o.cand = false;
+  o.nc = 0;
   o.cell = kDead;
   const int jx = ix >= g.nx ? ix - g.nx : (ix < 0 ? ix + g.nx : ix);
   const int jy = iy >= g.ny ? iy - g.ny : (iy < 0 ? iy + g.ny : iy);
@@ -1102,26 +1021,16 @@ __device__ __forceinline__ void finish_push_m(PartsM& p, long long i, PushM q,
   } else {
     o.cell = ((unsigned)iz * (unsigned)g.ny + (unsigned)jy) * (unsigned)g.nx +
              (unsigned)jx;
+    o.ci = jx; o.cj = jy; o.ck = iz;
+    if (sp == 0 && m.enabled) o.nc = ncount[o.cell];
     p.cell[i] = o.cell;
     p.ox[i] = q.ox; p.oy[i] = q.oy; p.oz[i] = q.oz;
     o.oxf = q.ox; o.oyf = q.oy; o.ozf = q.oz;
-    if (SP != 1) {
+    if (sp != 1) {
       p.vx[i] = q.vx; p.vy[i] = q.vy; p.vz[i] = q.vz;
     }
   }
   key[i] = o.cell;
-  if (SP == 0 && o.cell != kDead && m.enabled) {
-    const int nc = ncount[o.cell];
-    if (nc > 0) {
-      const double pstar = 1.0 - exp(-((double)nc * m.c_coll));
-      double u1, u2;
-      const unsigned long long idv = p.id[i];
-      uniform2(idv, step, kTagMcc0, seed, u1, u2);
-      o.id = idv;
-      if (fabs(u1 - pstar) < 1e-6) atomicAdd(&dc->n_near, 1ull);
-      o.cand = u1 < pstar;
-    }
-  }
 }
 
 // FP32 CIC gather with the quantised weights; E nodes from LDS (tile) or
@@ -1130,8 +1039,7 @@ __device__ __forceinline__ void gather_m(const float* sx, const float* sy,
                                          const float* sz, int lrow, int rs,
                                          int ps, int fx, int fy, int fz,
                                          float& ex, float& ey, float& ez) {
-  const long long wx[2] = {kQ - fx, fx}, wy[2] = {kQ - fy, fy},
-                  wz[2] = {kQ - fz, fz};
+  const CicW cw(fx, fy, fz);
   ex = 0.0f; ey = 0.0f; ez = 0.0f;
 #pragma unroll
   for (int c = 0; c < 2; ++c)
@@ -1139,7 +1047,7 @@ __device__ __forceinline__ void gather_m(const float* sx, const float* sy,
     for (int b = 0; b < 2; ++b)
 #pragma unroll
       for (int a = 0; a < 2; ++a) {
-        const float w = (float)(wx[a] * wy[b] * wz[c]) * 0x1p-39f;
+        const float w = (float)cw.w(a, b, c);
         const int q = lrow + c * ps + b * rs + a;
         ex = ex + w * sx[q];
         ey = ey + w * sy[q];
@@ -1152,8 +1060,7 @@ __device__ __forceinline__ void gather_m_global(const float* __restrict__ E,
                                                 int ix, int iy, int iz, int fx,
                                                 int fy, int fz, float& ex,
                                                 float& ey, float& ez) {
-  const long long wx[2] = {kQ - fx, fx}, wy[2] = {kQ - fy, fy},
-                  wz[2] = {kQ - fz, fz};
+  const CicW cw(fx, fy, fz);
   ex = 0.0f; ey = 0.0f; ez = 0.0f;
 #pragma unroll
   for (int c = 0; c < 2; ++c)
@@ -1163,7 +1070,7 @@ __device__ __forceinline__ void gather_m_global(const float* __restrict__ E,
           ((long long)(iz + c) * g.ny + wrap_index(iy + b, g.ny)) * g.nx;
 #pragma unroll
       for (int a = 0; a < 2; ++a) {
-        const float w = (float)(wx[a] * wy[b] * wz[c]) * 0x1p-39f;
+        const float w = (float)cw.w(a, b, c);
         const long long node = row + wrap_index(ix + a, g.nx);
         ex = ex + w * E[node];
         ey = ey + w * E[nn + node];
@@ -1172,40 +1079,69 @@ __device__ __forceinline__ void gather_m_global(const float* __restrict__ E,
     }
 }
 
-struct TileArgsM {
-  PartsM pe, pi;
-  const uint32_t *tse, *tsi;
-  const uint2* chunks;
-  const unsigned* nchunks;
-  uint32_t *keye, *keyi;
-  float qm_e, qm_i, dtdx;
-  int* ncount;
-  CandRec* cand;
-  uint32_t* cand_cnt;
-  Rec* ab_rec;
-  double *ab_pos, *ab_vel;
-  long long ab_cap;
-  double *part_e, *part_i;
-  unsigned *cnt_e, *cnt_i;   // destination-tile counts for the binning
-  long long* dep;            // charge of the pushed state (int64 units)
-  uint32_t* dead2;           // removed ions' indices
+// One particle as loaded from its arrays.
+struct InD {
+  double x, y, z, vx, vy, vz;
+};
+struct InM {
+  unsigned cell;
+  float ox, oy, oz, vx, vy, vz;
 };
 
-template <int SP>
-__device__ __forceinline__ void push_one_m(PartsM& p, long long i,
-                                           const float* sx, const float* sy,
-                                           const float* sz, int x0, int y0,
-                                           int z0, const float* __restrict__ E,
-                                           long long nn, const GridC& g,
-                                           float qm, float dtdx, uint32_t* key,
-                                           int* ncount, const MccC& m,
-                                           uint32_t step, uint64_t seed,
-                                           Counters* dc, PushOut& o) {
-  PushM q;
-  Acc<PartsM>::decode(p.cell[i], g, q.ix, q.iy, q.iz);
+__device__ __forceinline__ void load_in(const Parts& p, long long i, InD& q) {
+  q.x = p.x[i]; q.y = p.y[i]; q.z = p.z[i];
+  q.vx = p.vx[i]; q.vy = p.vy[i]; q.vz = p.vz[i];
+}
+
+__device__ __forceinline__ void load_in(const PartsM& p, long long i, InM& q) {
+  q.cell = p.cell[i];
   q.ox = p.ox[i]; q.oy = p.oy[i]; q.oz = p.oz[i];
   q.vx = p.vx[i]; q.vy = p.vy[i]; q.vz = p.vz[i];
-  if (SP != 1) {
+}
+
+// Kick and drift of one loaded particle of species sp.  sx, sy, sz: the
+// field of the tile at (x0, y0, z0) in LDS, or null (neutrals, and the
+// lists: field from global memory).  len: dt, mixed dt / dx.
+__device__ __forceinline__ void push_one(Parts& p, long long i, const InD& q,
+                                         const double* sx, const double* sy,
+                                         const double* sz, int x0, int y0,
+                                         int z0, const double* __restrict__ E,
+                                         long long nn, const GridC& g,
+                                         double qm, double len, uint32_t* key,
+                                         const int* ncount, const MccC& m,
+                                         Counters* dc, PushOut& o, int sp) {
+  int ix, fx, iy, fy, iz, fz;
+  cic_axis(q.x, g.inv_dx, ix, fx);
+  cic_axis(q.y, g.inv_dx, iy, fy);
+  cic_axis(q.z, g.inv_dx, iz, fz);
+  if (ix >= g.nx) ix -= g.nx;
+  if (iy >= g.ny) iy -= g.ny;
+  const int lx = ix - x0, ly = iy - y0, lz = iz - z0;
+  double ex, ey, ez;
+  if (lx >= 0 && lx < kTile && ly >= 0 && ly < kTile && lz >= 0 && lz < kTile)
+    gather_lds(sx, sy, sz, lx, ly, lz, fx, fy, fz, ex, ey, ez);
+  else
+    gather_global(E, nn, g, q.x, q.y, q.z, ex, ey, ez);
+  const double vx = q.vx + qm * ex;
+  const double vy = q.vy + qm * ey;
+  const double vz = q.vz + qm * ez;
+  finish_push(p, i, q.x, q.y, q.z, vx, vy, vz, len, g, key, ncount, m, dc, o,
+              sp);
+}
+
+__device__ __forceinline__ void push_one(PartsM& p, long long i, const InM& in,
+                                         const float* sx, const float* sy,
+                                         const float* sz, int x0, int y0,
+                                         int z0, const float* __restrict__ E,
+                                         long long nn, const GridC& g,
+                                         float qm, float len, uint32_t* key,
+                                         const int* ncount, const MccC& m,
+                                         Counters* dc, PushOut& o, int sp) {
+  PushM q;
+  Acc<PartsM>::decode(in.cell, g, q.ix, q.iy, q.iz);
+  q.ox = in.ox; q.oy = in.oy; q.oz = in.oz;
+  q.vx = in.vx; q.vy = in.vy; q.vz = in.vz;
+  if (sp != 1) {
     const int fx = (int)floorf(q.ox * 8192.0f + 0.5f);
     const int fy = (int)floorf(q.oy * 8192.0f + 0.5f);
     const int fz = (int)floorf(q.oz * 8192.0f + 0.5f);
@@ -1220,7 +1156,7 @@ __device__ __forceinline__ void push_one_m(PartsM& p, long long i,
     q.vy = q.vy + qm * ey;
     q.vz = q.vz + qm * ez;
   }
-  finish_push_m<SP>(p, i, q, dtdx, g, key, ncount, m, step, seed, dc, o);
+  finish_push_m(p, i, q, len, g, key, ncount, m, dc, o, sp);
 }
 
 // Sink record from an FP64 PushOut, shared with the FP64 layout.
@@ -1248,105 +1184,207 @@ __device__ __forceinline__ void sink_m(const PartsM& p, long long i, int sp,
   }
 }
 
-__global__ void __launch_bounds__(kT) k_push_tile_m(
-    TileArgsM A, const float* __restrict__ E, long long nn, GridC g, MccC m,
-    uint32_t step, uint64_t seed, Counters* dc) {
-  __shared__ float sx[729], sy[729], sz[729];
+// Sink records of one species, whichever layout.
+__device__ __forceinline__ void sink_any(const Parts& p, long long i, int sp,
+                                         const PushOut& o, const GridC& g,
+                                         Rec* ab_rec, double* ab_pos,
+                                         double* ab_vel, long long ab_cap,
+                                         Counters* dc) {
+  sink(p, i, o, g, ab_rec, ab_pos, ab_vel, ab_cap, dc, sp);
+}
+__device__ __forceinline__ void sink_any(const PartsM& p, long long i, int sp,
+                                         const PushOut& o, const GridC& g,
+                                         Rec* ab_rec, double* ab_pos,
+                                         double* ab_vel, long long ab_cap,
+                                         Counters* dc) {
+  sink_m(p, i, sp, o, g, ab_rec, ab_pos, ab_vel, ab_cap, dc);
+}
+
+// ---- push of the binned particles ----------------------------------------------
+template <class PT> struct InOf;
+template <> struct InOf<Parts> { using type = InD; using real = double; };
+template <> struct InOf<PartsM> { using type = InM; using real = float; };
+
+// One species of a tile push.
+template <class PT>
+struct TileSp {
+  PT p;
+  const uint32_t* ts;
+  uint32_t* key;
+  typename InOf<PT>::real qm;
+  double* part;              // kinetic sums, one per chunk
+  unsigned* cnt;             // destination-tile counts for the binning
+};
+
+template <class PT>
+struct TileArgs {
+  TileSp<PT> sp[2];          // electrons, ions
+  const uint2* chunks;
+  const unsigned* nchunks;
+  typename InOf<PT>::real len;   // dt (mixed: dt / dx)
+  int* ncount;
+  CandRec* cand;
+  uint32_t* cand_cnt;
+  Rec* ab_rec;
+  double *ab_pos, *ab_vel;
+  long long ab_cap;
+  long long* dep;            // charge of the pushed state (int64 units)
+  uint32_t* dead2;           // removed ions' indices
+  const typename InOf<PT>::real* E;
+  long long nn;
+  GridC g;
+  MccC m;
+  uint32_t step;
+  uint64_t seed;
+  Counters* dc;
+};
+
+// The kernel's argument, read again from the kernel argument segment: the
+// tile push has more uniform values than scalar registers, and those the
+// compiler would keep over its loop it moves to and from vector lanes
+// (400 v_readlane and v_writelane), where a scalar load costs one request.
+template <class A>
+__device__ __forceinline__ const A& reread() {
+  typedef const __attribute__((address_space(4))) A* Seg;
+  Seg p = (Seg)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  return *(const A*)p;
+}
+
+// One workgroup per chunk of a tile.  Its waves take the chunk's ions and
+// then its electrons 64 at a time, wave w the groups w, w + 4, ..., so a wave
+// idles for at most one group (the two species in turn, 256 particles at a
+// time, left the last waves idle in each: 693 against 663 us, FP64, 10 M
+// electrons and 5 M ions on 128 x 128 x 512 cells; 578 against 531 us mixed).
+// The uniform values are read again from the argument segment (no vector
+// lanes for spilled scalars), the collision probabilities of few neutrals
+// come from a table in LDS, and the two kinetic sums take one barrier: 621
+// and 509 us.  The deposit's last add kept out of a flat atomic: 610 and
+// 493 us.  What bounds it: 2.4 GB through HBM (reads, writes and the charge
+// block's 3.4 M atomics) are 470 us of the FP64 push at a copy's rate; the
+// gather, the deposit, the flush and the collision draw each cost 60 to 100
+// us when left out alone, so no single one hides behind memory.  More waves
+// per SIMD (96 registers, some spilled: 640 and 488 us) and loading the next
+// group while pushing one (no change) do not help.
+template <class PT>
+__global__ void __launch_bounds__(kT) k_push_tile(TileArgs<PT> args) {
+  using real = typename InOf<PT>::real;
+  using In = typename InOf<PT>::type;
+  using Args = TileArgs<PT>;
+  __shared__ real sx[729], sy[729], sz[729];
   __shared__ unsigned long long sq[kDepN];
-  __shared__ double sk[kT];
+  __shared__ double spn[kPTab], sk[2][kT / 64];
   __shared__ unsigned s_cand;
   __shared__ unsigned s_nc[2][27], s_nd[2][27];  // destinations: e, ions
-  const unsigned nchk = *A.nchunks;
+  const unsigned nchk = *args.nchunks;
   if (blockIdx.x >= nchk) return;
   const unsigned cb = xcd_block(blockIdx.x, nchk);
-  const unsigned t = A.chunks[cb].x, kp = A.chunks[cb].y;
+  const unsigned t = args.chunks[cb].x, kp = args.chunks[cb].y;
   unsigned be, ee, bi, ei;
-  piece(A.tse, t, kp, be, ee);
-  piece(A.tsi, t, kp, bi, ei);
+  piece(args.sp[0].ts, t, kp, be, ee);
+  piece(args.sp[1].ts, t, kp, bi, ei);
   if (be == ee && bi == ei) {
     if (threadIdx.x == 0) {
-      A.part_e[cb] = 0.0;
-      A.part_i[cb] = 0.0;
-      A.cand_cnt[cb] = 0;
+      args.sp[0].part[cb] = 0.0;
+      args.sp[1].part[cb] = 0.0;
+      args.cand_cnt[cb] = 0;
     }
     return;
   }
-  const int tx = (int)(t % g.tnx);
-  const int ty = (int)((t / g.tnx) % g.tny);
-  const int tz = (int)(t / ((unsigned)g.tnx * g.tny));
+  const int tx = (int)(t % args.g.tnx);
+  const int ty = (int)((t / args.g.tnx) % args.g.tny);
+  const int tz = (int)(t / ((unsigned)args.g.tnx * args.g.tny));
   const int x0 = tx * kTile, y0 = ty * kTile, z0 = tz * kTile;
   for (int q = threadIdx.x; q < 729; q += blockDim.x) {
     const int a = q % 9, b = (q / 9) % 9, c = q / 81;
     const int gk = z0 + c;
-    float vx = 0.0f, vy = 0.0f, vz = 0.0f;
-    if (gk <= g.nz) {
-      const long long node = ((long long)gk * g.ny + wrap_index(y0 + b, g.ny)) *
-                                 g.nx + wrap_index(x0 + a, g.nx);
-      vx = E[node]; vy = E[nn + node]; vz = E[2 * nn + node];
+    real vx = 0, vy = 0, vz = 0;
+    if (gk <= args.g.nz) {
+      const long long node =
+          ((long long)gk * args.g.ny + wrap_index(y0 + b, args.g.ny)) *
+              args.g.nx + wrap_index(x0 + a, args.g.nx);
+      vx = args.E[node]; vy = args.E[args.nn + node];
+      vz = args.E[2 * args.nn + node];
     }
     sx[q] = vx; sy[q] = vy; sz[q] = vz;
   }
   for (int q = threadIdx.x; q < kDepN; q += blockDim.x) sq[q] = 0ull;
   if (threadIdx.x == 0) s_cand = 0;
   if (threadIdx.x < 54) (&s_nc[0][0])[threadIdx.x] = 0u;
-  __syncthreads();
-  double ke_i = 0.0, ke_e = 0.0;
-  for (unsigned base = bi; base < ei; base += blockDim.x) {
-    const long long i = base + threadIdx.x;
-    PushOut o;
-    o.cathode = false;
-    o.anode = false;
-    bool moved = false;
-    if (i < ei) {
-      push_one_m<2>(A.pi, i, sx, sy, sz, x0, y0, z0, E, nn, g, A.qm_i, A.dtdx,
-                    A.keyi, A.ncount, m, step, seed, dc, o);
-      ke_i = ke_i + o.ke;
-      moved = count_dest(o.cell, tx, ty, tz, g, s_nc[1], s_nd[1], A.cnt_i) != kSlotSelf &&
-              o.cell != kDead;
-      if (o.cell != kDead) {
-        int dx_, fx_, dy_, fy_, dz_, fz_;
-        cic_stored(PartsM(), o, g, dx_, fx_, dy_, fy_, dz_, fz_);
-        dep_tile(sq, A.dep, g, x0, y0, z0, dx_, fx_, dy_, fy_, dz_, fz_, 1);
-      }
-    }
-    sink_m(A.pi, i, 2, o, g, A.ab_rec, A.ab_pos, A.ab_vel, A.ab_cap, dc);
-    wave_count(moved, &dc->ion_moved);
-    list_dead(i < ei && o.cell == kDead, i, A.dead2, &dc->n_dead2);
+  if (threadIdx.x >= kT - kPTab) {
+    const int nc = (int)threadIdx.x - (kT - kPTab);
+    spn[nc] = mcc_p(args.m.c_coll, nc);
   }
-  for (unsigned base = be; base < ee; base += blockDim.x) {
-    const long long i = base + threadIdx.x;
+  __syncthreads();
+  const unsigned gi = (ei - bi + 63) / 64, gt = gi + (ee - be + 63) / 64;
+  const unsigned lane = threadIdx.x & 63;
+  const unsigned wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  double ke_i = 0.0, ke_e = 0.0;
+  for (unsigned u = wave; u < gt; u += kT / 64) {
+    const bool el = u >= gi;       // (wave-uniform)
+    const int sp = el ? 0 : 2;
+    const unsigned i = el ? be + 64 * (u - gi) + lane : bi + 64 * u + lane;
+    const bool live = i < (el ? ee : ei);
     PushOut o;
     o.cathode = false;
     o.anode = false;
     o.cand = false;
-    if (i < ee) {
-      push_one_m<0>(A.pe, i, sx, sy, sz, x0, y0, z0, E, nn, g, A.qm_e, A.dtdx,
-                    A.keye, A.ncount, m, step, seed, dc, o);
-      ke_e = ke_e + o.ke;
-      count_dest(o.cell, tx, ty, tz, g, s_nc[0], s_nd[0], A.cnt_e);
+    bool moved = false;
+    if (live) {
+      {
+        const Args& A = reread<Args>();
+        const TileSp<PT>& S = A.sp[el ? 0 : 1];
+        PT p = S.p;
+        In q;
+        load_in(p, i, q);
+        if (el && A.m.enabled) o.id = p.id[i];
+        push_one(p, i, q, sx, sy, sz, x0, y0, z0, A.E, A.nn, A.g, S.qm, A.len,
+                 S.key, A.ncount, A.m, A.dc, o, sp);
+      }
+      const Args& A = reread<Args>();
+      if (el) ke_e = ke_e + o.ke; else ke_i = ke_i + o.ke;
+      moved = count_dest(o, tx, ty, tz, A.g, s_nc[el ? 0 : 1],
+                         s_nd[el ? 0 : 1], A.sp[el ? 0 : 1].cnt) != kSlotSelf &&
+              o.cell != kDead;
       if (o.cell != kDead) {
         int dx_, fx_, dy_, fy_, dz_, fz_;
-        cic_stored(PartsM(), o, g, dx_, fx_, dy_, fy_, dz_, fz_);
-        dep_tile(sq, A.dep, g, x0, y0, z0, dx_, fx_, dy_, fy_, dz_, fz_, -1);
+        cic_stored(PT(), o, A.g, dx_, fx_, dy_, fy_, dz_, fz_);
+        dep_tile(sq, A.dep, A.g, x0, y0, z0, dx_, fx_, dy_, fy_, dz_, fz_,
+                 el ? -1 : 1);
       }
-      if (o.cand) A.cand[be + atomicAdd(&s_cand, 1u)] = cand_rec(o, i);
+      if (el) {
+        mcc_draw(A.m, A.step, A.seed, A.dc, o, o.id, spn);
+        if (o.cand) A.cand[be + atomicAdd(&s_cand, 1u)] = cand_rec(o, i);
+      }
     }
-    sink_m(A.pe, i, 0, o, g, A.ab_rec, A.ab_pos, A.ab_vel, A.ab_cap, dc);
+    const Args& A = reread<Args>();
+    sink_any(A.sp[el ? 0 : 1].p, i, sp, o, A.g, A.ab_rec, A.ab_pos, A.ab_vel,
+             A.ab_cap, A.dc);
+    if (!el) {
+      wave_count(moved, &A.dc->ion_moved);
+      list_dead(live && o.cell == kDead, i, A.dead2, &A.dc->n_dead2);
+    }
   }
-  const double si = block_sum(ke_i, sk);
-  const double se = block_sum(ke_e, sk);
-  if (threadIdx.x == 0) {
-    A.part_i[cb] = si;
-    A.part_e[cb] = se;
-    A.cand_cnt[cb] = s_cand;
+  ke_i = wave_sum(ke_i);
+  ke_e = wave_sum(ke_e);
+  if (lane == 0) {
+    sk[0][wave] = ke_e;
+    sk[1][wave] = ke_i;
   }
-  // The destination counts are complete (block_sum synchronised).
+  __syncthreads();
+  const Args& A = reread<Args>();
+  if (threadIdx.x < 2) {
+    double s = 0.0;
+    for (int w = 0; w < kT / 64; ++w) s = s + sk[threadIdx.x][w];
+    A.sp[threadIdx.x].part[cb] = s;
+  }
+  if (threadIdx.x == 0) A.cand_cnt[cb] = s_cand;
   if (threadIdx.x < 54) {
-    const int sp = threadIdx.x / 27, d = threadIdx.x % 27;
-    const unsigned n = s_nc[sp][d];
-    if (n) atomicAdd(&(sp ? A.cnt_i : A.cnt_e)[s_nd[sp][d]], n);
+    const int k = threadIdx.x / 27, d = threadIdx.x % 27;
+    const unsigned n = s_nc[k][d];
+    if (n) atomicAdd(&A.sp[k].cnt[s_nd[k][d]], n);
   }
-  dep_flush(sq, A.dep, g, x0, y0, z0);
+  dep_flush(sq, A.dep, A.g, x0, y0, z0);
 }
 
 template <int SP>
@@ -1368,8 +1406,11 @@ __global__ void __launch_bounds__(kT) k_push_list_m(
   o.cand = false;
   o.ke = 0.0;
   if (live) {
-    push_one_m<SP>(p, i, nullptr, nullptr, nullptr, 0, 0, 0, E, nn, g, qm,
-                   dtdx, key, ncount, m, step, seed, dc, o);
+    InM q;
+    load_in(p, i, q);
+    push_one(p, i, q, nullptr, nullptr, nullptr, 0, 0, 0, E, nn, g, qm, dtdx,
+             key, ncount, m, dc, o, SP);
+    if (SP == 0) mcc_draw(m, step, seed, dc, o, p.id[i], nullptr);
     if (SP != 1 && o.cell != kDead) {
       int dx_, fx_, dy_, fy_, dz_, fz_;
       cic_stored(PartsM(), o, g, dx_, fx_, dy_, fy_, dz_, fz_);
@@ -1416,6 +1457,7 @@ __device__ __forceinline__ void hist_add(unsigned* hk, int* hc, unsigned cell,
     if (k == kHistEmpty) k = atomicCAS(&hk[s], kHistEmpty, cell);
     if (k == kHistEmpty || k == cell) {
       atomicAdd(&hc[s], 1);
+      asm volatile("");   // (not one flat atomic with the global add)
       return;
     }
   }
@@ -1461,8 +1503,8 @@ __global__ void __launch_bounds__(kT) k_push_neutral(
       if (i < n) {
         const double x = p.x[i], y = p.y[i], z = p.z[i];
         const unsigned prev = i < n_old ? cell_of(x, y, z, g) : kDead;
-        finish_push<1>(p, i, x, y, z, p.vx[i], p.vy[i], p.vz[i], dt, g, key,
-                       ncount, m, step, seed, dc, o, 0ull);
+        finish_push(p, i, x, y, z, p.vx[i], p.vy[i], p.vz[i], dt, g, key,
+                    ncount, m, dc, o, 1);
         if (o.cell != prev) {
           if (prev != kDead) atomicSub(&ncount[prev], 1);
           if (o.cell != kDead) {
@@ -1474,7 +1516,7 @@ __global__ void __launch_bounds__(kT) k_push_neutral(
         }
         ke = ke + o.ke;
       }
-      sink<1>(p, i, o, g, ab_rec, ab_pos, ab_vel, ab_cap, dc);
+      sink(p, i, o, g, ab_rec, ab_pos, ab_vel, ab_cap, dc, 1);
       list_dead(i < n && o.cell == kDead, i, dead1, &dc->n_dead1);
     }
     if (fresh) {
@@ -1514,8 +1556,10 @@ __global__ void __launch_bounds__(kT) k_push_neutral_m(
       o.cand = false;
       if (i < n) {
         const unsigned prev = i < n_old ? p.cell[i] : kDead;
-        push_one_m<1>(p, i, nullptr, nullptr, nullptr, 0, 0, 0, nullptr, 0, g,
-                      0.0f, dtdx, key, ncount, m, step, seed, dc, o);
+        InM q;
+        load_in(p, i, q);
+        push_one(p, i, q, nullptr, nullptr, nullptr, 0, 0, 0, nullptr, 0, g,
+                 0.0f, dtdx, key, ncount, m, dc, o, 1);
         if (o.cell != prev) {
           if (prev != kDead) atomicSub(&ncount[prev], 1);
           if (o.cell != kDead) {
@@ -2786,18 +2830,14 @@ void push_fp64(pic_ctx* c, double dt, const MccC& m, double* part_e,
   const long long nt = c->ntiles;
   const long long ab_cap = c->cfg.max_events;
   tmark(c, PIC_PH_PUSH_ELECTRON, true);
-  TileArgs A;
-  A.pe = cur<Parts>(c, 0);
-  A.pi = cur<Parts>(c, 2);
-  A.tse = ts_cur(c, 0);
-  A.tsi = ts_cur(c, 2);
+  TileArgs<Parts> A;
+  A.sp[0] = {cur<Parts>(c, 0), ts_cur(c, 0), c->key[0], qm_dt(0, dt),
+             part_e, c->tcnt[0]};
+  A.sp[1] = {cur<Parts>(c, 2), ts_cur(c, 2), c->key[2], qm_dt(2, dt),
+             part_i, c->tcnt[1]};
   A.chunks = c->chunks;
   A.nchunks = c->cstart + nt;
-  A.keye = c->key[0];
-  A.keyi = c->key[2];
-  A.qm_e = qm_dt(0, dt);
-  A.qm_i = qm_dt(2, dt);
-  A.dt = dt;
+  A.len = dt;
   A.ncount = c->ncount;
   A.cand = c->cand;
   A.cand_cnt = c->cand_cnt;
@@ -2805,14 +2845,16 @@ void push_fp64(pic_ctx* c, double dt, const MccC& m, double* part_e,
   A.ab_pos = c->ab_raw_pos;
   A.ab_vel = c->ab_raw_vel;
   A.ab_cap = ab_cap;
-  A.part_e = part_e;
-  A.part_i = part_i;
-  A.cnt_e = c->tcnt[0];
-  A.cnt_i = c->tcnt[1];
   A.dep = c->acc_next;
   A.dead2 = c->dead2;
-  k_push_tile<<<(unsigned)c->nch_bound, kT, 0, st>>>(A, c->E, nn, c->g, m,
-                                                         step, seed, c->dc);
+  A.E = c->E;
+  A.nn = nn;
+  A.g = c->g;
+  A.m = m;
+  A.step = step;
+  A.seed = seed;
+  A.dc = c->dc;
+  k_push_tile<Parts><<<(unsigned)c->nch_bound, kT, 0, st>>>(A);
   tmark(c, PIC_PH_PUSH_ELECTRON, false);
   tmark(c, PIC_PH_PUSH_ION, true);
   const long long tail_i = std::max(0ll, bound(c, 2) - c->n_binned[2]);
@@ -2852,18 +2894,14 @@ void push_mixed(pic_ctx* c, double dt, const MccC& m, double* part_e,
   const float* E = reinterpret_cast<const float*>(c->E);
   const float dtdx = (float)(dt * c->g.inv_dx);
   tmark(c, PIC_PH_PUSH_ELECTRON, true);
-  TileArgsM A;
-  A.pe = cur<PartsM>(c, 0);
-  A.pi = cur<PartsM>(c, 2);
-  A.tse = ts_cur(c, 0);
-  A.tsi = ts_cur(c, 2);
+  TileArgs<PartsM> A;
+  A.sp[0] = {cur<PartsM>(c, 0), ts_cur(c, 0), c->key[0], (float)qm_dt(0, dt),
+             part_e, c->tcnt[0]};
+  A.sp[1] = {cur<PartsM>(c, 2), ts_cur(c, 2), c->key[2], (float)qm_dt(2, dt),
+             part_i, c->tcnt[1]};
   A.chunks = c->chunks;
   A.nchunks = c->cstart + nt;
-  A.keye = c->key[0];
-  A.keyi = c->key[2];
-  A.qm_e = (float)qm_dt(0, dt);
-  A.qm_i = (float)qm_dt(2, dt);
-  A.dtdx = dtdx;
+  A.len = dtdx;
   A.ncount = c->ncount;
   A.cand = c->cand;
   A.cand_cnt = c->cand_cnt;
@@ -2871,14 +2909,16 @@ void push_mixed(pic_ctx* c, double dt, const MccC& m, double* part_e,
   A.ab_pos = c->ab_raw_pos;
   A.ab_vel = c->ab_raw_vel;
   A.ab_cap = ab_cap;
-  A.part_e = part_e;
-  A.part_i = part_i;
-  A.cnt_e = c->tcnt[0];
-  A.cnt_i = c->tcnt[1];
   A.dep = c->acc_next;
   A.dead2 = c->dead2;
-  k_push_tile_m<<<(unsigned)c->nch_bound, kT, 0, st>>>(A, E, nn, c->g, m,
-                                                           step, seed, c->dc);
+  A.E = E;
+  A.nn = nn;
+  A.g = c->g;
+  A.m = m;
+  A.step = step;
+  A.seed = seed;
+  A.dc = c->dc;
+  k_push_tile<PartsM><<<(unsigned)c->nch_bound, kT, 0, st>>>(A);
   tmark(c, PIC_PH_PUSH_ELECTRON, false);
   tmark(c, PIC_PH_PUSH_ION, true);
   const long long tail_i = std::max(0ll, bound(c, 2) - c->n_binned[2]);
