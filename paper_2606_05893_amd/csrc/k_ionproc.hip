@@ -5,20 +5,25 @@
 //
 // Electrons, Cu+ and Cu atoms are grouped by cell: their index words are
 // binned by tile plane as for the Coulomb collisions, then one wavefront a
-// plane writes the cells' offsets and, in each cell's segment, 16-byte
-// records keyed by species and a random order draw: sorted by (key, id) in
-// cells of at most kSmall, unsorted in the crowded ones (the few planes of
-// many records, the atoms piled above an evaporating spot, are grouped by
-// cell over the whole GPU instead).  Every cell is then processed in
-// sequence by one thread (a workgroup sorts the crowded ones, their atoms a
-// window at a time): first each electron in turn against the
+// plane counts its cells and writes their offsets.  Collisions are rare, and
+// a draw too high for any speed of its pair is known from its particle's id
+// alone, so that pass only finds the cells in which something may happen;
+// just their records are written, 16 bytes keyed by species and a random
+// order draw, and sorted by (key, id) in cells of at most kSmall (the
+// crowded ones' are written unsorted; the few planes of many records, the
+// atoms piled above an evaporating spot, are grouped by cell over the whole
+// GPU instead).  Such a cell is then processed in sequence by one thread (a
+// workgroup sorts the crowded ones, their atoms a window at a time): first
+// each electron in turn against the
 // cell's Cu+ (Eq. 4 evaluated per electron; the r-th colliding electron
 // takes the r-th ion), then the Cu+ left against the cell's atoms (ion k with atom k mod N_n,
 // the real relative speed).  Recombinations and charge exchanges are applied
 // in place (records swapped, atoms appended, the charge of the pushed state
 // corrected); Cu+ ionisations are listed, sorted by primary id and
 // committed in that order, which fixes the secondaries' ids.
+#include <algorithm>
 #include <cmath>
+#include <limits>
 
 #include "cell_groups.h"
 #include "pic_ctx.h"
@@ -41,6 +46,9 @@ enum : uint32_t {
 
 struct IonC {
   double s_rec, a2, I2, cx_a, cx_b;
+  // Bounds of sigma v dt (see no_event): electrons, and Cu+ with atoms; with
+  // a constant cross section (cx_b = 0) the latter is per unit of speed.
+  double h_e, h_cx;
   double w_dx3, dt, half_me, two_e_me;
   unsigned step;
   unsigned long long seed;
@@ -155,38 +163,98 @@ __device__ void swap_records<PartsM>(const PartsM& a, unsigned i,
   b.id[j] = u;
 }
 
-// A cell's records in (key, id) order as a plane pass holds them in LDS:
-// the keys and index words by slot, the sorted places' slots in perm.
-struct LdsRecs {
-  const unsigned long long* key;    // species in the top two bits
-  const unsigned* ix;               // array indices
-  const unsigned short* perm;
-  int b;                            // the cell's first place
-  unsigned cell;                    // its tile-major number
-  __device__ Rec operator[](int j) const {
-    const int p = perm[b + j];
-    Rec r;
-    r.lo = key[p];
-    r.hi = (cell << 2) | (unsigned)(key[p] >> 62);
-    r.val = ix[p];
-    return r;
-  }
-  __device__ LdsRecs operator+(int d) const {
-    LdsRecs x = *this;
-    x.b += d;
-    return x;
-  }
+struct Tally {
+  unsigned rec = 0, cx = 0, starved = 0, near = 0;
 };
 
-struct Tally {
-  unsigned long long rec = 0, cx = 0, starved = 0, near = 0;
+// With P = 1 - exp(-dens sigma v dt) <= dens h, h the largest sigma v dt of
+// the pair's possible speeds, a draw u1 beyond dens h neither collides nor
+// comes near P.  (h carries the margin for rounding.)
+__device__ __forceinline__ bool no_event(double u1, double dens, double h) {
+  return u1 > dens * h + 2.0 * kNear;
+}
+
+// An electron's collision draw against the Cu+ of its cell (dens: their
+// density): it collides when u1 < P, and recombines when also u2 < frac.
+// Returns false if it surely does not collide.
+struct EDraw {
+  double vx, vy, vz, P, frac, u1, u2;
+  unsigned long long id;
 };
+
+template <class PT>
+__device__ __forceinline__ bool e_draw(const Sp3<PT>& S, unsigned e,
+                                       double dens, const IonC& k, EDraw& d) {
+  d.id = S.e.id[e];
+  uniform2(d.id, k.step, kTagEI0, k.seed, d.u1, d.u2);
+  if (no_event(d.u1, dens, k.h_e)) return false;
+  Acc<PT>::vel(S.e, e, d.vx, d.vy, d.vz);
+  const double v2 = (d.vx * d.vx + d.vy * d.vy) + d.vz * d.vz;
+  const double v = sqrt(v2);
+  const double E = (k.half_me * v2) / kE;
+  const double sr = sigma_rec(k, E), si = sigma_ion2(k, E);
+  const double st = sr + si;
+  d.P = 1.0 - exp(-(((dens * st) * v) * k.dt));
+  d.frac = sr / st;
+  return true;
+}
+
+// Colliding electron e (draw d) takes Cu+ ion of the cell.
+template <class PT>
+__device__ void e_take(const Sp3<PT>& S, unsigned e, const EDraw& d,
+                       unsigned ion, unsigned cell, const IonC& k,
+                       const GridC& g, int* __restrict__ ncount,
+                       long long* __restrict__ acc,
+                       uint32_t* __restrict__ dead2, Rec* __restrict__ ev,
+                       uint2* __restrict__ evp, Counters* dc, Tally& t) {
+  if (fabs(d.u2 - d.frac) < kNear) t.near += 1;
+  S.ki[ion] = kDead;
+  if ((long long)ion < k.nb_i) atomicSub(&k.tcnt_i[tile_of(cell, g)], 1u);
+  const unsigned long long d2 = atomicAdd(&dc->n_dead2, 1ull);
+  if (d2 < (unsigned long long)kDeadList) dead2[d2] = ion;
+  if (d.u2 < d.frac) {
+    // Recombination: a Cu atom with the ion's position and id and the
+    // pair's centre-of-mass velocity; the electron and the ion leave.
+    const unsigned long long slot = atomicAdd(&dc->n[1], 1ull);
+    if ((long long)slot >= k.cap_n) {
+      atomicOr(&dc->err, kErrCapacity);
+    } else {
+      double ivx, ivy, ivz;
+      Acc<PT>::vel(S.i, ion, ivx, ivy, ivz);
+      const double den = kMcu + kMe;
+      Acc<PT>::copy_pos(S.i, ion, S.n, (long long)slot);
+      Acc<PT>::set_vel(S.n, (long long)slot, (kMcu * ivx + kMe * d.vx) / den,
+                       (kMcu * ivy + kMe * d.vy) / den,
+                       (kMcu * ivz + kMe * d.vz) / den);
+      S.n.id[slot] = S.i.id[ion];
+      S.kn[slot] = cell;
+      atomicAdd(&ncount[cell], 1);
+    }
+    S.ke[e] = kDead;
+    if ((long long)e < k.nb_e) atomicSub(&k.tcnt_e[tile_of(cell, g)], 1u);
+    dep_add(S.e, e, g, acc, 1);
+    dep_add(S.i, ion, g, acc, -1);
+    t.rec += 1;
+  } else {
+    const unsigned long long q = atomicAdd(&dc->f3_ion2, 1ull);
+    if ((long long)q < k.max_ev) {
+      Rec x;
+      x.lo = d.id;
+      x.hi = 0u;
+      x.val = (unsigned)q;
+      ev[q] = x;
+      evp[q] = make_uint2(e, ion);
+    } else {
+      atomicOr(&dc->err, kErrEvents);
+    }
+  }
+}
 
 // Electrons re[0..ne) against the cell's Cu+ ri[0..ni), both in their
 // random order; returns the number of Cu+ taken.
-template <class PT, class RV>
-__device__ int ip_electrons(const Sp3<PT>& S, RV re, int ne,
-                            RV ri, int ni, unsigned cell,
+template <class PT>
+__device__ int ip_electrons(const Sp3<PT>& S, const Rec* re, int ne,
+                            const Rec* ri, int ni, unsigned cell,
                             const IonC& k, const GridC& g,
                             int* __restrict__ ncount,
                             long long* __restrict__ acc,
@@ -197,67 +265,17 @@ __device__ int ip_electrons(const Sp3<PT>& S, RV re, int ne,
     const double dens = (double)ni * k.w_dx3;
     for (int a = 0; a < ne; ++a) {
       const unsigned e = re[a].val;
-      double vx, vy, vz;
-      Acc<PT>::vel(S.e, e, vx, vy, vz);
-      const double v2 = (vx * vx + vy * vy) + vz * vz;
-      const double v = sqrt(v2);
-      const double E = (k.half_me * v2) / kE;
-      const double sr = sigma_rec(k, E), si = sigma_ion2(k, E);
-      const double st = sr + si;
-      const double P = 1.0 - exp(-(((dens * st) * v) * k.dt));
-      const unsigned long long eid = S.e.id[e];
-      double u1, u2;
-      uniform2(eid, k.step, kTagEI0, k.seed, u1, u2);
-      const double frac = sr / st;
-      if (fabs(u1 - P) < kNear) t.near += 1;
-      if (!(u1 < P)) continue;
+      EDraw d;
+      if (!e_draw(S, e, dens, k, d)) continue;
+      if (fabs(d.u1 - d.P) < kNear) t.near += 1;
+      if (!(d.u1 < d.P)) continue;
       if (used >= ni) {
         t.starved += 1;
         continue;
       }
-      if (fabs(u2 - frac) < kNear) t.near += 1;
-      const unsigned ion = ri[used].val;
+      e_take(S, e, d, ri[used].val, cell, k, g, ncount, acc, dead2, ev, evp,
+             dc, t);
       ++used;
-      S.ki[ion] = kDead;
-      if ((long long)ion < k.nb_i) atomicSub(&k.tcnt_i[tile_of(cell, g)], 1u);
-      const unsigned long long d2 = atomicAdd(&dc->n_dead2, 1ull);
-      if (d2 < (unsigned long long)kDeadList) dead2[d2] = ion;
-      if (u2 < frac) {
-        // Recombination: a Cu atom with the ion's position and id and the
-        // pair's centre-of-mass velocity; the electron and the ion leave.
-        const unsigned long long slot = atomicAdd(&dc->n[1], 1ull);
-        if ((long long)slot >= k.cap_n) {
-          atomicOr(&dc->err, kErrCapacity);
-        } else {
-          double ivx, ivy, ivz;
-          Acc<PT>::vel(S.i, ion, ivx, ivy, ivz);
-          const double den = kMcu + kMe;
-          Acc<PT>::copy_pos(S.i, ion, S.n, (long long)slot);
-          Acc<PT>::set_vel(S.n, (long long)slot, (kMcu * ivx + kMe * vx) / den,
-                           (kMcu * ivy + kMe * vy) / den,
-                           (kMcu * ivz + kMe * vz) / den);
-          S.n.id[slot] = S.i.id[ion];
-          S.kn[slot] = cell;
-          atomicAdd(&ncount[cell], 1);
-        }
-        S.ke[e] = kDead;
-        if ((long long)e < k.nb_e) atomicSub(&k.tcnt_e[tile_of(cell, g)], 1u);
-        dep_add(S.e, e, g, acc, 1);
-        dep_add(S.i, ion, g, acc, -1);
-        t.rec += 1;
-      } else {
-        const unsigned long long q = atomicAdd(&dc->f3_ion2, 1ull);
-        if ((long long)q < k.max_ev) {
-          Rec x;
-          x.lo = eid;
-          x.hi = 0u;
-          x.val = (unsigned)q;
-          ev[q] = x;
-          evp[q] = make_uint2(e, ion);
-        } else {
-          atomicOr(&dc->err, kErrEvents);
-        }
-      }
     }
   }
   return used;
@@ -291,8 +309,8 @@ __device__ void cx_pair(const Sp3<PT>& S, unsigned ion, unsigned at, int nn,
 
 // One small cell's processes on records r[0..n) in (key, id) order:
 // electrons, then Cu+, then atoms.
-template <class PT, class RV>
-__device__ void ip_cell(const Sp3<PT>& S, RV r, int n, unsigned cell,
+template <class PT>
+__device__ void ip_cell(const Sp3<PT>& S, const Rec* r, int n, unsigned cell,
                         const IonC& k, const GridC& g, int* __restrict__ ncount,
                         long long* __restrict__ acc, uint32_t* __restrict__ dead2,
                         Rec* __restrict__ ev, uint2* __restrict__ evp,
@@ -301,8 +319,8 @@ __device__ void ip_cell(const Sp3<PT>& S, RV r, int n, unsigned cell,
   while (ne < n && ip_sp(r[ne]) == 0u) ++ne;
   while (ne + ni < n && ip_sp(r[ne + ni]) == 1u) ++ni;
   const int nn = n - ne - ni;
-  const RV ri = r + ne;
-  const RV rn = r + ne + ni;
+  const Rec* ri = r + ne;
+  const Rec* rn = r + ne + ni;
   int used = 0;
   if (ni > 0)
     used = ip_electrons(S, r, ne, ri, ni, cell, k, g, ncount, acc, dead2, ev,
@@ -315,10 +333,10 @@ __device__ void ip_cell(const Sp3<PT>& S, RV r, int n, unsigned cell,
 
 template <class PT>
 __device__ void flush_tally(const Tally& t, Counters* dc) {
-  if (t.rec) atomicAdd(&dc->f3_rec, t.rec);
-  if (t.cx) atomicAdd(&dc->f3_cx, t.cx);
-  if (t.starved) atomicAdd(&dc->f3_starved, t.starved);
-  if (t.near) atomicAdd(&dc->n_near, t.near);
+  if (t.rec) atomicAdd(&dc->f3_rec, (unsigned long long)t.rec);
+  if (t.cx) atomicAdd(&dc->f3_cx, (unsigned long long)t.cx);
+  if (t.starved) atomicAdd(&dc->f3_starved, (unsigned long long)t.starved);
+  if (t.near) atomicAdd(&dc->n_near, (unsigned long long)t.near);
 }
 
 // ---- grouping ----------------------------------------------------------------
@@ -355,16 +373,6 @@ __device__ __forceinline__ Rec make_rec(const Sp3<PT>& S, const JointIx& J,
   r.hi = (cell << 2) | s;
   r.val = i;
   return r;
-}
-
-// The id of a particle given its sort key (species in the top two bits)
-// and its array index.
-template <class PT>
-__device__ __forceinline__ unsigned long long key_id(const Sp3<PT>& S,
-                                                     unsigned long long key,
-                                                     unsigned i) {
-  const unsigned s = (unsigned)(key >> 62);
-  return s == 0 ? S.e.id[i] : (s == 1 ? S.i.id[i] : S.n.id[i]);
 }
 
 // Live particles per plane.
@@ -450,13 +458,15 @@ __global__ void __launch_bounds__(kScanB) k_ig_scan_apply(
   if (i < n) off[i + 1] += bsum[blockIdx.x];
 }
 
-// Each live particle's index word into its plane's range (order inside the
-// range arbitrary); per chunk one range per distinct plane is reserved with
-// one global atomic.
+// Each live particle's index word, and a byte of its cell in the plane and
+// its species << 6, into its plane's range (order inside the range
+// arbitrary); per chunk one range per distinct plane is reserved with one
+// global atomic.
 template <class PT>
 __global__ void __launch_bounds__(kT) k_pg_scatter(
     Sp3<PT> S, const Counters* dc, GridC g, const unsigned* __restrict__ poff,
-    unsigned* __restrict__ cnt, unsigned* __restrict__ pidx) {
+    unsigned* __restrict__ cnt, unsigned* __restrict__ pidx,
+    unsigned char* __restrict__ pcs) {
   __shared__ unsigned hk[kPHash];
   __shared__ unsigned hc[kPHash];
   __shared__ unsigned hb[kPHash];
@@ -492,41 +502,40 @@ __global__ void __launch_bounds__(kT) k_pg_scatter(
       unsigned gi;
       const uint32_t c = joint_key(S, ne, ni, t, gi);
       if (c == kDead) continue;
-      const unsigned u = plane_of(c, g);
+      const unsigned tm = tile_major(c, g), u = tm >> kPlaneShift;
       // The table is unchanged since the count (see k_cu_scatter).
       const int q = plane_slot(hk, u);
       const unsigned slot = q >= 0 ? hb[q] + atomicAdd(&hc[q], 1u)
                                    : poff[u] + atomicSub(&cnt[u], 1u) - 1u;
       pidx[slot] = gi;
+      pcs[slot] = (unsigned char)((tm & (kPlaneCells - 1)) |
+                                  (t < ne ? 0u : (t < ne + ni ? 64u : 128u)));
     }
     __syncthreads();
   }
 }
 
 // Per plane, one wavefront: its cells' offsets into off (a global prefix
-// over the tile-major cells), the records of its crowded cells (more than
-// kSmall) into rec unsorted, those cells listed for the workgroup pass.
-// A plane of at most kPCap records is read once; its small cells (2 to
-// kSmall records) are ranked in LDS and their processes run right there, a
-// cell per lane, on the sorted records in LDS.  A larger plane ranks its
-// small cells in batches into srt and is listed for k_ip_small; a plane of
-// more than kHot records is listed for the hot-plane passes (and
-// k_ip_small).  Four wavefronts per SIMD (128 registers, seven spilled):
-// 1.11 ms against 1.25 at three, at the 128x128x512 workload.
-constexpr int kPCap = 512;
+// over the tile-major cells); the cells of more than kSmall records listed
+// for the workgroup pass, their records written to rec unsorted; of the
+// small cells (2 to kSmall records) with a Cu+, those in which an electron's
+// or a Cu+'s draw may collide: their records to rec, the plane to rest with
+// a mask of these cells.  A plane of more than kHot records is listed for
+// the hot-plane passes, and in rest with every cell.
+//
+// A record's cell and species are a byte; of the records whose cell may hold
+// a trial the id is gathered, and the speed of a Cu+ next to an atom (their
+// tile's lines, shared by the eight planes of a tile).  Nothing of the atoms,
+// whose lines are scattered, is read.  At 25 M particles on 128 x 128 x 512
+// cells 354 us; with every record's key and id gathered and ranked and
+// every pair's probability evaluated, a cell per lane, 1290 us.
 constexpr int kHot = 4096;
 
 struct PlaneLds {
-  unsigned long long key[kPCap];
-  unsigned gi[kPCap];             // array indices (the species is in key)
-  unsigned char cell[kPCap];
-  unsigned short ord[kPCap];      // one-pass plane: cell order -> slot
-  unsigned short perm[kPCap];     // one-pass plane: sorted place -> slot
   unsigned cnt[kPlaneCells];
-  unsigned off[kPlaneCells + 1];
-  unsigned start[kPlaneCells];    // batch-local first slot of a small cell
-  unsigned cur[kPlaneCells];
-  int hi, nb;
+  unsigned nei[kPlaneCells];      // electrons, Cu+ << 16
+  unsigned cur[kPlaneCells];      // next place of a written cell
+  unsigned flag[2];               // cells in which a draw may collide
 };
 
 __device__ __forceinline__ bool small_cell(unsigned m) {
@@ -534,49 +543,51 @@ __device__ __forceinline__ bool small_cell(unsigned m) {
 }
 
 template <class PT>
-__global__ void __launch_bounds__(kPlaneCells, 4) k_pg_cells(
-    Sp3<PT> S, GridC g, const unsigned* __restrict__ poff, long long nplanes,
-    const unsigned* __restrict__ pidx, unsigned* __restrict__ off,
-    Rec* __restrict__ rec, Rec* __restrict__ srt, unsigned* __restrict__ big,
-    unsigned* __restrict__ nbig, long long big_cap, unsigned* __restrict__ hot,
-    unsigned* __restrict__ nhot, unsigned* __restrict__ rest,
-    unsigned* __restrict__ nrest, IonC k, int* __restrict__ ncount,
-    long long* __restrict__ acc, uint32_t* __restrict__ dead2,
-    Rec* __restrict__ ev, uint2* __restrict__ evp, Counters* dc) {
+struct PgArgs {
+  Sp3<PT> S;
+  const unsigned* poff;
+  long long nplanes;
+  const unsigned* pidx;
+  const unsigned char* pcs;
+  unsigned* off;
+  Rec* rec;
+  unsigned *big, *nbig;
+  long long big_cap;
+  unsigned *hot, *nhot, *rest, *nrest;
+  unsigned long long* rmask;
+  IonC k;
+  const Counters* dc;
+};
+
+template <class PT>
+__global__ void __launch_bounds__(kPlaneCells) k_pg_cells(PgArgs<PT> A) {
   __shared__ PlaneLds L;
   const int tid = (int)threadIdx.x;
-  const unsigned step = k.step;
-  const unsigned long long seed = k.seed;
-  Tally t;
-
-  for (long long u = plane_first(); u < nplanes; u += gridDim.x) {
-    const unsigned base = poff[u];
-    const int n = (int)(poff[u + 1] - base);
+  const Sp3<PT>& S = A.S;
+  const IonC& k = A.k;
+  const JointIx J = joint_ix(A.dc);
+  const double vmax = sqrt(__longlong_as_double((long long)A.dc->n_vmax2));
+  for (long long u = plane_first(); u < A.nplanes; u += gridDim.x) {
+    const unsigned base = A.poff[u];
+    const int n = (int)(A.poff[u + 1] - base);
     const unsigned c0 = (unsigned)u << kPlaneShift;
-    // (Read per plane, so that it is not held through the processes.)
-    const JointIx J = joint_ix(dc);
     if (n > kHot) {
       if (tid == 0) {
-        hot[atomicAdd(nhot, 1u)] = (unsigned)u;
-        rest[atomicAdd(nrest, 1u)] = (unsigned)u;
+        A.hot[atomicAdd(A.nhot, 1u)] = (unsigned)u;
+        const unsigned q = atomicAdd(A.nrest, 1u);
+        A.rest[q] = (unsigned)u;
+        A.rmask[q] = ~0ull;
       }
       continue;
     }
     L.cnt[tid] = 0u;
+    L.nei[tid] = 0u;
+    if (tid < 2) L.flag[tid] = 0u;
     __syncthreads();
-    // A plane of at most kPCap records is read once: its records are made
-    // as it is counted and kept in LDS in load order.
-    const bool one = n <= kPCap;
     for (int j = tid; j < n; j += kPlaneCells) {
-      const unsigned gi = pidx[base + j];
-      const unsigned c = tile_major(key_of(S, J, gi), g);
-      const int lc = (int)(c & (kPlaneCells - 1));
+      const unsigned cs = A.pcs[base + j], lc = cs & 63u, s = cs >> 6;
       atomicAdd(&L.cnt[lc], 1u);
-      if (one) {
-        L.key[j] = make_rec(S, J, gi, c, step, seed).lo;
-        L.gi[j] = J.ix(gi);
-        L.cell[j] = (unsigned char)lc;
-      }
+      if (s < 2u) atomicAdd(&L.nei[lc], s ? 1u << 16 : 1u);
     }
     __syncthreads();
     const unsigned m = L.cnt[tid];
@@ -586,154 +597,65 @@ __global__ void __launch_bounds__(kPlaneCells, 4) k_pg_cells(
         const unsigned y = __shfl_up(incl, o);
         if (tid >= o) incl += y;
       }
-      L.off[tid] = incl - m;
-      off[c0 + tid] = base + incl - m;
-      if (tid == kPlaneCells - 1) {
-        L.off[kPlaneCells] = incl;
-        if (u == nplanes - 1) off[c0 + kPlaneCells] = base + incl;
-      }
+      L.cur[tid] = incl - m;
+      A.off[c0 + tid] = base + incl - m;
+      if (tid == kPlaneCells - 1 && u == A.nplanes - 1)
+        A.off[c0 + kPlaneCells] = base + incl;
+    }
+    if (m > (unsigned)kSmall) {
+      const unsigned q = atomicAdd(A.nbig, 1u);
+      if ((long long)q < A.big_cap) A.big[q] = c0 + tid;
     }
     __syncthreads();
-    if (one) {
-      // Crowded cells' records from LDS into their segments; the small
-      // cells' slots in cell order, ranked by (key, id) into srt.
-      L.cur[tid] = L.off[tid];
-      if (m > (unsigned)kSmall) {
-        const unsigned q = atomicAdd(nbig, 1u);
-        if ((long long)q < big_cap) big[q] = c0 + tid;
+    for (int j = tid; j < n; j += kPlaneCells) {
+      const unsigned cs = A.pcs[base + j], lc = cs & 63u, s = cs >> 6;
+      const unsigned mc = L.cnt[lc], ne = L.nei[lc] & 0xFFFFu, ni = L.nei[lc] >> 16;
+      if (mc > (unsigned)kSmall) {
+        A.rec[base + atomicAdd(&L.cur[lc], 1u)] =
+            make_rec(S, J, A.pidx[base + j], c0 + lc, k.step, k.seed);
+        continue;
       }
-      __syncthreads();
-      for (int j = tid; j < n; j += kPlaneCells) {
-        const int lc = L.cell[j];
-        const unsigned mc = L.cnt[lc];
-        const unsigned x = atomicAdd(&L.cur[lc], 1u);
-        L.ord[x] = (unsigned short)j;
-        if (mc > (unsigned)kSmall) {
-          Rec r;
-          r.lo = L.key[j];
-          r.hi = ((c0 + (unsigned)lc) << 2) | (unsigned)(L.key[j] >> 62);
-          r.val = L.gi[j];
-          rec[base + x] = r;
-        }
+      // Electrons try the cell's Cu+, Cu+ its atoms.
+      const unsigned other = s ? mc - ne - ni : ni;
+      if (ni == 0u || s == 2u || other == 0u) continue;
+      const unsigned i = J.ix(A.pidx[base + j]);
+      const double dens = (double)other * k.w_dx3;
+      double h = s ? k.h_cx : k.h_e;
+      if (s && k.cx_b == 0.0) {
+        double vx, vy, vz;
+        Acc<PT>::vel(S.i, i, vx, vy, vz);
+        h = h * (sqrt((vx * vx + vy * vy) + vz * vz) + vmax);
       }
-      __syncthreads();
-      for (int x = tid; x < n; x += kPlaneCells) {
-        const int j = L.ord[x];
-        const int lc = L.cell[j];
-        if (!small_cell(L.cnt[lc])) continue;
-        const int b = (int)L.off[lc], mc = (int)L.cnt[lc];
-        const unsigned long long kp = L.key[j];
-        int rank = 0;
-        for (int y = b; y < b + mc; ++y) {
-          const int o = L.ord[y];
-          const unsigned long long ky = L.key[o];
-          if (ky < kp) {
-            ++rank;
-          } else if (ky == kp && o != j) {
-            rank += key_id(S, L.key[o], L.gi[o]) < key_id(S, kp, L.gi[j]);
-          }
-        }
-        L.perm[b + rank] = (unsigned short)j;
+      double u1, u2;
+      uniform2(s ? S.i.id[i] : S.e.id[i], k.step, s ? kTagCX : kTagEI0, k.seed,
+               u1, u2);
+      if (no_event(u1, dens, h)) continue;
+      if (s == 0u) {
+        // (Its own speed decides: the bound holds down to 1 meV.)
+        EDraw d;
+        e_draw(S, i, dens, k, d);
+        if (!(d.u1 < d.P) && !(fabs(d.u1 - d.P) < kNear)) continue;
       }
-      __syncthreads();
-      // The processes of the plane's small cells with a Cu+, a cell per
-      // lane, on the sorted records in LDS.
-      const unsigned mc = L.cnt[tid];
-      if (small_cell(mc)) {
-        LdsRecs r{L.key, L.gi, L.perm, (int)L.off[tid], c0 + tid};
-        bool has_ion = false;
-        for (int j = 0; j < (int)mc; ++j) has_ion = has_ion || ip_sp(r[j]) == 1u;
-        if (has_ion)
-          ip_cell(S, r, (int)mc, cell_of_tile_major(c0 + tid, g), k, g, ncount,
-                  acc, dead2, ev, evp, dc, t);
-      }
-      __syncthreads();
-      continue;
+      atomicOr(&L.flag[lc >> 5], 1u << (lc & 31));
     }
-    // A larger plane: its small cells' records go to srt and k_ip_small
-    // runs them.
-    if (tid == 0) rest[atomicAdd(nrest, 1u)] = (unsigned)u;
-    // Crowded cells: records straight into their segments, unsorted.
-    if (__ballot(m > (unsigned)kSmall)) {
-      L.cur[tid] = L.off[tid];
-      if (m > (unsigned)kSmall) {
-        const unsigned q = atomicAdd(nbig, 1u);
-        if ((long long)q < big_cap) big[q] = c0 + tid;
-      }
-      __syncthreads();
-      for (int j = tid; j < n; j += kPlaneCells) {
-        const unsigned gi = pidx[base + j];
-        const unsigned c = tile_major(key_of(S, J, gi), g);
-        const int lc = (int)(c & (kPlaneCells - 1));
-        if (L.cnt[lc] > (unsigned)kSmall)
-          rec[base + atomicAdd(&L.cur[lc], 1u)] = make_rec(S, J, gi, c, step, seed);
-      }
-      __syncthreads();
-    }
-    // Small cells in batches.
-    for (int c_lo = 0; c_lo < kPlaneCells;) {
+    __syncthreads();
+    const unsigned long long mask =
+        (unsigned long long)L.flag[1] << 32 | L.flag[0];
+    if (mask) {
       if (tid == 0) {
-        int c_hi = c_lo, nb = 0;
-        while (c_hi < kPlaneCells) {
-          const unsigned mc = L.cnt[c_hi];
-          const int add = small_cell(mc) ? (int)mc : 0;
-          if (nb + add > kPCap) break;
-          L.start[c_hi] = (unsigned)nb;
-          L.cur[c_hi] = (unsigned)nb;
-          nb += add;
-          ++c_hi;
-        }
-        L.hi = c_hi;
-        L.nb = nb;
+        const unsigned q = atomicAdd(A.nrest, 1u);
+        A.rest[q] = (unsigned)u;
+        A.rmask[q] = mask;
+      }
+      for (int j = tid; j < n; j += kPlaneCells) {
+        const unsigned lc = A.pcs[base + j] & 63u;
+        if (mask >> lc & 1ull)
+          A.rec[base + atomicAdd(&L.cur[lc], 1u)] =
+              make_rec(S, J, A.pidx[base + j], c0 + lc, k.step, k.seed);
       }
       __syncthreads();
-      const int c_hi = L.hi, nb = L.nb;
-      if (nb > 0) {
-        for (int j = tid; j < n; j += kPlaneCells) {
-          const unsigned gi = pidx[base + j];
-          const uint32_t kc = key_of(S, J, gi);
-          const int lc = (int)(tile_major(kc, g) & (kPlaneCells - 1));
-          if (lc < c_lo || lc >= c_hi || !small_cell(L.cnt[lc])) continue;
-          const int p = (int)atomicAdd(&L.cur[lc], 1u);
-          const Rec r = make_rec(S, J, gi, c0 + lc, step, seed);
-          L.key[p] = r.lo;
-          L.gi[p] = J.ix(gi);
-          L.cell[p] = (unsigned char)lc;
-        }
-        __syncthreads();
-        for (int p = tid; p < nb; p += kPlaneCells) {
-          const int lc = L.cell[p];
-          const int b = (int)L.start[lc], mc = (int)L.cnt[lc];
-          const unsigned long long kp = L.key[p];
-          int rank = 0;
-          for (int q = b; q < b + mc; ++q) {
-            const unsigned long long kq = L.key[q];
-            if (kq < kp) {
-              ++rank;
-            } else if (kq == kp && q != p) {
-              // Equal draws (practically never): id order.
-              rank += key_id(S, kq, L.gi[q]) < key_id(S, kp, L.gi[p]);
-            }
-          }
-          Rec r;
-          r.lo = kp;
-          r.hi = ((c0 + (unsigned)lc) << 2) | (unsigned)(kp >> 62);
-          r.val = L.gi[p];
-          srt[base + L.off[lc] + rank] = r;
-        }
-      }
-      __syncthreads();
-      c_lo = c_hi;
     }
   }
-  // The tallies, summed over the wavefront.
-  for (int o = 32; o > 0; o >>= 1) {
-    t.rec += __shfl_xor(t.rec, o);
-    t.cx += __shfl_xor(t.cx, o);
-    t.starved += __shfl_xor(t.starved, o);
-    t.near += __shfl_xor(t.near, o);
-  }
-  if (tid == 0) flush_tally<PT>(t, dc);
 }
 
 // Planes of more than kHot records (the atoms piled above an evaporating
@@ -921,19 +843,22 @@ __global__ void __launch_bounds__(kT) k_ph_scatter(
   }
 }
 
-// The small cells of the hot planes, a thread per (cell, record): rank in
-// the cell's (key, id) order from the scattered records.
+// The masked small cells of the planes in rest, a thread per (cell,
+// record): rank in the cell's (key, id) order from the scattered records.
 template <class PT>
 __global__ void __launch_bounds__(kT) k_ph_rank(
-    Sp3<PT> S, const unsigned* __restrict__ hot,
-    const unsigned* __restrict__ nhot, const unsigned* __restrict__ off,
+    Sp3<PT> S, const unsigned* __restrict__ rest,
+    const unsigned long long* __restrict__ rmask,
+    const unsigned* __restrict__ nrest, const unsigned* __restrict__ off,
     const Rec* __restrict__ rec, Rec* __restrict__ srt) {
-  const long long nt = (long long)*nhot * kPlaneCells * kSmall;
+  const long long nt = (long long)*nrest * kPlaneCells * kSmall;
   for (long long t = blockIdx.x * (long long)kT + threadIdx.x; t < nt;
        t += (long long)gridDim.x * kT) {
     const int r = (int)(t % kSmall);
     const long long hc = t / kSmall;
-    const unsigned c = (hot[hc / kPlaneCells] << kPlaneShift) + (unsigned)(hc % kPlaneCells);
+    const int lc = (int)(hc % kPlaneCells);
+    if (!(rmask[hc / kPlaneCells] >> lc & 1ull)) continue;
+    const unsigned c = (rest[hc / kPlaneCells] << kPlaneShift) + (unsigned)lc;
     const unsigned b = off[c];
     const int m = (int)(off[c + 1] - b);
     if (!small_cell((unsigned)m) || r >= m) continue;
@@ -947,16 +872,18 @@ __global__ void __launch_bounds__(kT) k_ph_rank(
   }
 }
 
-// Small cells with a Cu+ of the planes the plane pass did not run (more
-// than kPCap records, or hot), one thread each, on the sorted records.  Four
-// wavefronts per SIMD (128 registers, two spilled on rare paths): a chain of
-// gathers per cell wants occupancy, 1039 -> 935 us at the 128x128x512
-// workload; five (30 spilled) ran 1413 us.
+// The masked small cells with a Cu+ of the planes in rest, one thread each,
+// on the sorted records.  Four wavefronts per SIMD (128 registers, two
+// spilled on rare paths): a chain of gathers per cell wants occupancy, 1039
+// -> 935 us with every cell of the 128x128x512 workload; five (30 spilled)
+// ran 1413 us.
 template <class PT>
 __global__ void __launch_bounds__(kT, 4) k_ip_small(
     Sp3<PT> S, const unsigned* __restrict__ off,
-    const unsigned* __restrict__ rest, const unsigned* __restrict__ nrest,
-    const Rec* __restrict__ srt, IonC k, GridC g,
+    const unsigned* __restrict__ rest,
+    const unsigned long long* __restrict__ rmask,
+    const unsigned* __restrict__ nrest, const Rec* __restrict__ srt, IonC k,
+    GridC g,
     int* __restrict__ ncount, long long* __restrict__ acc,
     uint32_t* __restrict__ dead2, Rec* __restrict__ ev,
     uint2* __restrict__ evp, Counters* dc) {
@@ -964,7 +891,9 @@ __global__ void __launch_bounds__(kT, 4) k_ip_small(
   const long long nt = (long long)*nrest * kPlaneCells;
   for (long long q = blockIdx.x * (long long)kT + threadIdx.x; q < nt;
        q += (long long)gridDim.x * kT) {
-    const unsigned c = (rest[q / kPlaneCells] << kPlaneShift) + (unsigned)(q % kPlaneCells);
+    const int lc = (int)(q % kPlaneCells);
+    if (!(rmask[q / kPlaneCells] >> lc & 1ull)) continue;
+    const unsigned c = (rest[q / kPlaneCells] << kPlaneShift) + (unsigned)lc;
     const unsigned b = off[c], e = off[c + 1];
     const int n = (int)(e - b);
     if (n < 2 || n > kSmall) continue;
@@ -1265,6 +1194,32 @@ Parts sp_cur<Parts>(pic_ctx* c, int s) { return c->P[s][c->cur[s]]; }
 template <>
 PartsM sp_cur<PartsM>(pic_ctx* c, int s) { return c->PM[s][c->cur[s]]; }
 
+// The largest sigma v dt of an electron and of a Cu+-atom pair at any
+// energy.  Recombination: s_rec v / max(E, 1 meV) peaks at 1 meV;
+// ionisation: a2 ln(x) / (x I2^2) v(I2) sqrt(x), x = E / I2, at x = e^2.
+// Charge exchange: with s = a - b ln(eps), d(s^2 u)/du = s (s - 4 b), so it
+// grows up to s = 4 b (or the clamp of eps) and falls after; without that
+// fall it is a^2 times the speed (b = 0) or not bounded here (b < 0).  1e-6
+// is a margin for rounding.
+void event_bounds(IonC& k) {
+  const double inf = std::numeric_limits<double>::infinity();
+  const double ve = std::sqrt(1e-3 * kE / k.half_me);
+  const double vi = std::sqrt(k.I2 * kE / k.half_me);
+  k.h_e = k.s_rec * 1e3 * ve + k.a2 * 2.0 * vi / (std::exp(1.0) * k.I2 * k.I2);
+  k.h_cx = inf;
+  if (k.cx_b > 0.0) {
+    const double eps = std::max(1e-6, std::exp(k.cx_a / k.cx_b - 4.0));
+    const double s = std::max(0.0, k.cx_a - k.cx_b * std::log(eps));
+    k.h_cx = s * s * std::sqrt(eps * kE / (0.25 * kMcu));
+  } else if (k.cx_b == 0.0) {
+    k.h_cx = k.cx_a > 0.0 ? k.cx_a * k.cx_a : 0.0;
+  }
+  k.h_e *= k.dt * (1.0 + 1e-6);
+  k.h_cx *= k.dt * (1.0 + 1e-6);
+  if (!(k.h_e <= inf)) k.h_e = inf;      // (NaN)
+  if (!(k.h_cx <= inf)) k.h_cx = inf;
+}
+
 template <class PT>
 void ionproc_t(pic_ctx* c, double dt) {
   hipStream_t st = c->stream;
@@ -1281,6 +1236,7 @@ void ionproc_t(pic_ctx* c, double dt) {
   k.dt = dt;
   k.half_me = 0.5 * kMe;
   k.two_e_me = (2.0 * kE) / kMe;
+  event_bounds(k);
   k.step = (unsigned)c->step;
   k.seed = c->cfg.seed;
   k.cap_n = c->cfg.capacity[1];
@@ -1293,6 +1249,9 @@ void ionproc_t(pic_ctx* c, double dt) {
   const long long np = nc >> kPlaneShift;      // tile planes
   hipMemsetAsync(c->cg_cnt, 0, np * sizeof(unsigned), st);
   hipMemsetAsync(c->cg_nbig, 0, 3 * sizeof(unsigned), st);
+  // The records' cell bytes, in the memory of the sorted records (written
+  // once these bytes have been read).
+  unsigned char* pcs = reinterpret_cast<unsigned char*>(c->cg_srt);
   // Grids of a multiple of 8 workgroups (see xcd_block).
   k_pg_count<PT><<<4096, kT, 0, st>>>(S, c->dc, c->g, c->cg_cnt);
   const long long nb = (np + kScanB - 1) / kScanB;
@@ -1301,13 +1260,13 @@ void ionproc_t(pic_ctx* c, double dt) {
   k_ig_scan_sums<<<1, 1024, 0, st>>>(c->cg_bsum, (int)nb);
   k_ig_scan_apply<<<(unsigned)nb, kScanB, 0, st>>>(c->cg_poff, np, c->cg_bsum);
   k_pg_scatter<PT><<<4096, kT, 0, st>>>(S, c->dc, c->g, c->cg_poff, c->cg_cnt,
-                                        c->cg_idx);
-  // Counters: crowded cells, hot planes, planes left to k_ip_small.
-  k_pg_cells<PT><<<8192, kPlaneCells, 0, st>>>(
-      S, c->g, c->cg_poff, np, c->cg_idx, c->cg_off, c->cg_rec, c->cg_srt,
-      c->cg_big, c->cg_nbig, c->cg_big_cap, c->cg_hot, c->cg_nbig + 1,
-      c->cg_rest, c->cg_nbig + 2, k, c->ncount, c->acc_next, c->dead2,
-      c->ip_ev, c->ip_evp, c->dc);
+                                        c->cg_idx, pcs);
+  // Counters: crowded cells, hot planes, planes with cells for k_ip_small.
+  const PgArgs<PT> pg{S, c->cg_poff, np, c->cg_idx, pcs, c->cg_off,
+                      c->cg_rec, c->cg_big, c->cg_nbig, c->cg_big_cap,
+                      c->cg_hot, c->cg_nbig + 1, c->cg_rest, c->cg_nbig + 2,
+                      c->cg_rmask, k, c->dc};
+  k_pg_cells<PT><<<8192, kPlaneCells, 0, st>>>(pg);
   unsigned* nhot = c->cg_nbig + 1;
   k_ph_prep<<<1, 1024, 0, st>>>(c->cg_poff, c->cg_hot, nhot, c->cg_hpre,
                                 c->cg_cnt);
@@ -1319,10 +1278,12 @@ void ionproc_t(pic_ctx* c, double dt) {
   k_ph_scatter<PT><<<1024, kT, 0, st>>>(S, c->g, c->cg_poff, c->cg_hot, nhot,
                                         c->cg_hpre, c->cg_idx, c->cg_cnt,
                                         c->cg_rec, k.step, k.seed, c->dc);
-  k_ph_rank<PT><<<512, kT, 0, st>>>(S, c->cg_hot, nhot, c->cg_off, c->cg_rec,
+  k_ph_rank<PT><<<512, kT, 0, st>>>(S, c->cg_rest, c->cg_rmask,
+                                    c->cg_nbig + 2, c->cg_off, c->cg_rec,
                                     c->cg_srt);
-  k_ip_small<PT><<<512, kT, 0, st>>>(S, c->cg_off, c->cg_rest, c->cg_nbig + 2,
-                                     c->cg_srt, k, c->g, c->ncount,
+  k_ip_small<PT><<<512, kT, 0, st>>>(S, c->cg_off, c->cg_rest, c->cg_rmask,
+                                     c->cg_nbig + 2, c->cg_srt, k, c->g,
+                                     c->ncount,
                                      c->acc_next, c->dead2, c->ip_ev,
                                      c->ip_evp, c->dc);
   k_ip_big<PT><<<512, kT, 0, st>>>(S, c->cg_off, c->cg_rec, c->cg_big,

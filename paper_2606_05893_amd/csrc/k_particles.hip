@@ -263,6 +263,7 @@ __global__ void k_begin(Counters* dc, unsigned long long n0,
   dc->np_heat = 0.0;
   dc->coul_like = dc->coul_ei = 0;
   dc->f3_rec = dc->f3_ion2 = dc->f3_cx = dc->f3_starved = 0;
+  dc->n_vmax2 = 0;
 }
 
 // ---- sources ------------------------------------------------------------------
@@ -1239,18 +1240,6 @@ struct TileArgs {
   Counters* dc;
 };
 
-// The kernel's argument, read again from the kernel argument segment: the
-// tile push has more uniform values than scalar registers, and those the
-// compiler would keep over its loop it moves to and from vector lanes
-// (400 v_readlane and v_writelane), where a scalar load costs one request.
-template <class A>
-__device__ __forceinline__ const A& reread() {
-  typedef const __attribute__((address_space(4))) A* Seg;
-  Seg p = (Seg)__builtin_amdgcn_kernarg_segment_ptr();
-  asm volatile("" : "+s"(p));
-  return *(const A*)p;
-}
-
 // One workgroup per chunk of a tile.  Its waves take the chunk's ions and
 // then its electrons 64 at a time, wave w the groups w, w + 4, ..., so a wave
 // idles for at most one group (the two species in turn, 256 particles at a
@@ -1475,18 +1464,35 @@ __device__ __forceinline__ void hist_flush(unsigned* hk, int* hc,
 // only when their cell changes or they leave the domain, and the ones
 // appended since are added.  A neutral's previous cell is that of its
 // stored position, the value the previous step counted.
+//
+// vmax: also their largest |v|^2 to n_vmax2 (its bits, which order as the
+// values do; a neutral that is not finite is removed).
+__device__ __forceinline__ void note_vmax(double ke_max, Counters* dc) {
+  unsigned long long v = (unsigned long long)__double_as_longlong(ke_max);
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    const unsigned long long y = __shfl_xor(v, o, 64);
+    v = y > v ? y : v;
+  }
+  // (Most waves find a larger one there; a stale value only costs the add.)
+  if (lane_id() == 0 &&
+      v > __hip_atomic_load(&dc->n_vmax2, __ATOMIC_RELAXED,
+                            __HIP_MEMORY_SCOPE_AGENT))
+    atomicMax(&dc->n_vmax2, v);
+}
+
 __global__ void __launch_bounds__(kT) k_push_neutral(
     Parts p, uint32_t* __restrict__ key, GridC g, double dt,
     int* __restrict__ ncount, long long n_old, MccC m, uint32_t step,
     uint64_t seed, Rec* __restrict__ ab_rec, double* __restrict__ ab_pos,
     double* __restrict__ ab_vel, long long ab_cap, Counters* dc,
-    double* __restrict__ part, uint32_t* __restrict__ dead1) {
+    double* __restrict__ part, uint32_t* __restrict__ dead1, bool vmax) {
   __shared__ unsigned hk[kHist];
   __shared__ int hc[kHist];
   __shared__ double sk[kT];
   const long long n = (long long)dc->n[1];
   const long long nchunk = (n + kNChunk - 1) / kNChunk;
-  double ke = 0.0;
+  double ke = 0.0, ke_max = 0.0;
   for (long long cb = blockIdx.x; cb < nchunk; cb += gridDim.x) {
     const long long b0 = cb * kNChunk;
     const bool fresh = b0 + kNChunk > n_old;  // holds appended neutrals
@@ -1515,6 +1521,7 @@ __global__ void __launch_bounds__(kT) k_push_neutral(
           }
         }
         ke = ke + o.ke;
+        if (!(o.ke <= ke_max)) ke_max = o.ke;
       }
       sink(p, i, o, g, ab_rec, ab_pos, ab_vel, ab_cap, dc, 1);
       list_dead(i < n && o.cell == kDead, i, dead1, &dc->n_dead1);
@@ -1525,6 +1532,7 @@ __global__ void __launch_bounds__(kT) k_push_neutral(
       __syncthreads();
     }
   }
+  if (vmax) note_vmax(ke_max, dc);
   const double s = block_sum(ke, sk);
   if (threadIdx.x == 0) part[blockIdx.x] = s;
 }
@@ -1534,13 +1542,13 @@ __global__ void __launch_bounds__(kT) k_push_neutral_m(
     int* __restrict__ ncount, long long n_old, MccC m, uint32_t step,
     uint64_t seed, Rec* __restrict__ ab_rec, double* __restrict__ ab_pos,
     double* __restrict__ ab_vel, long long ab_cap, Counters* dc,
-    double* __restrict__ part, uint32_t* __restrict__ dead1) {
+    double* __restrict__ part, uint32_t* __restrict__ dead1, bool vmax) {
   __shared__ unsigned hk[kHist];
   __shared__ int hc[kHist];
   __shared__ double sk[kT];
   const long long n = (long long)dc->n[1];
   const long long nchunk = (n + kNChunk - 1) / kNChunk;
-  double ke = 0.0;
+  double ke = 0.0, ke_max = 0.0;
   for (long long cb = blockIdx.x; cb < nchunk; cb += gridDim.x) {
     const long long b0 = cb * kNChunk;
     const bool fresh = b0 + kNChunk > n_old;  // holds appended neutrals
@@ -1570,6 +1578,7 @@ __global__ void __launch_bounds__(kT) k_push_neutral_m(
           }
         }
         ke = ke + o.ke;
+        if (!(o.ke <= ke_max)) ke_max = o.ke;
       }
       sink_m(p, i, 1, o, g, ab_rec, ab_pos, ab_vel, ab_cap, dc);
       list_dead(i < n && o.cell == kDead, i, dead1, &dc->n_dead1);
@@ -1580,6 +1589,7 @@ __global__ void __launch_bounds__(kT) k_push_neutral_m(
       __syncthreads();
     }
   }
+  if (vmax) note_vmax(ke_max, dc);
   const double s = block_sum(ke, sk);
   if (threadIdx.x == 0) part[blockIdx.x] = s;
 }
@@ -2807,12 +2817,13 @@ void push_neutral_t(pic_ctx* c, double dt) {
     k_push_neutral_m<<<nb, kT, 0, st>>>(
         cur<PartsM>(c, 1), c->key[1], c->g, (float)(dt * c->g.inv_dx),
         c->ncount, n_old, m, step, seed, c->ab_rec, c->ab_raw_pos,
-        c->ab_raw_vel, ab_cap, c->dc, c->part_n, c->dead1);
+        c->ab_raw_vel, ab_cap, c->dc, c->part_n, c->dead1,
+        c->ionp.enabled != 0);
   else
     k_push_neutral<<<nb, kT, 0, st>>>(
         cur<Parts>(c, 1), c->key[1], c->g, dt, c->ncount, n_old, m, step,
         seed, c->ab_rec, c->ab_raw_pos, c->ab_raw_vel, ab_cap, c->dc,
-        c->part_n, c->dead1);
+        c->part_n, c->dead1, c->ionp.enabled != 0);
   c->ncount_valid = true;
   tmark(c, PIC_PH_PUSH_NEUTRAL, false);
   k_sum_partials<<<1, 1024, 0, st>>>(c->part_n, nb, nullptr, c->part_n, 0,

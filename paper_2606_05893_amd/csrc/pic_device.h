@@ -70,6 +70,18 @@ __device__ __forceinline__ void uniform2(uint64_t id, uint32_t step,
   ub = (double)b * 0x1p-53;
 }
 
+// A kernel's only argument, read again from the kernel argument segment.
+// A kernel with more uniform values than scalar registers keeps them in
+// spilled vector lanes over its loop (in the tile push 400 v_readlane and
+// v_writelane), where a scalar load of each at its use costs one request.
+template <class A>
+__device__ __forceinline__ const A& reread() {
+  typedef const __attribute__((address_space(4))) A* Seg;
+  Seg p = (Seg)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  return *(const A*)p;
+}
+
 // Cell index and quantised upper weight along one axis: g = x * inv_dx,
 // i = floor(g), fq = floor((g - i) * 8192 + 0.5) in [0, 8192].
 __device__ __forceinline__ void cic_axis(double x, double inv_dx, int& i,
@@ -277,6 +289,7 @@ struct Counters {
   unsigned long long f3_ion2;       // ionisations of Cu+ (listed)
   unsigned long long f3_cx;         // charge exchanges
   unsigned long long f3_starved;    // electron-ion events without an ion
+  unsigned long long n_vmax2;       // bits of the atoms' largest |v|^2
   long long total_charge;
   unsigned int err;                 // sticky error bits (kErr*)
   int vcycles;
