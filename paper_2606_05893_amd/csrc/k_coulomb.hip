@@ -316,14 +316,21 @@ __global__ void __launch_bounds__(kT) k_cu_scatter(
 // ---- the cell pass -------------------------------------------------------------
 // One wavefront per plane: a workgroup of one wavefront never waits at a
 // barrier for others, so a plane's serial stretches (the longest electron-ion
-// chain) leave the SIMD to the other planes' wavefronts.
+// chain) leave the SIMD to the other planes' wavefronts.  (20 M particles on
+// 128 x 128 x 512 cells: 1394 us, of them the gathers 330, the keys, order
+// and lists 150, like pairs 180, electron-ion chains 290 and the velocities
+// written back 440: a plane's particles lie scattered over its tile's range.
+// The eight planes of a tile as one workgroup that writes back together:
+// 1538 us; the electron-ion draws run a particle per lane ahead of their
+// chains: 100 us slower.)
 constexpr int kCT = 64;
 
 // LDS of a batch of whole cells.  Particles sit in load order (slots); the
 // cell order is a permutation of the slots, and each cell's part of it is
 // then ranked by (key, id).
 struct BatchLds {
-  unsigned long long key[kCap];   // species bit above the order draw
+  unsigned long long key[kCap];   // species bit above the order draw, in
+                                  // cell order
   unsigned long long id[kCap];
   double v[3][kCap];
   unsigned gi[kCap];              // index word (joint range)
@@ -340,8 +347,6 @@ struct PlaneLdsC {
   unsigned off[kPlaneCells + 1];   // cell offsets in the plane's particles
   unsigned cur[kPlaneCells];
   unsigned short ne[kPlaneCells];  // electrons per cell
-  unsigned cls[kNCls + 1];        // class offsets in the work list
-  unsigned ccur[kNCls];
   int nslot, hi;
 };
 
@@ -376,21 +381,15 @@ __device__ __forceinline__ void load_slot(const Sp2<PT>& S, const JointIx& J,
   L.cell[p] = (unsigned short)lc;
 }
 
-// The work a sorted place leads: its like class (0 pair, 1 triplet, -1
-// none) and electron-ion chain class (2, 3, 4 for one, two, three or more
-// collisions, -1 none).
-__device__ __forceinline__ void place_work(const BatchLds& L, const PlaneLdsC& U,
-                                           unsigned ob, int r, int& lcl,
+// The work the place of a given rank leads in its cell of ne electrons (the
+// first ranks) and ni ions: its like class (0 pair, 1 triplet, -1 none) and
+// electron-ion chain class (2, 3, 4 for one, two, three or more collisions,
+// -1 none).
+__device__ __forceinline__ void place_work(int rank, int ne, int ni, int& lcl,
                                            int& ecl) {
   lcl = ecl = -1;
-  const int p = L.perm[r];
-  const int lc = L.cell[p];
-  const int m = (int)(U.off[lc + 1] - U.off[lc]);
-  if (m < 2) return;
-  const int b = (int)(U.off[lc] - ob);
-  const int ne = U.ne[lc], ni = m - ne;
-  const int s = (int)(L.key[p] >> 63);
-  const int q = s ? r - b - ne : r - b;    // rank within the species
+  const int s = rank >= ne;
+  const int q = s ? rank - ne : rank;      // rank within the species
   const int N = s ? ni : ne;
   const int start = (N & 1) ? 3 : 0;
   const bool trip = (N & 1) && q == 0;
@@ -398,8 +397,8 @@ __device__ __forceinline__ void place_work(const BatchLds& L, const PlaneLdsC& U
     lcl = trip ? 1 : 0;
   if (ne > 0 && ni > 0 && s == (ne <= ni ? 0 : 1)) {
     const int K = ne > ni ? ne : ni, mm = ne < ni ? ne : ni;
-    const int len = (K - q + mm - 1) / mm;
-    ecl = len >= 3 ? 4 : len + 1;
+    const int left = K - q;                // collisions q, q + mm, ... < K
+    ecl = left > 2 * mm ? 4 : (left > mm ? 3 : 2);
   }
 }
 
@@ -415,20 +414,30 @@ __device__ void batch_collide(const Sp2<PT>& S, const JointIx& J, int c_lo,
   const int tid = (int)threadIdx.x;
   const unsigned ob = U.off[c_lo];
   for (int c = c_lo + tid; c < c_hi; c += kCT) U.cur[c] = U.off[c] - ob;
-  if (tid < kNCls) U.ccur[tid] = 0u;
   __syncthreads();
   // Cell order, and the keys of the particles that have a partner.
   for (int p = tid; p < nb; p += kCT) {
     const int lc = L.cell[p];
-    L.work[atomicAdd(&U.cur[lc], 1u)] = (unsigned short)p;
-    if (U.off[lc + 1] - U.off[lc] >= 2u) {
-      const unsigned gi = L.gi[p];
-      L.key[p] = (J.sp(gi) ? kSpBit : 0ull) | order_key(L.id[p], k.step, k.seed);
-    }
+    const unsigned x = atomicAdd(&U.cur[lc], 1u);
+    L.work[x] = (unsigned short)p;
+    if (U.off[lc + 1] - U.off[lc] >= 2u)
+      L.key[x] = (J.sp(L.gi[p]) ? kSpBit : 0ull) | order_key(L.id[p], k.step, k.seed);
   }
   __syncthreads();
-  // Rank of each particle in its cell's (key, id) order.
-  for (int x = tid; x < nb; x += kCT) {
+  // Rank of each particle in its cell's (key, id) order, and the work its
+  // place leads.  The keys lie in cell order, one read a comparison, and the
+  // work stays in registers until ballots place it, with no counters in LDS:
+  // 70 us of the pass over 20 M particles, 170 us with the keys read through
+  // the slots and the lists counted and placed by LDS atomics (the whole
+  // pass 1497 -> 1394 us).
+  constexpr int kPass = (kCap + kCT - 1) / kCT;
+  int place[kPass], lcl[kPass], ecl[kPass];
+#pragma unroll
+  for (int z = 0; z < kPass; ++z) {
+    const int x = z * kCT + tid;
+    place[z] = 0;
+    lcl[z] = ecl[z] = -1;
+    if (x >= nb) continue;
     const int p = L.work[x];
     const int lc = L.cell[p];
     const int b = (int)(U.off[lc] - ob), m = (int)(U.off[lc + 1] - U.off[lc]);
@@ -436,46 +445,43 @@ __device__ void batch_collide(const Sp2<PT>& S, const JointIx& J, int c_lo,
       L.perm[b] = (unsigned short)p;
       continue;
     }
-    const unsigned long long kp = L.key[p], ip = L.id[p];
-    int rank = 0, ne = 0;
+    const unsigned long long kp = L.key[x];
+    int rank = 0, ne = 0, same = 0;
     for (int q = b; q < b + m; ++q) {
-      const int o = L.work[q];
-      const unsigned long long kq = L.key[o];
+      const unsigned long long kq = L.key[q];
       ne += kq < kSpBit;
-      rank += kq < kp || (kq == kp && L.id[o] < ip);
+      rank += kq < kp;
+      same += kq == kp;
+    }
+    if (same > 1) {                        // (practically never: id order)
+      const unsigned long long ip = L.id[p];
+      for (int q = b; q < b + m; ++q)
+        rank += L.key[q] == kp && L.id[L.work[q]] < ip;
     }
     L.perm[b + rank] = (unsigned short)p;
     if (rank == 0) U.ne[lc] = (unsigned short)ne;
+    place[z] = b + rank;
+    place_work(rank, ne, m - ne, lcl[z], ecl[z]);
   }
   __syncthreads();
-  // Work items by class: count, class offsets, placement (the list takes
-  // the cell-order array's place).
-  for (int r = tid; r < nb; r += kCT) {
-    int lcl, ecl;
-    place_work(L, U, ob, r, lcl, ecl);
-    if (lcl >= 0) atomicAdd(&U.ccur[lcl], 1u);
-    if (ecl >= 0) atomicAdd(&U.ccur[ecl], 1u);
-  }
-  __syncthreads();
-  if (tid == 0) {
-    unsigned t = 0;
-    for (int c = 0; c < kNCls; ++c) {
-      U.cls[c] = t;
-      t += U.ccur[c];
-      U.ccur[c] = U.cls[c];
+  // The lists, class after class, in the cell-order array's place.
+  int n_pair = 0, n_like = 0, n_all = 0;
+#pragma unroll
+  for (int c = 0; c < kNCls; ++c) {
+#pragma unroll
+    for (int z = 0; z < kPass; ++z) {
+      const bool mine = (c < 2 ? lcl[z] : ecl[z]) == c;
+      const unsigned long long mask = __ballot(mine);
+      if (mine)
+        L.work[n_all + __popcll(mask & ((1ull << tid) - 1ull))] =
+            (unsigned short)place[z];
+      n_all += __popcll(mask);
     }
-    U.cls[kNCls] = t;
-  }
-  __syncthreads();
-  for (int r = tid; r < nb; r += kCT) {
-    int lcl, ecl;
-    place_work(L, U, ob, r, lcl, ecl);
-    if (lcl >= 0) L.work[atomicAdd(&U.ccur[lcl], 1u)] = (unsigned short)r;
-    if (ecl >= 0) L.work[atomicAdd(&U.ccur[ecl], 1u)] = (unsigned short)r;
+    if (c == 0) n_pair = n_all;
+    if (c == 1) n_like = n_all;
   }
   __syncthreads();
   // Like collisions: pairs, then leading triplets (three in order).
-  const int n_like = (int)U.cls[2], n_pair = (int)U.cls[1];
   for (int w = tid; w < n_like; w += kCT) {
     const int r = L.work[w];
     const int p = L.perm[r];
@@ -496,7 +502,6 @@ __device__ void batch_collide(const Sp2<PT>& S, const JointIx& J, int c_lo,
   }
   __syncthreads();
   // Electron-ion chains, shortest first.
-  const int n_all = (int)U.cls[kNCls];
   for (int w = n_like + tid; w < n_all; w += kCT) {
     const int r = L.work[w];
     const int p = L.perm[r];
