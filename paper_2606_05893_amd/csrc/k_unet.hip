@@ -62,13 +62,6 @@ __device__ __forceinline__ bf16x8 load8(const bf16* p) {
   __builtin_memcpy(&r, &v, 16);
   return r;
 }
-__device__ __forceinline__ bf16x8 zero8() {
-  const uint4 v = make_uint4(0, 0, 0, 0);
-  bf16x8 r;
-  __builtin_memcpy(&r, &v, 16);
-  return r;
-}
-
 struct Dims {
   int D, H, W;
   long long V;
@@ -111,57 +104,27 @@ __device__ __forceinline__ long long nb_voxel(const Dims& d, int z, int y,
   return ((long long)zz * d.H + yy) * d.W + xx;
 }
 
-constexpr int KP(int cin) { return (27 * cin + 63) / 64 * 64; }
-
-// Stage the halo of a tile for one slice of 16 input channels into LDS:
-// HV voxels of 32 B as two planes of 16-byte halves (x and y periodic, z
-// zero-padded).  The slice is channels c0 .. c0 + 15 of a tensor of C
-// channels per voxel: at the tile's dims, or (UP) at half of them, read as
-// its nearest upsampling (fine voxel (z, y, x) takes coarse (z/2, y/2,
-// x/2)).  Every global load of a thread is issued before the first LDS
-// store, so they are all in flight together.  ONE: the level is at least a
-// halo wide, so one wrap brings every coordinate into range.
-template <int HX, int HY, int HZ, int NTH, bool ONE, bool UP>
-__device__ __forceinline__ void stage_halo_w(uint4* lds, const bf16* __restrict__ in,
-                                             int C, int c0, const Dims& d, int x0,
-                                             int y0, int z0) {
-  constexpr int HV = HX * HY * HZ;
-  constexpr int PER = (2 * HV + NTH - 1) / NTH;
-  uint4 val[PER];
-#pragma unroll
-  for (int m = 0; m < PER; ++m) {
-    const int q = (int)threadIdx.x + m * NTH;
-    const int hv = q >> 1, hh = q & 1;
-    const int hx = hv % HX, hy = (hv / HX) % HY, hz = hv / (HX * HY);
-    const int gz = z0 + hz - 1;
-    val[m] = make_uint4(0, 0, 0, 0);
-    if (q < 2 * HV && gz >= 0 && gz < d.D) {
-      int gy = y0 + hy - 1, gx = x0 + hx - 1;
-      if constexpr (ONE) {
-        gy = gy < 0 ? gy + d.H : (gy >= d.H ? gy - d.H : gy);
-        gx = gx < 0 ? gx + d.W : (gx >= d.W ? gx - d.W : gx);
-      } else {
-        gy = (gy + d.H) % d.H;
-        gx = (gx + d.W) % d.W;
-      }
-      size_t gv;
-      if constexpr (UP)
-        gv = ((size_t)(gz >> 1) * (d.H >> 1) + (gy >> 1)) * (d.W >> 1) + (gx >> 1);
-      else
-        gv = ((size_t)gz * d.H + gy) * d.W + gx;
-      val[m] = ld16(in + gv * C + c0 + hh * 8);
-    }
-  }
-#pragma unroll
-  for (int m = 0; m < PER; ++m) {
-    const int q = (int)threadIdx.x + m * NTH;
-    if (q < 2 * HV) lds[(q & 1) * HV + (q >> 1)] = val[m];
-  }
+// Packed 3^3 weights, in the order the matrix instructions take them: per 16
+// output channels, 16 input channels (slice) and tap row (oz, oy) two
+// fragments of 64 lanes x 8 values, lane 16 (half + 2 slot) + channel.  The
+// first holds the taps ox = slot, the second ox = 2 in slot 0 and zeros.  A
+// wave's load of a fragment is 1 KB in a row; read from [channel][tap][in]
+// rows, 32 bytes a row, the weights took more than half of the requests of
+// the 48 -> 16 layer (562 -> 476 us at 128x128x512).
+constexpr int kFrag = 512;
+__host__ __device__ constexpr long long frag_at(int tile, int slices, int sl, int row) {
+  return (((long long)tile * slices + sl) * 9 + row) * 2 * kFrag;
+}
+__host__ __device__ constexpr long long wpack(int co, int ci) {
+  return frag_at(co / 16, ci / 16, 0, 0);
 }
 
-// The same halo held in registers between its loads and its LDS stores
-// (halo_load / halo_store), so that the loads of the next slice can be in
-// flight while the current one is computed.
+// The halo of a tile for one slice of 16 input channels (x and y periodic, z
+// zero-padded), held in registers between its loads and its LDS stores
+// (halo_load / halo_store; HV voxels of 32 B as two planes of 16-byte
+// halves), so that the loads of the next slice can be in flight while the
+// current one is computed.  UP: read from a tensor at half the dims as its
+// nearest upsampling (fine voxel (z, y, x) takes coarse (z/2, y/2, x/2)).
 template <int HX, int HY, int HZ, int NTH>
 struct HaloRegs {
   static constexpr int HV = HX * HY * HZ;
@@ -235,29 +198,72 @@ __device__ __forceinline__ void halo_store(uint4* lds, const HaloRegs<HX, HY, HZ
   }
 }
 
-// Slice sl of the input: of 'in' (CIN channels), or with CU > 0 of the
-// concatenation [up(in) (CU channels, half dims), skip (CIN - CU)].
-template <int CIN, int CU, int HX, int HY, int HZ, int NTH>
-__device__ __forceinline__ void stage_halo(uint4* lds, const bf16* __restrict__ in,
-                                           const bf16* __restrict__ skip,
-                                           const Dims& d, int x0, int y0, int z0,
-                                           int sl) {
+// The halo of slice sl straight into LDS (16-byte direct loads, no
+// registers): voxel-major, lds[2 voxel + half], which is the lanes' order, as
+// such a load writes lane after lane.  Planes outside the grid are zeroed.
+// halo_wait, then a barrier, before it is read.
+template <int HX, int HY, int HZ, int NTH, bool UP>
+__device__ __forceinline__ void halo_to_lds_c(uint4* lds, const bf16* __restrict__ in,
+                                              int C, int c0, const Dims& d, int x0,
+                                              int y0, int z0) {
+  constexpr int HV = HX * HY * HZ;
+  constexpr int PER = (2 * HV + NTH - 1) / NTH;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const bool one = d.H >= HY && d.W >= HX;
-  if (CU > 0 && sl * 16 < CU) {
-    if (one)
-      stage_halo_w<HX, HY, HZ, NTH, true, true>(lds, in, CU, sl * 16, d, x0, y0, z0);
-    else
-      stage_halo_w<HX, HY, HZ, NTH, false, true>(lds, in, CU, sl * 16, d, x0, y0, z0);
-    return;
+  const int hh = threadIdx.x & 1;
+  int hx = (int)(threadIdx.x >> 1) % HX, hy = (int)(threadIdx.x >> 1) / HX % HY,
+      hz = (int)(threadIdx.x >> 1) / (HX * HY);
+#pragma unroll
+  for (int m = 0; m < PER; ++m) {
+    const int q = (int)threadIdx.x + m * NTH;
+    if (m > 0) {  // NTH / 2 voxels on
+      constexpr int D = NTH / 2;
+      hx += D % HX;
+      if (hx >= HX) { hx -= HX; ++hy; }
+      hy += D / HX % HY;
+      if (hy >= HY) { hy -= HY; ++hz; }
+      hz += D / (HX * HY);
+    }
+    const int gz = z0 + hz - 1;
+    if (q >= 2 * HV) continue;
+    if (gz >= 0 && gz < d.D) {
+      int gy = y0 + hy - 1, gx = x0 + hx - 1;
+      if (one) {
+        gy = gy < 0 ? gy + d.H : (gy >= d.H ? gy - d.H : gy);
+        gx = gx < 0 ? gx + d.W : (gx >= d.W ? gx - d.W : gx);
+      } else {
+        gy = (gy + d.H) % d.H;
+        gx = (gx + d.W) % d.W;
+      }
+      size_t gv;
+      if constexpr (UP)
+        gv = ((size_t)(gz >> 1) * (d.H >> 1) + (gy >> 1)) * (d.W >> 1) + (gx >> 1);
+      else
+        gv = ((size_t)gz * d.H + gy) * d.W + gx;
+      __builtin_amdgcn_global_load_lds(
+          (const __attribute__((address_space(1))) void*)(in + gv * C + c0 + hh * 8),
+          (__attribute__((address_space(3))) void*)(lds + m * NTH + wave * 64), 16, 0, 0);
+    } else {
+      lds[q] = make_uint4(0, 0, 0, 0);
+    }
   }
-  const bf16* src = CU > 0 ? skip : in;
-  const int C = CU > 0 ? CIN - CU : CIN, c0 = sl * 16 - CU;
-  if (one)
-    stage_halo_w<HX, HY, HZ, NTH, true, false>(lds, src, C, c0, d, x0, y0, z0);
-  else
-    stage_halo_w<HX, HY, HZ, NTH, false, false>(lds, src, C, c0, d, x0, y0, z0);
 }
 
+template <int CIN, int CU, int HX, int HY, int HZ, int NTH>
+__device__ __forceinline__ void halo_to_lds(uint4* lds, const bf16* __restrict__ in,
+                                            const bf16* __restrict__ skip,
+                                            const Dims& d, int x0, int y0, int z0,
+                                            int sl) {
+  if (CU > 0 && sl * 16 < CU)
+    halo_to_lds_c<HX, HY, HZ, NTH, true>(lds, in, CU, sl * 16, d, x0, y0, z0);
+  else if (CU > 0)
+    halo_to_lds_c<HX, HY, HZ, NTH, false>(lds, skip, CIN - CU, sl * 16 - CU, d, x0, y0, z0);
+  else
+    halo_to_lds_c<HX, HY, HZ, NTH, false>(lds, in, CIN, sl * 16, d, x0, y0, z0);
+}
+
+// This wave's direct loads have landed (vmcnt 0).
+__device__ __forceinline__ void halo_wait() { __builtin_amdgcn_s_waitcnt(0x0F70); }
 
 // out = conv(in) for the backward-data shapes of the decoders' concatenations
 // (48, 96 and 192 output channels).  A workgroup owns 48 output channels of a
@@ -284,7 +290,6 @@ __global__ void __launch_bounds__(256, 2) k_conv3w(const bf16* __restrict__ in,
   constexpr int NT = 3, MT = 8, TY = 8, TZ = 4;
   constexpr int HX = 18, HY = TY + 2, HZ = TZ + 2;
   constexpr int HV = HX * HY * HZ;
-  constexpr int KPAD = KP(CIN);
   constexpr int NS = CIN / 16;
   __shared__ uint4 lds[HV * 2];
   __shared__ uint4 lw[14 * NT * 64];
@@ -305,8 +310,8 @@ __global__ void __launch_bounds__(256, 2) k_conv3w(const bf16* __restrict__ in,
       const int tap = 2 * ch + (l >> 5);
       uint4 v = make_uint4(0, 0, 0, 0);
       if (tap < 27)
-        v = ld16(Wk + (size_t)(cg * 48 + nt * 16 + (l & 15)) * KPAD + tap * CIN + sl * 16 +
-                 ((l >> 4) & 1) * 8);
+        v = ld16(Wk + frag_at(cg * NT + nt, NS, sl, tap / 3) + (tap % 3 == 2 ? kFrag : 0) +
+                 (((tap % 3 & 1) * 2 + ((l >> 4) & 1)) * 16 + (l & 15)) * 8);
       lw[e] = v;
     }
   };
@@ -380,7 +385,7 @@ __global__ void __launch_bounds__(256, 2) k_conv3w(const bf16* __restrict__ in,
 // (backward data: the activations the gradient goes to) the stored values are
 // zeroed where it is not positive.  A
 // workgroup owns an output tile of 16 (x) x 4WY x 4WZ voxels and stages its
-// halo per slice of 16 input channels in LDS (two 8-channel planes).  Each wave
+// halo per slice of 16 input channels in LDS (32 bytes a voxel).  Each wave
 // owns one 16-channel tile of C_out and a block of 4 x 4 output rows (y, z)
 // of 16 voxels.  An input row of the halo is one MFMA operand whose K of 32
 // is two x-offsets of the row (x offsets 0 and 1, or 2 and a slot whose
@@ -408,10 +413,10 @@ __global__ void __launch_bounds__(64 * (COUT / 16) * WY * WZ) k_conv3r(
   constexpr int HX = TX + 2, HY = TY + 2, HZ = TZ + 2;
   constexpr int HV = HX * HY * HZ;
   constexpr int NTH = 64 * NTC * WY * WZ;
-  constexpr int KPAD = KP(CIN);
   constexpr int NS = CIN / 16;
   static_assert(CIN % 16 == 0 && COUT % 16 == 0, "channel multiples of 16");
-  __shared__ uint4 lds[HV * 2];
+  constexpr int NB = NS > 1 ? 2 : 1;
+  __shared__ uint4 lds[NB][HV * 2];
   // The wave index is uniform: scalar, so the per-row tests are scalar.
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -425,125 +430,64 @@ __global__ void __launch_bounds__(64 * (COUT / 16) * WY * WZ) k_conv3r(
   const int x0 = tx * TX, y0 = ty * TY, z0 = tz * TZ;
   const int kg = lane >> 4, rl = lane & 15;
   const int half = kg & 1, slot = kg >> 1;
-  const bf16* wrow = Wk + (size_t)(nt * 16 + rl) * KPAD + half * 8;
+  const bf16* wlane = Wk + lane * 8;
   f4 acc[RZ][RY];
 #pragma unroll
   for (int zo = 0; zo < RZ; ++zo)
 #pragma unroll
     for (int yo = 0; yo < RY; ++yo) acc[zo][yo] = f4{0.f, 0.f, 0.f, 0.f};
-  // PF: the next slice's halo loads are issued before the current slice is
-  // computed and stored to LDS once it is done, holding the halo share in
-  // registers through the MFMAs.  That paid where the kernel still fits two
-  // waves per SIMD (32 and 64 output channels) and lost elsewhere.
-  constexpr bool PF = CU == 0 && (COUT == 32 || COUT == 64) && NS > 1;
-  if constexpr (PF) {
-    HaloRegs<HX, HY, HZ, NTH> hr;
-    halo_load(hr, in, CIN, d, x0, y0, z0, 0);
-    halo_store(lds, hr);
-    for (int sl = 0; sl < NS; ++sl) {
-      if (sl + 1 < NS) halo_load(hr, in, CIN, d, x0, y0, z0, sl + 1);
-      // Weight fragments of the slice: tap (oz, oy, ox) with ox = slot in the
-      // first x-pair and ox = 2 (slot 0 only; zero in slot 1) in the second.
-      bf16x8 wa[3][3], wb[3][3];
+  // The next slice's halo goes to the other buffer while this one is
+  // computed.
+  halo_to_lds<CIN, CU, HX, HY, HZ, NTH>(lds[0], in, skip, d, x0, y0, z0, 0);
+  for (int sl = 0; sl < NS; ++sl) {
+    // Weight fragments of the slice: taps ox = slot, and ox = 2 in slot 0
+    // (zero in slot 1).
+    bf16x8 wa[3][3], wb[3][3];
 #pragma unroll
-      for (int oz = 0; oz < 3; ++oz)
+    for (int oz = 0; oz < 3; ++oz)
 #pragma unroll
-        for (int oy = 0; oy < 3; ++oy) {
-          const int t0 = oz * 9 + oy * 3;
-          wa[oz][oy] = load8(wrow + (t0 + slot) * CIN + sl * 16);
-          const bf16x8 w2 = load8(wrow + (t0 + 2) * CIN + sl * 16);
-          wb[oz][oy] = slot == 0 ? w2 : zero8();
-        }
-      __syncthreads();
-      const uint4* lh = lds + half * HV + rl;
-#pragma unroll
-      for (int iz = 0; iz < RZ + 2; ++iz)
-#pragma unroll
-        for (int iy = 0; iy < RY + 2; ++iy) {
-          const int hv = ((wz * RZ + iz) * HY + (wy * RY + iy)) * HX;
-          // Slot 1 of the second pair reads the x + 2 voxel too (its weights
-          // are zero): no divergent load.
-          bf16x8 fa, fb;
-          {
-            const uint4 w0 = lh[hv + slot], w1 = lh[hv + 2];
-            __builtin_memcpy(&fa, &w0, 16);
-            __builtin_memcpy(&fb, &w1, 16);
-          }
-          // The products of one fragment go to distinct accumulators, so the
-          // MFMAs of a pass are independent.
-#pragma unroll
-          for (int oz = 0; oz < 3; ++oz)
-#pragma unroll
-            for (int oy = 0; oy < 3; ++oy) {
-              const int zo = iz - oz, yo = iy - oy;
-              if (zo >= 0 && zo < RZ && yo >= 0 && yo < RY)
-                acc[zo][yo] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wa[oz][oy], fa, acc[zo][yo], 0, 0, 0);
-            }
-#pragma unroll
-          for (int oz = 0; oz < 3; ++oz)
-#pragma unroll
-            for (int oy = 0; oy < 3; ++oy) {
-              const int zo = iz - oz, yo = iy - oy;
-              if (zo >= 0 && zo < RZ && yo >= 0 && yo < RY)
-                acc[zo][yo] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wb[oz][oy], fb, acc[zo][yo], 0, 0, 0);
-            }
-        }
-      if (sl + 1 < NS) {
-        __syncthreads();
-        halo_store(lds, hr);
+      for (int oy = 0; oy < 3; ++oy) {
+        const bf16* w = wlane + frag_at(nt, NS, sl, oz * 3 + oy);
+        wa[oz][oy] = load8(w);
+        wb[oz][oy] = load8(w + kFrag);
       }
-    }
-  } else {
-    for (int sl = 0; sl < NS; ++sl) {
-      stage_halo<CIN, CU, HX, HY, HZ, NTH>(lds, in, skip, d, x0, y0, z0, sl);
-      // Weight fragments of the slice: tap (oz, oy, ox) with ox = slot in the
-      // first x-pair and ox = 2 (slot 0 only; zero in slot 1) in the second.
-      bf16x8 wa[3][3], wb[3][3];
+    halo_wait();
+    __syncthreads();
+    if (sl + 1 < NS)
+      halo_to_lds<CIN, CU, HX, HY, HZ, NTH>(lds[(sl + 1) % NB], in, skip, d, x0, y0, z0, sl + 1);
+    const uint4* lh = lds[sl % NB] + half + 2 * rl;
 #pragma unroll
-      for (int oz = 0; oz < 3; ++oz)
+    for (int iz = 0; iz < RZ + 2; ++iz)
 #pragma unroll
-        for (int oy = 0; oy < 3; ++oy) {
-          const int t0 = oz * 9 + oy * 3;
-          wa[oz][oy] = load8(wrow + (t0 + slot) * CIN + sl * 16);
-          const bf16x8 w2 = load8(wrow + (t0 + 2) * CIN + sl * 16);
-          wb[oz][oy] = slot == 0 ? w2 : zero8();
+      for (int iy = 0; iy < RY + 2; ++iy) {
+        const int hv = ((wz * RZ + iz) * HY + (wy * RY + iy)) * HX;
+        // Slot 1 of the second fragment reads the x + 2 voxel too (its
+        // weights are zero): no divergent load.
+        bf16x8 fa, fb;
+        {
+          const uint4 w0 = lh[2 * (hv + slot)], w1 = lh[2 * (hv + 2)];
+          __builtin_memcpy(&fa, &w0, 16);
+          __builtin_memcpy(&fb, &w1, 16);
         }
-      __syncthreads();
-      const uint4* lh = lds + half * HV + rl;
+        // The products of one fragment go to distinct accumulators, so the
+        // MFMAs of a pass are independent.
 #pragma unroll
-      for (int iz = 0; iz < RZ + 2; ++iz)
+        for (int oz = 0; oz < 3; ++oz)
 #pragma unroll
-        for (int iy = 0; iy < RY + 2; ++iy) {
-          const int hv = ((wz * RZ + iz) * HY + (wy * RY + iy)) * HX;
-          // Slot 1 of the second pair reads the x + 2 voxel too (its weights
-          // are zero): no divergent load.
-          bf16x8 fa, fb;
-          {
-            const uint4 w0 = lh[hv + slot], w1 = lh[hv + 2];
-            __builtin_memcpy(&fa, &w0, 16);
-            __builtin_memcpy(&fb, &w1, 16);
+          for (int oy = 0; oy < 3; ++oy) {
+            const int zo = iz - oz, yo = iy - oy;
+            if (zo >= 0 && zo < RZ && yo >= 0 && yo < RY)
+              acc[zo][yo] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wa[oz][oy], fa, acc[zo][yo], 0, 0, 0);
           }
-          // The products of one fragment go to distinct accumulators, so the
-          // MFMAs of a pass are independent.
 #pragma unroll
-          for (int oz = 0; oz < 3; ++oz)
+        for (int oz = 0; oz < 3; ++oz)
 #pragma unroll
-            for (int oy = 0; oy < 3; ++oy) {
-              const int zo = iz - oz, yo = iy - oy;
-              if (zo >= 0 && zo < RZ && yo >= 0 && yo < RY)
-                acc[zo][yo] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wa[oz][oy], fa, acc[zo][yo], 0, 0, 0);
-            }
-#pragma unroll
-          for (int oz = 0; oz < 3; ++oz)
-#pragma unroll
-            for (int oy = 0; oy < 3; ++oy) {
-              const int zo = iz - oz, yo = iy - oy;
-              if (zo >= 0 && zo < RZ && yo >= 0 && yo < RY)
-                acc[zo][yo] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wb[oz][oy], fb, acc[zo][yo], 0, 0, 0);
-            }
-        }
-      __syncthreads();
-    }
+          for (int oy = 0; oy < 3; ++oy) {
+            const int zo = iz - oz, yo = iy - oy;
+            if (zo >= 0 && zo < RZ && yo >= 0 && yo < RY)
+              acc[zo][yo] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wb[oz][oy], fb, acc[zo][yo], 0, 0, 0);
+          }
+      }
   }
   // Lane: voxel x0 + rl, channels nt * 16 + 4 kg .. +3.
   const int x = x0 + rl;
@@ -591,22 +535,28 @@ __global__ void __launch_bounds__(64 * (COUT / 16) * WY * WZ) k_conv3r(
 // k_conv3r for 16 output channels as a persistent kernel: as many
 // workgroups as the GPU holds at once, each taking a contiguous run of
 // tiles (of one XCD's range, so that neighbouring tiles share its L2), its
-// (tile, slice) items in turn.  The halo loads of the next item are issued
-// before the current item is computed and stored to LDS after it, and with
-// one slice the weight fragments are loaded once per workgroup; a one-shot
-// workgroup otherwise waits on its halo loads with nothing to compute.
-template <int CIN, int CU = 0>
-__global__ void __launch_bounds__(256) k_conv3p(
+// (tile, slice) items in turn; with one slice the weight fragments are
+// loaded once per workgroup.
+//
+// Bound: the matrix products (a quarter with zero weights) take 216 of the
+// 476 us of 48 -> 16 at 128x128x512 at the clock they run at; the rest is the
+// loads a workgroup waits for that its neighbour does not cover.  The halo
+// goes straight to LDS, so the registers (242 a lane) let two workgroups
+// share a compute unit; held in registers beside the products (351 a lane,
+// one workgroup) it took 840 us, of which the loads and LDS stores were 430
+// (16 -> 16: 231 -> 166).  The mask of the backward form costs 55 us in its
+// epilogue, as a pass of its own 126.
+template <int CIN, int CU = 0, bool MASK = false>
+__global__ void __launch_bounds__(256, 2) k_conv3p(
     const bf16* __restrict__ in, const bf16* __restrict__ skip,
     const bf16* __restrict__ Wk, const float* __restrict__ bias,
-    bf16* __restrict__ out, Dims d, int relu) {
+    bf16* __restrict__ out, Dims d, int relu, const bf16* __restrict__ mask) {
   static_assert(CU % 16 == 0 && CU < CIN && CIN % 16 == 0, "channel slices");
   constexpr int RY = 4, RZ = 4, WY = 2;
   constexpr int TX = 16, TY = 8, TZ = 8;
   constexpr int HX = TX + 2, HY = TY + 2, HZ = TZ + 2;
   constexpr int HV = HX * HY * HZ;
   constexpr int NTH = 256;
-  constexpr int KPAD = KP(CIN);
   constexpr int NS = CIN / 16;
   __shared__ uint4 lds[HV * 2];
   const int lane = threadIdx.x & 63;
@@ -621,7 +571,7 @@ __global__ void __launch_bounds__(256) k_conv3p(
   const int nitems = (hi - lo) * NS;
   const int kg = lane >> 4, rl = lane & 15;
   const int half = kg & 1, slot = kg >> 1;
-  const bf16* wrow = Wk + (size_t)rl * KPAD + half * 8;
+  const bf16* wlane = Wk + lane * 8;
   const int c0 = 4 * kg;
   float bv[4];
 #pragma unroll
@@ -642,38 +592,31 @@ __global__ void __launch_bounds__(256) k_conv3p(
     for (int oz = 0; oz < 3; ++oz)
 #pragma unroll
       for (int oy = 0; oy < 3; ++oy) {
-        const int t0 = oz * 9 + oy * 3;
-        wa[oz][oy] = load8(wrow + (t0 + slot) * CIN + sl * 16);
-        const bf16x8 w2 = load8(wrow + (t0 + 2) * CIN + sl * 16);
-        wb[oz][oy] = slot == 0 ? w2 : zero8();
+        const bf16* w = wlane + frag_at(0, NS, sl, oz * 3 + oy);
+        wa[oz][oy] = load8(w);
+        wb[oz][oy] = load8(w + kFrag);
       }
   };
   if (NS == 1) load_w(0);
-  HaloRegs<HX, HY, HZ, NTH> hr;
-  {
-    int x0, y0, z0;
-    origin(lo, x0, y0, z0);
-    halo_load_cat<CIN, CU>(hr, in, skip, d, x0, y0, z0, 0);
-    halo_store(lds, hr);
-  }
   for (int j = 0; j < nitems; ++j) {
     const int t = lo + j / NS, sl = j % NS;
-    if (j + 1 < nitems) {
+    {
       int x0, y0, z0;
-      origin(lo + (j + 1) / NS, x0, y0, z0);
-      halo_load_cat<CIN, CU>(hr, in, skip, d, x0, y0, z0, (j + 1) % NS);
+      origin(t, x0, y0, z0);
+      halo_to_lds<CIN, CU, HX, HY, HZ, NTH>(lds, in, skip, d, x0, y0, z0, sl);
     }
     if (NS > 1) load_w(sl);
+    halo_wait();
     __syncthreads();
-    const uint4* lh = lds + half * HV + rl + (wz * RZ * HY + wy * RY) * HX;
+    const uint4* lh = lds + half + 2 * (rl + (wz * RZ * HY + wy * RY) * HX);
     // The input rows in a ring of three, each read two rows ahead of its
     // MFMAs so that the LDS latency is covered.
     constexpr int NP = (RZ + 2) * (RY + 2);
     uint4 ring[3][2];
     auto fetch = [&](int p, uint4 (&r)[2]) {
       const int hv = ((p / (RY + 2)) * HY + p % (RY + 2)) * HX;
-      r[0] = lh[hv + slot];
-      r[1] = lh[hv + 2];
+      r[0] = lh[2 * (hv + slot)];
+      r[1] = lh[2 * (hv + 2)];
     };
     fetch(0, ring[0]);
     fetch(1, ring[1]);
@@ -707,6 +650,18 @@ __global__ void __launch_bounds__(256) k_conv3p(
       int x0, y0, z0;
       origin(t, x0, y0, z0);
       const int x = x0 + rl;
+      // The mask words of all rows in flight before the first is needed.
+      uint2 mw[RZ][RY];
+      if constexpr (MASK)
+#pragma unroll
+        for (int zo = 0; zo < RZ; ++zo)
+#pragma unroll
+          for (int yo = 0; yo < RY; ++yo) {
+            const int gx = min(x, d.W - 1), gy = min(y0 + wy * RY + yo, d.H - 1),
+                      gz = min(z0 + wz * RZ + zo, d.D - 1);
+            mw[zo][yo] = *reinterpret_cast<const uint2*>(
+                mask + (((size_t)gz * d.H + gy) * d.W + gx) * 16 + c0);
+          }
 #pragma unroll
       for (int zo = 0; zo < RZ; ++zo)
 #pragma unroll
@@ -722,15 +677,16 @@ __global__ void __launch_bounds__(256) k_conv3p(
             uint2 w;
             w.x = f2bf2(v[0], v[1]);
             w.y = f2bf2(v[2], v[3]);
+            if constexpr (MASK) {
+              w.x = relu_mask2(w.x, mw[zo][yo].x);
+              w.y = relu_mask2(w.y, mw[zo][yo].y);
+            }
             *reinterpret_cast<uint2*>(out + (((size_t)gz * d.H + gy) * d.W + x) * 16 + c0) = w;
           }
           acc[zo][yo] = f4{0.f, 0.f, 0.f, 0.f};
         }
     }
-    if (j + 1 < nitems) {
-      __syncthreads();
-      halo_store(lds, hr);
-    }
+    __syncthreads();
   }
 }
 
@@ -1114,15 +1070,6 @@ __global__ void __launch_bounds__(256, 2) k_wgrad_first(const float* __restrict_
     }
 }
 
-// g = 0 where y is not positive, 8 values a thread.
-__global__ void k_relu_bwd(bf16* __restrict__ g, const bf16* __restrict__ y, long long n) {
-  const unsigned t = blockIdx.x * blockDim.x + threadIdx.x;
-  if ((unsigned long long)t * 8 >= (unsigned long long)n) return;
-  const uint4 gv = ld16(g + (size_t)t * 8), yv = ld16(y + (size_t)t * 8);
-  st16(g + (size_t)t * 8, make_uint4(relu_mask2(gv.x, yv.x), relu_mask2(gv.y, yv.y),
-                                     relu_mask2(gv.z, yv.z), relu_mask2(gv.w, yv.w)));
-}
-
 // Average pooling 2^3 (out dims d = input dims / 2), 8 channels a thread.
 __global__ void k_pool(const bf16* __restrict__ in, bf16* __restrict__ out,
                        Dims d, int C) {
@@ -1377,20 +1324,30 @@ __global__ void k_adam(float* __restrict__ p, float* __restrict__ m,
   p[i] = p[i] - lr * (mi / c1) / (sqrtf(vi / c2) + eps);
 }
 
-// BF16 copies of a layer's weights: forward Wk[co][k = tap*ci_n + ci] and
-// backward-data Wd[ci][k' = tap'*co_n + co] = W[co][26 - tap'][ci].
+// BF16 fragments (see kFrag) of a layer's weights W[co][tap][ci]: forward Wk
+// of its co output channels, backward-data Wd, whose output channels are ci
+// and whose taps are mirrored.
 __global__ void k_pack_w(const float* __restrict__ W, int ci_n, int co_n,
-                         bf16* __restrict__ Wk, int kpf, bf16* __restrict__ Wd,
-                         int kpd) {
+                         bf16* __restrict__ Wk, bf16* __restrict__ Wd) {
   const long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x;
-  const long long n = (long long)co_n * 27 * ci_n;
-  if (i >= n) return;
-  const int co = (int)(i / (27 * ci_n));
-  const int r = (int)(i % (27 * ci_n));
-  const int tap = r / ci_n, ci = r % ci_n;
-  const bf16 h = f2bf(W[i]);
-  Wk[(long long)co * kpf + tap * ci_n + ci] = h;
-  if (Wd) Wd[(long long)ci * kpd + (26 - tap) * co_n + co] = h;
+  const long long n = wpack(co_n, ci_n);
+  if (i >= 2 * n) return;
+  const bool back = i >= n;
+  const int out_n = back ? ci_n : co_n, in_n = back ? co_n : ci_n;
+  long long q = back ? i - n : i;
+  bf16* dst = (back ? Wd : Wk) + q;
+  const int e = (int)(q % 8), lane = (int)(q / 8 % 64), second = (int)(q / kFrag % 2);
+  q /= 2 * kFrag;
+  const int row = (int)(q % 9), sl = (int)(q / 9 % (in_n / 16)), tile = (int)(q / 9 / (in_n / 16));
+  const int kg = lane / 16, slot = kg / 2;
+  const int o = tile * 16 + lane % 16, c = sl * 16 + (kg & 1) * 8 + e;
+  const int tap = row * 3 + (second ? 2 : slot);
+  if (second && slot) {
+    *dst = 0;
+    return;
+  }
+  *dst = f2bf(back ? W[((long long)c * 27 + 26 - tap) * ci_n + o]
+                   : W[((long long)o * 27 + tap) * ci_n + c]);
 }
 
 __global__ void k_f32_to_f64(const float* __restrict__ a, double* __restrict__ b,
@@ -1429,8 +1386,6 @@ long long param_count() {
 
 // Workgroups (and partial sums) of the loss.
 constexpr int kLossParts = 2048;
-
-constexpr int kpad(int cin) { return (27 * cin + 63) / 64 * 64; }
 
 }  // namespace
 
@@ -1488,8 +1443,8 @@ size_t unet_carve(pic_unet* u, char* base) {
     off += (long long)kLayers[l].co * 27 * kLayers[l].ci;
     u->boff[l] = off;
     off += kLayers[l].co;
-    u->wk[l] = cv.take<bf16>((long long)kLayers[l].co * kpad(kLayers[l].ci));
-    u->wd[l] = cv.take<bf16>((long long)kLayers[l].ci * kpad(kLayers[l].co));
+    u->wk[l] = cv.take<bf16>(pic::wpack(kLayers[l].co, kLayers[l].ci));
+    u->wd[l] = cv.take<bf16>(pic::wpack(kLayers[l].ci, kLayers[l].co));
   }
   u->hoff = off;
   u->x_in = cv.take<float>(2 * V0);
@@ -1523,14 +1478,14 @@ Dims dims_at(const pic_unet* u, int D, int H, int W, int level) {
 }
 
 // Workgroups of k_conv3p<CIN, CU> the current device holds at once.
-template <int CIN, int CU>
+template <int CIN, int CU, bool MASK>
 unsigned conv3p_slots() {
   static unsigned cached[64] = {};
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) dev = 0;
   if (!cached[dev]) {
     int per_cu = 0, cus = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, pic::k_conv3p<CIN, CU>, 256, 0) !=
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, pic::k_conv3p<CIN, CU, MASK>, 256, 0) !=
             hipSuccess || per_cu < 1)
       per_cu = 1;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
@@ -1541,25 +1496,22 @@ unsigned conv3p_slots() {
   return cached[dev];
 }
 
-template <int CIN, int CU>
+template <int CIN, int CU, bool MASK>
 void conv3p_launch(hipStream_t st, const bf16* in, const bf16* skip, const bf16* Wk,
-                   const float* b, bf16* out, Dims d, int relu) {
+                   const float* b, bf16* out, Dims d, int relu, const bf16* mask) {
   const long long ntiles = (long long)((d.W + 15) / 16) * ((d.H + 7) / 8) * ((d.D + 7) / 8);
-  const unsigned slots = conv3p_slots<CIN, CU>();
+  const unsigned slots = conv3p_slots<CIN, CU, MASK>();
   const unsigned grid = ntiles < (long long)slots ? (unsigned)ntiles : slots;
-  pic::k_conv3p<CIN, CU><<<grid, 256, 0, st>>>(in, skip, Wk, b, out, d, relu);
+  pic::k_conv3p<CIN, CU, MASK><<<grid, 256, 0, st>>>(in, skip, Wk, b, out, d, relu, mask);
 }
 
 // The register-blocked k_conv3r for 32 to 128 output channels, its persistent
-// form k_conv3p for 16; there the mask is a pass of its own (two of 157 us a
-// gradient at 128x128x512: in the epilogue of the persistent kernel, whose
-// registers hold no prefetch of it, it cost 240 us each).
+// form k_conv3p for 16.
 template <int CIN, int COUT, bool MASK>
 void conv_launch(hipStream_t st, const bf16* in, const bf16* Wk, const float* b,
                  bf16* out, Dims d, int relu, const bf16* mask) {
   if constexpr (COUT == 16) {
-    conv3p_launch<CIN, 0>(st, in, nullptr, Wk, b, out, d, relu);
-    if (MASK) pic::k_relu_bwd<<<nb(d.V * 2), 256, 0, st>>>(out, mask, d.V * 16);
+    conv3p_launch<CIN, 0, MASK>(st, in, nullptr, Wk, b, out, d, relu, mask);
   } else {
     constexpr int WY = 1, WZ = COUT >= 64 ? 1 : 2;
     constexpr int TY = 4 * WY, TZ = 4 * WZ;
@@ -1616,15 +1568,15 @@ template <int CIN, int COUT, int CU>
 void conv_upcat_launch(hipStream_t st, const bf16* coarse, const bf16* skip,
                        const bf16* Wk, const float* b, bf16* out, Dims d) {
   if constexpr (COUT == 16) {
-    conv3p_launch<CIN, CU>(st, coarse, skip, Wk, b, out, d, 1);
-    return;
+    conv3p_launch<CIN, CU, false>(st, coarse, skip, Wk, b, out, d, 1, nullptr);
+  } else {
+    constexpr int WY = 1, WZ = COUT == 64 ? 1 : 2;
+    constexpr int TY = 4 * WY, TZ = 4 * WZ;
+    const long long nbk = (long long)((d.W + 15) / 16) * ((d.H + TY - 1) / TY) *
+                          ((d.D + TZ - 1) / TZ);
+    pic::k_conv3r<CIN, COUT, WY, WZ, CU><<<(unsigned)nbk, 64 * (COUT / 16) * WY * WZ, 0, st>>>(
+        coarse, skip, Wk, b, out, d, 1, nullptr);
   }
-  constexpr int WY = COUT == 16 ? 2 : 1, WZ = COUT == 64 ? 1 : 2;
-  constexpr int TY = 4 * WY, TZ = 4 * WZ;
-  const long long nbk = (long long)((d.W + 15) / 16) * ((d.H + TY - 1) / TY) *
-                        ((d.D + TZ - 1) / TZ);
-  pic::k_conv3r<CIN, COUT, WY, WZ, CU><<<(unsigned)nbk, 64 * (COUT / 16) * WY * WZ, 0, st>>>(
-      coarse, skip, Wk, b, out, d, 1, nullptr);
 }
 
 // One round of resident workgroups over all (co, ci) pairs, at least two tiles
@@ -1666,9 +1618,8 @@ void pack_weights(pic_unet* u) {
   for (int l = 0; l < kNL; ++l) {
     const LayerSpec& s = kLayers[l];
     if (l == E0A) continue;  // FP32 first layer
-    pic::k_pack_w<<<nb((long long)s.co * 27 * s.ci), 256, 0, u->stream>>>(
-        u->p + u->woff[l], s.ci, s.co, u->wk[l], kpad(s.ci), u->wd[l],
-        kpad(s.co));
+    pic::k_pack_w<<<nb(2 * pic::wpack(s.co, s.ci)), 256, 0, u->stream>>>(
+        u->p + u->woff[l], s.ci, s.co, u->wk[l], u->wd[l]);
   }
 }
 
