@@ -422,7 +422,9 @@ __device__ __forceinline__ double ipow(double b, int e) {
 // neighbour twice).  With the Neumann face on top the planes run downwards.
 // A thread runs SEG planes of one system in registers; the segments' ends are
 // joined through LDS.  No pivots are stored or divided: the pass reads and
-// writes the spectrum once.
+// writes the spectrum once.  At 512 planes of 128 x 128: 84 us with the rows'
+// addresses kept from the loads to the stores and each join a pass over the
+// registers (102 of them spilled), 38 us now; 1024 of 256 x 256 565 -> 254.
 template <int SEG>
 __global__ void __launch_bounds__(SEG > 32 ? 512 : 1024) k_sp_tri(SpGrid G, double* __restrict__ s,
                                                                   int lgc, const Counters* dc) {
@@ -450,13 +452,19 @@ __global__ void __launch_bounds__(SEG > 32 ? 512 : 1024) k_sp_tri(SpGrid G, doub
   const bool rev = G.bc_hi == PIC_BC_NEUMANN;
   const bool neu = rev || G.bc_lo == PIC_BC_NEUMANN;
   const int np = G.np, p0 = sg * SEG;
-  double* base = s + cc;
+  const int nv = np - p0;                      // planes of this and later segments
+  const long long step = rev ? -G.nxy : G.nxy;
+  double* base = s + cc + (rev ? (long long)(np - 1) * G.nxy : 0) + p0 * step;
   double b[SEG];
+  {
+    const double* r = base;
 #pragma unroll
-  for (int q = 0; q < SEG; ++q) {
-    const int p = p0 + q;
-    const int pc = p < np ? (rev ? np - 1 - p : p) : 0;
-    b[q] = base[(long long)pc * G.nxy];
+    for (int q = 0; q < SEG; ++q) {
+      b[q] = *r;                               // (past the end: the last plane)
+      r += q + 1 < nv ? step : 0;
+      // (Eight addresses at a time: all of them beside the loads spill.)
+      if (q % 8 == 7) __builtin_amdgcn_sched_barrier(0);
+    }
   }
   const double sx = sinpi((double)kx / G.nx), sy = sinpi((double)ky / G.ny);
   const double qq = sx * sx + sy * sy;  // (d - 2) / 4
@@ -467,7 +475,7 @@ __global__ void __launch_bounds__(SEG > 32 ? 512 : 1024) k_sp_tri(SpGrid G, doub
   double y = 0.0;
 #pragma unroll
   for (int q = 0; q < SEG; ++q) {
-    y = p0 + q < np ? l * (b[q] + y) : 0.0;
+    y = q < nv ? l * (b[q] + y) : 0.0;
     b[q] = y;
   }
   jz[threadIdx.x] = y;
@@ -479,7 +487,7 @@ __global__ void __launch_bounds__(SEG > 32 ? 512 : 1024) k_sp_tri(SpGrid G, doub
   double w = l * y;
 #pragma unroll
   for (int q = 0; q < SEG; ++q) {
-    if (p0 + q < np) b[q] += w;
+    if (q < nv) b[q] += w;
     w *= l;
   }
   double x = 0.0;
@@ -492,16 +500,15 @@ __global__ void __launch_bounds__(SEG > 32 ? 512 : 1024) k_sp_tri(SpGrid G, doub
   __syncthreads();
   x = 0.0;
   for (int q = nsg - 1; q > sg; --q) x = fma(lseg, x, jz[(q << lgc) + c]);
+  // The join adds w l^(SEG-1-q) to this segment's x'; for the face's
+  // coefficient the first two planes take it now, the others with the
+  // second exponential, whose powers are the same.
   w = l * x;
-#pragma unroll
-  for (int q = SEG - 1; q >= 0; --q) {
-    b[q] += w;
-    w *= l;
-  }
   __syncthreads();
   if (sg == 0) {
-    jz[c] = b[0];
-    jz[cols + c] = b[1];
+    const double w1 = w * ipow(l, SEG - 2);
+    jz[c] = fma(w1, l, b[0]);
+    jz[cols + c] = b[1] + w1;
   }
   __syncthreads();
   const double x0 = jz[c], x1 = jz[cols + c];
@@ -516,32 +523,42 @@ __global__ void __launch_bounds__(SEG > 32 ? 512 : 1024) k_sp_tri(SpGrid G, doub
     cf = (l * x0 - (np > 1 ? x1 : 0.0)) / dh;
   }
   cf *= den;
-  double ea = ipow(l, p0 + 1);
-  const int pe = p0 + SEG < np ? p0 + SEG : np;  // one past the last plane
-  // The second exponential runs down from the segment's last plane.
-  double eb = ipow(l, 2 * np + 2 - pe > 0 ? 2 * np + 2 - pe : 0);
   if (flat) {
-#pragma unroll
-    for (int q = 0; q < SEG; ++q) b[q] -= cf * (double)(np - (p0 + q));
-  } else {
+    // (l = 1: the join is w everywhere, the h_p are linear.)
+    double h = cf * (double)(np - p0);
 #pragma unroll
     for (int q = 0; q < SEG; ++q) {
-      b[q] = fma(-cf, ea, b[q]);
+      b[q] += w - h;
+      h -= cf;
+    }
+  } else {
+    double ea = -cf * ipow(l, p0 + 1);
+#pragma unroll
+    for (int q = 0; q < SEG; ++q) {
+      b[q] += ea;
       ea *= l;
     }
+    // Down from the segment's last plane (the last segment's w is zero).
+    const int pe = nv < SEG ? np : p0 + SEG;  // one past it
+    w = fma(cf, ipow(l, 2 * np + 2 - pe), w);
 #pragma unroll
     for (int q = SEG - 1; q >= 0; --q) {
-      if (p0 + q < pe) {
-        b[q] = fma(cf, eb, b[q]);
-        eb *= l;
+      if (q < nv) {
+        b[q] += w;
+        w *= l;
       }
     }
   }
   if (ok) {
+    // The rows' addresses anew: kept from the loads they spill.
+    int z = 0;
+    asm volatile("" : "+v"(z));
+    double* o = base + z;
 #pragma unroll
     for (int q = 0; q < SEG; ++q) {
-      const int p = p0 + q;
-      if (p < np) base[(long long)(rev ? np - 1 - p : p) * G.nxy] = b[q];
+      if (q < nv) *o = b[q];
+      o += step;
+      if (q % 8 == 7) __builtin_amdgcn_sched_barrier(0);
     }
   }
 }
