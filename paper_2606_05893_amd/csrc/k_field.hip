@@ -211,10 +211,15 @@ __global__ void k_final(const double* __restrict__ part,
 // side of the correction solve, and with ef != nullptr zeroes the FP32
 // correction (the start of the next correction solve, unless its first
 // smoothing pass starts from zero by itself).
+//
+// RHO: f is the caller's density, from which the right-hand side is formed as
+// k_rhs forms it.
+template <bool RHO = false>
 __global__ void k_residual(const double* __restrict__ u,
                            const double* __restrict__ f, LevelC L,
                            double* __restrict__ part, const Counters* dc,
-                           float* __restrict__ rf, float* __restrict__ ef) {
+                           float* __restrict__ rf, float* __restrict__ ef,
+                           SpRhs R = SpRhs{}) {
   __shared__ double sb[kThreads];
   if (dc->done) return;
   // Work item: an x-pair (i0, i0 + 1) of one row over a segment of the
@@ -255,7 +260,11 @@ __global__ void k_residual(const double* __restrict__ u,
       const double2 up = pair(k < L.nz ? k + 1 : k, r0);
       const double2 ym = pair(k, rm), yp = pair(k, rp);
       const double xl = u[base + r0 + im], xr = u[base + r0 + ip];
-      const double2 fv = *reinterpret_cast<const double2*>(f + base + r0 + i0);
+      double2 fv = *reinterpret_cast<const double2*>(f + base + r0 + i0);
+      if (RHO) {
+        fv.x = sp_rhs(R, k, L.nz, fv.x);
+        fv.y = sp_rhs(R, k, L.nz, fv.y);
+      }
       double z0, z1;
       if (k == 0) {
         z0 = 2.0 * up.x;
@@ -2197,6 +2206,31 @@ static void fill_solve_info(pic_ctx* c, bool used_net, pic_solve_info* info,
   if (!info->converged) *status = PIC_ERR_NOCONV;
 }
 
+// Direct solve of A u = b(rho) for a caller's density and start u0 (null:
+// zero), with no right-hand side or start of the context's own: the transform
+// forms b and its norm, the correction writes u and, unless null, out.  u may
+// be u0; rho is read until the end, so neither u nor out may overlap it.
+void field_solve_rho(pic_ctx* c, const double* rho, const double* u0, double* u,
+                     double* out, pic_solve_info* info, int* status) {
+  LevelC Lc = level_c(c, 0);
+  const SpRhs R = sp_rhs_of(c);
+  *status = PIC_OK;
+  int launched = 0;
+  while (true) {
+    spectral_solve_rho(c, R, rho, launched ? u : u0, u, out, launched == 0);
+    ++launched;
+    k_residual<true><<<kRedBlocks, kThreads, 0, c->stream>>>(u, rho, Lc, c->partials, c->dc,
+                                                             nullptr, nullptr, R);
+    k_final<<<1, 1024, 0, c->stream>>>(c->partials, c->qpartials, kRedBlocks, c->dc,
+                                       c->mixed ? 4 : 1, c->cfg.rel_tol, 1);
+    read_solve_counters(c);
+    if (c->hc.done || launched >= c->cfg.max_vcycles) break;
+  }
+  const int keep = c->last_vcycles;
+  fill_solve_info(c, false, info, status);
+  c->last_vcycles = keep;
+}
+
 // Solve A phi = b on level 0 (phi holds the warm start, or zero), directly or
 // by V-cycles.  One
 // synchronisation per batch of V-cycles; the batch size follows the last
@@ -2226,7 +2260,7 @@ void field_solve(pic_ctx* c, bool warm, bool direct, pic_solve_info* info,
     double vref = 1.0;
     if (c->cfg.bc_lo == PIC_BC_DIRICHLET && fabs(c->cfg.v_lo) > vref) vref = fabs(c->cfg.v_lo);
     if (c->cfg.bc_hi == PIC_BC_DIRICHLET && fabs(c->cfg.v_hi) > vref) vref = fabs(c->cfg.v_hi);
-    k_residual<<<kRedBlocks, kThreads, 0, st>>>(L0.u, L0.f, Lc, c->partials,
+    k_residual<><<<kRedBlocks, kThreads, 0, st>>>(L0.u, L0.f, Lc, c->partials,
                                                 c->dc, nullptr, nullptr);
     k_warm_final<<<1, 1024, 0, st>>>(c->partials, kRedBlocks, c->dc, 0,
                                      (double)nu);
@@ -2240,7 +2274,7 @@ void field_solve(pic_ctx* c, bool warm, bool direct, pic_solve_info* info,
       used_net = true;
       k_warm_apply<<<kRedBlocks, kThreads, 0, st>>>(L0.u, c->warm_prev, out,
                                                     Lc, c->dc);
-      k_residual<<<kRedBlocks, kThreads, 0, st>>>(L0.u, L0.f, Lc, c->partials,
+      k_residual<><<<kRedBlocks, kThreads, 0, st>>>(L0.u, L0.f, Lc, c->partials,
                                                   c->dc, nullptr, nullptr);
       k_warm_final<<<1, 1024, 0, st>>>(c->partials, kRedBlocks, c->dc, 1,
                                        (double)nu);
@@ -2262,7 +2296,7 @@ void field_solve(pic_ctx* c, bool warm, bool direct, pic_solve_info* info,
         k_final<<<1, 1024, 0, st>>>(c->partials, c->qpartials, nw, c->dc, 2, c->cfg.rel_tol);
       spectral_correct(c);
       ++launched;
-      k_residual<<<kRedBlocks, kThreads, 0, st>>>(L0.u, L0.f, Lc, c->partials, c->dc, nullptr,
+      k_residual<><<<kRedBlocks, kThreads, 0, st>>>(L0.u, L0.f, Lc, c->partials, c->dc, nullptr,
                                                   nullptr);
       k_final<<<1, 1024, 0, st>>>(c->partials, c->qpartials, kRedBlocks, c->dc,
                                   c->mixed ? 4 : 1, c->cfg.rel_tol, 1);
@@ -2277,7 +2311,7 @@ void field_solve(pic_ctx* c, bool warm, bool direct, pic_solve_info* info,
     return;
   }
   // Initial check of the warm start.
-  k_residual<<<kRedBlocks, kThreads, 0, st>>>(L0.u, L0.f, Lc, c->partials,
+  k_residual<><<<kRedBlocks, kThreads, 0, st>>>(L0.u, L0.f, Lc, c->partials,
                                               c->dc, rf, ef);
   k_final<<<1, 1024, 0, st>>>(c->partials, c->qpartials, kRedBlocks, c->dc, 2,
                               c->cfg.rel_tol);
@@ -2307,7 +2341,7 @@ void field_solve(pic_ctx* c, bool warm, bool direct, pic_solve_info* info,
         }
         if (!mixed_fused)
           k_correct<<<nblocks(nu), kThreads, 0, st>>>(L0.u, L0.uf, Lc, c->dc);
-        k_residual<<<kRedBlocks, kThreads, 0, st>>>(L0.u, L0.f, Lc, c->partials,
+        k_residual<><<<kRedBlocks, kThreads, 0, st>>>(L0.u, L0.f, Lc, c->partials,
                                                     c->dc, rf, ef);
         k_final<<<1, 1024, 0, st>>>(c->partials, c->qpartials, kRedBlocks,
                                     c->dc, 4, c->cfg.rel_tol, n_in);
@@ -2316,14 +2350,14 @@ void field_solve(pic_ctx* c, bool warm, bool direct, pic_solve_info* info,
       vcycle<double>(c, 0);
       ++pending;
       if (launched++ < unchecked) continue;
-      k_residual<<<kRedBlocks, kThreads, 0, st>>>(L0.u, L0.f, Lc, c->partials,
+      k_residual<><<<kRedBlocks, kThreads, 0, st>>>(L0.u, L0.f, Lc, c->partials,
                                                   c->dc, rf, ef);
       k_final<<<1, 1024, 0, st>>>(c->partials, c->qpartials, kRedBlocks,
                                   c->dc, 1, c->cfg.rel_tol, pending);
       pending = 0;
     }
     if (pending) {  // the cycle limit ended the batch before its check
-      k_residual<<<kRedBlocks, kThreads, 0, st>>>(L0.u, L0.f, Lc, c->partials,
+      k_residual<><<<kRedBlocks, kThreads, 0, st>>>(L0.u, L0.f, Lc, c->partials,
                                                   c->dc, rf, ef);
       k_final<<<1, 1024, 0, st>>>(c->partials, c->qpartials, kRedBlocks,
                                   c->dc, 1, c->cfg.rel_tol, pending);

@@ -16,13 +16,14 @@
 // and both lines' (real) modes for ky = 0 and ny/2.  Every real number of the
 // plane is then its own tridiagonal system in z.
 //
-// Bound: the passes move 9 doubles a node (start and right-hand side read,
-// spectrum written; four times read and written; start read, phi written).
-// 128x128x512 nodes in FP64, one solve with its residual check: 910 us as four
-// V-cycles, 325 us here (x 54 and 53, y 35 each way, z 80, check 32);
-// poisson_solve 1270 -> 420 us, on 256x256x1024 in the mixed form 8.8 -> 3.1
-// ms, on the ragged 40x20x36 385 -> 111 us.  The potential is 1e-14 from the
-// exact one where the V-cycles stop at 1e-12.
+// Bound: the passes move 12 doubles a node (start and right-hand side or
+// density read, spectrum written; four times read and written between the
+// transforms; start read, phi written; the check's two reads).  128x128x512
+// nodes in FP64, one solve with its residual check: 910 us as four V-cycles,
+// 260 us here (x 52 and 42, y 35 each way, z 38, check 32); poisson_solve
+// 1269 -> 286 us, on 256x256x1024 in the mixed form 8.8 -> 2.3 ms, on the
+// ragged 40x20x36 382 -> 93 us.  The potential is 1e-14 from the exact one
+// where the V-cycles stop at 1e-12.
 #include <algorithm>
 
 #include "pic_ctx.h"
@@ -47,6 +48,16 @@ struct SpGrid {
   int nx, ny, nz, k0, np, bc_lo, bc_hi;
   long long nxy;
 };
+
+// Start of the solve at a node of plane k: the face value of a Dirichlet
+// plane, else the caller's potential or zero.
+__device__ __forceinline__ double sp_start(const SpGrid& G, const SpRhs& R,
+                                           const double* __restrict__ u0, int k,
+                                           long long idx) {
+  if (k == 0 && G.bc_lo == PIC_BC_DIRICHLET) return R.v_lo;
+  if (k == G.nz && G.bc_hi == PIC_BC_DIRICHLET) return R.v_hi;
+  return u0 ? u0[idx] : 0.0;
+}
 
 FftPlan make_plan(int n) {
   FftPlan p;
@@ -225,10 +236,13 @@ __device__ __forceinline__ void fill_tw(double2* tw, int n) {
 
 // x forward: the residual of two neighbouring rows as one complex line.
 // Contiguous ranges of lines go to one XCD, so the three planes a residual
-// reads stay in its L2.
+// reads stay in its L2.  RHO: f is the caller's density and u its start (null:
+// zero), see field_solve_rho; part then also takes the partials of ||b||^2,
+// after those of the residual.
+template <bool RHO>
 __global__ void __launch_bounds__(kSpThreads) k_sp_xfwd(
     SpGrid G, const double* __restrict__ u, const double* __restrict__ f, double* __restrict__ s,
-    FftPlan P, int nlines, int lpw, int stride, double* __restrict__ part) {
+    FftPlan P, int nlines, int lpw, int stride, double* __restrict__ part, SpRhs R) {
   extern __shared__ double2 sm[];
   double2* tw = sm;
   double2* buf = sm + P.n;
@@ -237,7 +251,7 @@ __global__ void __launch_bounds__(kSpThreads) k_sp_xfwd(
   const int line0 = wg * lpw;
   const int lines = nlines - line0 < lpw ? nlines - line0 : lpw;
   const float rnx = 1.0f / (float)nx;
-  double s2 = 0.0;
+  double s2 = 0.0, sb = 0.0;
 #pragma unroll
   for (int b = 0; b < kSpElems; ++b) {
     const int e = threadIdx.x + b * blockDim.x;
@@ -247,19 +261,42 @@ __global__ void __launch_bounds__(kSpThreads) k_sp_xfwd(
       const int p = gl / nyp, j = 2 * (gl - p * nyp), k = G.k0 + p;
       const int im = i ? i - 1 : nx - 1, ip = i + 1 < nx ? i + 1 : 0;
       const int jm = j ? j - 1 : G.ny - 1, jp = j + 2 < G.ny ? j + 2 : 0;
-      const double* pl = u + (long long)k * G.nxy;
-      const double* ra = pl + j * nx;
-      const double* rb = ra + nx;
-      const double ca = ra[i], cb = rb[i];
       const long long za = (long long)j * nx + i;
-      const double* dn = u + (long long)(k > 0 ? k - 1 : 1) * G.nxy + za;
-      const double* up = u + (long long)(k < G.nz ? k + 1 : G.nz - 1) * G.nxy + za;
-      const double* fr = f + (long long)k * G.nxy + za;
+      const long long at = (long long)k * G.nxy + za;
+      const int kd = k > 0 ? k - 1 : 1, ku = k < G.nz ? k + 1 : G.nz - 1;
+      const long long ad = (long long)kd * G.nxy + za, au = (long long)ku * G.nxy + za;
+      double fa = f[at], fb = f[at + nx];
+      // The nodes (a: row j, b: row j + 1), their x and outer y neighbours,
+      // and the planes below and above.
+      double ca = 0.0, cb = 0.0, xa = 0.0, xb = 0.0, ym = 0.0, yp = 0.0;
+      double da, db, ua, ub;
+      if (!RHO || u) {
+        const double* pl = u + (long long)k * G.nxy;
+        const double* ra = pl + j * nx;
+        const double* rb = ra + nx;
+        ca = ra[i]; cb = rb[i];
+        xa = ra[im] + ra[ip]; xb = rb[im] + rb[ip];
+        ym = pl[jm * nx + i]; yp = pl[jp * nx + i];
+      }
+      if (RHO) {
+        fa = sp_rhs(R, k, G.nz, fa);
+        fb = sp_rhs(R, k, G.nz, fb);
+        // ||b|| of the system with the Dirichlet data on its right.
+        const double lo = k == 1 && G.bc_lo == PIC_BC_DIRICHLET ? R.v_lo : 0.0;
+        const double hi = k == G.nz - 1 && G.bc_hi == PIC_BC_DIRICHLET ? R.v_hi : 0.0;
+        const double ba = (fa + lo) + hi, bb = (fb + lo) + hi;
+        sb += ba * ba + bb * bb;
+        da = sp_start(G, R, u, kd, ad); db = sp_start(G, R, u, kd, ad + nx);
+        ua = sp_start(G, R, u, ku, au); ub = sp_start(G, R, u, ku, au + nx);
+      } else {
+        da = u[ad]; db = u[ad + nx];
+        ua = u[au]; ub = u[au + nx];
+      }
       // The stencil sum of one node: x pair, then y pair, then z pair (a
       // Neumann face's mirrored neighbour taken twice).
-      const double sa = ((ra[im] + ra[ip]) + (pl[jm * nx + i] + cb)) + (dn[0] + up[0]);
-      const double sb = ((rb[im] + rb[ip]) + (ca + pl[jp * nx + i])) + (dn[nx] + up[nx]);
-      const double va = fr[0] - (6.0 * ca - sa), vb = fr[nx] - (6.0 * cb - sb);
+      const double na = (xa + (ym + cb)) + (da + ua);
+      const double nb = (xb + (ca + yp)) + (db + ub);
+      const double va = fa - (6.0 * ca - na), vb = fb - (6.0 * cb - nb);
       s2 += va * va + vb * vb;
       buf[l * stride + pad8(i)] = make_double2(va, vb);
     }
@@ -290,16 +327,63 @@ __global__ void __launch_bounds__(kSpThreads) k_sp_xfwd(
       *reinterpret_cast<double2*>(o + nx) = xb;
     }
   }
-  // Sum of squares of the residual: one partial per workgroup.
+  // Sums of squares of the residual (and of b): one partial per workgroup.
   __syncthreads();
   double* red = reinterpret_cast<double*>(buf);
-  for (int o = 32; o > 0; o >>= 1) s2 += __shfl_down(s2, o);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s2;
+  const unsigned nw = (blockDim.x + 63) / 64;
+  for (int o = 32; o > 0; o >>= 1) {
+    s2 += __shfl_down(s2, o);
+    if (RHO) sb += __shfl_down(sb, o);
+  }
+  if ((threadIdx.x & 63) == 0) {
+    red[threadIdx.x >> 6] = s2;
+    if (RHO) red[nw + (threadIdx.x >> 6)] = sb;
+  }
   __syncthreads();
-  if (threadIdx.x == 0) {
+  if (threadIdx.x < (RHO ? 2u : 1u)) {
     double a = 0.0;
-    for (unsigned w = 0; w < (blockDim.x + 63) / 64; ++w) a += red[w];
-    part[wg] = a;
+    for (unsigned w = 0; w < nw; ++w) a += red[threadIdx.x * nw + w];
+    part[threadIdx.x * gridDim.x + wg] = a;
+  }
+}
+
+// Start of a solve from the two sums: ||b||, the counters at zero, and the
+// initial check.
+__global__ void __launch_bounds__(1024) k_sp_begin(const double* __restrict__ part, int n,
+                                                   Counters* dc, double tol) {
+  __shared__ double s[2][16];
+  double a = 0.0, b = 0.0;
+  for (int i = threadIdx.x; i < n; i += 1024) {
+    a += part[i];
+    b += part[n + i];
+  }
+  for (int o = 32; o > 0; o >>= 1) {
+    a += __shfl_down(a, o);
+    b += __shfl_down(b, o);
+  }
+  if ((threadIdx.x & 63) == 0) {
+    s[0][threadIdx.x >> 6] = a;
+    s[1][threadIdx.x >> 6] = b;
+  }
+  __syncthreads();
+  if (threadIdx.x) return;
+  for (int w = 1; w < 16; ++w) {
+    a += s[0][w];
+    b += s[1][w];
+  }
+  const double bn = sqrt(b), rr = bn > 0.0 ? sqrt(a) / bn : 0.0;
+  dc->b_norm = bn;
+  dc->total_charge = 0;
+  dc->vcycles = 0;
+  dc->refinements = 0;
+  dc->rel_res = rr;
+  dc->rel_res0 = rr;
+  dc->done = 0;
+  if (!(rr == rr)) {
+    dc->err |= kErrNonFinite;
+    dc->done = 1;
+  } else if (rr <= tol) {
+    dc->done = 1;
   }
 }
 
@@ -357,51 +441,78 @@ __global__ void __launch_bounds__(kSpThreads) k_sp_y(SpGrid G, double* __restric
 }
 
 // x inverse and correction: phi = phi_0 + the transform of two rows' slots.
+// RHO: phi_0 is u0 (null: zero); u and (unless null) out take phi, with the
+// Dirichlet planes' values beside the planes next to them, also where the
+// start needs no correction.
+template <bool RHO>
 __global__ void __launch_bounds__(kSpThreads) k_sp_xinv(SpGrid G, const double* __restrict__ s,
-                                                        double* __restrict__ u, FftPlan P,
-                                                        int nlines, int lpw, int stride,
-                                                        const Counters* dc) {
+                                                        const double* u0, double* u, double* out,
+                                                        FftPlan P, int nlines, int lpw, int stride,
+                                                        const Counters* dc, SpRhs R) {
   extern __shared__ double2 sm[];
-  if (dc->done) return;
+  const bool done = dc->done;
+  if (!RHO && done) return;
   double2* tw = sm;
   double2* buf = sm + P.n;
   const int nx = G.nx, nh = nx / 2;
   const int line0 = xcd_block(blockIdx.x, gridDim.x) * lpw;
   const int lines = nlines - line0 < lpw ? nlines - line0 : lpw;
-  const float rnh = 1.0f / (float)nh;
+  if (!done) {
+    const float rnh = 1.0f / (float)nh;
 #pragma unroll
-  for (int b = 0; b < kSpElems / 2; ++b) {
-    const int e = threadIdx.x + b * blockDim.x;
-    if (e < lines * nh) {
-      const int l = fdiv(e, rnh), kx = e - l * nh;
-      const double* o = s + (long long)(line0 + l) * 2 * nx + 2 * kx;
-      const double2 ga = *reinterpret_cast<const double2*>(o);
-      const double2 gb = *reinterpret_cast<const double2*>(o + nx);
-      double2* dst = buf + l * stride;
-      if (kx == 0) {
-        dst[0] = make_double2(ga.x, gb.x);
-        dst[pad8(nh)] = make_double2(ga.y, gb.y);
-      } else {
-        dst[pad8(kx)] = make_double2(ga.x - gb.y, ga.y + gb.x);
-        dst[pad8(nx - kx)] = make_double2(ga.x + gb.y, gb.x - ga.y);
+    for (int b = 0; b < kSpElems / 2; ++b) {
+      const int e = threadIdx.x + b * blockDim.x;
+      if (e < lines * nh) {
+        const int l = fdiv(e, rnh), kx = e - l * nh;
+        const double* o = s + (long long)(line0 + l) * 2 * nx + 2 * kx;
+        const double2 ga = *reinterpret_cast<const double2*>(o);
+        const double2 gb = *reinterpret_cast<const double2*>(o + nx);
+        double2* dst = buf + l * stride;
+        if (kx == 0) {
+          dst[0] = make_double2(ga.x, gb.x);
+          dst[pad8(nh)] = make_double2(ga.y, gb.y);
+        } else {
+          dst[pad8(kx)] = make_double2(ga.x - gb.y, ga.y + gb.x);
+          dst[pad8(nx - kx)] = make_double2(ga.x + gb.y, gb.x - ga.y);
+        }
       }
     }
+    fill_tw(tw, P.n);
+    __syncthreads();
+    fft_lines(buf, tw, P, lines, stride, 1.0);
   }
-  fill_tw(tw, P.n);
-  __syncthreads();
-  fft_lines(buf, tw, P, lines, stride, 1.0);
   const double sc = 1.0 / ((double)nx * (double)G.ny);
   const float rnx = 1.0f / (float)nx;
-  double* base = u + (long long)G.k0 * G.nxy;
+  const long long base = (long long)G.k0 * G.nxy;
 #pragma unroll
   for (int b = 0; b < kSpElems; ++b) {
     const int e = threadIdx.x + b * blockDim.x;
     if (e < lines * nx) {
       const int l = fdiv(e, rnx), i = e - l * nx;
-      const double2 v = buf[l * stride + pad8(i)];
-      double* o = base + (long long)(line0 + l) * 2 * nx + i;
-      o[0] = o[0] + sc * v.x;
-      o[nx] = o[nx] + sc * v.y;
+      const long long at = base + (long long)(line0 + l) * 2 * nx + i;
+      double va = !RHO || u0 ? u0[at] : 0.0, vb = !RHO || u0 ? u0[at + nx] : 0.0;
+      if (!done) {
+        const double2 v = buf[l * stride + pad8(i)];
+        va = va + sc * v.x;
+        vb = vb + sc * v.y;
+      }
+      auto put = [&](long long q, double x) {
+        u[q] = x;
+        if (RHO && out) out[q] = x;
+      };
+      put(at, va);
+      put(at + nx, vb);
+      if (RHO) {
+        const int k = G.k0 + (int)((line0 + l) / (G.ny / 2));
+        if (k == 1 && G.bc_lo == PIC_BC_DIRICHLET) {
+          put(at - G.nxy, R.v_lo);
+          put(at - G.nxy + nx, R.v_lo);
+        }
+        if (k == G.nz - 1 && G.bc_hi == PIC_BC_DIRICHLET) {
+          put(at + G.nxy, R.v_hi);
+          put(at + G.nxy + nx, R.v_hi);
+        }
+      }
     }
   }
 }
@@ -617,12 +728,13 @@ int spectral_partials(const pic_ctx* c) {
 void spectral_forward(pic_ctx* c) {
   const SpGrid G = sp_grid(c);
   const LineLaunch a = line_launch(G.nx, (long long)G.np * (G.ny / 2));
-  k_sp_xfwd<<<a.grid, a.threads, a.lds, c->stream>>>(G, c->lev[0].u, c->lev[0].f,
-                                                     c->spec_d, a.plan, a.nlines, a.lpw,
-                                                     a.stride, c->partials);
+  k_sp_xfwd<false><<<a.grid, a.threads, a.lds, c->stream>>>(
+      G, c->lev[0].u, c->lev[0].f, c->spec_d, a.plan, a.nlines, a.lpw, a.stride, c->partials,
+      SpRhs{});
 }
 
-void spectral_correct(pic_ctx* c) {
+// The passes between the two x transforms.
+static void spectral_modes(pic_ctx* c) {
   const SpGrid G = sp_grid(c);
   double* s = c->spec_d;
   const LineLaunch y = line_launch(G.ny, (long long)G.np * (G.nx / 2));
@@ -645,9 +757,34 @@ void spectral_correct(pic_ctx* c) {
     k_sp_tri<64><<<grid, nt, lds, c->stream>>>(G, s, lgc, c->dc);
   k_sp_y<true><<<y.grid, y.threads, y.lds, c->stream>>>(G, s, y.plan, y.nlines, y.lpw, y.stride,
                                                         c->dc);
+}
+
+void spectral_correct(pic_ctx* c) {
+  const SpGrid G = sp_grid(c);
+  spectral_modes(c);
   const LineLaunch x = line_launch(G.nx, (long long)G.np * (G.ny / 2));
-  k_sp_xinv<<<x.grid, x.threads, x.lds, c->stream>>>(G, s, c->lev[0].u, x.plan, x.nlines, x.lpw,
-                                                     x.stride, c->dc);
+  double* u = c->lev[0].u;
+  k_sp_xinv<false><<<x.grid, x.threads, x.lds, c->stream>>>(
+      G, c->spec_d, u, u, nullptr, x.plan, x.nlines, x.lpw, x.stride, c->dc, SpRhs{});
+}
+
+SpRhs sp_rhs_of(const pic_ctx* c) {
+  const double dx = c->g.dx;
+  return SpRhs{(dx * dx) / kEps0, 2.0 * dx, c->cfg.v_lo, c->cfg.v_hi, c->cfg.bc_lo,
+               c->cfg.bc_hi};
+}
+
+void spectral_solve_rho(pic_ctx* c, const SpRhs& R, const double* rho, const double* u0,
+                        double* u, double* out, bool first) {
+  const SpGrid G = sp_grid(c);
+  const LineLaunch x = line_launch(G.nx, (long long)G.np * (G.ny / 2));
+  k_sp_xfwd<true><<<x.grid, x.threads, x.lds, c->stream>>>(
+      G, u0, rho, c->spec_d, x.plan, x.nlines, x.lpw, x.stride, c->partials, R);
+  if (first)
+    k_sp_begin<<<1, 1024, 0, c->stream>>>(c->partials, (int)x.grid, c->dc, c->cfg.rel_tol);
+  spectral_modes(c);
+  k_sp_xinv<true><<<x.grid, x.threads, x.lds, c->stream>>>(
+      G, c->spec_d, u0, u, out, x.plan, x.nlines, x.lpw, x.stride, c->dc, R);
 }
 
 }  // namespace pic

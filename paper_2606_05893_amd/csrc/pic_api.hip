@@ -810,10 +810,35 @@ pic_status pic_step(pic_ctx* c, double dt, pic_absorbed* out, pic_diag* diag) {
   return pic_advance(c, dt, out, diag);
 }
 
+// Whether a direct solve reads the caller's density and start and writes its
+// potential itself (256 x 256 x 1024: 2.8 -> 2.3 ms without the copies, the
+// right-hand side pass and the zeroed start; 40 x 20 x 36: 111 -> 93 us): not
+// where the two arrays overlap (the density is read to the end) or lie on odd
+// 8-byte words (the residual reads pairs), or the learned start keeps its own
+// record.
+static bool solves_in_place(const pic_ctx* c, const double* rho, const double* phi,
+                            int32_t warm) {
+  const uintptr_t a = (uintptr_t)rho, b = (uintptr_t)phi;
+  const uintptr_t n = (uintptr_t)c->nnodes * sizeof(double);
+  if (!c->direct || ((a | b) & 15) || (a < b + n && b < a + n)) return false;
+  return warm != PIC_WARM_GIVEN ||
+         (c->warm_mode != PIC_WS_RECORD && c->warm_mode != PIC_WS_UNET);
+}
+
 pic_status poisson_solve(pic_ctx* c, const double* rho, double* phi,
                          int32_t warm, pic_solve_info* info) {
   if (!c || !rho || !phi) return PIC_ERR_ARG;
   c->u_solved = c->hist_valid = false;
+  if (solves_in_place(c, rho, phi, warm)) {
+    int st = PIC_OK;
+    pic_solve_info loc;
+    field_solve_rho(c, rho, warm == PIC_WARM_GIVEN ? phi : nullptr, c->lev[0].u, phi, &loc, &st);
+    if (info) *info = loc;
+    if (!hip_ok(c, hipStreamSynchronize(c->stream), "synchronise")) return PIC_ERR_HIP;
+    if (st != PIC_OK)
+      return set_err(c, (pic_status)st, "Poisson solve did not converge");
+    return PIC_OK;
+  }
   if (warm == PIC_WARM_GIVEN) {
     if (!hip_ok(c, hipMemcpyAsync(c->lev[0].u, phi, c->nnodes * sizeof(double),
                                   hipMemcpyDeviceToDevice, c->stream),
@@ -907,6 +932,14 @@ pic_status poisson_solve_static(const pic_config* cfg, const double* rho,
   const long long n16 = (long long)(need / 16);
   k_zero16<<<1024, 256, 0, c.stream>>>(reinterpret_cast<uint4*>(base), n16);
   if (hipGetLastError() != hipSuccess) return PIC_ERR_HIP;
+  if (solves_in_place(&c, rho, phi, warm)) {
+    int st = PIC_OK;
+    pic_solve_info loc;
+    field_solve_rho(&c, rho, warm == PIC_WARM_GIVEN ? phi : nullptr, phi, nullptr, &loc, &st);
+    if (info) *info = loc;
+    if (hipStreamSynchronize(c.stream) != hipSuccess) return PIC_ERR_HIP;
+    return (pic_status)st;
+  }
   if (warm == PIC_WARM_GIVEN &&
       hipMemcpyAsync(c.lev[0].u, phi, c.nnodes * sizeof(double),
                      hipMemcpyDeviceToDevice, c.stream) != hipSuccess)

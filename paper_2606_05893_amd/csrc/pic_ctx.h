@@ -241,6 +241,8 @@ inline void tmark(pic_ctx* c, int ph, bool begin) {
 
 // ---- field (k_field.hip) ---------------------------------------------------
 void field_rhs(pic_ctx* c, const double* rho_or_null);
+void field_solve_rho(pic_ctx* c, const double* rho, const double* u0, double* u,
+                     double* out, pic_solve_info* info, int* status);
 void field_solve(pic_ctx* c, bool warm, bool direct, pic_solve_info* info,
                  int* status);
 void field_efield(pic_ctx* c);
@@ -265,6 +267,23 @@ void spectral_forward(pic_ctx* c);
 int spectral_partials(const pic_ctx* c);
 // The rest of the solve: lev[0].u += A^-1 of that residual.
 void spectral_correct(pic_ctx* c);
+// The right-hand side of a caller's density (k_rhs): scale rho, and a Neumann
+// face's data.
+struct SpRhs {
+  double scale, two_dx, v_lo, v_hi;
+  int bc_lo, bc_hi;
+};
+__device__ __forceinline__ double sp_rhs(const SpRhs& R, int k, int nz, double rho) {
+  double v = rho * R.scale;
+  if (k == 0 && R.bc_lo != PIC_BC_DIRICHLET) v = v - R.two_dx * R.v_lo;
+  if (k == nz && R.bc_hi != PIC_BC_DIRICHLET) v = v + R.two_dx * R.v_hi;
+  return v;
+}
+SpRhs sp_rhs_of(const pic_ctx* c);
+// One correction of the start u0 (null: zero) for the density rho, into u and
+// (unless null) out; on the first one the norm of b and the initial check.
+void spectral_solve_rho(pic_ctx* c, const SpRhs& R, const double* rho, const double* u0,
+                        double* u, double* out, bool first);
 
 // ---- particles (k_particles.hip) -------------------------------------------
 // ---- diagnostics (k_debye.hip) ---------------------------------------------

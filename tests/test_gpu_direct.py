@@ -77,3 +77,54 @@ def test_multigrid_paths_unchanged(gpu_lib, n, precision):
     ref = P.solve_exact(P.rhs_from_density(rho, g), g)
     for phi, _ in out.values():
         assert np.max(np.abs(phi - ref)) <= 1e-6 * np.max(np.abs(ref))
+
+
+@pytest.mark.parametrize("static", [False, True])
+@pytest.mark.parametrize("bc", BCS)
+@pytest.mark.parametrize("form", ["apart", "odd word", "same array", "overlap"])
+def test_caller_arrays(gpu_lib, form, bc, static):
+    """The solve reads the caller's density and start and writes its potential
+    itself, or works on copies where the arrays overlap or lie on odd 8-byte
+    words: the same potential (FP64 rounding apart), in the caller's array and
+    in the context, from zero and from a start, also one that needs no
+    correction."""
+    import ctypes
+
+    import torch
+    from paper_2606_05893_amd import pic as G
+    p, g, rho = _case((24, 20, 30), bc, 8)
+    scale = np.max(np.abs(ref := P.solve_exact(P.rhs_from_density(rho, g), g)))
+    n = ref.size
+    gpu = G.Pic(p, capacity=(16, 16, 16))
+    cfg = G.make_config(p, capacity=(0, 0, 0), queue_capacity=0, max_events=1)
+    buf = torch.zeros(3 * n + 64, dtype=torch.float64, device="cuda")
+    off = {"apart": (0, n + n % 2), "odd word": (1, n + 2 + (n + 1) % 2),
+           "same array": (0, 0), "overlap": (0, n // 2 - n // 2 % 2)}[form]
+    a, b = buf[off[0]:off[0] + n], buf[off[1]:off[1] + n]
+    for start in (None, 0.3 * ref, ref):
+        if start is not None and off[1] < n:
+            continue                       # (a start cannot share the density's words)
+        b.copy_(torch.full((n,), 7.0) if start is None else torch.tensor(start).reshape(-1))
+        a.copy_(torch.tensor(rho).reshape(-1))
+        info = G.SolveInfo()
+        warm = 0 if start is None else 1
+        ptr = [ctypes.c_void_p(t.data_ptr()) for t in (a, b)]
+        if static:
+            st = G.load_library().poisson_solve_static(
+                ctypes.byref(cfg), ptr[0], ptr[1], warm, ctypes.byref(info),
+                ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+        else:
+            torch.cuda.synchronize()
+            st = gpu.lib.poisson_solve(gpu.ctx, ptr[0], ptr[1], warm, ctypes.byref(info))
+        torch.cuda.synchronize()
+        assert st == 0 and info.converged == 1
+        assert info.vcycles == (0 if start is ref else 1)
+        phi = b.cpu().numpy().reshape(ref.shape)
+        assert np.max(np.abs(phi - ref)) <= 1e-10 * scale, (form, warm)
+        for k, face in ((0, bc[0] == 0), (-1, bc[1] == 0)):
+            if face:
+                assert np.array_equal(phi[k], np.full_like(phi[k], p["v_lo"] if k == 0 else p["v_hi"]))
+        if not static:
+            assert np.array_equal(gpu.read_fields()[1].cpu().numpy(), phi)
+        if form in ("apart", "odd word"):
+            assert np.array_equal(a.cpu().numpy().reshape(ref.shape), rho)
