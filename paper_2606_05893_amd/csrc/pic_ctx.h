@@ -103,6 +103,7 @@ struct pic_ctx {
   bool spec_ready;               // pivots computed
   double* partials;          // reduction partials
   double* part_n;            // neutral push partials (one per workgroup)
+  long long part_n_blocks;          // partial sums of the neutral push
   int npartials;
   long long* qpartials;      // integer reduction partials
 
