@@ -40,12 +40,13 @@ HBM_PEAK_GBS = 8000.0
 # when measured; set to None when they change.
 MEASURED_TRAFFIC = {
     ("c2", "fp64", "k_smooth2"): 241.2e6,
-    ("c2", "fp64", "k_push_tile"): 2562.9e6,
-    # profiles/c2_mixed_hbm_traffic.md; the smoother's figure is the mean
+    ("c2", "fp64", "k_push_tile"): 2558.0e6,
+    # profiles/c2_mixed_hbm_traffic.md; the smoother's figures are of steps
+    # that ran V-cycles (unchanged since), the mixed one the mean
     # over the four finest-level passes of a refinement round (zero start,
     # two plain, FP64 accumulation).
     ("c2", "mixed", "k_smooth2"): (77.2e6 + 2 * 120.7e6 + 237.0e6) / 4,
-    ("c2", "mixed", "k_push_tile"): 1626.0e6,
+    ("c2", "mixed", "k_push_tile"): 1623.8e6,
 }
 
 
@@ -368,7 +369,7 @@ def variant_rooflines(p, r, workload):
     """Algorithmic-bytes rooflines of one variant's dominant kernels, from
     its HIP-event-timed phases.
 
-    push (k_push_tile / k_push_tile_m): per electron x, y, z, vx, vy, vz
+    push (k_push_tile, both layouts): per electron x, y, z, vx, vy, vz
     read and written (96 B FP64; 56 B mixed as cell + FP32 offsets and
     velocities), id read (8 B), cell key written (4 B); per ion the same
     without the id; per node the three E components read once (24 B FP64,
@@ -399,7 +400,7 @@ def variant_rooflines(p, r, workload):
            + nodes * per_node + cells * 4)
     t_push = ms_push / max(n_push, 1) * 1e-3
     ach = alg / t_push / 1e9 if t_push > 0 else 0.0
-    kname = "k_push_tile_m" if mixed else "k_push_tile"
+    kname = "k_push_tile<PartsM>" if mixed else "k_push_tile"
     push = {"bound": "hbm", "kernel": kname,
             "achieved": round(ach, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": round(ach / HBM_PEAK_GBS, 4),
