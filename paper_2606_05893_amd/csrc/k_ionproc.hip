@@ -46,9 +46,9 @@ enum : uint32_t {
 
 struct IonC {
   double s_rec, a2, I2, cx_a, cx_b;
-  // Bounds of sigma v dt (see no_event): electrons, and Cu+ with atoms; with
-  // a constant cross section (cx_b = 0) the latter is per unit of speed.
-  double h_e, h_cx;
+  // Electrons' bound of sigma v dt (see no_event), and the speed up to which
+  // charge exchange's sigma u grows.
+  double h_e, u_cx;
   double w_dx3, dt, half_me, two_e_me;
   unsigned step;
   unsigned long long seed;
@@ -125,6 +125,16 @@ __device__ __forceinline__ double sigma_cx(const IonC& k, double eps) {
   double t = k.cx_a - k.cx_b * log(eps > 1e-6 ? eps : 1e-6);
   t = t > 0.0 ? t : 0.0;
   return t * t;
+}
+
+// Bound of sigma u dt of a charge exchange at relative speeds up to u (1e-6 is
+// a margin for rounding).
+__device__ __forceinline__ double cx_bound(const IonC& k, double u) {
+  u = fmin(u, k.u_cx);
+  // (A constant one without the logarithm: 337 -> 317 us of k_pg_cells.)
+  const double s = k.cx_b == 0.0 ? fmax(k.cx_a, 0.0) * k.cx_a
+                                 : sigma_cx(k, ((0.25 * kMcu) * (u * u)) / kE);
+  return s * u * k.dt * (1.0 + 1e-6);
 }
 
 // Exchange two particle records (position, velocity, id) of one layout.
@@ -519,16 +529,22 @@ __global__ void __launch_bounds__(kT) k_pg_scatter(
 // over the tile-major cells); the cells of more than kSmall records listed
 // for the workgroup pass, their records written to rec unsorted; of the
 // small cells (2 to kSmall records) with a Cu+, those in which an electron's
-// or a Cu+'s draw may collide: their records to rec, the plane to rest with
-// a mask of these cells.  A plane of more than kHot records is listed for
-// the hot-plane passes, and in rest with every cell.
+// or a Cu+'s draw may collide: their records to rec, the cell to the plane's
+// mask.  A plane of more than kHot records is listed for the hot-plane passes,
+// and all its cells are marked.  k_pg_list lists the cells: with the ranking
+// and the cells' pass walking every place of the marked planes, and a request
+// per plane on one counter here, a step with 1.8e5 charge exchanges took 6.1
+// ms, 2.9 now (3.4 with all processes run in this pass).
 //
 // A record's cell and species are a byte; of the records whose cell may hold
 // a trial the id is gathered, and the speed of a Cu+ next to an atom (their
 // tile's lines, shared by the eight planes of a tile).  Nothing of the atoms,
-// whose lines are scattered, is read.  At 25 M particles on 128 x 128 x 512
-// cells 354 us; with every record's key and id gathered and ranked and
-// every pair's probability evaluated, a cell per lane, 1290 us.
+// whose lines are scattered, is read: the pair's speed is at most the Cu+'s
+// plus the atoms' largest, and sigma u grows with it, up to u_cx.  (Bounded by
+// its peak over every speed, cx_a = 2.4e-9 and cx_b = 1e-10 marked nearly
+// every cell: 6.1 ms a step, 2.1 now.)  At 25 M particles on 128 x 128 x 512
+// cells 317 us; with every record's key and id gathered and ranked and every
+// pair's probability evaluated, a cell per lane, 1290 us.
 constexpr int kHot = 4096;
 
 struct PlaneLds {
@@ -553,8 +569,8 @@ struct PgArgs {
   Rec* rec;
   unsigned *big, *nbig;
   long long big_cap;
-  unsigned *hot, *nhot, *rest, *nrest;
-  unsigned long long* rmask;
+  unsigned *hot, *nhot;
+  unsigned long long* mask;
   IonC k;
   const Counters* dc;
 };
@@ -574,9 +590,7 @@ __global__ void __launch_bounds__(kPlaneCells) k_pg_cells(PgArgs<PT> A) {
     if (n > kHot) {
       if (tid == 0) {
         A.hot[atomicAdd(A.nhot, 1u)] = (unsigned)u;
-        const unsigned q = atomicAdd(A.nrest, 1u);
-        A.rest[q] = (unsigned)u;
-        A.rmask[q] = ~0ull;
+        A.mask[u] = ~0ull;
       }
       continue;
     }
@@ -619,16 +633,16 @@ __global__ void __launch_bounds__(kPlaneCells) k_pg_cells(PgArgs<PT> A) {
       const unsigned other = s ? mc - ne - ni : ni;
       if (ni == 0u || s == 2u || other == 0u) continue;
       const unsigned i = J.ix(A.pidx[base + j]);
+      const unsigned long long id = s ? S.i.id[i] : S.e.id[i];
       const double dens = (double)other * k.w_dx3;
-      double h = s ? k.h_cx : k.h_e;
-      if (s && k.cx_b == 0.0) {
+      double h = k.h_e;
+      if (s) {
         double vx, vy, vz;
         Acc<PT>::vel(S.i, i, vx, vy, vz);
-        h = h * (sqrt((vx * vx + vy * vy) + vz * vz) + vmax);
+        h = cx_bound(k, sqrt((vx * vx + vy * vy) + vz * vz) + vmax);
       }
       double u1, u2;
-      uniform2(s ? S.i.id[i] : S.e.id[i], k.step, s ? kTagCX : kTagEI0, k.seed,
-               u1, u2);
+      uniform2(id, k.step, s ? kTagCX : kTagEI0, k.seed, u1, u2);
       if (no_event(u1, dens, h)) continue;
       if (s == 0u) {
         // (Its own speed decides: the bound holds down to 1 meV.)
@@ -641,12 +655,8 @@ __global__ void __launch_bounds__(kPlaneCells) k_pg_cells(PgArgs<PT> A) {
     __syncthreads();
     const unsigned long long mask =
         (unsigned long long)L.flag[1] << 32 | L.flag[0];
+    if (tid == 0) A.mask[u] = mask;
     if (mask) {
-      if (tid == 0) {
-        const unsigned q = atomicAdd(A.nrest, 1u);
-        A.rest[q] = (unsigned)u;
-        A.rmask[q] = mask;
-      }
       for (int j = tid; j < n; j += kPlaneCells) {
         const unsigned lc = A.pcs[base + j] & 63u;
         if (mask >> lc & 1ull)
@@ -655,6 +665,45 @@ __global__ void __launch_bounds__(kPlaneCells) k_pg_cells(PgArgs<PT> A) {
       }
       __syncthreads();
     }
+  }
+}
+
+// The cells marked in the planes' masks as a list: a request on its counter
+// per 256 planes (one per plane, in the pass above, queued for 1.1 ms where
+// every plane had some), each plane's cells written by a wave.
+__global__ void __launch_bounds__(kT) k_pg_list(const unsigned long long* __restrict__ mask,
+                                                long long nplanes, unsigned* __restrict__ list,
+                                                unsigned* __restrict__ nlist) {
+  __shared__ unsigned wsum[kT / 64], base;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  for (long long u0 = blockIdx.x * (long long)kT; u0 < nplanes; u0 += gridDim.x * (long long)kT) {
+    const long long u = u0 + threadIdx.x;
+    const unsigned long long m = u < nplanes ? mask[u] : 0ull;
+    const unsigned n = (unsigned)__popcll(m);
+    unsigned incl = n;
+    for (int o = 1; o < 64; o <<= 1) {
+      const unsigned y = __shfl_up(incl, o);
+      if (lane >= o) incl += y;
+    }
+    if (lane == 63) wsum[wave] = incl;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      unsigned t = 0;
+      for (int w = 0; w < kT / 64; ++w) t += wsum[w];
+      base = t ? atomicAdd(nlist, t) : 0u;
+    }
+    __syncthreads();
+    unsigned at = base + incl - n;
+    for (int w = 0; w < wave; ++w) at += wsum[w];
+    for (unsigned long long some = __ballot(n != 0u); some; some &= some - 1) {
+      const int l = __ffsll((long long)some) - 1;
+      const unsigned long long ml = __shfl(m, l);
+      const unsigned al = __shfl(at, l);
+      if (ml >> lane & 1ull)
+        list[al + __popcll(ml & ((1ull << lane) - 1ull))] =
+            ((unsigned)(u0 + 64 * wave + l) << kPlaneShift) + lane;
+    }
+    __syncthreads();
   }
 }
 
@@ -843,57 +892,54 @@ __global__ void __launch_bounds__(kT) k_ph_scatter(
   }
 }
 
-// The masked small cells of the planes in rest, a thread per (cell,
-// record): rank in the cell's (key, id) order from the scattered records.
+// The listed small cells, kRankLanes threads each: the records' ranks in the
+// cell's (key, id) order from the scattered records.
+constexpr int kRankLanes = 8;
 template <class PT>
 __global__ void __launch_bounds__(kT) k_ph_rank(
-    Sp3<PT> S, const unsigned* __restrict__ rest,
-    const unsigned long long* __restrict__ rmask,
-    const unsigned* __restrict__ nrest, const unsigned* __restrict__ off,
+    Sp3<PT> S, const unsigned* __restrict__ list,
+    const unsigned* __restrict__ nlist, const unsigned* __restrict__ off,
     const Rec* __restrict__ rec, Rec* __restrict__ srt) {
-  const long long nt = (long long)*nrest * kPlaneCells * kSmall;
+  const long long nt = (long long)*nlist * kRankLanes;
   for (long long t = blockIdx.x * (long long)kT + threadIdx.x; t < nt;
        t += (long long)gridDim.x * kT) {
-    const int r = (int)(t % kSmall);
-    const long long hc = t / kSmall;
-    const int lc = (int)(hc % kPlaneCells);
-    if (!(rmask[hc / kPlaneCells] >> lc & 1ull)) continue;
-    const unsigned c = (rest[hc / kPlaneCells] << kPlaneShift) + (unsigned)lc;
+    const unsigned c = list[t / kRankLanes];
     const unsigned b = off[c];
     const int m = (int)(off[c + 1] - b);
-    if (!small_cell((unsigned)m) || r >= m) continue;
-    const Rec x = rec[b + r];
-    int rank = 0;
-    for (int j = 0; j < m; ++j) {
-      const Rec y = rec[b + j];
-      rank += j != r && (y.lo < x.lo || (y.lo == x.lo && rid(S, y) < rid(S, x)));
+    if (!small_cell((unsigned)m)) continue;
+    for (int r = (int)(t % kRankLanes); r < m; r += kRankLanes) {
+      const Rec x = rec[b + r];
+      int rank = 0;
+      for (int j = 0; j < m; ++j) {
+        const Rec y = rec[b + j];
+        rank += j != r && (y.lo < x.lo || (y.lo == x.lo && rid(S, y) < rid(S, x)));
+      }
+      srt[b + rank] = x;
     }
-    srt[b + rank] = x;
   }
 }
 
-// The masked small cells with a Cu+ of the planes in rest, one thread each,
-// on the sorted records.  Four wavefronts per SIMD (128 registers, two
+// The listed small cells with a Cu+, one thread each, on the sorted records.  Four wavefronts per SIMD (128 registers, two
 // spilled on rare paths): a chain of gathers per cell wants occupancy, 1039
 // -> 935 us with every cell of the 128x128x512 workload; five (30 spilled)
 // ran 1413 us.
 template <class PT>
 __global__ void __launch_bounds__(kT, 4) k_ip_small(
     Sp3<PT> S, const unsigned* __restrict__ off,
-    const unsigned* __restrict__ rest,
-    const unsigned long long* __restrict__ rmask,
-    const unsigned* __restrict__ nrest, const Rec* __restrict__ srt, IonC k,
-    GridC g,
+    const unsigned* __restrict__ list, const unsigned* __restrict__ nlist,
+    const Rec* __restrict__ srt, IonC k, GridC g,
     int* __restrict__ ncount, long long* __restrict__ acc,
     uint32_t* __restrict__ dead2, Rec* __restrict__ ev,
     uint2* __restrict__ evp, Counters* dc) {
   Tally t;
-  const long long nt = (long long)*nrest * kPlaneCells;
-  for (long long q = blockIdx.x * (long long)kT + threadIdx.x; q < nt;
-       q += (long long)gridDim.x * kT) {
-    const int lc = (int)(q % kPlaneCells);
-    if (!(rmask[q / kPlaneCells] >> lc & 1ull)) continue;
-    const unsigned c = (rest[q / kPlaneCells] << kPlaneShift) + (unsigned)lc;
+  // A run of the list per wave, so that few cells, whose paths differ, go to
+  // a wave each.
+  const unsigned nt = *nlist, nw = gridDim.x * (kT / 64);
+  const unsigned per = (nt + nw - 1) / nw;
+  const unsigned q0 = (blockIdx.x * (kT / 64) + threadIdx.x / 64) * per;
+  const unsigned q1 = q0 < nt ? min(q0 + per, nt) : q0;
+  for (unsigned q = q0 + threadIdx.x % 64; q < q1; q += 64) {
+    const unsigned c = list[q];
     const unsigned b = off[c], e = off[c + 1];
     const int n = (int)(e - b);
     if (n < 2 || n > kSmall) continue;
@@ -1194,30 +1240,22 @@ Parts sp_cur<Parts>(pic_ctx* c, int s) { return c->P[s][c->cur[s]]; }
 template <>
 PartsM sp_cur<PartsM>(pic_ctx* c, int s) { return c->PM[s][c->cur[s]]; }
 
-// The largest sigma v dt of an electron and of a Cu+-atom pair at any
-// energy.  Recombination: s_rec v / max(E, 1 meV) peaks at 1 meV;
+// The largest sigma v dt of an electron at any energy, and the speed up to
+// which a Cu+-atom pair's sigma u grows.  Recombination: s_rec v / max(E, 1 meV) peaks at 1 meV;
 // ionisation: a2 ln(x) / (x I2^2) v(I2) sqrt(x), x = E / I2, at x = e^2.
 // Charge exchange: with s = a - b ln(eps), d(s^2 u)/du = s (s - 4 b), so it
-// grows up to s = 4 b (or the clamp of eps) and falls after; without that
-// fall it is a^2 times the speed (b = 0) or not bounded here (b < 0).  1e-6
-// is a margin for rounding.
+// grows up to s = 4 b (or the clamp of eps) and falls after; for b <= 0 it
+// grows throughout.  1e-6 is a margin for rounding.
 void event_bounds(IonC& k) {
   const double inf = std::numeric_limits<double>::infinity();
   const double ve = std::sqrt(1e-3 * kE / k.half_me);
   const double vi = std::sqrt(k.I2 * kE / k.half_me);
   k.h_e = k.s_rec * 1e3 * ve + k.a2 * 2.0 * vi / (std::exp(1.0) * k.I2 * k.I2);
-  k.h_cx = inf;
-  if (k.cx_b > 0.0) {
-    const double eps = std::max(1e-6, std::exp(k.cx_a / k.cx_b - 4.0));
-    const double s = std::max(0.0, k.cx_a - k.cx_b * std::log(eps));
-    k.h_cx = s * s * std::sqrt(eps * kE / (0.25 * kMcu));
-  } else if (k.cx_b == 0.0) {
-    k.h_cx = k.cx_a > 0.0 ? k.cx_a * k.cx_a : 0.0;
-  }
+  k.u_cx = inf;
+  if (k.cx_b > 0.0)
+    k.u_cx = std::sqrt(std::max(1e-6, std::exp(k.cx_a / k.cx_b - 4.0)) * kE / (0.25 * kMcu));
   k.h_e *= k.dt * (1.0 + 1e-6);
-  k.h_cx *= k.dt * (1.0 + 1e-6);
   if (!(k.h_e <= inf)) k.h_e = inf;      // (NaN)
-  if (!(k.h_cx <= inf)) k.h_cx = inf;
 }
 
 template <class PT>
@@ -1261,12 +1299,13 @@ void ionproc_t(pic_ctx* c, double dt) {
   k_ig_scan_apply<<<(unsigned)nb, kScanB, 0, st>>>(c->cg_poff, np, c->cg_bsum);
   k_pg_scatter<PT><<<4096, kT, 0, st>>>(S, c->dc, c->g, c->cg_poff, c->cg_cnt,
                                         c->cg_idx, pcs);
-  // Counters: crowded cells, hot planes, planes with cells for k_ip_small.
+  // Counters: crowded cells, hot planes, cells for k_ip_small.
   const PgArgs<PT> pg{S, c->cg_poff, np, c->cg_idx, pcs, c->cg_off,
                       c->cg_rec, c->cg_big, c->cg_nbig, c->cg_big_cap,
-                      c->cg_hot, c->cg_nbig + 1, c->cg_rest, c->cg_nbig + 2,
-                      c->cg_rmask, k, c->dc};
+                      c->cg_hot, c->cg_nbig + 1, c->cg_mask, k, c->dc};
   k_pg_cells<PT><<<8192, kPlaneCells, 0, st>>>(pg);
+  k_pg_list<<<(unsigned)std::min<long long>((np + kT - 1) / kT, 1024), kT, 0, st>>>(
+      c->cg_mask, np, c->cg_list, c->cg_nbig + 2);
   unsigned* nhot = c->cg_nbig + 1;
   k_ph_prep<<<1, 1024, 0, st>>>(c->cg_poff, c->cg_hot, nhot, c->cg_hpre,
                                 c->cg_cnt);
@@ -1278,12 +1317,10 @@ void ionproc_t(pic_ctx* c, double dt) {
   k_ph_scatter<PT><<<1024, kT, 0, st>>>(S, c->g, c->cg_poff, c->cg_hot, nhot,
                                         c->cg_hpre, c->cg_idx, c->cg_cnt,
                                         c->cg_rec, k.step, k.seed, c->dc);
-  k_ph_rank<PT><<<512, kT, 0, st>>>(S, c->cg_rest, c->cg_rmask,
-                                    c->cg_nbig + 2, c->cg_off, c->cg_rec,
-                                    c->cg_srt);
-  k_ip_small<PT><<<512, kT, 0, st>>>(S, c->cg_off, c->cg_rest, c->cg_rmask,
-                                     c->cg_nbig + 2, c->cg_srt, k, c->g,
-                                     c->ncount,
+  k_ph_rank<PT><<<512, kT, 0, st>>>(S, c->cg_list, c->cg_nbig + 2, c->cg_off,
+                                    c->cg_rec, c->cg_srt);
+  k_ip_small<PT><<<512, kT, 0, st>>>(S, c->cg_off, c->cg_list, c->cg_nbig + 2,
+                                     c->cg_srt, k, c->g, c->ncount,
                                      c->acc_next, c->dead2, c->ip_ev,
                                      c->ip_evp, c->dc);
   k_ip_big<PT><<<512, kT, 0, st>>>(S, c->cg_off, c->cg_rec, c->cg_big,

@@ -216,8 +216,8 @@ size_t carve(pic_ctx* c, char* base) {
   c->dc = cv.take<Counters>(1);
   c->cg_cnt = c->cg_off = c->cg_bsum = c->cg_big = c->cg_nbig = nullptr;
   c->cg_rec = c->cg_srt = nullptr;
-  c->cg_idx = c->cg_poff = c->cg_hot = c->cg_hpre = c->cg_rest = nullptr;
-  c->cg_rmask = nullptr;
+  c->cg_idx = c->cg_poff = c->cg_hot = c->cg_hpre = c->cg_list = nullptr;
+  c->cg_mask = nullptr;
   c->cg_work_cap = 0;
   c->ip_ev = nullptr;
   c->ip_evp = nullptr;
@@ -238,12 +238,15 @@ size_t carve(pic_ctx* c, char* base) {
     c->cg_poff = cv.take<unsigned>(c->cg_nkeys / (kTile * kTile) + 1);
     c->cg_hot = cv.take<unsigned>(c->cg_nkeys / (kTile * kTile));
     c->cg_hpre = cv.take<unsigned>(c->cg_nkeys / (kTile * kTile) + 1);
-    c->cg_rest = cv.take<unsigned>(c->cg_nkeys / (kTile * kTile));
-    c->cg_rmask = cv.take<unsigned long long>(c->cg_nkeys / (kTile * kTile));
+    c->cg_mask = cv.take<unsigned long long>(c->cg_nkeys / (kTile * kTile));
     c->ip_ev = cv.take<Rec>(c->ev_cap_p2);
     c->ip_evp = cv.take<uint2>(c->ev_cap_p2);
   }
   c->dbg_mom = cv.take<double>(debye_moment_doubles(c->ncells));
+  // The ion processes' cells lie in the Debye check's records (the one fills
+  // and reads them within a step, the other within a call): at most all cells,
+  // and the 64 of a tile plane with at least four, in ten doubles a cell.
+  if (f.flags & PIC_FLAG_CELL_GROUPS) c->cg_list = reinterpret_cast<unsigned*>(c->dbg_mom);
   c->dbg_qpart = cv.take<long long>(2048);
   c->dbg_part = cv.take<double>(2048);
   c->dbg_out = cv.take<double>(4);

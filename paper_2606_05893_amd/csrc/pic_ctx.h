@@ -161,8 +161,8 @@ struct pic_ctx {
   unsigned* cg_poff;                // tile planes' offsets into cg_idx
   unsigned* cg_hot;                 // planes of many records (ion processes)
   unsigned* cg_hpre;                // their sizes prefixed
-  unsigned* cg_rest;                // planes with cells k_ip_small runs
-  unsigned long long* cg_rmask;     // ... and these cells, a bit each
+  unsigned long long* cg_mask;      // cells of each plane k_ip_small runs
+  unsigned* cg_list;                // ... all of them (in dbg_mom)
   long long cg_big_cap;
   long long cg_nkeys;               // tile-major cell numbers (tiles x 512)
   // Recombination, Cu+ ionisation, charge exchange: settings and the listed
