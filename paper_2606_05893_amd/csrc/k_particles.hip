@@ -1819,19 +1819,40 @@ __global__ void __launch_bounds__(kT) k_mcc(
 // Every record to the number of smaller ones, from the list itself to another
 // buffer: 64 records per workgroup, each of its 16 waves comparing them with a
 // sixteenth of the list, whose records it reads by scalar loads.  n^2 / 16
-// comparisons a lane and one launch; correct for any n, and the faster way to
-// about 10^4 records.  The four lists of a 128x128x512 step (690 to some
+// comparisons a lane and one launch, the faster way to about 10^4 records.  The
+// four lists of a 128x128x512 step (690 to some
 // thousand records in a capacity of 4 M) take 59 us; the chunk sorts and LDS
 // merges took 94, and the ten merge rounds of two runs and the copy that
 // followed each, which found nothing to do, another 134.  Empty lists cost 2 us
 // each against 13 (32x32x64, capacity 65536).
+//
+// aw: the same list, or null.  A list that has grown past kRankList since the
+// last step, whose length chose this way, then has its segments of kMergeSeg
+// sorted in place instead, for k_rank_segs.  (Ranked here as well, a cathode
+// list that jumped from nothing took the step from 0.13 to 1.8 ms at 65536
+// records and 442 ms at 2^20; 0.45 and 2.8 now, half of it the push.)
+__device__ void sort_segment(Rec* s, int m);
+
 __global__ void __launch_bounds__(1024) k_rank_sort(const Rec* __restrict__ a,
+                                                    Rec* __restrict__ aw,
                                                     Rec* __restrict__ out,
                                                     const unsigned long long* __restrict__ count,
                                                     long long cap) {
-  __shared__ unsigned rank[64];
+  __shared__ Rec seg[kMergeSeg];
+  unsigned* rank = reinterpret_cast<unsigned*>(seg);   // (64 of them)
   const long long nl = (long long)*count;
   const unsigned n = (unsigned)(nl < cap ? nl : cap);
+  if (aw && n > kRankList) {
+    for (unsigned long long b = blockIdx.x * (unsigned long long)kMergeSeg; b < n;
+         b += gridDim.x * (unsigned long long)kMergeSeg) {
+      const int m = (int)(n - b < kMergeSeg ? n - b : kMergeSeg);
+      for (int i = threadIdx.x; i < m; i += 1024) seg[i] = aw[b + i];
+      sort_segment(seg, m);
+      for (int i = threadIdx.x; i < m; i += 1024) aw[b + i] = seg[i];
+      __syncthreads();
+    }
+    return;
+  }
   const unsigned lane = threadIdx.x & 63;
   const unsigned wave = (unsigned)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const unsigned per = (n + 15) / 16;
@@ -1864,6 +1885,103 @@ __global__ void __launch_bounds__(1024) k_rank_sort(const Rec* __restrict__ a,
     atomicAdd(&rank[lane], r);
     __syncthreads();
     if (threadIdx.x < 64 && i < n) out[rank[lane]] = x;
+    __syncthreads();
+  }
+}
+
+// s[0..m), m <= kMergeSeg, in place by a workgroup of 1024 (bitonic, padded
+// with the largest key); called and left by all its threads together.
+__device__ void sort_segment(Rec* s, int m) {
+  Rec maxr;
+  maxr.lo = ~0ull; maxr.hi = ~0u; maxr.val = 0u;
+  for (int i = m + (int)threadIdx.x; i < kMergeSeg; i += 1024) s[i] = maxr;
+  __syncthreads();
+  for (int k = 2; k <= kMergeSeg; k <<= 1)
+    for (int j = k >> 1; j > 0; j >>= 1) {
+      for (int t = threadIdx.x; t < kMergeSeg / 2; t += 1024) {
+        const int q = ((t & ~(j - 1)) << 1) | (t & (j - 1));
+        const Rec x = s[q], y = s[q | j];
+        if ((q & k) == 0 ? rec_less(y, x) : rec_less(x, y)) { s[q] = y; s[q | j] = x; }
+      }
+      __syncthreads();
+    }
+}
+
+// Adds to pos[k] the number of a whole sorted segment's records below x[k]
+// (EQ: or equal).
+template <bool EQ, int N>
+__device__ __forceinline__ void rank_in(const Rec* seg, const Rec (&x)[N], unsigned (&pos)[N]) {
+  unsigned p[N];
+#pragma unroll
+  for (int k = 0; k < N; ++k) p[k] = 0u;
+#pragma unroll
+  for (int step = kMergeSeg / 2; step >= 0; step = step > 1 ? step / 2 : step - 1)
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+      // (Step 0: the last candidate.)
+      const Rec z = seg[p[k] + (step ? step - 1 : 0)];
+      const bool below = EQ ? !rec_less(x[k], z) : rec_less(z, x[k]);
+      p[k] += below ? (step ? step : 1) : 0;
+    }
+#pragma unroll
+  for (int k = 0; k < N; ++k) pos[k] += p[k];
+}
+
+// The second launch of a list that has grown past kRankList: every record to
+// its place in its own sorted segment plus the numbers of smaller ones in the
+// others, which a workgroup reads through LDS in turn (the next one in flight)
+// while its threads search them for four records each: n^2 / 4096 searches.  2^20
+// records 1.0 ms (1.8 without the one in flight), against 0.2 of the merges.
+__global__ void __launch_bounds__(1024) k_rank_segs(const Rec* __restrict__ a,
+                                                    Rec* __restrict__ out,
+                                                    const unsigned long long* __restrict__ count,
+                                                    long long cap) {
+  __shared__ __align__(16) Rec seg[kMergeSeg];
+  const long long nl = (long long)*count;
+  const unsigned n = (unsigned)(nl < cap ? nl : cap);
+  if (n <= kRankList) return;
+  const uint4* list = reinterpret_cast<const uint4*>(a);
+  constexpr int kPer = kMergeSeg / 1024;
+  for (unsigned long long b0 = blockIdx.x * (unsigned long long)kMergeSeg; b0 < n;
+       b0 += gridDim.x * (unsigned long long)kMergeSeg) {
+    const unsigned b = (unsigned)b0;
+    unsigned long long at = n;                 // the segment in LDS: none yet
+    Rec x[kPer];
+    unsigned pos[kPer];
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+      const unsigned i = b + k * 1024 + threadIdx.x;
+      x[k] = a[i < n ? i : n - 1];
+      pos[k] = i - b;
+    }
+    // The other segments in turn, the next one in flight.
+    uint4 y[kPer];
+    unsigned long long o = b ? 0u : kMergeSeg;
+    for (;;) {
+#pragma unroll
+      for (int k = 0; k < kPer; ++k) {
+        const unsigned long long i = o + k * 1024 + threadIdx.x;
+        y[k] = list[i < n ? i : n - 1];
+        if (i >= n) y[k] = make_uint4(~0u, ~0u, ~0u, ~0u);   // (above every key)
+      }
+      if (at < n) {
+        // (Equal keys keep the segments' order.)
+        if (at < b)
+          rank_in<true>(seg, x, pos);
+        else
+          rank_in<false>(seg, x, pos);
+      }
+      if (o >= n) break;
+      __syncthreads();
+#pragma unroll
+      for (int k = 0; k < kPer; ++k) reinterpret_cast<uint4*>(seg)[k * 1024 + threadIdx.x] = y[k];
+      __syncthreads();
+      at = o;
+      o += o + kMergeSeg == b ? 2 * kMergeSeg : kMergeSeg;
+    }
+#pragma unroll
+    for (int k = 0; k < kPer; ++k)
+      if (b + k * 1024 + threadIdx.x < n) out[pos[k]] = x[k];
     __syncthreads();
   }
 }
@@ -2659,17 +2777,24 @@ uint32_t* ts_cur(pic_ctx* c, int s) { return c->tsb[s][c->tcur[s]]; }
 // Sort a record list of at most cap entries (device count).  The result is in
 // a: the short way sorts into the spare buffer (as large) and swaps the two.
 // The way is chosen by the list's length in the last step (SortList slot;
-// unknown after a load or a failed step): lengths change little from step to
-// step, and either way is right for any length.
-constexpr long long kRankList = 8192;
+// unknown after a load or a failed step), as lengths change little from step
+// to step; either way is right for any length.  most: a bound of the length:
+// up to kRankMost the launch behind the ranks, which finds nothing to do unless
+// the list has jumped, is not worth its 2 us (a 32x32x64 run: 1.6 %), as the
+// ranks of that many take 0.4 ms.
+constexpr long long kRankMost = 32768;
 
 void sort_records(pic_ctx* c, Rec*& a, const unsigned long long* count, long long cap,
-                  SortList slot) {
+                  SortList slot, long long most) {
   hipStream_t st = c->stream;
   const long long hint = c->sort_len[slot];
   if (hint >= 0 && hint <= kRankList) {
     const unsigned grid = (unsigned)std::min<long long>((cap + 63) / 64, 256);
-    k_rank_sort<<<grid, 1024, 0, st>>>(a, c->rec_tmp, count, cap);
+    most = std::min(most, cap);
+    k_rank_sort<<<grid, 1024, 0, st>>>(a, most > kRankMost ? a : nullptr, c->rec_tmp, count, cap);
+    if (most > kRankMost)
+      k_rank_segs<<<(unsigned)std::min<long long>((most + kMergeSeg - 1) / kMergeSeg, 256), 1024,
+                    0, st>>>(a, c->rec_tmp, count, cap);
     std::swap(a, c->rec_tmp);
     return;
   }
@@ -3004,6 +3129,9 @@ void push_collide_t(pic_ctx* c, double dt) {
        &c->dc->kinetic[3]}}};
   k_sum_partials<<<nb3 > 0 ? 4 : 3, 1024, 0, st>>>(sums);
   const long long cap = c->cfg.max_events;
+  // An event per electron, a record per particle that was pushed.
+  const long long n_el = bound(c, 0), n_neu = bound(c, 1);
+  const long long n_push = n_el + n_neu + bound(c, 2) + bound(c, 3);
   tmark(c, PIC_PH_COLLIDE, true);
   if (m.enabled) {
     // Waves: one per chunk, then the unbinned electrons' candidates (at
@@ -3015,12 +3143,12 @@ void push_collide_t(pic_ctx* c, double dt) {
         cur<PT>(c, 0), c->key[0], c->cand, ts_cur(c, 0), c->cand_cnt,
         c->chunks, c->cstart + nt, c->n_binned[0], m, step, seed, c->ev,
         c->flag, cap, c->el_cnt, c->dc);
-    sort_records(c, c->ev, &c->dc->n_events, cap, kSortEvents);
+    sort_records(c, c->ev, &c->dc->n_events, cap, kSortEvents, n_el);
     k_neutral_cands<PT><<<(unsigned)((bound(c, 1) + kNCChunk - 1) / kNCChunk), kT, 0, st>>>(
         cur<PT>(c, 1), c->key[1], c->flag, c->nc, cap, c->dc);
-    sort_records(c, c->nc, &c->dc->n_ncand, cap, kSortNeutrals);
+    sort_records(c, c->nc, &c->dc->n_ncand, cap, kSortNeutrals, n_neu);
     k_match<<<std::min<unsigned>(nblk(cap), kFixedBlocks), kT, 0, st>>>(c->ev, c->nc, c->ok, c->okp, cap, c->dc);
-    sort_records(c, c->ok, &c->dc->n_ok, cap, kSortMatched);
+    sort_records(c, c->ok, &c->dc->n_ok, cap, kSortMatched, n_el);
     k_ionise<PT><<<64, kT, 0, st>>>(cur<PT>(c, 0), cur<PT>(c, 1), cur<PT>(c, 2),
                                     c->key[0], c->key[1], c->key[2], c->ok,
                                     c->okp, m, step, seed, c->cfg.capacity[0],
@@ -3051,7 +3179,7 @@ void push_collide_t(pic_ctx* c, double dt) {
   tmark(c, PIC_PH_COLLIDE, false);
   // Cathode list sorted by (species, id).
   tmark(c, PIC_PH_ABSORBED, true);
-  sort_records(c, c->ab_rec, &c->dc->n_ab, cap, kSortAbsorbed);
+  sort_records(c, c->ab_rec, &c->dc->n_ab, cap, kSortAbsorbed, n_push);
   k_ab_gather<<<64, kT, 0, st>>>(c->ab_rec, c->ab_raw_pos, c->ab_raw_vel,
                                  c->ab_species, c->ab_id, c->ab_pos, c->ab_vel,
                                  cap, c->dc);
@@ -3240,7 +3368,7 @@ void compact_neutrals_t(pic_ctx* c) {
 }  // namespace
 
 void sort_event_records(pic_ctx* c, Rec*& a, unsigned long long* count) {
-  sort_records(c, a, count, c->cfg.max_events, kSortIon2);
+  sort_records(c, a, count, c->cfg.max_events, kSortIon2, c->cfg.max_events);
 }
 
 void parts_md_return(pic_ctx* c, double lattice_a, unsigned mask,

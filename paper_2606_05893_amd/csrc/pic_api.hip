@@ -520,6 +520,7 @@ pic_status pic_init(const pic_config* cfg, void* ws, size_t bytes,
   std::memset(&c->last_solve, 0, sizeof(c->last_solve));
   std::memset(&c->hc, 0, sizeof(c->hc));
   note_list_lengths(c, false);
+  c->last_add = 0;
   c->timing = false;
   c->ev_made = false;
   if (!hip_ok(c, hipMemsetAsync(ws, 0, bytes, c->stream), "workspace clear") ||
@@ -793,6 +794,11 @@ pic_status pic_advance(pic_ctx* c, double dt, pic_absorbed* out,
   long long add[PIC_NSPECIES];
   const pic_status v = advance_check(c, dt, add);
   if (v != PIC_OK) return v;
+  // A burst of new particles may fill lists that were short.
+  long long added = 0;
+  for (long long a : add) added += a;
+  if (added > c->last_add + kRankList) note_list_lengths(c, false);
+  c->last_add = added;
   parts_sources_host(c);
   parts_push_neutral(c, dt);
   const pic_status st = advance_finish(c, dt, add, out, diag);

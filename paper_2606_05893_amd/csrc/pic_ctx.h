@@ -50,6 +50,8 @@ constexpr long long kDirectStepNodes = 1ll << 18;
 constexpr int kDeadList = 4096;
 
 // The sorted record lists of a step.
+// Those of at most kRankList records are sorted by rank (sort_records).
+constexpr long long kRankList = 8192;
 enum SortList { kSortEvents, kSortNeutrals, kSortMatched, kSortAbsorbed, kSortIon2, kSortLists };
 
 struct QueueCall {
@@ -134,6 +136,7 @@ struct pic_ctx {
   uint2* okp;                // (electron, neutral) index of a matched event
   pic::Rec* rec_tmp;         // spare buffer of the record sorts
   long long sort_len[pic::kSortLists];  // lists' lengths last step (-1: unknown)
+  long long last_add;        // particles the last step's sources and queue added
   long long ev_cap_p2;       // power-of-two capacity of the record lists
 
   // Cathode-absorbed list: raw (unsorted) and sorted outputs.
