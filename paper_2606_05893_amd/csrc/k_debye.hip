@@ -5,21 +5,26 @@
 // A workgroup takes a tile of 8^3 cells at a time, which holds whole blocks
 // (block divides 8): it streams the tile's binned electrons and ions once, sums
 // the moments (count, sum of v, sum of |v|^2) per cell in LDS, joins the cells
-// of a block, and forms lambda_D and the criterion there.  Nothing but lambda_D
-// is written.  Ions outside their tile (the unbinned tail, and ions that
-// crossed a tile face since the last binning) are few: their moments go to a
-// global record per block first, in the tiles they flag.
+// of a block, and forms lambda_D and the criterion there; with one block a tile
+// a wave sums it in registers.  Nothing but lambda_D is written.  The
+// workgroups' runs of tiles hold as many particles each.
+//
+// Two kinds of particles go to a global record per block first, cleared where
+// there are any and added in by the workgroup of the tile: the ions outside their
+// tile (the unbinned tail, and ions that crossed a tile face since the last
+// binning), and those of crowded tiles, which many workgroups share, a chunk of
+// the push at a time.
 //
 // Bound: the LDS adds (four FP64 and a count per particle) beside the 48 bytes
-// (28 mixed) read per particle.  On 128x128x512 cells with 10 M electrons and 10
-// M ions 246 us for blocks of 1 and of 8 (the read alone 190).  Summing each 2048 particles in a
-// hash table and adding every entry to its block's 80-byte record took 3390 and
-// 630 us: with blocks of one cell nearly every particle was its own global
-// atomic, and the records were cleared, added to and read back.
-//
-// That form stays where tiles are crowded (more than kCrowded particles on
-// average): there a tile per workgroup would leave the chip idle, and a
-// workgroup's particles fall into few blocks.
+// (28 mixed) read per particle.  A check of 10 M electrons and 10 M ions on
+// 128x128x512 cells, just binned: 231 us for blocks of 1, 114 for blocks of 8
+// (24 bytes read per particle); after steps, which leave some thousand ions
+// outside their tiles, 60 more.  All of them in the lowest eighth of the box 235
+// and 160, in a 64x64x16 corner 830 and 252; 4 M in one tile of 64^3 cells 505 and
+// 129.  (Summing each 2048 particles in a hash table and adding every entry to
+// its block's record: 3230 and 630, 1600 and 630, 1510 and 630, 900 and 205.  Equal
+// runs of tiles and no crowded ones: 232 and 270, 890 and 930, 5180 and 5200,
+// 10300.)
 #include <algorithm>
 #include <cmath>
 
@@ -29,14 +34,11 @@ namespace pic {
 namespace {
 
 constexpr int kT = 256;
-constexpr int kPer = 8;                 // particles per thread
-constexpr int kDChunk = kT * kPer;      // particles per workgroup
-constexpr int kHash = 1024;             // LDS table entries
 constexpr int kMom = 5;                 // count, sum vx, vy, vz, sum |v|^2
-constexpr unsigned kEmpty = 0xFFFFFFFFu;
-constexpr int kFinBlocks = 1024;
+constexpr int kFinBlocks = kRuns;
 constexpr int kCells = kTile * kTile * kTile;
-constexpr long long kCrowded = 8192;
+// A tile's clearing and finishing in particles' time.
+constexpr unsigned kTileCost = 256;
 
 struct BlockGeo {
   int b, bx, by;                        // block edge (cells), blocks per axis
@@ -136,38 +138,85 @@ __device__ __forceinline__ unsigned tile_of(int i, int j, int k, const GridC& g)
   return ((unsigned)(k / kTile) * g.tny + j / kTile) * g.tnx + i / kTile;
 }
 
-// The ions outside their tile.  ADD = false: flag the tiles they are in; true:
-// add their moments to their blocks' records.  Workgroup t < ntiles scans tile
-// t's binned ions, the others the tail.
-template <class PT, bool ADD>
-__global__ void __launch_bounds__(kT) k_debye_strays(PT p, long long n, long long n_binned,
-                                                     const uint32_t* __restrict__ ts, unsigned nt,
-                                                     GridC g, BlockGeo q,
-                                                     uint32_t* __restrict__ flag,
-                                                     double* __restrict__ mom) {
+// The tiles' particles in the chunks of the push: (tile, piece k) covers up to
+// kPushChunk of its electrons and of its ions.
+struct Chunks {
+  const uint32_t* ts[2];                // tile starts: electrons, ions
+  const uint2* chunks;
+  const unsigned* cstart;               // a tile's first chunk
+  unsigned nt;
+  unsigned most;                        // chunks of a tile that is not crowded
+  bool uneven;                          // equal runs of tiles are not equal work
+  __device__ unsigned total() const { return cstart[nt]; }
+  __device__ void range(int s, unsigned t, unsigned k, long long& a, long long& b) const {
+    a = ts[s][t] + (long long)k * kPushChunk;
+    b = ts[s][t + 1];
+    if (a > b) a = b;
+    if (b - a > kPushChunk) b = a + kPushChunk;
+  }
+  __device__ bool crowded(unsigned t) const { return cstart[t + 1] - cstart[t] > most; }
+};
+
+// The ions outside their tile, found in one pass over the positions: their blocks
+// get a bit, their blocks' ion records are cleared and they go to a list, whose
+// moments k_debye_add puts in the records.  Workgroup c < nchb scans the binned
+// ions of chunk c (if there is one), the others the tail.
+struct Strays {
+  uint32_t* bits;                       // a bit per block (null: no ion is outside)
+  Rec* list;                            // block, ion
+  unsigned long long* n;
+  unsigned long long cap;               // (never reached: stray_cap)
+  __device__ bool has(long long r) const { return bits && (bits[r >> 5] >> (r & 31) & 1u); }
+};
+
+__global__ void k_debye_none(Strays S, long long blocks) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) *S.n = 0;
+  const long long words = (blocks + 31) / 32;
+  for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < words;
+       i += (long long)gridDim.x * blockDim.x)
+    S.bits[i] = 0u;
+}
+
+template <class PT>
+__global__ void __launch_bounds__(kT) k_debye_find(PT p, long long n, long long n_binned, Chunks C,
+                                                   unsigned nchb, GridC g, BlockGeo q, Strays S,
+                                                   double* __restrict__ mom) {
   long long a, b, step = kT;
   unsigned own = 0xFFFFFFFFu;
-  if (blockIdx.x < nt) {
-    own = blockIdx.x;
-    a = ts[own];
-    b = ts[own + 1];
+  if (blockIdx.x < nchb) {
+    if (blockIdx.x >= C.total()) return;
+    own = C.chunks[blockIdx.x].x;
+    C.range(1, own, C.chunks[blockIdx.x].y, a, b);
   } else {
-    a = n_binned + (long long)(blockIdx.x - nt) * kT;
+    a = n_binned + (long long)(blockIdx.x - nchb) * kT;
     b = n;
-    step = (long long)(gridDim.x - nt) * kT;
+    step = (long long)(gridDim.x - nchb) * kT;
   }
   for (long long idx = a + threadIdx.x; idx < b; idx += step) {
     int i, j, k;
     cell_ijk(p, idx, g, i, j, k);
-    const unsigned t = tile_of(i, j, k, g);
-    if (t == own) continue;
-    if (!ADD) {
-      flag[t] = 1u;
-      continue;
-    }
+    if (tile_of(i, j, k, g) == own) continue;
+    const unsigned r = block_of(i, j, k, q);
+    atomicOr(&S.bits[r >> 5], 1u << (r & 31));
+    for (int m = kMom; m < 2 * kMom; ++m) mom[(size_t)r * (2 * kMom) + m] = 0.0;
+    Rec x;
+    x.lo = r;
+    x.hi = 0u;
+    x.val = (unsigned)idx;
+    const unsigned long long slot = atomicAdd(S.n, 1ull);
+    if (slot < S.cap) S.list[slot] = x;
+  }
+}
+
+template <class PT>
+__global__ void __launch_bounds__(kT) k_debye_add(PT p, Strays S, double* __restrict__ mom) {
+  const long long n = (long long)min(*S.n, S.cap);
+  for (long long x = blockIdx.x * (long long)kT + threadIdx.x; x < n;
+       x += (long long)gridDim.x * kT) {
+    const Rec y = S.list[x];
     double vx, vy, vz;
-    Acc<PT>::vel(p, idx, vx, vy, vz);
-    double* rec = mom + (size_t)block_of(i, j, k, q) * (2 * kMom) + kMom;
+    Acc<PT>::vel(p, y.val, vx, vy, vz);
+    double* rec = mom + (size_t)y.lo * (2 * kMom) + kMom;
     atomicAdd(rec + 0, 1.0);
     atomicAdd(rec + 1, vx);
     atomicAdd(rec + 2, vy);
@@ -176,238 +225,377 @@ __global__ void __launch_bounds__(kT) k_debye_strays(PT p, long long n, long lon
   }
 }
 
-// The blocks of a tile in LDS order (cells of a block are consecutive): block
-// bl of the tile, or -1 where the grid ends inside it.
-__device__ __forceinline__ long long tile_block(unsigned t, int bl, const GridC& g,
-                                                const BlockGeo& q) {
-  const int e = kTile / q.b;
-  const int tx = (int)(t % g.tnx), ty = (int)(t / g.tnx % g.tny), tz = (int)(t / (g.tnx * g.tny));
-  const int bx = tx * e + bl % e, by = ty * e + bl / e % e, bz = tz * e + bl / (e * e);
-  if (bx * q.b >= g.nx || by * q.b >= g.ny || bz * q.b >= g.nz) return -1;
-  return ((long long)bz * q.by + by) * q.bx + bx;
-}
+// A tile: its first cell, and its blocks (edge 1 << LGB): block(bl) is block bl
+// of it, or -1 where the grid ends inside the tile.
+template <int LGB>
+struct TileGeo {
+  int x, y, z;
+  __device__ TileGeo(unsigned t, const GridC& g) {
+    const unsigned r = t / (unsigned)g.tnx;
+    x = (int)(t % (unsigned)g.tnx) * kTile;
+    y = (int)(r % (unsigned)g.tny) * kTile;
+    z = (int)(r / (unsigned)g.tny) * kTile;
+  }
+  __device__ __forceinline__ long long block(int bl, const GridC& g, const BlockGeo& q) const {
+    constexpr int le = 3 - LGB, m = (1 << le) - 1;   // (kTile = 8)
+    const int bx = (x >> LGB) + (bl & m), by = (y >> LGB) + ((bl >> le) & m),
+              bz = (z >> LGB) + (bl >> (2 * le));
+    if (bx << LGB >= g.nx || by << LGB >= g.ny || bz << LGB >= g.nz) return -1;
+    return ((long long)bz * q.by + by) * q.bx + bx;
+  }
+};
+static_assert(kTile == 8, "TileGeo::block");
 
-// Clear the stray records of flagged tiles.
-__global__ void __launch_bounds__(kT) k_debye_clear(const uint32_t* __restrict__ flag, unsigned nt,
-                                                    GridC g, BlockGeo q, double* __restrict__ mom) {
-  const int e = kTile / q.b, nb = e * e * e;
-  for (unsigned t = blockIdx.x; t < nt; t += gridDim.x) {
-    if (!flag[t]) continue;
-    for (int bl = threadIdx.x; bl < nb; bl += kT) {
-      const long long r = tile_block(t, bl, g, q);
+// Clear the records of crowded tiles.
+template <int LGB>
+__global__ void __launch_bounds__(kT) k_debye_clear(Chunks C, GridC g, BlockGeo q,
+                                                    double* __restrict__ mom) {
+  for (unsigned t = blockIdx.x; t < C.nt; t += gridDim.x) {
+    if (!C.crowded(t)) continue;
+    const TileGeo<LGB> o(t, g);
+    for (int bl = threadIdx.x; bl < kCells >> (3 * LGB); bl += kT) {
+      const long long r = o.block(bl, g, q);
       if (r < 0) continue;
       for (int m = 0; m < 2 * kMom; ++m) mom[r * (2 * kMom) + m] = 0.0;
     }
   }
 }
 
-// Tiles: moments per cell in LDS, joined per block, lambda_D.  flag: null when
-// no ion is outside its tile.
-template <class PT>
-__global__ void __launch_bounds__(kT) k_debye_tiles(
-    PT pe, PT pi, const uint32_t* __restrict__ tse, const uint32_t* __restrict__ tsi, unsigned nt,
-    GridC g, BlockGeo q, DebyeC d, const uint32_t* __restrict__ flag,
-    const double* __restrict__ mom, double* __restrict__ lam_out, long long* __restrict__ qpart,
-    double* __restrict__ part) {
-  __shared__ double hv[2][4][kCells];
-  __shared__ unsigned hn[2][kCells];
-  const int lgb = 31 - __clz(q.b), e = kTile >> lgb;
-  DebyeTally y;
-  // Contiguous tiles per workgroup, one XCD's workgroups side by side.
-  const unsigned wg = xcd_block(blockIdx.x, gridDim.x);
-  const unsigned t0 = (unsigned)((unsigned long long)nt * wg / gridDim.x);
-  const unsigned t1 = (unsigned)((unsigned long long)nt * (wg + 1) / gridDim.x);
-  for (unsigned t = t0; t < t1; ++t) {
-    for (int c = threadIdx.x; c < kCells; c += kT)
+// A block's record, of its ions alone where no electron is in it, and its sums.
+__device__ __forceinline__ void record_read(const double* __restrict__ mom, long long r, bool ions,
+                                            double (&mo)[2][kMom]) {
 #pragma unroll
-      for (int s = 0; s < 2; ++s) {
-        hn[s][c] = 0u;
+  for (int s = 0; s < 2; ++s)
+    if (s || !ions)
 #pragma unroll
-        for (int m = 0; m < 4; ++m) hv[s][m][c] = 0.0;
-      }
-    __syncthreads();
-    const int tx = (int)(t % g.tnx), ty = (int)(t / g.tnx % g.tny), tz = (int)(t / (g.tnx * g.tny));
+    for (int m = 0; m < kMom; ++m) mo[s][m] += mom[r * (2 * kMom) + s * kMom + m];
+}
+__device__ __forceinline__ void record_add(double* __restrict__ mom, long long r,
+                                           const double (&mo)[2][kMom]) {
 #pragma unroll
-    for (int s = 0; s < 2; ++s) {
-      const PT p = s ? pi : pe;
-      const long long a = (s ? tsi : tse)[t], b = (s ? tsi : tse)[t + 1];
-      for (long long idx = a + threadIdx.x; idx < b; idx += kT) {
-        int i, j, k;
-        cell_ijk(p, idx, g, i, j, k);
-        double vx, vy, vz;
-        Acc<PT>::vel(p, idx, vx, vy, vz);
-        i -= tx * kTile;
-        j -= ty * kTile;
-        k -= tz * kTile;
-        // An ion that left its tile is in its block's stray record.
-        if ((unsigned)i >= kTile || (unsigned)j >= kTile || (unsigned)k >= kTile) continue;
-        const int bl = ((k >> lgb) * e + (j >> lgb)) * e + (i >> lgb);
-        const int w = q.b - 1;
-        const int c = (((bl << lgb | (k & w)) << lgb | (j & w)) << lgb) | (i & w);
-        atomicAdd(&hn[s][c], 1u);
-        atomicAdd(&hv[s][0][c], vx);
-        atomicAdd(&hv[s][1][c], vy);
-        atomicAdd(&hv[s][2][c], vz);
-        atomicAdd(&hv[s][3][c], (vx * vx + vy * vy) + vz * vz);
-      }
-    }
-    __syncthreads();
-    const bool strays = flag && flag[t];
-    auto finish = [&](int bl, double (&mo)[2][kMom]) {
-      const long long r = tile_block(t, bl, g, q);
-      if (r < 0) return;
-      if (strays)
+  for (int s = 0; s < 2; ++s)
+    if (mo[s][0] > 0.0)
 #pragma unroll
-        for (int s = 0; s < 2; ++s)
-#pragma unroll
-          for (int m = 0; m < kMom; ++m) mo[s][m] += mom[r * (2 * kMom) + s * kMom + m];
-      const double lam = block_lambda(mo, d, y);
-      if (lam_out) lam_out[r] = lam;
-    };
-    if (q.b == 1) {
-      for (int c = threadIdx.x; c < kCells; c += kT) {
-        double mo[2][kMom];
-#pragma unroll
-        for (int s = 0; s < 2; ++s) {
-          mo[s][0] = (double)hn[s][c];
-#pragma unroll
-          for (int m = 0; m < 4; ++m) mo[s][m + 1] = hv[s][m][c];
-        }
-        finish(c, mo);
-      }
-      __syncthreads();
-    } else {
-      // Two neighbouring cells per thread, then b^3 / 2 lanes of a block.
-      double mo[2][kMom];
-      const int c = 2 * threadIdx.x;
-#pragma unroll
-      for (int s = 0; s < 2; ++s) {
-        mo[s][0] = (double)(hn[s][c] + hn[s][c + 1]);
-#pragma unroll
-        for (int m = 0; m < 4; ++m) mo[s][m + 1] = hv[s][m][c] + hv[s][m][c + 1];
-      }
-      const int lanes = (q.b * q.b * q.b) / 2;
-      for (int o = (lanes < 64 ? lanes : 64) / 2; o > 0; o >>= 1)
-#pragma unroll
-        for (int s = 0; s < 2; ++s)
-#pragma unroll
-          for (int m = 0; m < kMom; ++m) mo[s][m] += __shfl_down(mo[s][m], o);
-      __syncthreads();
-      if (lanes > 64) {  // one block: the four waves' sums through LDS
-        double* w = &hv[0][0][0];
-        if ((threadIdx.x & 63) == 0)
-#pragma unroll
-          for (int s = 0; s < 2; ++s)
-#pragma unroll
-            for (int m = 0; m < kMom; ++m) w[(threadIdx.x >> 6) * 2 * kMom + s * kMom + m] = mo[s][m];
-        __syncthreads();
-        if (threadIdx.x == 0)
-#pragma unroll
-          for (int s = 0; s < 2; ++s)
-#pragma unroll
-            for (int m = 0; m < kMom; ++m) {
-              const int o = s * kMom + m;
-              mo[s][m] = (w[o] + w[2 * kMom + o]) + (w[4 * kMom + o] + w[6 * kMom + o]);
-            }
-        __syncthreads();
-      }
-      if ((threadIdx.x & (lanes - 1)) == 0) finish(threadIdx.x / lanes, mo);
-    }
-  }
-  tally_out(&hv[0][0][0], y, qpart, part);
+      for (int m = 0; m < kMom; ++m) atomicAdd(&mom[r * (2 * kMom) + s * kMom + m], mo[s][m]);
 }
 
-// Moments of one species (slot sidx of the block record) summed per block.
-template <class PT>
-__global__ void __launch_bounds__(kT) k_debye_acc(PT p, long long n, int sidx,
-                                                  GridC g, BlockGeo q,
-                                                  double* __restrict__ mom) {
-  __shared__ unsigned hk[kHash];
-  __shared__ double hv[kMom][kHash];
-  const long long base = (long long)blockIdx.x * kDChunk;
-  if (base >= n) return;
-  for (int t = threadIdx.x; t < kHash; t += kT) {
-    hk[t] = kEmpty;
+// ---- blocks of 1, 2 and 4 cells ----------------------------------------------
+// A tile's moments in LDS, per cell with those of a block side by side, or where
+// a tile has few particles (kFew) per block.
+struct TileMom {
+  double v[2][4][kCells];
+  unsigned n[2][kCells];
+};
+constexpr unsigned kFew = 1024;
+
+__device__ __forceinline__ void tile_clear(TileMom& L, int places) {
+  for (int c = threadIdx.x; c < places; c += kT)
 #pragma unroll
-    for (int m = 0; m < kMom; ++m) hv[m][t] = 0.0;
-  }
-  __syncthreads();
-  for (int r = 0; r < kPer; ++r) {
-    const long long idx = base + (long long)r * kT + threadIdx.x;
-    if (idx >= n) break;
+    for (int s = 0; s < 2; ++s) {
+      L.n[s][c] = 0u;
+#pragma unroll
+      for (int m = 0; m < 4; ++m) L.v[s][m][c] = 0.0;
+    }
+}
+
+// Particles [a, b) of species s, those inside the tile.
+template <int LGB, class PT>
+__device__ __forceinline__ void tile_add(TileMom& L, const PT& p, int s, long long a, long long b,
+                                         bool few, const TileGeo<LGB>& o, const GridC& g) {
+  constexpr int e = kTile >> LGB, w = (1 << LGB) - 1;
+  for (long long idx = a + threadIdx.x; idx < b; idx += kT) {
     int i, j, k;
     cell_ijk(p, idx, g, i, j, k);
     double vx, vy, vz;
     Acc<PT>::vel(p, idx, vx, vy, vz);
-    const unsigned key = block_of(i, j, k, q);
-    const double v2 = (vx * vx + vy * vy) + vz * vz;
-    unsigned h = (key * 2654435761u) & (kHash - 1);
-    int slot = -1;
-    for (int probe = 0; probe < 32; ++probe) {
-      const unsigned old = atomicCAS(&hk[h], kEmpty, key);
-      if (old == kEmpty || old == key) {
-        slot = (int)h;
-        break;
+    i -= o.x;
+    j -= o.y;
+    k -= o.z;
+    // An ion that left its tile is in its block's record.
+    if ((unsigned)i >= kTile || (unsigned)j >= kTile || (unsigned)k >= kTile) continue;
+    int c = ((k >> LGB) * e + (j >> LGB)) * e + (i >> LGB);
+    if (LGB > 0 && !few) c = (((c << LGB | (k & w)) << LGB | (j & w)) << LGB) | (i & w);
+    atomicAdd(&L.n[s][c], 1u);
+    atomicAdd(&L.v[s][0][c], vx);
+    atomicAdd(&L.v[s][1][c], vy);
+    atomicAdd(&L.v[s][2][c], vz);
+    atomicAdd(&L.v[s][3][c], (vx * vx + vy * vy) + vz * vz);
+  }
+}
+
+// The tile's sums, each block's passed once to f(block of the tile, moments); all
+// threads call it, the sums are consumed.
+template <int LGB, class F>
+__device__ __forceinline__ void tile_join(TileMom& L, bool few, F f) {
+  constexpr int kLgc = 3 * LGB, kNb = kCells >> kLgc;
+  if (LGB == 0 || few) {
+    for (int c = threadIdx.x; c < kNb; c += kT) {
+      double mo[2][kMom];
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        mo[s][0] = (double)L.n[s][c];
+#pragma unroll
+        for (int m = 0; m < 4; ++m) mo[s][m + 1] = L.v[s][m][c];
       }
-      h = (h + 1) & (kHash - 1);
+      f(c, mo);
     }
-    if (slot >= 0) {
-      atomicAdd(&hv[0][slot], 1.0);
-      atomicAdd(&hv[1][slot], vx);
-      atomicAdd(&hv[2][slot], vy);
-      atomicAdd(&hv[3][slot], vz);
-      atomicAdd(&hv[4][slot], v2);
-    } else {
-      // Table crowded: straight to the global record.
-      double* rec = mom + (size_t)key * (2 * kMom) + sidx * kMom;
-      atomicAdd(rec + 0, 1.0);
-      atomicAdd(rec + 1, vx);
-      atomicAdd(rec + 2, vy);
-      atomicAdd(rec + 3, vz);
-      atomicAdd(rec + 4, v2);
+    __syncthreads();
+    return;
+  }
+  // 2 kMom sums a block over its cells, by one thread each (two for blocks of 4;
+  // the cells' order turned by the block, so that the threads of a wave meet
+  // other banks), left in LDS for one thread a block.  (Every thread with all the
+  // sums of two cells, and then rounds of shuffles: 256 us at 128x128x512 for
+  // blocks of 4.)
+  constexpr int kLgp = LGB == 2 ? 1 : 0, kSums = 2 * kMom * kNb;
+  constexpr int kRounds = ((kSums << kLgp) + kT - 1) / kT;
+  double r[kRounds];
+#pragma unroll
+  for (int z = 0; z < kRounds; ++z) {
+    const int x = (z * kT + (int)threadIdx.x) >> kLgp;
+    r[z] = 0.0;
+    if (x < kSums) {
+      const int bl = x & (kNb - 1), m = x / kNb, sp = m >= kMom ? 1 : 0, q = m - sp * kMom;
+      constexpr int per = 1 << (kLgc - kLgp);
+      const int at = (bl << kLgc) + (threadIdx.x & ((1 << kLgp) - 1));
+#pragma unroll 4
+      for (int k = 0; k < per; ++k) {
+        const int c = at + (((k + bl) & (per - 1)) << kLgp);
+        r[z] += q == 0 ? (double)L.n[sp][c] : L.v[sp][q - 1][c];
+      }
     }
+    if (kLgp) r[z] += __shfl_down(r[z], 1);
   }
   __syncthreads();
-  for (int t = threadIdx.x; t < kHash; t += kT) {
-    const unsigned key = hk[t];
-    if (key == kEmpty) continue;
-    double* rec = mom + (size_t)key * (2 * kMom) + sidx * kMom;
+  double* w = &L.v[0][0][0];
 #pragma unroll
-    for (int m = 0; m < kMom; ++m) atomicAdd(rec + m, hv[m][t]);
+  for (int z = 0; z < kRounds; ++z) {
+    const int x = (z * kT + (int)threadIdx.x) >> kLgp;
+    if (x < kSums && (threadIdx.x & ((1 << kLgp) - 1)) == 0) w[x] = r[z];
   }
-}
-
-__global__ void k_debye_zero_u32(uint32_t* __restrict__ p, unsigned n) {
-  for (unsigned i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x)
-    p[i] = 0u;
-}
-
-__global__ void k_debye_zero(double* __restrict__ mom, long long n) {
-  const long long stride = (long long)gridDim.x * blockDim.x;
-  for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n;
-       i += stride)
-    mom[i] = 0.0;
-}
-
-// lambda_D per block from the global records; block partials of (checked,
-// unresolved) counts, the smallest lambda_D and the largest dx / d_max.
-__global__ void __launch_bounds__(kT) k_debye_final(
-    const double* __restrict__ mom, long long nb, DebyeC d,
-    double* __restrict__ lam_out, long long* __restrict__ qpart,
-    double* __restrict__ part) {
-  DebyeTally y;
-  const long long stride = (long long)gridDim.x * blockDim.x;
-  for (long long b = blockIdx.x * (long long)blockDim.x + threadIdx.x; b < nb;
-       b += stride) {
+  __syncthreads();
+  if (threadIdx.x < kNb) {
     double mo[2][kMom];
 #pragma unroll
-    for (int s = 0; s < 2; ++s)
-#pragma unroll
-      for (int m = 0; m < kMom; ++m) mo[s][m] = mom[(size_t)b * (2 * kMom) + s * kMom + m];
-    const double lam = block_lambda(mo, d, y);
-    if (lam_out) lam_out[b] = lam;
+    for (int m = 0; m < 2 * kMom; ++m) mo[m / kMom][m % kMom] = w[m * kNb + threadIdx.x];
+    f(threadIdx.x, mo);
   }
+  __syncthreads();
+}
+
+// Crowded tiles: two chunks of one per workgroup at a time (one for blocks of
+// more than a cell, whose records are few), their sums added to the records.
+template <class PT, int LGB>
+__global__ void __launch_bounds__(kT) k_debye_pieces(PT pe, PT pi, Chunks C, GridC g, BlockGeo q,
+                                                     double* __restrict__ mom) {
+  __shared__ TileMom L;
+  constexpr unsigned kRun = LGB == 0 ? 2 : 1;
+  const unsigned nch = C.total();
+  for (unsigned c0 = blockIdx.x; c0 < nch; c0 += gridDim.x) {
+    const unsigned t = C.chunks[c0].x;
+    if (C.chunks[c0].y % kRun || !C.crowded(t)) continue;
+    const unsigned end = min(c0 + kRun, C.cstart[t + 1]);
+    const TileGeo<LGB> o(t, g);
+    __syncthreads();
+    tile_clear(L, kCells);
+    __syncthreads();
+    for (unsigned c = c0; c < end; ++c)
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        long long a, b;
+        C.range(s, t, C.chunks[c].y, a, b);
+        tile_add(L, s ? pi : pe, s, a, b, false, o, g);
+      }
+    __syncthreads();
+    tile_join<LGB>(L, false, [&](int bl, double (&mo)[2][kMom]) {
+      const long long r = o.block(bl, g, q);
+      if (r >= 0) record_add(mom, r, mo);
+    });
+  }
+}
+
+// The first tile whose particles, with those of the tiles before it and
+// kTileCost a tile, reach target (nt: none); by the workgroup, 256 probes a
+// round.
+__device__ __forceinline__ unsigned long long tile_weight(const Chunks& C, unsigned t) {
+  return (unsigned long long)C.ts[0][t] + C.ts[1][t] + (unsigned long long)kTileCost * t;
+}
+__device__ unsigned first_tile(const Chunks& C, unsigned long long target) {
+  unsigned lo = 0, len = C.nt + 1;      // candidates; the last one holds
+  while (len > 1) {
+    const unsigned step = (len + kT - 1) / kT;
+    const unsigned at = min((threadIdx.x + 1) * step, len) - 1;
+    const unsigned c = (unsigned)__syncthreads_count(tile_weight(C, lo + at) < target);
+    lo += c * step;
+    len = min(step, len - c * step);
+  }
+  return lo;
+}
+
+// The workgroup's tiles, contiguous, one XCD's workgroups side by side: equal runs
+// where these hold about as many particles, else runs of equal weight (one tile
+// more than the mean is 6 % of 128x128x512 evenly filled cells).
+__device__ __forceinline__ void tile_run(const Chunks& C, unsigned& t0, unsigned& t1) {
+  const unsigned wg = xcd_block(blockIdx.x, gridDim.x);
+  t0 = (unsigned)((unsigned long long)C.nt * wg / gridDim.x);
+  t1 = (unsigned)((unsigned long long)C.nt * (wg + 1) / gridDim.x);
+  if (C.uneven) {
+    const unsigned long long all = tile_weight(C, C.nt);
+    t0 = first_tile(C, all * wg / gridDim.x);
+    t1 = first_tile(C, all * (wg + 1) / gridDim.x);
+  }
+}
+
+// Tiles: their moments, and the records of crowded ones and of stray ions, to
+// lambda_D.
+template <class PT, int LGB>
+__global__ void __launch_bounds__(kT) k_debye_tiles(
+    PT pe, PT pi, Chunks C, GridC g, BlockGeo q, DebyeC d, Strays S,
+    const double* __restrict__ mom, double* __restrict__ lam_out, long long* __restrict__ qpart,
+    double* __restrict__ part) {
+  __shared__ TileMom L;
+  constexpr int kNb = kCells >> (3 * LGB);
+  DebyeTally y;
+  unsigned t0, t1;
+  tile_run(C, t0, t1);
+  // Starts of the tile's electrons, ions and chunks, the next tile's loaded a
+  // tile ahead: whether and how to clear the sums depends on them.
+  struct Starts {
+    unsigned e, i, c;
+  };
+  auto starts = [&](unsigned t) {
+    t = min(t, C.nt);
+    return Starts{C.ts[0][t], C.ts[1][t], C.cstart[t]};
+  };
+  Starts a, b = starts(t0), next = starts(t0 + 1);
+  for (unsigned t = t0; t < t1; ++t) {
+    a = b;
+    b = next;
+    next = starts(t + 2);
+    const bool pieces = b.c - a.c > C.most;
+    const TileGeo<LGB> o(t, g);
+    const unsigned n = pieces ? 0u : (b.e - a.e) + (b.i - a.i);
+    auto finish = [&](int bl, double (&mo)[2][kMom]) {
+      const long long r = o.block(bl, g, q);
+      if (r < 0) return;
+      if (pieces || S.has(r)) record_read(mom, r, !pieces, mo);
+      const double lam = block_lambda(mo, d, y);
+      if (lam_out) lam_out[r] = lam;
+    };
+    if (n == 0u) {
+      for (int bl = threadIdx.x; (lam_out || S.bits || pieces) && bl < kNb; bl += kT) {
+        double mo[2][kMom] = {};
+        finish(bl, mo);
+      }
+      continue;
+    }
+    const bool few = LGB > 0 && n < kFew;
+    tile_clear(L, few ? kNb : kCells);
+    __syncthreads();
+    tile_add(L, pe, 0, a.e, b.e, few, o, g);
+    tile_add(L, pi, 1, a.i, b.i, few, o, g);
+    __syncthreads();
+    tile_join<LGB>(L, few, finish);
+  }
+  __syncthreads();
+  tally_out(&L.v[0][0][0], y, qpart, part);
+}
+
+// ---- blocks of a whole tile ------------------------------------------------------
+// No cells, so a wave sums a tile in registers and reads the velocities alone (the
+// electrons lie in their tiles, the ions too unless some are strays): 114
+// us at 128x128x512 against 268 through LDS.
+
+// Sums of particles [a, b) (IN: those inside the tile) by a wave, a part per lane.
+template <class PT, bool IN>
+__device__ __forceinline__ void wave_add(double (&mo)[kMom], const PT& p, long long a, long long b,
+                                         const TileGeo<3>& o, const GridC& g) {
+  // Four at a time, all loads in flight before the first sum.
+  constexpr int kN = 4;
+  for (long long idx = a + (threadIdx.x & 63); idx < b; idx += 64 * kN) {
+    double v[kN][3];
+    bool in[kN];
+#pragma unroll
+    for (int u = 0; u < kN; ++u) {
+      const long long x = idx + 64 * u, at = x < b ? x : b - 1;
+      Acc<PT>::vel(p, at, v[u][0], v[u][1], v[u][2]);
+      in[u] = x < b;
+      if (IN) {
+        int i, j, k;
+        cell_ijk(p, at, g, i, j, k);
+        in[u] = in[u] && (unsigned)(i - o.x) < kTile && (unsigned)(j - o.y) < kTile &&
+                (unsigned)(k - o.z) < kTile;
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < kN; ++u) {
+      const double x = in[u] ? v[u][0] : 0.0, y = in[u] ? v[u][1] : 0.0, z = in[u] ? v[u][2] : 0.0;
+      mo[0] += in[u] ? 1.0 : 0.0;
+      mo[1] += x;
+      mo[2] += y;
+      mo[3] += z;
+      mo[4] += (x * x + y * y) + z * z;
+    }
+  }
+}
+
+template <class PT>
+__device__ __forceinline__ void wave_sums(double (&mo)[2][kMom], const PT& pe, const PT& pi,
+                                          long long ae, long long be, long long ai, long long bi,
+                                          bool strays, const TileGeo<3>& o, const GridC& g) {
+  wave_add<PT, false>(mo[0], pe, ae, be, o, g);
+  if (strays)
+    wave_add<PT, true>(mo[1], pi, ai, bi, o, g);
+  else
+    wave_add<PT, false>(mo[1], pi, ai, bi, o, g);
+#pragma unroll
+  for (int s = 0; s < 2; ++s)
+#pragma unroll
+    for (int m = 0; m < kMom; ++m)
+      for (int x = 32; x > 0; x >>= 1) mo[s][m] += __shfl_down(mo[s][m], x);
+}
+
+// Crowded tiles, a chunk per wave.
+template <class PT>
+__global__ void __launch_bounds__(kT) k_debye_whole_pieces(PT pe, PT pi, Chunks C, GridC g,
+                                                           BlockGeo q, bool strays,
+                                                           double* __restrict__ mom) {
+  const unsigned nch = C.total(), nw = gridDim.x * (kT / 64);
+  for (unsigned c = blockIdx.x * (kT / 64) + threadIdx.x / 64; c < nch; c += nw) {
+    const unsigned t = C.chunks[c].x;
+    if (!C.crowded(t)) continue;
+    const TileGeo<3> o(t, g);
+    long long ae, be, ai, bi;
+    C.range(0, t, C.chunks[c].y, ae, be);
+    C.range(1, t, C.chunks[c].y, ai, bi);
+    double mo[2][kMom] = {};
+    wave_sums(mo, pe, pi, ae, be, ai, bi, strays, o, g);
+    if ((threadIdx.x & 63) == 0) record_add(mom, o.block(0, g, q), mo);
+  }
+}
+
+template <class PT>
+__global__ void __launch_bounds__(kT) k_debye_whole(
+    PT pe, PT pi, Chunks C, GridC g, BlockGeo q, DebyeC d, Strays S,
+    const double* __restrict__ mom, double* __restrict__ lam_out, long long* __restrict__ qpart,
+    double* __restrict__ part) {
   __shared__ double lds[4 * kT];
+  DebyeTally y;
+  unsigned t0, t1;
+  tile_run(C, t0, t1);
+  for (unsigned t = t0 + threadIdx.x / 64; t < t1; t += kT / 64) {
+    const TileGeo<3> o(t, g);
+    const bool pieces = C.crowded(t);
+    double mo[2][kMom] = {};
+    if (!pieces)
+      wave_sums(mo, pe, pi, C.ts[0][t], C.ts[0][t + 1], C.ts[1][t], C.ts[1][t + 1],
+                S.bits != nullptr, o, g);
+    if (threadIdx.x & 63) continue;
+    const long long r = o.block(0, g, q);
+    if (pieces || S.has(r)) record_read(mom, r, !pieces, mo);
+    const double lam = block_lambda(mo, d, y);
+    if (lam_out) lam_out[r] = lam;
+  }
   tally_out(lds, y, qpart, part);
 }
 
@@ -455,42 +643,54 @@ Parts species_arrays<Parts>(pic_ctx* c, int s) { return c->P[s][c->cur[s]]; }
 template <>
 PartsM species_arrays<PartsM>(pic_ctx* c, int s) { return c->PM[s][c->cur[s]]; }
 
-template <class PT>
-void accumulate(pic_ctx* c, const BlockGeo& q) {
-  const int sp[2] = {0, 2};
-  for (int k = 0; k < 2; ++k) {
-    const int s = sp[k];
-    const long long n = c->n[s];
-    if (n <= 0) continue;
-    const unsigned nblk = (unsigned)((n + kDChunk - 1) / kDChunk);
-    k_debye_acc<PT><<<nblk, kT, 0, c->stream>>>(species_arrays<PT>(c, s), n,
-                                                 k, c->g, q, c->dbg_mom);
+template <class PT, int LGB>
+void tiles(pic_ctx* c, const BlockGeo& q, const DebyeC& d, double* lam_out) {
+  const unsigned nt = (unsigned)c->ntiles;
+  const ChunkSpread& sp = parts_spread(c);
+  // A tile is crowded when one workgroup (a wave, for whole tiles) to itself
+  // would be the last to end: a workgroup reads 400 particles a microsecond and a
+  // chunk has up to 4096.  Records of single cells are many, so there more are
+  // left to a tile's workgroup.
+  const long long fair = LGB == 3 ? std::min(4ll, std::max(1ll, sp.chunks / 2048))
+                                  : std::min(8ll, std::max(LGB ? 2ll : 4ll, sp.chunks / 512));
+  const Chunks C{{c->tsb[0][c->tcur[0]], c->tsb[2][c->tcur[2]]}, c->chunks, c->cstart, nt,
+                 (unsigned)fair, sp.uneven};
+  const PT pe = species_arrays<PT>(c, 0), pi = species_arrays<PT>(c, 2);
+  const bool crowd = sp.most > fair;
+  // The electrons are binned every step.
+  const long long tail = c->n[2] - c->n_binned[2];
+  const bool strays = tail > 0 || c->ion_moved_accum > 0;
+  hipStream_t st = c->stream;
+  Strays S{nullptr, c->dbg_list, &c->dc->n_stray,
+           (unsigned long long)stray_cap(c->cfg.capacity[2])};
+  if (crowd) k_debye_clear<LGB><<<std::min(nt, 1024u), kT, 0, st>>>(C, c->g, q, c->dbg_mom);
+  if (strays) {
+    S.bits = c->dbg_bits;
+    const unsigned nchb = (unsigned)c->nch_bound;
+    const unsigned grid = nchb + (tail > 0 ? (unsigned)std::min(256ll, (tail + kT - 1) / kT) : 0u);
+    k_debye_none<<<256, kT, 0, st>>>(S, c->ncells >> (3 * LGB));
+    k_debye_find<PT><<<grid, kT, 0, st>>>(pi, c->n[2], c->n_binned[2], C, nchb, c->g, q, S,
+                                          c->dbg_mom);
+    k_debye_add<PT><<<256, kT, 0, st>>>(pi, S, c->dbg_mom);
+  }
+  if constexpr (LGB == 3) {
+    if (crowd)
+      k_debye_whole_pieces<PT><<<1024, kT, 0, st>>>(pe, pi, C, c->g, q, strays, c->dbg_mom);
+    k_debye_whole<PT><<<kFinBlocks, kT, 0, st>>>(pe, pi, C, c->g, q, d, S, c->dbg_mom, lam_out,
+                                                 c->dbg_qpart, c->dbg_part);
+  } else {
+    if (crowd) k_debye_pieces<PT, LGB><<<1024, kT, 0, st>>>(pe, pi, C, c->g, q, c->dbg_mom);
+    k_debye_tiles<PT, LGB><<<kFinBlocks, kT, 0, st>>>(pe, pi, C, c->g, q, d, S, c->dbg_mom,
+                                                      lam_out, c->dbg_qpart, c->dbg_part);
   }
 }
 
-template <class PT>
-void tiles(pic_ctx* c, const BlockGeo& q, const DebyeC& d, double* lam_out) {
-  const unsigned nt = (unsigned)c->ntiles;
-  const uint32_t* tse = c->tsb[0][c->tcur[0]];
-  const uint32_t* tsi = c->tsb[2][c->tcur[2]];
-  // The electrons are binned every step.
-  const long long tail = c->n[2] - c->n_binned[2];
-  uint32_t* flag = nullptr;
-  if (tail > 0 || c->ion_moved_accum > 0) {
-    flag = c->tile_cursor;  // scratch of the binning passes
-    k_debye_zero_u32<<<64, kT, 0, c->stream>>>(flag, nt);
-    const unsigned grid = nt + (tail > 0 ? (unsigned)std::min(256ll, (tail + kT - 1) / kT) : 0u);
-    k_debye_strays<PT, false><<<grid, kT, 0, c->stream>>>(species_arrays<PT>(c, 2), c->n[2],
-                                                          c->n_binned[2], tsi, nt, c->g, q, flag,
-                                                          c->dbg_mom);
-    k_debye_clear<<<std::min(nt, 1024u), kT, 0, c->stream>>>(flag, nt, c->g, q, c->dbg_mom);
-    k_debye_strays<PT, true><<<grid, kT, 0, c->stream>>>(species_arrays<PT>(c, 2), c->n[2],
-                                                         c->n_binned[2], tsi, nt, c->g, q, flag,
-                                                         c->dbg_mom);
-  }
-  k_debye_tiles<PT><<<kFinBlocks, kT, 0, c->stream>>>(
-      species_arrays<PT>(c, 0), species_arrays<PT>(c, 2), tse, tsi, nt, c->g, q, d, flag,
-      c->dbg_mom, lam_out, c->dbg_qpart, c->dbg_part);
+template <int LGB>
+void tiles_any(pic_ctx* c, const BlockGeo& q, const DebyeC& d, double* lam_out) {
+  if (c->mixed)
+    tiles<PartsM, LGB>(c, q, d, lam_out);
+  else
+    tiles<Parts, LGB>(c, q, d, lam_out);
 }
 
 }  // namespace
@@ -516,19 +716,14 @@ void parts_debye(pic_ctx* c, int block, double alpha_D, double* lam_out,
   d.eps0 = kEps0;
   d.dx = c->g.dx;
   d.dmax_per_lambda = 3.4 * alpha_D;
-  if (c->n[0] + c->n[2] > kCrowded * c->ntiles) {
-    k_debye_zero<<<1024, kT, 0, c->stream>>>(c->dbg_mom, 2 * kMom * nb);
-    if (c->mixed)
-      accumulate<PartsM>(c, q);
-    else
-      accumulate<Parts>(c, q);
-    k_debye_final<<<kFinBlocks, kT, 0, c->stream>>>(
-        c->dbg_mom, nb, d, lam_out, c->dbg_qpart, c->dbg_part);
-  } else if (c->mixed) {
-    tiles<PartsM>(c, q, d, lam_out);
-  } else {
-    tiles<Parts>(c, q, d, lam_out);
-  }
+  if (block == 1)
+    tiles_any<0>(c, q, d, lam_out);
+  else if (block == 2)
+    tiles_any<1>(c, q, d, lam_out);
+  else if (block == 4)
+    tiles_any<2>(c, q, d, lam_out);
+  else
+    tiles_any<3>(c, q, d, lam_out);
   k_debye_reduce<<<1, 1024, 0, c->stream>>>(c->dbg_qpart, c->dbg_part,
                                             kFinBlocks, out);
 }

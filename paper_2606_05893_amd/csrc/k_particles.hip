@@ -209,11 +209,9 @@ struct CicW {
 constexpr double kQUnits = 0x1p39;   // charge units of a whole weight
 
 // ---- chunk work lists ----------------------------------------------------------
-// A tile's binned particles of a species are split into pieces of at most
-// kChunk, so a crowded tile (e.g. the neutrals above an evaporating disk)
-// spreads over several workgroups.  A chunk (tile, piece) serves every
-// species of its list: piece k of a tile covers [ts[t] + k kChunk, ...).
-constexpr unsigned kChunk = 2048;
+// A crowded tile (e.g. the neutrals above an evaporating disk) spreads over
+// several workgroups; piece k of a tile covers [ts[t] + k kChunk, ...).
+constexpr unsigned kChunk = kPushChunk;
 
 __device__ __forceinline__ void piece(const uint32_t* __restrict__ ts,
                                       unsigned t, unsigned k, unsigned& b,
@@ -226,8 +224,9 @@ __device__ __forceinline__ void piece(const uint32_t* __restrict__ ts,
 
 __global__ void k_chunk_count(const uint32_t* __restrict__ ta,
                               const uint32_t* __restrict__ tb, long long nt,
-                              unsigned* __restrict__ cnt) {
+                              unsigned* __restrict__ cnt, Counters* dc) {
   const long long t = blockIdx.x * (long long)blockDim.x + threadIdx.x;
+  if (t == 0) dc->ch_most = dc->ch_uneven = 0;
   if (t >= nt) return;
   const unsigned na = ta[t + 1] - ta[t];
   const unsigned nb = tb ? tb[t + 1] - tb[t] : 0u;
@@ -235,12 +234,23 @@ __global__ void k_chunk_count(const uint32_t* __restrict__ ta,
   cnt[t] = ca > cb ? ca : cb;
 }
 
-__global__ void k_chunk_fill(const unsigned* __restrict__ cstart, long long nt,
-                             uint2* __restrict__ chunks) {
+__global__ void k_chunk_fill(const uint32_t* __restrict__ ta,
+                             const uint32_t* __restrict__ tb,
+                             const unsigned* __restrict__ cstart, long long nt,
+                             uint2* __restrict__ chunks, Counters* dc) {
   const long long t = blockIdx.x * (long long)blockDim.x + threadIdx.x;
   if (t >= nt) return;
   const unsigned b = cstart[t], e = cstart[t + 1];
   for (unsigned k = 0; b + k < e; ++k) chunks[b + k] = make_uint2((unsigned)t, k);
+  // How evenly they lie (ChunkSpread).
+  if (t == 0) dc->ch_all = cstart[nt];
+  if (e - b > 1u && e - b > dc->ch_most) atomicMax(&dc->ch_most, (unsigned long long)(e - b));
+  if (t < (long long)kRuns) {
+    const long long t0 = nt * t / kRuns, t1 = nt * (t + 1) / kRuns;
+    const unsigned long long run = (ta[t1] - ta[t0]) + (unsigned long long)(tb[t1] - tb[t0]);
+    const unsigned long long all = ta[nt] + (unsigned long long)tb[nt];
+    if (4 * run * kRuns > 5 * all) dc->ch_uneven = 1;
+  }
 }
 
 // ---- step bookkeeping ---------------------------------------------------------
@@ -3458,10 +3468,25 @@ void parts_chunks(pic_ctx* c, const long long hb[3]) {
   hipStream_t st = c->stream;
   const long long nt = c->ntiles;
   k_chunk_count<<<nblk(nt), kT, 0, st>>>(ts_cur(c, 0), ts_cur(c, 2), nt,
-                                         c->tile_cursor);
+                                         c->tile_cursor, c->dc);
   scan_tiles(c, c->tile_cursor, c->cstart, nullptr);
-  k_chunk_fill<<<nblk(nt), kT, 0, st>>>(c->cstart, nt, c->chunks);
+  k_chunk_fill<<<nblk(nt), kT, 0, st>>>(ts_cur(c, 0), ts_cur(c, 2), c->cstart, nt, c->chunks,
+                                        c->dc);
+  c->spread.known = false;
   c->nch_bound = std::min<long long>(nt + (hb[0] + hb[2]) / kChunk + 2, c->nch_cap);
+}
+
+const ChunkSpread& parts_spread(pic_ctx* c) {
+  ChunkSpread& sp = c->spread;
+  if (!sp.known) {
+    unsigned long long v[3];
+    static_assert(offsetof(Counters, ch_uneven) == offsetof(Counters, ch_all) + 16, "");
+    if (hipMemcpyAsync(v, &c->dc->ch_all, sizeof(v), hipMemcpyDeviceToHost, c->stream) !=
+            hipSuccess || hipStreamSynchronize(c->stream) != hipSuccess)
+      v[0] = v[1] = v[2] = 0;   // (right for any; the call reports the error)
+    sp = ChunkSpread{true, (long long)v[0], (long long)v[1], v[2] != 0};
+  }
+  return sp;
 }
 
 // In-place removal of a step's few removed particles of species s (listed
@@ -3543,7 +3568,6 @@ void remove_listed_t(pic_ctx* c, int s, uint32_t* list,
 // per step a bound of a few ten thousand balances its growth against one
 // binning pass.  The decision reads this step's counters, copied as soon as
 // the collisions are done, while the electrons bin.
-constexpr long long kIonLazy = 1 << 15;
 
 void parts_bin(pic_ctx* c) {
   hipStream_t st = c->stream;

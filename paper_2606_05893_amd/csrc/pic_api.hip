@@ -247,6 +247,8 @@ size_t carve(pic_ctx* c, char* base) {
   // and reads them within a step, the other within a call): at most all cells,
   // and the 64 of a tile plane with at least four, in ten doubles a cell.
   if (f.flags & PIC_FLAG_CELL_GROUPS) c->cg_list = reinterpret_cast<unsigned*>(c->dbg_mom);
+  c->dbg_bits = cv.take<uint32_t>((c->ncells + 31) / 32);
+  c->dbg_list = cv.take<Rec>(stray_cap(f.capacity[2]));
   c->dbg_qpart = cv.take<long long>(2048);
   c->dbg_part = cv.take<double>(2048);
   c->dbg_out = cv.take<double>(4);
@@ -493,6 +495,7 @@ pic_status pic_init(const pic_config* cfg, void* ws, size_t bytes,
     c->n_binned[s] = 0;
   }
   c->nch_bound = 1;
+  c->spread = ChunkSpread{false, 0, 0, false};
   c->tcounted = false;
   c->ncount_valid = false;
   c->acc_next_valid = false;
@@ -758,6 +761,8 @@ pic_status advance_finish(pic_ctx* c, double dt,
   if (!hip_ok(c, hipGetLastError(), "advance launch")) return PIC_ERR_HIP;
   pic_status st = sync_counters(c);
   if (st != PIC_OK) return st;
+  c->spread = ChunkSpread{true, (long long)c->hc.ch_all, (long long)c->hc.ch_most,
+                          c->hc.ch_uneven != 0};
   for (int k = 0; k < PIC_NSPECIES; ++k) {
     if (k == 2 && !c->ions_binned) {
       c->n[k] = (long long)c->hc.n[k];   // binned ranges kept, tail grown

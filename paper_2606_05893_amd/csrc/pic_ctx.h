@@ -49,6 +49,18 @@ constexpr long long kDirectStepNodes = 1ll << 18;
 // Removed ions a step can list for the in-place removal (more: full binning).
 constexpr int kDeadList = 4096;
 
+// Ions outside their tile (the unbinned tail, and those moved since the last
+// binning) that a step leaves: at most kIonLazy and 1/1024 of them (parts_bin).
+constexpr long long kIonLazy = 1 << 15;
+inline long long stray_cap(long long ions) { return kIonLazy + ions / 1024 + 1; }
+
+// How the chunk list lies in the tiles (Counters::ch_*).
+struct ChunkSpread {
+  bool known;
+  long long chunks, most;    // all of them, of one tile (0: at most one)
+  bool uneven;
+};
+
 // The sorted record lists of a step.
 // Those of at most kRankList records are sorted by rank (sort_records).
 constexpr long long kRankList = 8192;
@@ -85,6 +97,7 @@ struct pic_ctx {
   uint2* chunks;             // (tile, piece) work list of the charged species
   uint32_t* cstart;          // ntiles + 1 chunk offsets
   long long nch_bound;       // host bound of the chunk count
+  pic::ChunkSpread spread;   // how evenly its chunks lie
   long long nch_cap;         // capacity of the chunk list
   // Neutrals are compacted in place between full binning passes.
   uint32_t* cmp_idx;         // holes then movers, capacity[1] each
@@ -177,6 +190,8 @@ struct pic_ctx {
   // Debye-length check: per-block moments of electrons and ions, block
   // partials of its reductions and its four results.
   double* dbg_mom;
+  uint32_t* dbg_bits;        // a bit per block that stray ions are in
+  pic::Rec* dbg_list;        // the stray ions (stray_cap)
   long long* dbg_qpart;
   double* dbg_part;
   double* dbg_out;
@@ -325,6 +340,9 @@ long long neutral_push_blocks(long long n);
 void parts_bin(pic_ctx* c);
 void parts_bin_species(pic_ctx* c, int s);
 void parts_chunks(pic_ctx* c, const long long hb[3]);
+// How the charged particles lie in the tiles: a step's readback has it, after a
+// load it is read here.
+const ChunkSpread& parts_spread(pic_ctx* c);
 // Device arrays of species s (current buffer, native layout) and their
 // element sizes; returns the number of arrays.
 int parts_arrays(pic_ctx* c, int s, void** ptr, size_t* elem);

@@ -259,6 +259,13 @@ struct Acc<PartsM> {
 
 // Device-resident counters of one step.  All are updated with atomics or by
 // single-thread kernels and copied to the host once at the end of a step.
+// A tile's binned particles of a species are split into pieces of at most
+// kPushChunk; a chunk (tile, piece) of the push serves electrons and ions.
+constexpr unsigned kPushChunk = 2048;
+
+// Equal runs of tiles that Counters::ch_uneven speaks of.
+constexpr unsigned kRuns = 1024;
+
 struct Counters {
   unsigned long long n[4];          // live particles
   unsigned long long next_id;
@@ -290,6 +297,10 @@ struct Counters {
   unsigned long long f3_cx;         // charge exchanges
   unsigned long long f3_starved;    // electron-ion events without an ion
   unsigned long long n_vmax2;       // bits of the atoms' largest |v|^2
+  unsigned long long ch_all;        // chunks of the push
+  unsigned long long ch_most;       // ... of the tile that has most
+  unsigned long long ch_uneven;     // a run of tiles has a quarter above its share
+  unsigned long long n_stray;       // ions outside their tile (Debye check)
   long long total_charge;
   unsigned int err;                 // sticky error bits (kErr*)
   int vcycles;
