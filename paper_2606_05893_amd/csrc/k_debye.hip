@@ -705,7 +705,6 @@ void parts_debye(pic_ctx* c, int block, double alpha_D, double* lam_out,
   q.b = block;
   q.bx = c->cfg.nx / block;
   q.by = c->cfg.ny / block;
-  const long long nb = (long long)q.bx * q.by * (c->cfg.nz / block);
   DebyeC d;
   d.mass[0] = kMe;
   d.mass[1] = kMcu;

@@ -75,33 +75,6 @@ __device__ __forceinline__ void wave_count(bool pred,
     atomicAdd(counter, (unsigned long long)__popcll(mask));
 }
 
-// Run-length aggregated counter increment for keys that arrive grouped
-// (binned particles): the first lane of each run of equal keys adds the run
-// length.  Returns, per lane, its slot when 'fetch' is set (the counter's
-// old value plus its rank in the run).  All lanes must call it.
-__device__ __forceinline__ unsigned run_add(unsigned key, unsigned* counters,
-                                            bool fetch) {
-  const int lane = lane_id();
-  const unsigned prev = __shfl_up(key, 1);
-  const bool head = lane == 0 || key != prev;
-  const unsigned long long hm = __ballot(head);
-  const unsigned long long above = lane == 63 ? 0ull : (hm >> (lane + 1));
-  const int len = above ? __ffsll((long long)above) : 64 - lane;
-  // Head lane of this lane's run: highest set bit of hm at or below lane.
-  const unsigned long long upto = hm & (lane == 63 ? ~0ull : ((2ull << lane) - 1ull));
-  const int head_lane = 63 - __clzll((long long)upto);
-  unsigned base = 0;
-  if (head && key != kDead) {
-    if (fetch)
-      base = atomicAdd(&counters[key], (unsigned)len);
-    else
-      atomicAdd(&counters[key], (unsigned)len);
-  }
-  if (!fetch) return 0;
-  base = __shfl(base, head_lane);
-  return base + (unsigned)(lane - head_lane);
-}
-
 __device__ __forceinline__ unsigned tile_of_cell(unsigned cell, const GridC& g) {
   const unsigned i = cell % (unsigned)g.nx;
   const unsigned r = cell / (unsigned)g.nx;
@@ -395,7 +368,8 @@ __global__ void k_fn_count(const TE* __restrict__ Ez, unsigned* __restrict__ cnt
 // waves' totals give each wave its offset, and a second pass scans them
 // 64 at a time (shuffles) with a running carry.  Every access is
 // coalesced, and the loads of each pass go out kScanB at a time (clamped
-// to a valid index), not as a chain.
+// to a valid index), not as a chain.  again: also takes the prefixes (not the
+// total); it may be 'in', whose values are read before they are replaced.
 constexpr int kScanB = 16;
 __device__ __forceinline__ unsigned wave_incl_scan(unsigned v, int lane) {
 #pragma unroll
@@ -406,9 +380,6 @@ __device__ __forceinline__ unsigned wave_incl_scan(unsigned v, int lane) {
   return v;
 }
 
-//
-// again: also takes the prefixes (not the total); it may be 'in', whose
-// values are read before they are replaced.
 __global__ void __launch_bounds__(1024) k_scan1(const unsigned* in,
                                                 unsigned* __restrict__ out,
                                                 long long n,
@@ -1476,13 +1447,7 @@ __device__ __forceinline__ void hist_flush(unsigned* hk, int* hc,
     if (hk[s] != kHistEmpty) atomicAdd(&ncount[hk[s]], hc[s]);
 }
 
-// Neutrals per cell are kept up to date across steps: the first n_old
-// neutrals (those at the start of the step, all counted) change the count
-// only when their cell changes or they leave the domain, and the ones
-// appended since are added.  A neutral's previous cell is that of its
-// stored position, the value the previous step counted.
-//
-// vmax: also their largest |v|^2 to n_vmax2 (its bits, which order as the
+// The largest |v|^2 of the neutrals to n_vmax2 (its bits, which order as the
 // values do; a neutral that is not finite is removed).
 __device__ __forceinline__ void note_vmax(double ke_max, Counters* dc) {
   unsigned long long v = (unsigned long long)__double_as_longlong(ke_max);
@@ -1498,12 +1463,17 @@ __device__ __forceinline__ void note_vmax(double ke_max, Counters* dc) {
     atomicMax(&dc->n_vmax2, v);
 }
 
+// Neutrals per cell are kept up to date across steps: the first n_old
+// neutrals (those at the start of the step, all counted) change the count
+// only when their cell changes or they leave the domain, and the ones
+// appended since are added.  A neutral's previous cell is that of its
+// stored position, the value the previous step counted.  vmax: note_vmax too.
 __global__ void __launch_bounds__(kT) k_push_neutral(
     Parts p, uint32_t* __restrict__ key, GridC g, double dt,
-    int* __restrict__ ncount, long long n_old, MccC m, uint32_t step,
-    uint64_t seed, Rec* __restrict__ ab_rec, double* __restrict__ ab_pos,
-    double* __restrict__ ab_vel, long long ab_cap, Counters* dc,
-    double* __restrict__ part, uint32_t* __restrict__ dead1, bool vmax) {
+    int* __restrict__ ncount, long long n_old, Rec* __restrict__ ab_rec,
+    double* __restrict__ ab_pos, double* __restrict__ ab_vel, long long ab_cap,
+    Counters* dc, double* __restrict__ part, uint32_t* __restrict__ dead1,
+    bool vmax) {
   __shared__ unsigned hk[kHist];
   __shared__ int hc[kHist];
   __shared__ double sk[kT];
@@ -1527,7 +1497,7 @@ __global__ void __launch_bounds__(kT) k_push_neutral(
         const double x = p.x[i], y = p.y[i], z = p.z[i];
         const unsigned prev = i < n_old ? cell_of(x, y, z, g) : kDead;
         finish_push(p, i, x, y, z, p.vx[i], p.vy[i], p.vz[i], dt, g, key,
-                    ncount, m, dc, o, 1);
+                    ncount, MccC(), dc, o, 1);
         if (o.cell != prev) {
           if (prev != kDead) atomicSub(&ncount[prev], 1);
           if (o.cell != kDead) {
@@ -1556,10 +1526,10 @@ __global__ void __launch_bounds__(kT) k_push_neutral(
 
 __global__ void __launch_bounds__(kT) k_push_neutral_m(
     PartsM p, uint32_t* __restrict__ key, GridC g, float dtdx,
-    int* __restrict__ ncount, long long n_old, MccC m, uint32_t step,
-    uint64_t seed, Rec* __restrict__ ab_rec, double* __restrict__ ab_pos,
-    double* __restrict__ ab_vel, long long ab_cap, Counters* dc,
-    double* __restrict__ part, uint32_t* __restrict__ dead1, bool vmax) {
+    int* __restrict__ ncount, long long n_old, Rec* __restrict__ ab_rec,
+    double* __restrict__ ab_pos, double* __restrict__ ab_vel, long long ab_cap,
+    Counters* dc, double* __restrict__ part, uint32_t* __restrict__ dead1,
+    bool vmax) {
   __shared__ unsigned hk[kHist];
   __shared__ int hc[kHist];
   __shared__ double sk[kT];
@@ -1584,7 +1554,7 @@ __global__ void __launch_bounds__(kT) k_push_neutral_m(
         InM q;
         load_in(p, i, q);
         push_one(p, i, q, nullptr, nullptr, nullptr, 0, 0, 0, nullptr, 0, g,
-                 0.0f, dtdx, key, ncount, m, dc, o, 1);
+                 0.0f, dtdx, key, ncount, MccC(), dc, o, 1);
         if (o.cell != prev) {
           if (prev != kDead) atomicSub(&ncount[prev], 1);
           if (o.cell != kDead) {
@@ -2957,9 +2927,6 @@ void sources_fn_t(pic_ctx* c, double dt) {
 template <class PT>
 void push_neutral_t(pic_ctx* c, double dt) {
   hipStream_t st = c->stream;
-  const uint32_t step = (uint32_t)c->step;
-  const uint64_t seed = c->cfg.seed;
-  const MccC m = mcc_constants(c, dt);
   const long long ab_cap = c->cfg.max_events;
   // Neutrals per cell: updated from the counts of the step before, or
   // counted afresh after the population was replaced.
@@ -2970,14 +2937,13 @@ void push_neutral_t(pic_ctx* c, double dt) {
   if (c->mixed)
     k_push_neutral_m<<<nb, kT, 0, st>>>(
         cur<PartsM>(c, 1), c->key[1], c->g, (float)(dt * c->g.inv_dx),
-        c->ncount, n_old, m, step, seed, c->ab_rec, c->ab_raw_pos,
-        c->ab_raw_vel, ab_cap, c->dc, c->part_n, c->dead1,
-        c->ionp.enabled != 0);
+        c->ncount, n_old, c->ab_rec, c->ab_raw_pos, c->ab_raw_vel, ab_cap,
+        c->dc, c->part_n, c->dead1, c->ionp.enabled != 0);
   else
     k_push_neutral<<<nb, kT, 0, st>>>(
-        cur<Parts>(c, 1), c->key[1], c->g, dt, c->ncount, n_old, m, step,
-        seed, c->ab_rec, c->ab_raw_pos, c->ab_raw_vel, ab_cap, c->dc,
-        c->part_n, c->dead1, c->ionp.enabled != 0);
+        cur<Parts>(c, 1), c->key[1], c->g, dt, c->ncount, n_old, c->ab_rec,
+        c->ab_raw_pos, c->ab_raw_vel, ab_cap, c->dc, c->part_n, c->dead1,
+        c->ionp.enabled != 0);
   c->ncount_valid = true;
   c->part_n_blocks = nb;
   tmark(c, PIC_PH_PUSH_NEUTRAL, false);
@@ -3196,11 +3162,6 @@ void push_collide_t(pic_ctx* c, double dt) {
   tmark(c, PIC_PH_ABSORBED, false);
 }
 
-// Bin one species by tile into the other buffer (removing dead particles):
-// destination counts from the binned ranges (per chunk) and the appended
-// tail (per particle), an exclusive scan, then the scatter.  The neutrals
-// keep no tile ranges between passes (they are compacted in place), so all
-// of them bin as one tail.
 // Exclusive scan of the tile counts into out (its total last) and, unless
 // null, cursor: by one workgroup up to kScanOne tiles, where its two passes
 // over the counts (9 us at 16384 tiles) take less than three launches
@@ -3221,6 +3182,11 @@ static void scan_tiles(pic_ctx* c, unsigned* in, unsigned* out,
                                              out, cursor);
 }
 
+// Bin one species by tile into the other buffer (removing dead particles):
+// destination counts from the binned ranges (per chunk) and the appended
+// tail (per particle), an exclusive scan, then the scatter.  The neutrals
+// keep no tile ranges between passes (they are compacted in place), so all
+// of them bin as one tail.
 template <class PT>
 void bin_species_t(pic_ctx* c, int s) {
   hipStream_t st = c->stream;

@@ -91,19 +91,6 @@ __device__ __forceinline__ void voxel_xyz(unsigned v, const Dims& d, int& x,
   z = (int)(r / (unsigned)d.H);
 }
 
-__device__ __forceinline__ long long nb_voxel(const Dims& d, int z, int y,
-                                              int x, int tap) {
-  const int dz = tap / 9 - 1, dy = (tap / 3) % 3 - 1, dx = tap % 3 - 1;
-  const int zz = z + dz;
-  if (zz < 0 || zz >= d.D) return -1;
-  int yy = y + dy, xx = x + dx;
-  if (yy < 0) yy += d.H;
-  if (yy >= d.H) yy -= d.H;
-  if (xx < 0) xx += d.W;
-  if (xx >= d.W) xx -= d.W;
-  return ((long long)zz * d.H + yy) * d.W + xx;
-}
-
 // Packed 3^3 weights, in the order the matrix instructions take them: per 16
 // output channels, 16 input channels (slice) and tap row (oz, oy) two
 // fragments of 64 lanes x 8 values, lane 16 (half + 2 slot) + channel.  The
@@ -935,7 +922,7 @@ __global__ void __launch_bounds__(256, 2) k_wgrad_first(const float* __restrict_
                                                         float* __restrict__ dW,
                                                         float* __restrict__ db, Dims d, int nsp) {
   using T = WgTile<16>;
-  constexpr int YB = T::YB, P = T::P, TY = T::TY, TZ = T::TZ, HY = T::HY, HZ = T::HZ;
+  constexpr int YB = T::YB, P = T::P, TY = T::TY, TZ = T::TZ, HY = T::HY;
   constexpr int HV = T::HV, GV = T::GV;
   // One voxel of slack: the last row's shift +2 (dropped) reads past it.
   constexpr int kRed = 18 * 256 * 4 / 16;
@@ -1333,7 +1320,7 @@ __global__ void k_pack_w(const float* __restrict__ W, int ci_n, int co_n,
   const long long n = wpack(co_n, ci_n);
   if (i >= 2 * n) return;
   const bool back = i >= n;
-  const int out_n = back ? ci_n : co_n, in_n = back ? co_n : ci_n;
+  const int in_n = back ? co_n : ci_n;
   long long q = back ? i - n : i;
   bf16* dst = (back ? Wd : Wk) + q;
   const int e = (int)(q % 8), lane = (int)(q / 8 % 64), second = (int)(q / kFrag % 2);
@@ -1348,12 +1335,6 @@ __global__ void k_pack_w(const float* __restrict__ W, int ci_n, int co_n,
   }
   *dst = f2bf(back ? W[((long long)c * 27 + 26 - tap) * ci_n + o]
                    : W[((long long)o * 27 + tap) * ci_n + c]);
-}
-
-__global__ void k_f32_to_f64(const float* __restrict__ a, double* __restrict__ b,
-                             long long n) {
-  const long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x;
-  if (i < n) b[i] = a[i];
 }
 
 }  // namespace
@@ -1405,7 +1386,6 @@ struct pic_unet {
   float *out, *gout, *target;
   // Gradient scratch per level: buffers of the level's widest tensor.
   bf16 *ga[4], *gb[4], *gs[4];
-  float* dscratch;             // double partials (as float storage)
   double* dpart;
   int t;                       // Adam step
   int loss_mode, loss_k0;      // PIC_UNET_LOSS_*, first unknown plane
