@@ -13,13 +13,16 @@ bytes per launch over its HIP-event-timed duration), and the CPU oracle on a
 bounded sample of the same workload.
 
 The forms of the step run one after another on the same preload: plain
-FP64 multigrid (the JSON line's value), mixed precision, mixed precision
-with the learned warm start, and plain FP64 again with the previous
-potential as the start instead of the extrapolated one; every solve to the
-same residual.
+FP64 (the JSON line's value), mixed precision, mixed precision with the
+learned warm start, and plain FP64 again with the previous potential as the
+start instead of the extrapolated one; every solve to the same residual.
+Grids of this size solve Poisson's equation directly, so a better start saves
+nothing there; the _mg forms ask for a multigrid depth and run V-cycles from
+the extrapolated or the learned start.
 
 Usage: python bench.py [--gpus 1] [--steps K] [--warmup W]
-                       [--variant all|fp64|mixed|learned_mixed|fp64_prev]
+                       [--variant all|fp64|mixed|learned_mixed|fp64_prev|
+                        fp64_mg|mixed_mg|learned_mixed_mg|...]
                        [--no-cpu-baseline]
 """
 import argparse
@@ -63,11 +66,14 @@ def parse():
     ap.add_argument("--workload", default="c2")
     ap.add_argument("--variant", default="all",
                     choices=["all", "fp64", "mixed", "learned_mixed", "fp64_prev",
+                             "fp64_mg", "mixed_mg", "learned_mixed_mg",
                              "fp64_np", "fp64_coulomb", "fp64_ionproc"],
-                    help="fp64: plain FP64 multigrid; mixed: FP32 particles and "
-                         "smoothing with FP64 refinement; learned_mixed: mixed "
-                         "with the U-Net warm start (trained first on pairs "
-                         "from another run); all: the three, value = fp64")
+                    help="fp64: plain FP64; mixed: FP32 particles; "
+                         "learned_mixed: mixed with the U-Net warm start "
+                         "(trained first on pairs from another run); _mg: the "
+                         "same with V-cycles (mixed: FP32 smoothing with FP64 "
+                         "refinement) instead of the direct solve; all: every "
+                         "one, value = fp64")
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--phases", action="store_true",
                     help="print per-phase times to stderr")
@@ -310,14 +316,16 @@ def run_variant(G, p, precision, pre, n0, cap, steps, warmup, net=None,
         diag = {}
         n_charged = gpu.count(0) + gpu.count(2)
         for block in (1, 8):
+            # (Once before: a kernel's first launch loads it.)
+            gpu.debye_check(block, 0.5, with_lambda=False)
             gpu.enable_timing(True)
             for _ in range(5):
                 info, _ = gpu.debye_check(block, 0.5, with_lambda=False)
             ms, calls = gpu.phase_times()["debye"]
             nb = info["blocks"]
-            # 48 B per charged particle (x, y, z, vx, vy, vz read); per block
-            # the 80-byte moment record cleared, updated once and read once.
-            alg = 48 * n_charged + 240 * nb
+            # Per charged particle its position and velocity read (48 B), for
+            # blocks of a whole tile the velocity (24 B).
+            alg = (24 if block == 8 else 48) * n_charged
             t = ms / max(calls, 1) * 1e-3
             diag[f"debye_block{block}"] = {
                 "ms": round(t * 1e3, 4), "blocks": nb,
@@ -377,8 +385,8 @@ def variant_rooflines(p, r, workload):
     once (16 B); per cell the neutral count read once (4 B).
 
     smooth (finest level): with two sweeps before and after the coarse
-    correction on a grid at least one owned column wide (64 x 16 nodes in
-    FP64, 32 x 16 in FP32) it is k_smooth2, one launch per two red-black
+    correction on a grid at least one owned column wide (16 x 16 nodes) it is
+    k_smooth2, one launch per two red-black
     sweeps, whose algorithmic bytes are u and f read and u written once: 24 B
     per unknown in FP64; in the mixed form's correction solve 13 B, the mean
     of a refinement round's four passes (8 B from a zero start, 12, 12, and
@@ -410,9 +418,9 @@ def variant_rooflines(p, r, workload):
     ms_sm, n_sm = ph["smooth_l0"]
     if n_sm == 0:  # the steps solved directly: no smoothing to report
         return {"push": push}
-    # The fused pass needs a level at least one owned column wide (64 x 16
-    # nodes in FP64, 32 x 16 in FP32).
-    fused = p["nx"] >= (32 if mixed else 64) and p["ny"] >= 16 and r["_nu"] == 4
+    # The fused pass needs a level at least one owned column wide (16 x 16
+    # nodes).
+    fused = p["nx"] >= 16 and p["ny"] >= 16 and r["_nu"] == 4
     if fused:
         n_eff = 2 * r["_vcycles_total"]
         # Mixed: a refinement round's four finest-level passes move 8 (zero
@@ -457,13 +465,14 @@ def main():
     if cpu is not None:
         progress(f"cpu baseline: {cpu['value']:.3e} particle-steps/s on "
                  f"{cpu['cores']} cores")
-    variants = (["fp64", "mixed", "learned_mixed", "fp64_prev", "fp64_np",
-                 "fp64_coulomb", "fp64_ionproc"]
+    variants = (["fp64", "mixed", "learned_mixed", "fp64_prev", "fp64_mg",
+                 "mixed_mg", "learned_mixed_mg", "fp64_np", "fp64_coulomb",
+                 "fp64_ionproc"]
                 if a.variant == "all" else [a.variant])
     cap, per_step_n = capacities(p, a.warmup + 2 * a.steps)
     torch.cuda.set_device(0)
     net, train_info = None, None
-    if "learned_mixed" in variants:
+    if any(v.startswith("learned") for v in variants):
         tp, tcap = p, cap
         if p["nx"] * p["ny"] * p["nz"] > 128 * 128 * 512:
             # A larger grid takes the network trained on the 128x128x512
@@ -483,6 +492,8 @@ def main():
     for v in variants:
         prec = "fp64" if v.startswith("fp64") else "mixed"
         pv = p
+        if v.endswith("_mg"):
+            pv = dict(p, mg_levels=16)  # (as deep as the grid allows)
         if v == "fp64_np":
             # A nanoparticle of 5 nm radius at z = 200 nm over the disk
             # centre absorbing electrons (alpha_EH = 0.5); no extra source.
@@ -504,7 +515,7 @@ def main():
                                        lotz_a2=4.5e-18, I2_eV=20.29,
                                        cx_a=7.0710678118654755e-10, cx_b=0.0)
         res[v] = run_variant(G, pv, prec, pre, n0, cap, a.steps, a.warmup,
-                             net if v == "learned_mixed" else None,
+                             net if v.startswith("learned") else None,
                              warm="prev" if v == "fp64_prev" else "extrap",
                              diagnostics=(v == "fp64"))
         progress(f"{v}: {res[v]['ms_per_step']:.3f} ms/step")
@@ -513,7 +524,7 @@ def main():
     mixed = head["precision"] == "mixed"
     rooflines = {}
     for v, r in res.items():
-        if v in ("fp64", "mixed"):
+        if v in ("fp64", "mixed", "fp64_mg", "mixed_mg"):
             rooflines[v] = variant_rooflines(p, r, a.workload)
     if variants[0] in rooflines:
         hr = rooflines[variants[0]]
@@ -558,6 +569,13 @@ def main():
         if "mixed" in res:
             out["learned_mixed_vs_mixed_step_time"] = round(
                 lm["ms_per_step"] / res["mixed"]["ms_per_step"], 4)
+    if "learned_mixed_mg" in res:
+        for v in ("fp64_mg", "mixed_mg"):
+            if v in res:
+                out[f"learned_mixed_mg_vs_{v}_step_time"] = round(
+                    res["learned_mixed_mg"]["ms_per_step"] / res[v]["ms_per_step"], 4)
+                out[f"learned_mixed_mg_vs_{v}_vcycles"] = [
+                    res["learned_mixed_mg"]["vcycles_avg"], res[v]["vcycles_avg"]]
     if cpu is not None:
         out["cpu_baseline"] = cpu
     if a.phases:
