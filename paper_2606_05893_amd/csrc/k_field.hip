@@ -1975,6 +1975,11 @@ void spectral_solve(pic_ctx* c, int l) {
 }
 
 // Workgroups of k_smooth2<T, SmoothTile<T>, *> the current device runs at once.
+// The split for the small column too, of which a CU holds three to four times
+// as many (1024 and 1536 against 256 and 512): the levels that take it have so
+// few columns that segments are at their shortest either way (a solve 380 us
+// with either count on 32x32x64), and on the longer ones more segments gain
+// nothing (24x40x200: 370 us, 383 with its own count; 16x16x1024: 651, 645).
 template <typename T>
 long long smooth_slots() {
   static long long cached[64] = {0};

@@ -675,7 +675,12 @@ __global__ void __launch_bounds__(SEG > 32 ? 512 : 1024) k_sp_tri(SpGrid G, doub
 }
 
 // Lines per workgroup: what the threads hold, fewer where that would leave
-// the chip idle.
+// the chip idle, so at least 512 workgroups (two a CU) as long as each has
+// four lines.  poisson_solve with at least 256 / 512 / 1024 / 2048: 118 / 106 /
+// 104 / 104 us on 48x48x96, 168 / 152 / 147 / 160 on 120x90x100, 113 / 113 /
+// 105 / 106 on 64x64x128; from 128x128x128 on the threads' limit decides.  With
+// at least 1 / 2 / 4 / 8 lines: 98 / 98 / 98 / 106 on 64x64x64, 106 / 106 / 106
+// / 115 on 48x48x96.
 int lines_per_wg(int n, long long nlines) {
   const int most = kSpThreads * kSpElems / n;
   const long long spread = std::max(4LL, (nlines + 511) / 512);
@@ -740,6 +745,14 @@ static void spectral_modes(pic_ctx* c) {
   const LineLaunch y = line_launch(G.ny, (long long)G.np * (G.nx / 2));
   k_sp_y<false><<<y.grid, y.threads, y.lds, c->stream>>>(G, s, y.plan, y.nlines, y.lpw, y.stride,
                                                          c->dc);
+  // Planes a thread holds: a workgroup takes 32 columns (whole 256-byte rows)
+  // and as many segments as cover the planes, at most 512 threads' worth with 8
+  // and 16 planes and 1024 with 32; past 1024 planes 64, whose registers allow
+  // 512 threads, so 16 columns.  The limits of 1024 and 2048 planes are the
+  // workgroup's; those of 128 and 256 (256 and 512 would fit) cost nothing:
+  // poisson_solve with 8 / 16 / 32 / 64 takes 149 / 147 / 150 / 153 us on
+  // 128x128x128, 175 / 172 / 175 / 177 on 128x128x256, with 16 / 32 / 64 275 /
+  // 276 / 279 on 128x128x512, with 32 / 64 1931 / 1950 on 256x256x1024.
   const int seg = G.np <= 128 ? 8 : G.np <= 256 ? 16 : G.np <= 1024 ? 32 : 64;
   const int nsg = std::max(1, (G.np + seg - 1) / seg);
   const int lgc = seg == 64 ? 4 : 5;

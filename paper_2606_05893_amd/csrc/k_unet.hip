@@ -1523,8 +1523,11 @@ bool conv(hipStream_t st, int cin, int cout, const bf16* in, const bf16* Wk,
 
 // Gradient of a decoder's concatenation (cin channels in, 3 cin out), its part
 // of the upsampled coarse output and its skip part.  One round of resident
-// workgroups over the channel groups with one slice, whose weights stay; else
-// shorter runs.
+// workgroups (two on each of 256 CUs) over the channel groups with one slice,
+// whose weights stay; else runs half as long.  A training sample's gradient on
+// 128x128x512 with 256 / 512 / 768 / 1024 workgroups for 16 channels: 5922 /
+// 5796 / 5830 / 5807 us; with 256 / 512 / 1024 / 2048 for 32 and 64: 5979 /
+// 5808 / 5815 / 5807.
 bool conv_cat_grad(hipStream_t st, int cin, const bf16* in, const bf16* Wk, bf16* gup, bf16* gskip,
                    Dims d) {
   const long long ntiles = (long long)((d.W + 15) / 16) * ((d.H + 7) / 8) * ((d.D + 3) / 4);
@@ -1559,8 +1562,11 @@ void conv_upcat_launch(hipStream_t st, const bf16* coarse, const bf16* skip,
   }
 }
 
-// One round of resident workgroups over all (co, ci) pairs, at least two tiles
-// each: every workgroup ends with 27 x 256 atomic adds per pair.
+// One round of resident workgroups (two on each of 256 CUs, as the kernels'
+// launch bounds have it) over all (co, ci) pairs, at least two tiles each: every
+// workgroup ends with 27 x 256 atomic adds per pair.  A training sample's
+// gradient with 256 / 512 / 768 / 1024 workgroups: 6477 / 5813 / 6135 / 6055 us
+// on 128x128x512, 1616 / 1639 / 1709 / 1779 on 128x128x64; below that the same.
 template <int COUT>
 long long wgrad_runs(Dims d, int pairs) {
   using T = pic::WgTile<COUT>;
