@@ -1796,6 +1796,8 @@ __global__ void __launch_bounds__(kT) k_mcc(
 // and a last pass brings the result back into the first buffer when an odd
 // number of them ran.
 
+__device__ void sort_segment(Rec* s, int m);
+
 // Every record to the number of smaller ones, from the list itself to another
 // buffer: 64 records per workgroup, each of its 16 waves comparing them with a
 // sixteenth of the list, whose records it reads by scalar loads.  n^2 / 16
@@ -1810,9 +1812,8 @@ __global__ void __launch_bounds__(kT) k_mcc(
 // last step, whose length chose this way, then has its segments of kMergeSeg
 // sorted in place instead, for k_rank_segs.  (Ranked here as well, a cathode
 // list that jumped from nothing took the step from 0.13 to 1.8 ms at 65536
-// records and 442 ms at 2^20; 0.45 and 2.8 now, half of it the push.)
-__device__ void sort_segment(Rec* s, int m);
-
+// records and 442 ms at 2^20; 0.32 and 1.5 now, 0.45 and 2.8 where the step also
+// pushes as many electrons injected in it.)
 __global__ void __launch_bounds__(1024) k_rank_sort(const Rec* __restrict__ a,
                                                     Rec* __restrict__ aw,
                                                     Rec* __restrict__ out,
